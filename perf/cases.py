@@ -1,0 +1,259 @@
+"""What is timed: the work that a user of this package has it do, through its public entry points.
+
+Every case is one configuration of `CLTStep` (or of the activation normalisation that runs before training) on
+synthetic activations of the kind the package is used on: a full training step (forward, loss, backward, Adam), the
+gradients alone (the caller accumulates or clips them), an evaluation (forward and loss) and the forward pass on one
+prompt.  Sizes are those of the repository's own workloads (tiny, gpt2, llama1b, gemma2b and their variants), of its
+ragged parity shapes, or plain powers and odd numbers in between.
+
+A case holds
+  kind      step | grads | evaluate | forward | normalise
+  L d F B   layers, model width, features per layer, tokens of the batch
+  dtype     bf16 | f32 storage;  int8: inputs and targets as int8 codes with one scale per token row
+  master    fp32 master copies of the matrices;  fused: Adam inside the backward call (kind step)
+  mode      dense | auto: the package's switch between the dense and the list-driven kernels
+  density   share of the features that is active per token, set through the thresholds (0: threshold 0.03, the dense
+            regime at the beginning of training);  topk: k of the TopK activation instead (0: JumpReLU)
+  log_theta the threshold is stored as its logarithm;  lambda1: weight of the dead-feature term
+  heavy     log-normal token norms and a few outlier dimensions (activations that were not normalised)
+"""
+import math
+
+import torch
+
+from paper_2603_21014_amd import binding as K
+
+DEVICE = "cuda:0"
+MATRICES = ("W_enc", "W_dec")
+MODES = {"dense": K.DECODE_DENSE, "auto": K.DECODE_AUTO}
+# a later step of a training run: moments in place, decayed learning rate.  Where the thresholds set the density the rate
+# is that of the very end of the decay, so that many passes over one batch leave the density where it was.
+LR, LR_LAST, FIRST_STEP = 2e-5, 1e-7, 1001
+C, WINDOW = 4.0, 0.05
+
+
+def _case(name, kind, L, d, F, B, dtype="bf16", int8=False, master=False, fused=True, mode="dense", density=0.0, topk=0,
+          log_theta=False, lambda0=2.0, lambda1=0.0, heavy=False):
+    return {"name": name, "kind": kind, "L": L, "d": d, "F": F, "B": B, "dtype": dtype, "int8": int8, "master": master,
+            "fused": fused, "mode": mode, "density": density, "topk": topk, "log_theta": log_theta, "lambda0": lambda0,
+            "lambda1": lambda1, "heavy": heavy}
+
+
+def listed():
+    return [
+        # the smallest training step (unit tests, notebooks): bound by launches and host work
+        _case("tiny_f32_step", "step", 4, 64, 256, 128, dtype="f32"),
+        # GPT-2 shape in full fp32 (the precision the method was trained in on it), a micro batch, Adam as its own call
+        _case("gpt2_f32_step", "step", 12, 768, 6144, 1024, dtype="f32", fused=False),
+        # gradients of a small micro batch, to be accumulated or clipped by the caller; odd token count
+        _case("gpt2_micro_grads", "grads", 12, 768, 6144, 300),
+        # the GPT-2 training step
+        _case("gpt2_step", "step", 12, 768, 6144, 4096),
+        # sizes that fit no tile, with the dead-feature term and the log threshold
+        _case("ragged_dead_step", "step", 6, 2056, 8200, 4100, log_theta=True, lambda1=0.1, heavy=True),
+        # the benchmark's training step, early in training (about half of the features active)
+        _case("llama1b_step", "step", 16, 2048, 8192, 4096, lambda0=12.0, heavy=True),
+        # the same from the int8 activation cache later in training, 1 % active: dense decode, list-driven backward
+        _case("llama1b_int8_auto_step", "step", 16, 2048, 8192, 4096, int8=True, mode="auto", density=0.01, lambda0=12.0),
+        # TopK with 16 active features: everything list-driven
+        _case("llama1b_topk16_auto_step", "step", 16, 2048, 8192, 4096, mode="auto", topk=16, lambda0=0.0, heavy=True),
+        # a wide model with fp32 master weights (a slice of the gemma2b workload's 26 layers): optimiser-bound
+        _case("gemma2b_slice_master_step", "step", 8, 2304, 16384, 2048, master=True, lambda0=12.0),
+        # one prompt through a trained transcoder: feature activations and reconstruction for looking at them
+        _case("llama1b_prompt_forward", "forward", 16, 2048, 8192, 100, density=0.01),
+        # validation loss on cached int8 activations, sparse regime
+        _case("gpt2_int8_evaluate", "evaluate", 12, 768, 6144, 4096, int8=True, mode="auto", density=0.002),
+        # activation normalisation of a batch before training
+        _case("llama1b_normalise", "normalise", 16, 2048, 8192, 4096, heavy=True),
+    ]
+
+
+def _log_between(rng, lo, hi):
+    return math.exp(rng.uniform(math.log(lo), math.log(hi)))
+
+
+def _multiple_of_8(x, rng):
+    n = max(8, int(round(x / 8)) * 8)
+    if n >= 256 and rng.random() < 0.5:      # half of the wide ones are the round sizes that models have
+        n = n // 256 * 256
+    return n
+
+
+def draw(rng):
+    kind = rng.choice(["step", "step", "step", "grads", "grads", "forward", "evaluate", "normalise"])
+    dtype = "f32" if rng.random() < 0.25 else "bf16"
+    while True:
+        L = int(round(_log_between(rng, 2, 16)))
+        d = _multiple_of_8(_log_between(rng, 64, 2304), rng)
+        F = _multiple_of_8(d * _log_between(rng, 2, 16), rng)
+        B = int(round(_log_between(rng, 32, 4096)))
+        if rng.random() < 0.5 and B >= 64:
+            B = B // 64 * 64
+        P = L * (L + 1) // 2
+        params = (P + L) * F * d
+        flop = (2 * L + 3 * P) * 2.0 * B * F * d
+        # no more work and memory than the largest listed cases of the type
+        if F <= 16384 and (flop <= 2.4e12 and params <= 7e8 if dtype == "f32" else flop <= 5e13 and params <= 1.6e9):
+            break
+    int8 = dtype == "bf16" and rng.random() < 0.3
+    topk = int(_log_between(rng, 4, 64)) if kind != "normalise" and F >= 512 and rng.random() < 0.15 else 0
+    density = 0.0 if topk or rng.random() < 0.5 else round(_log_between(rng, 0.001, 0.05), 4)
+    mode = "auto" if (topk or density) and rng.random() < 0.6 else "dense"
+    dead = kind in ("step", "grads") and not topk and rng.random() < 0.25
+    c = _case("", kind, L, d, F, B, dtype, int8, kind == "step" and dtype == "bf16" and rng.random() < 0.2,
+              rng.random() < 0.75, mode, density, topk, dead and rng.random() < 0.5,
+              0.0 if topk else rng.choice([2.0, 12.0]), 0.1 if dead else 0.0, rng.random() < 0.3)
+    del c["name"]
+    return c
+
+
+def _quantize_rows(t):
+    absmax = t.abs().amax(dim=2)
+    s = torch.where(absmax > 0, absmax / 127.0, torch.ones_like(absmax))
+    return torch.clamp(torch.round(t / s[:, :, None]), -127, 127).to(torch.int8), s
+
+
+def _thresholds(case, x, W_enc):
+    """[L, F]: 0.03, or per layer the value that a `density` share of its pre-activations exceeds (on a sample)."""
+    L, d, F, B = case["L"], case["d"], case["F"], case["B"]
+    theta = torch.full((L, F), 0.03, device=DEVICE)
+    if case["density"]:
+        for l in range(L):
+            pre = (x[l, :512] @ W_enc[l, :, :2048]).reshape(-1)[:1 << 20]
+            kth = max(1, int(round(pre.numel() * (1.0 - case["density"]))))
+            theta[l] = torch.kthvalue(pre, kth).values.clamp_min(1e-3)
+    return theta.log() if case["log_theta"] else theta
+
+
+def prepare(case, seed):
+    L, d, F, B, kind = case["L"], case["d"], case["F"], case["B"], case["kind"]
+    P, bf16 = L * (L + 1) // 2, case["dtype"] == "bf16"
+    T = torch.bfloat16 if bf16 else torch.float32
+    g = torch.Generator(device=DEVICE).manual_seed(int(seed))
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device=DEVICE)
+
+    # residual-stream-like inputs, norms growing with depth; targets correlated from layer to layer
+    x = normal(L, B, d) * (1.0 + 0.25 * torch.arange(L, device=DEVICE))[:, None, None]
+    if case["heavy"]:
+        x *= torch.exp(0.5 * normal(B))[None, :, None]
+        x[:, :, torch.randperm(d, generator=g, device=DEVICE)[:4]] *= 20.0
+    y = normal(L, B, d)
+    for l in range(1, L):
+        y[l] += 0.7 * y[l - 1]
+    state = {"case": case}
+    if kind == "normalise":
+        if case["int8"]:
+            state["a"], state["scale"] = _quantize_rows(x)
+            state["out"] = torch.empty_like(state["scale"])
+        else:
+            state["a"], state["scale"] = x.to(T), None
+            state["out"] = torch.empty_like(state["a"])
+        cfg = K.make_config(L, d, F, B, K.DTYPE_BF16 if bf16 else K.DTYPE_F32,
+                            K.INPUT_INT8_ROWSCALE if case["int8"] else K.INPUT_NATIVE)
+        workspace = torch.empty(K.clt_workspace_bytes(cfg), dtype=torch.uint8, device=DEVICE)
+        state["handle"] = K.clt_init(cfg, workspace)
+        state["norm_sum"] = torch.zeros(L, dtype=torch.float64, device=DEVICE)
+        return state
+
+    a = 1.0 / math.sqrt(d)
+    W_enc = torch.rand((L, d, F), generator=g, device=DEVICE).mul_(2 * a).sub_(a)
+    W_dec = torch.empty((P, F, d), dtype=T, device=DEVICE)
+    master_dec = torch.empty((P, F, d), device=DEVICE) if case["master"] else None
+    for p in range(P):       # block by block: small temporaries
+        w = torch.rand((F, d), generator=g, device=DEVICE).mul_(2 * a).sub_(a)
+        W_dec[p] = w
+        if master_dec is not None:
+            master_dec[p] = w
+    theta = _thresholds(case, x, W_enc)
+    params = {"W_enc": W_enc.to(T), "b_enc": 0.01 * normal(L, F), "theta": theta, "W_dec": W_dec, "b_dec": 0.01 * normal(L, d)}
+    x_scale = y_scale = None
+    if case["int8"]:
+        x, x_scale = _quantize_rows(x)
+        y, y_scale = _quantize_rows(y)
+    else:
+        x, y = x.to(T), y.to(T)
+    state.update(x=x, y=y, x_scale=x_scale, y_scale=y_scale, params=params, t=FIRST_STEP, master=None, m=None, v=None)
+    if kind == "step":
+        if case["master"]:
+            state["master"] = {"W_enc": W_enc, "W_dec": master_dec}
+        # moments of a run that is under way
+        state["m"], state["v"] = {}, {}
+        for k, w in params.items():
+            m = torch.randn(w.shape, generator=g, device=DEVICE).mul_(MOMENT)
+            state["v"][k] = torch.rand(w.shape, generator=g, device=DEVICE).add_(0.5).mul_(MOMENT * MOMENT)
+            state["m"][k] = m
+    step_fused = kind == "step" and case["fused"]
+    state["step"] = K.CLTStep(L, d, F, B, dtype=case["dtype"], int8_inputs=case["int8"], master_weights=case["master"], C_=C,
+                              ste_bandwidth=WINDOW, device=DEVICE, keep_pre=case["lambda1"] > 0, decode_mode=MODES[case["mode"]],
+                              matrix_grads=kind == "grads" or (kind == "step" and not step_fused), log_threshold=case["log_theta"],
+                              topk=case["topk"] or None, reuse_decoder_norms=step_fused)
+    return state
+
+
+MOMENT = 1e-3      # size of the running gradient moments
+
+
+def run(state):
+    case = state["case"]
+    if case["kind"] == "normalise":
+        H, a, scale, out, sums = state["handle"], state["a"], state["scale"], state["out"], state["norm_sum"]
+        sums.zero_()
+        K.clt_norm_accumulate(H, a, sums, scale)
+        if case["int8"]:
+            K.clt_normalise(H, sums, case["B"], scale_in=scale, scale_out=out)
+        else:
+            K.clt_normalise(H, sums, case["B"], a_in=a, a_out=out)
+        return {"norm_sum": sums, "normalised": out}
+    st, params = state["step"], state["params"]
+    if case["kind"] == "forward":
+        st.forward(state["x"], params, state["x_scale"])
+        return {"z": st.z, "act_class": st.act_class, "y_hat": st.y_hat}
+    if case["kind"] == "step":
+        st.train_step(state["x"], state["y"], params, state["m"], state["v"], state["t"], LR_LAST if case["density"] else LR,
+                      case["lambda0"], state["master"], state["x_scale"], state["y_scale"], case["fused"], case["lambda1"])
+        state["t"] += 1
+        return {"params": params, "m": state["m"], "v": state["v"], "master": state["master"], "loss": st.loss_dev}
+    st.forward(state["x"], params, state["x_scale"])
+    st.loss(state["y"], case["lambda0"], state["y_scale"], False, case["lambda1"], params)
+    if case["kind"] == "evaluate":
+        return {"y_hat": st.y_hat, "loss": st.loss_dev}
+    st.backward(state["x"], params, state["x_scale"])
+    return {"grads": st.grads, "loss": st.loss_dev}
+
+
+def work(case):
+    """The contractions on the active features only, each operand and each result once."""
+    L, d, F, B, kind = case["L"], case["d"], case["F"], case["B"], case["kind"]
+    P, e = L * (L + 1) // 2, 2 if case["dtype"] == "bf16" else 4
+    ex = 1 if case["int8"] else e
+    if kind == "normalise":
+        return {"bytes": L * B * (d + 8.0) if case["int8"] else 2.0 * L * B * d * e, "flops": 2.0 * L * B * d}
+    lists = case["mode"] == "auto"
+    k = min(F, case["topk"] or case["density"] * F) if lists else F      # features per token that the sums run over
+    flops = 2.0 * B * d * (L * F + P * k)
+    bytes_ = L * B * d * ex + (L + P) * F * d * e
+    if kind in ("forward", "evaluate"):
+        bytes_ += 4.0 * L * B * d + (L * B * F * (e + 1.0) if kind == "forward" else L * B * d * ex)
+        return {"bytes": bytes_, "flops": flops}
+    flops += 2.0 * B * d * (2 * P + L) * k
+    bytes_ += L * B * d * ex
+    if kind == "grads":
+        bytes_ += (L + P) * F * d * e
+    else:      # weights written, both moments and the master copy read and written
+        bytes_ += (L + P) * F * d * (e + 16.0 + (8.0 if case["master"] else 0.0))
+    return {"bytes": bytes_, "flops": flops}
+
+
+def tolerance(case):
+    """Four times what the path differs by from itself with tokens, features and columns in another order (every sum in
+    another order, results put back).  Largest of it are the entries whose pre-activation lies within rounding of the
+    threshold or of its window and falls on the other side: gradients of theta 2.4e-3 (bf16) and 8.5e-4 (f32) over the
+    tensor, and single entries of sparse gradients by about their own size."""
+    bf16 = case["dtype"] == "bf16"
+    if case["kind"] == "normalise":      # fp32 row norms; the division rounds to the storage type
+        return {"rel": 1e-3, "max": 2e-2} if bf16 else {"rel": 2e-6, "max": 2e-5}
+    if case["kind"] in ("forward", "evaluate"):      # 4.5e-5 (bf16), 4e-7 (f32)
+        return {"rel": 1e-3 if bf16 else 1e-5, "max": 0.9, "differ": 1e-4}
+    return {"rel": 1e-2 if bf16 else 4e-3, "max": 0.9}
