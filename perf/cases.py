@@ -223,6 +223,105 @@ def run(state):
     return {"grads": st.grads, "loss": st.loss_dev}
 
 
+def _exact_forward(case, state):
+    """64-bit forward: inputs, targets, pre-activations, active set, features, decoder norms, reconstruction."""
+    L, F, par = case["L"], case["F"], state["params"]
+    x, y = state["x"].double(), state["y"].double()
+    if case["int8"]:
+        x, y = x * state["x_scale"].double()[:, :, None], y * state["y_scale"].double()[:, :, None]
+    theta = par["theta"].double().exp() if case["log_theta"] else par["theta"].double()
+    y_hat = par["b_dec"].double()[:, None, :].repeat(1, case["B"], 1)
+    n2 = torch.zeros((L, F), dtype=torch.float64, device=DEVICE)
+    pre, active = [], []
+    p = 0
+    for l in range(L):
+        pre.append(x[l] @ par["W_enc"][l].double() + par["b_enc"][l].double())
+        if case["topk"]:
+            a = torch.zeros_like(pre[l], dtype=torch.bool)
+            active.append(a.scatter_(1, pre[l].topk(case["topk"], dim=1).indices, True))
+        else:
+            active.append(pre[l] > theta[l])
+        z = pre[l] * active[l]
+        for lp in range(l, L):      # blocks are packed by source
+            w = par["W_dec"][p].double()
+            y_hat[lp] += z @ w
+            n2[l] += (w * w).sum(1)
+            p += 1
+    return x, y, theta, pre, active, n2.sqrt(), y_hat
+
+
+def exact(case, seed):
+    """What `run` returns, from the method's definition in 64-bit torch."""
+    state = prepare(case, seed)
+    L, B, kind = case["L"], case["B"], case["kind"]
+    if kind == "normalise":
+        a = state["a"].double()
+        if case["int8"]:
+            a = a * state["scale"].double()[:, :, None]
+        sums = a.norm(dim=2).sum(1)
+        out = state["scale"].double() if case["int8"] else a
+        return {"norm_sum": sums, "normalised": out / (sums / B).view(-1, *[1] * (out.dim() - 1))}
+    del state["step"]
+    x, y, theta, pre, active, n, y_hat = _exact_forward(case, state)
+    if kind == "forward":
+        return {"z": torch.stack([p * a for p, a in zip(pre, active)]), "act_class": None, "y_hat": y_hat}
+    lam0, lam1, par = case["lambda0"] / B, case["lambda1"] / B, state["params"]
+    r = y_hat - y
+    rec, sp, dead = (r * r).sum() / B, 0.0, 0.0
+    dy = 2.0 / B * r
+    m, v, master = state["m"], state["v"], state["master"]
+    out = {"params": {}, "m": {}, "v": {}, "master": {}} if kind == "step" else {k: torch.empty_like(w, dtype=torch.float64) for k, w in par.items()}
+    if kind == "step":
+        for g in ("params", "m", "v"):
+            out[g] = {k: torch.empty_like(w, dtype=torch.float64) for k, w in par.items()}
+        out["master"] = {k: out["params"][k] for k in MATRICES} if master else None
+    lr = LR_LAST if case["density"] else LR
+
+    def give(name, i, g):      # one layer's or block's gradient: as it is, or through Adam
+        if kind != "step":
+            out[name][i] = g
+            return
+        mi, vi = 0.9 * m[name][i].double() + 0.1 * g, 0.999 * v[name][i].double() + 0.001 * g * g
+        w = (master[name] if master and name in MATRICES else par[name])[i].double()
+        step = mi / (1 - 0.9 ** state["t"]) / ((vi / (1 - 0.999 ** state["t"])).sqrt() + 1e-8)
+        out["params"][name][i], out["m"][name][i], out["v"][name][i] = w - lr * step, mi, vi
+
+    p = 0
+    for l in range(L):
+        z, below = pre[l] * active[l], pre[l] < theta[l]
+        th = torch.tanh(C * z * n[l])
+        sp += lam0 * th.sum()
+        sech2 = 1.0 - th * th
+        G = lam0 * (C * z * sech2).sum(0)
+        dz = lam0 * C * n[l] * sech2
+        if lam1:
+            gap = (theta[l] - pre[l]).clamp_min(0)
+            dead += lam1 * (gap * n[l]).sum()
+            G += lam1 * gap.sum(0)
+        if kind == "evaluate":
+            continue
+        for lp in range(l, L):
+            w = par["W_dec"][p].double()
+            dz += dy[lp] @ w.T
+            give("W_dec", p, z.T @ dy[lp] + (G / n[l].clamp_min(1e-30))[:, None] * w)
+            p += 1
+        dpre = dz * active[l]
+        dtheta = torch.zeros_like(theta[l])
+        if not case["topk"]:
+            dtheta = -theta[l] / WINDOW * (dz * ((pre[l] - theta[l]).abs() < WINDOW / 2)).sum(0)
+        if lam1:
+            dpre -= lam1 * n[l] * below
+            dtheta += lam1 * n[l] * below.sum(0)
+        give("W_enc", l, x[l].T @ dpre)
+        give("b_enc", l, dpre.sum(0))
+        give("theta", l, dtheta * theta[l] if case["log_theta"] else dtheta)
+        give("b_dec", l, dy[l].sum(0))
+    loss = torch.stack([torch.as_tensor(q, dtype=torch.float64, device=DEVICE) for q in (rec + sp + dead, rec, sp, dead)])
+    if kind == "evaluate":
+        return {"y_hat": y_hat, "loss": loss}
+    return dict(out, loss=loss) if kind == "step" else {"grads": out, "loss": loss}
+
+
 def work(case):
     """The contractions on the active features only, each operand and each result once."""
     L, d, F, B, kind = case["L"], case["d"], case["F"], case["B"], case["kind"]
