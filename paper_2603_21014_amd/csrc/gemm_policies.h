@@ -11,6 +11,7 @@
 //   M, N, kseg   tile-space extents and the length of one K segment
 //   ginfo(order) group visited at position `order` of the launch (longest K first)
 //   nseg(gi), a_seg(gi,s), b_seg(gi,s)   K segments of a group
+//   krange(gi, spseg)   the group's share of the K steps, counted through its segments at spseg steps each
 //   epi_begin(st, gi, col, ok, row0)   once per tile and lane: loads what depends on the lane's
 //                columns only (biases, thresholds, norms) when `ok` (col inside the matrix); row0 is the
 //                first row of the block whose rows this lane will see (wave-uniform in the bf16 kernel)
@@ -98,6 +99,9 @@ __device__ __forceinline__ X* epi_ptr(X* base, size_t uoff, uint32_t loff) {
   return reinterpret_cast<X*>(reinterpret_cast<Byte*>(base + uoff) + loff * (uint32_t)sizeof(X));
 }
 
+// A run of K steps, counted from the start of the group's first segment.
+struct KRange { int first, count; };
+
 // Adam fused into a weight-gradient epilogue: the fp32 gradient of 4 consecutive
 // parameters goes straight from the accumulators into the moments and the
 // weights (App. C Table 1 update rule; same arithmetic as adam_kernel).
@@ -150,6 +154,7 @@ struct EncPolicy {
   struct Epi { int count; float4 b, th; };
   __device__ GInfo ginfo(int order) const { return {order}; }
   __device__ int nseg(const GInfo&) const { return 1; }
+  __device__ KRange krange(const GInfo& g, int spseg) const { return {0, nseg(g) * spseg}; }
   __device__ const TA* a_seg(const GInfo& g, int) const { return x + (size_t)g.l * D.B * D.d; }
   __device__ const T* b_seg(const GInfo& g, int) const { return W_enc + (size_t)g.l * D.d * D.F; }
   static constexpr int EPI_BATCH = 8, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
@@ -228,6 +233,7 @@ struct DecPolicy {
   struct Epi { float4 b; };
   __device__ GInfo ginfo(int order) const { return {D.L - 1 - order}; }   // longest K first
   __device__ int nseg(const GInfo& g) const { return g.lp + 1; }
+  __device__ KRange krange(const GInfo& g, int spseg) const { return {0, nseg(g) * spseg}; }
   __device__ const T* a_seg(const GInfo&, int s) const { return z + (size_t)s * D.B * D.F; }
   __device__ const T* b_seg(const GInfo& g, int s) const {
     return W_dec + (size_t)packed_index(s, g.lp, D.L) * D.F * D.d;
@@ -279,6 +285,7 @@ struct DzPolicy {
   struct Epi { float4 karg, kamp, dead; float4 st, sb, nb; int col, prow; bool ok; };
   __device__ GInfo ginfo(int order) const { return {order}; }             // K = (L-l) d, longest first
   __device__ int nseg(const GInfo& g) const { return D.L - g.l; }
+  __device__ KRange krange(const GInfo& g, int spseg) const { return {0, nseg(g) * spseg}; }
   __device__ const T* a_seg(const GInfo& g, int s) const { return d_yhat + (size_t)(g.l + s) * D.B * D.d; }
   __device__ const T* b_seg(const GInfo& g, int s) const {
     return W_dec + (size_t)packed_index(g.l, g.l + s, D.L) * D.F * D.d;
@@ -399,6 +406,7 @@ struct DWdecPolicy {
     return {order + p0, l, l + r};
   }
   __device__ int nseg(const GInfo&) const { return 1; }
+  __device__ KRange krange(const GInfo& g, int spseg) const { return {0, nseg(g) * spseg}; }
   __device__ const T* a_seg(const GInfo& g, int) const { return z + (size_t)g.l * D.B * D.F; }
   __device__ const T* b_seg(const GInfo& g, int) const { return d_yhat + (size_t)g.lp * D.B * D.d; }
   // up to 16 registers per row group in flight: a short window while most accumulators are still live
@@ -462,6 +470,7 @@ struct DWencPolicy {
   struct Epi {};
   __device__ GInfo ginfo(int order) const { return {order}; }
   __device__ int nseg(const GInfo&) const { return 1; }
+  __device__ KRange krange(const GInfo& g, int spseg) const { return {0, nseg(g) * spseg}; }
   __device__ const TA* a_seg(const GInfo& g, int) const { return x + (size_t)g.l * D.B * D.d; }
   __device__ const T* b_seg(const GInfo& g, int) const { return dpre + (size_t)g.l * D.B * D.F; }
   static constexpr int EPI_BATCH = 4, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;

@@ -1,91 +1,197 @@
-// fp32 path of the five CLT contractions: fp32 storage, fp32 FMA accumulate
-// (no reduced-precision matrix mode), LDS-staged 64x64x16 tiles, one 4x4
-// micro-tile per lane.  This is the exact-arithmetic path used by small fp32
-// configurations; the bf16 MFMA path lives in kernels_gemm_bf16.hip.
+// fp32 path of the five CLT contractions on gfx950: fp32 storage, fp32 products and fp32 accumulation on the
+// matrix cores (v_mfma_f32_16x16x4_f32, a full-precision fused multiply-add; no reduced-precision mode).  The bf16
+// path lives in kernels_gemm_bf16.hip.
+//
+// What bounds it: the fp32 matrix rate (157 TFLOP/s nominal; a large library product reaches 153 here).  Vector FMAs
+// without packed arithmetic end at half of that, and the operand traffic is small beside either.
+//
+// Against the vector-FMA kernel before it (64x64x16 tiles, scalar loads): L = 12, d = 768, F = 6144, B = 1024: decode
+// 16.6 -> 7.9 ms (95 TFLOP/s), dz 12.0 -> 6.5 (115), dW_dec 12.2 -> 6.8 (110); L = 4, d = 64, F = 256, B = 128: decode
+// 186 -> 31 us, dz 42 -> 14, dW_dec 72 -> 36.
+//
+// One workgroup = 4 wavefronts computes a TxT tile (T = 128: 64x64 per wavefront as 4x4 accumulators; T = 64: 32x32),
+// K advances in steps of 32 through two LDS stages, two workgroups per CU cover each other's barriers.  Operands keep
+// their memory order in LDS: one that is contiguous along K as [row][32 k] (a lane reads four consecutive k of its
+// row in one go), one that is strided along K as [k][T rows] (four single reads).  Both leave the lane with k = 4 * (lane
+// / 16) + q for MFMA q of a 16-wide slice, so any pair of layouts agrees and nothing is transposed.
+// Loads go through buffer descriptors: a chunk outside the matrix gets an offset beyond the descriptor's range and
+// reads as zero, so sizes that fit no tile run the same code as those that do.
+// The MFMA's operands are swapped (D = B^T A^T): a lane then holds four consecutive columns of one row, which is what
+// the policies' epilogues take.
 #include "common.h"
 #include "gemm_policies.h"
 
 namespace clt {
 namespace {
 
-constexpr int FTM = 64, FTN = 64, FTK = 16;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-template <class P>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(P p, TileGrid tg) {
-  __shared__ float As[FTK][FTM + 4];
-  __shared__ float Bs[FTK][FTN + 4];
+constexpr int FTK = 32;
+constexpr uint32_t OUT_OF_RANGE = 0x80000000u;      // lane offset that no descriptor below covers
+
+__device__ __forceinline__ f32x4 load_chunk(const float* base, uint32_t voff) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0x7fffffff, 0x00027000);
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0));
+}
+
+// One operand's T x 32 tile: staging by 256 lanes (T / 32 chunks of 16 bytes each) and fragment reads.
+template <bool KC, int T>
+struct Operand {
+  static constexpr int NCH = T / 32;                       // chunks per lane
+  static constexpr int PITCH = KC ? FTK + 4 : T + 4;       // floats; +4 spreads the fragment reads over all banks
+  static constexpr int LDS_FLOATS = KC ? T * PITCH : FTK * PITCH;
+  static constexpr int RSTEP = KC ? 32 : 1024 / T;         // rows (KC) or k (strided) between a lane's chunks
+  uint32_t voff, ok;      // lane byte offset inside the tile; bit i: chunk i's row lies inside the matrix
+  int klane, lds;         // KC: first k of the lane's chunks; strided: the k of its first chunk
+  size_t step;            // elements between a lane's consecutive chunks (uniform)
+  __device__ __forceinline__ void init(int t, int ld, int rows_left) {
+    const int a = KC ? t >> 3 : t / (T / 4), b = KC ? (t & 7) * 4 : (t % (T / 4)) * 4;
+    voff = (uint32_t)((size_t)a * ld + b) * 4u;
+    lds = a * PITCH + b;
+    step = (size_t)RSTEP * ld;
+    klane = KC ? b : a;
+    ok = 0;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+      if ((KC ? a + RSTEP * i : b) < rows_left) ok |= 1u << i;
+  }
+  __device__ __forceinline__ void load(f32x4 (&r)[NCH], const float* base, int k_left) const {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const bool in = ((ok >> i) & 1u) && (KC ? klane : klane + RSTEP * i) < k_left;
+      r[i] = load_chunk(base + i * step, in ? voff : OUT_OF_RANGE);
+    }
+  }
+  __device__ __forceinline__ void store(float* s, const f32x4 (&r)[NCH]) const {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) *reinterpret_cast<f32x4*>(s + lds + i * RSTEP * PITCH) = r[i];
+  }
+  // fragment of the 16 rows from `row0` on for k slice `sl` (16 wide): element q is k = 16 sl + 4 (lane / 16) + q
+  __device__ __forceinline__ static f32x4 frag(const float* s, int row0, int sl, int lane) {
+    const int row = row0 + (lane & 15), k = 16 * sl + 4 * (lane >> 4);
+    if (KC) return *reinterpret_cast<const f32x4*>(s + row * PITCH + k);
+    f32x4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = s[(k + q) * PITCH + row];
+    return v;
+  }
+};
+
+template <class P, int T>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
+  constexpr int NB = T / 32, W = T / 2;      // 16-blocks per wavefront and direction, wavefront block edge
+  typedef Operand<P::A_KC, T> OA;
+  typedef Operand<P::B_KC, T> OB;
+  __shared__ __align__(16) float smem[2 * (OA::LDS_FLOATS + OB::LDS_FLOATS)];
   int gorder, tm, tn;
   if (!tg.decode(blockIdx.x, gorder, tm, tn) || p.skip()) return;
   const typename P::GInfo gi = p.ginfo(gorder);
-  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-  const int m0 = tm * FTM, n0 = tn * FTN;
-  const int M = p.M, N = p.N, kseg = p.kseg, nseg = p.nseg(gi);
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = (w >> 1) * W, wn = (w & 1) * W;
+  const int m0 = tm * T, n0 = tn * T;
+  const int M = p.M, N = p.N, kseg = p.kseg;
+  const int spseg = (kseg + FTK - 1) / FTK;
+  const KRange kr = p.krange(gi, spseg);
 
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-  for (int s = 0; s < nseg; ++s) {
-    const float* A = p.a_seg(gi, s);
-    const float* Bm = p.b_seg(gi, s);
-    for (int k0 = 0; k0 < kseg; k0 += FTK) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int idx = t + 256 * i;
-        int m, k;
-        if (P::A_KC) { m = idx >> 4; k = idx & 15; } else { k = idx >> 6; m = idx & 63; }
-        float v = 0.f;
-        if (m0 + m < M && k0 + k < kseg)
-          v = P::A_KC ? A[(size_t)(m0 + m) * p.lda + k0 + k] : A[(size_t)(k0 + k) * p.lda + m0 + m];
-        As[k][m] = v;
-        int n;
-        if (P::B_KC) { n = idx >> 4; k = idx & 15; } else { k = idx >> 6; n = idx & 63; }
-        v = 0.f;
-        if (n0 + n < N && k0 + k < kseg)
-          v = P::B_KC ? Bm[(size_t)(n0 + n) * p.ldb + k0 + k] : Bm[(size_t)(k0 + k) * p.ldb + n0 + n];
-        Bs[k][n] = v;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < FTK; ++k) {
-        const float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-        const float4 b = *reinterpret_cast<const float4*>(&Bs[k][tx * 4]);
-        const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-      }
-      __syncthreads();
+  OA oa;
+  OB ob;
+  oa.init(t, p.lda, M - m0);
+  ob.init(t, p.ldb, N - n0);
+  int seg = kr.first / spseg, k0 = (kr.first - seg * spseg) * FTK;
+  const size_t a0 = P::A_KC ? (size_t)m0 * p.lda : (size_t)m0, b0 = P::B_KC ? (size_t)n0 * p.ldb : (size_t)n0;
+  const float* Aseg = p.a_seg(gi, seg) + a0;
+  const float* Bseg = p.b_seg(gi, seg) + b0;
+  const int last = kr.first + kr.count - 1;
+  f32x4 ra[OA::NCH], rb[OB::NCH];
+  auto fetch = [&](int s) {      // step s (absolute), then the cursor moves on
+    oa.load(ra, Aseg + (P::A_KC ? (size_t)k0 : (size_t)k0 * p.lda), kseg - k0);
+    ob.load(rb, Bseg + (P::B_KC ? (size_t)k0 : (size_t)k0 * p.ldb), kseg - k0);
+    k0 += FTK;
+    if (k0 >= kseg && s < last) {
+      k0 = 0;
+      ++seg;
+      Aseg = p.a_seg(gi, seg) + a0;
+      Bseg = p.b_seg(gi, seg) + b0;
     }
+  };
+
+  f32x4 acc[NB][NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  constexpr int STAGE = OA::LDS_FLOATS + OB::LDS_FLOATS;
+  fetch(kr.first);
+  oa.store(smem, ra);
+  ob.store(smem + OA::LDS_FLOATS, rb);
+  if (kr.count > 1) fetch(kr.first + 1);
+  __syncthreads();
+  for (int kt = 0; kt < kr.count; ++kt) {
+    const float* sa = smem + (kt & 1) * STAGE;
+    const float* sb = sa + OA::LDS_FLOATS;
+#pragma unroll
+    for (int sl = 0; sl < FTK / 16; ++sl) {
+      f32x4 fa[NB], fb[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) fa[i] = OA::frag(sa, wm + 16 * i, sl, lane);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) fb[j] = OB::frag(sb, wn + 16 * j, sl, lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][q], fa[i][q], acc[i][j], 0, 0, 0);
+    }
+    // the other stage was last read before the barrier that ended the previous step
+    if (kt + 1 < kr.count) {
+      float* s = smem + ((kt + 1) & 1) * STAGE;
+      oa.store(s, ra);
+      ob.store(s + OA::LDS_FLOATS, rb);
+      if (kt + 2 < kr.count) fetch(kr.first + kt + 2);
+    }
+    __syncthreads();
   }
 
-  typename P::Epi est;
-  const int col = n0 + tx * 4;
-  p.epi_begin(est, gi, col, col < N, m0);
-  if (col < N) {
-    typename P::EpiRegs er[4];
-    EpiPos pos{m0, n0, 0, tx * 4};
+  // a lane's four columns of block j and row lane % 16 of block i
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      pos.rl = ty * 4 + i;
-      if (pos.row() < M) p.epi_load(er[i], gi, pos);
+  for (int j = 0; j < NB; ++j) {
+    typename P::Epi est;
+    EpiPos pos{m0 + wm, n0 + wn + 16 * j, lane & 15, 4 * (lane >> 4)};
+    const bool col_ok = pos.col() < N;
+    p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm);
+    typename P::EpiRegs er[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      pos.ru = m0 + wm + 16 * i;
+      if (col_ok && pos.row() < M) p.epi_load(er[i], gi, pos);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      pos.rl = ty * 4 + i;
-      if (pos.row() < M) p.epi4(est, gi, pos, make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]), er[i]);
+    for (int i = 0; i < NB; ++i) {
+      pos.ru = m0 + wm + 16 * i;
+      const f32x4 v = acc[i][j];
+      if (col_ok && pos.row() < M) p.epi4(est, gi, pos, make_float4(v[0], v[1], v[2], v[3]), er[i]);
     }
+    p.epi_end(est, gi, nullptr);
   }
-  p.epi_end(est, gi, nullptr);
 }
+
+int g_cus = 256;
 
 template <class P>
 hipError_t launch(hipStream_t s, const P& p, int G) {
-  const TileGrid tg = TileGrid::make(G, p.M, p.N, FTM, FTN);
-  hipLaunchKernelGGL((gemm_f32_kernel<P>), dim3(tg.num_wg()), dim3(256), 0, s, p, tg);
+  const TileGrid big = TileGrid::make(G, p.M, p.N, 128, 128);
+  // 128x128 tiles read each operand half as often, 64x64 tiles fill the chip at a quarter of the size: the small
+  // tile where the large one leaves half of the two workgroups per CU without work
+  if ((long)big.mt * big.nt * G >= g_cus) {
+    hipLaunchKernelGGL((gemm_f32_kernel<P, 128>), dim3(big.num_wg()), dim3(256), 0, s, p, big);
+  } else {
+    const TileGrid tg = TileGrid::make(G, p.M, p.N, 64, 64);
+    hipLaunchKernelGGL((gemm_f32_kernel<P, 64>), dim3(tg.num_wg()), dim3(256), 0, s, p, tg);
+  }
   return hipGetLastError();
 }
 

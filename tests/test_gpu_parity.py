@@ -44,6 +44,15 @@ def test_ragged_shapes_full_step(dtype, L, d, F, B):
     show(f"{dtype} L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL[dtype]))
 
 
+@pytest.mark.parametrize("d,F,B", [(136, 8200, 516), (128, 8192, 512), (264, 4104, 513)])
+def test_fp32_large_tiles(d, F, B):
+    """Enough tiles for the 128x128 fp32 kernel in the encoder, dz and weight-gradient launches, with and without
+    remainders in rows, columns and K (steps of 32)."""
+    w = S.scaled(S.WORKLOADS["tiny"], L=2, d=d, F=F, B=B, seed=51 + d)
+    g, o = run_both(w)
+    show(f"f32 large tiles d{d} F{F} B{B}", compare_step(w, g, o, TOL["f32"]))
+
+
 def test_bf16_several_tiles_and_segments():
     """Spans 2x3 output tiles of 256x256 per group and up to 4 K segments."""
     w = S.scaled(S.WORKLOADS["gpt2"], L=4, d=512, F=768, B=512, k_active=16)
