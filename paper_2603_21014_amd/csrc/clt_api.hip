@@ -23,10 +23,11 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
-  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part,
+  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part,
          fl_off, fl_cnt, fl_tok, fl_val, fl_seg, total;
   int kcap;
   int ecap;
+  DecSplit split;
 };
 
 thread_local char g_err[256] = "";
@@ -192,6 +193,12 @@ Plan make_plan(const clt_config* c) {
     per_token = std::min(FUSED_DZ_ENTRIES_PER_TOKEN_MAX, (int)(1.25 * backward_threshold(c) * F) + 32);
   p.ecap = (int)(B * (size_t)std::min(p.kcap, per_token));
   p.dz_part = o;    o += align_up((L * (L + 1) / 2) * 8 * (size_t)p.ecap * 4);
+  // fp32 partial sums of the dense decode where its K ranges are cut
+  if (c->decode_mode != CLT_DECODE_GATHER) {
+    const Dims D{c->L, c->d, c->F, c->B};
+    p.split = c->dtype == CLT_DTYPE_BF16 ? dec_split_bf16(D) : dec_split_f32(D);
+  }
+  p.split_part = o; o += align_up((size_t)p.split.groups * B * d * 4);
   p.total = o;
   return p;
 }
@@ -519,7 +526,8 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
              h->cfg.log_threshold != 0, pre32};
   const int mode = h->cfg.decode_mode;
   DecArgs da{z, W_dec, b_dec, y_hat, mode == CLT_DECODE_AUTO ? flags : nullptr, h->plan.kcap,
-             reinterpret_cast<uint32_t*>(h->ws + h->plan.xcd_sync)};
+             reinterpret_cast<uint32_t*>(h->ws + h->plan.xcd_sync), h->plan.split,
+             reinterpret_cast<float*>(h->ws + h->plan.split_part)};
   GatherLists gl{reinterpret_cast<int32_t*>(h->ws + h->plan.g_idx), reinterpret_cast<float*>(h->ws + h->plan.g_val),
                  reinterpret_cast<int32_t*>(h->ws + h->plan.g_counts),
                  reinterpret_cast<int32_t*>(h->ws + h->plan.g_counts_w), h->plan.kcap, list_stride(h->plan.kcap)};

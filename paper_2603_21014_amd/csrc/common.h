@@ -150,11 +150,22 @@ struct EncArgs {       // pre = x W_enc + b_enc; JumpReLU; classes; L0 counts
   bool log_threshold;     // theta holds tau = log(theta)
   float* pre32 = nullptr; // TopK activation: store only the fp32 pre-activation (activation applied by launch_topk_select)
 };
+// Decode with the K range of a target cut into chunks: every chunk is a group of tiles of its own and leaves fp32
+// partial sums in a slot [B][d] of the workspace, launch_decode_combine adds a target's slots up.
+struct DecSplit {
+  int chunk = 0;     // K steps of a chunk at most
+  int groups = 0;    // chunks of all targets; 0: one group per target, no partial sums
+  int spseg = 0;     // K steps of one source layer
+  __host__ __device__ int chunks(int lp) const { return ((lp + 1) * spseg + chunk - 1) / chunk; }
+};
+DecSplit dec_split_f32(Dims D);      // the cut that the shape gets (see choose_dec_split)
+DecSplit dec_split_bf16(Dims D);
 struct DecArgs {       // y_hat[lp] = sum_{l<=lp} z[l] W_dec[p(l,lp)] + b_dec[lp]
   const void* z; const void* W_dec; const float* b_dec; float* y_hat;
   const int32_t* skip_flags;   // optional decode switch (see GatherLists); NULL = always run
   int kcap;
   uint32_t* xcd_sync = nullptr;   // bf16 kernel: 8 x 64 words of pacing counters (zeroed by the launch), or NULL
+  DecSplit split; float* split_part = nullptr;   // split.groups > 0: that many slots of B * d floats
 };
 struct DzArgs {        // dz[l] = sum_{lp>=l} dyhat[lp] W_dec[p(l,lp)]^T + g_sp, kept where active|window
   const void* d_yhat; const void* W_dec; const void* z; const uint8_t* cls; const float* norms;
@@ -215,6 +226,10 @@ hipError_t launch_normalise(hipStream_t s, bool bf16, bool int8_a, Dims D, const
 // ties) -> z = pre there, 0 elsewhere; class byte CLS_ACTIVE or 0; l0[l] += k per row
 hipError_t launch_topk_select(hipStream_t s, bool bf16, Dims D, const float* pre32, int k, void* z, uint8_t* cls,
                               int32_t* l0);
+// y_hat[lp] = b_dec[lp] + the slots of target lp, in order; slots of the last target come first.  Stands down with the
+// dense decode (skip_flags).
+hipError_t launch_decode_combine(hipStream_t s, Dims D, DecSplit sp, const float* part, const float* b_dec, float* y_hat,
+                                 const int32_t* skip_flags, int kcap);
 hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_dec, float* norms);
 // the same norms from the partial sums of squares a fused weight-gradient launch left behind:
 // n[l,f] = sqrt(sum over the blocks p(l, l..L-1) and their d / 64 column runs of n2_part[p][run][f]), in that order

@@ -26,6 +26,7 @@
 #pragma once
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace clt {
@@ -97,6 +98,44 @@ template <typename X>
 __device__ __forceinline__ X* epi_ptr(X* base, size_t uoff, uint32_t loff) {
   typedef typename std::conditional<std::is_const<X>::value, const char, char>::type Byte;
   return reinterpret_cast<X*>(reinterpret_cast<Byte*>(base + uoff) + loff * (uint32_t)sizeof(X));
+}
+
+// How the decode's K ranges are cut.  Target lp sums over (lp + 1) F features, so with few tiles per target (B or d
+// small) the launch is as long as the last target's tile while most CUs stand idle: one prompt of 100 tokens at
+// L = 16, d = 2048, F = 8192 has 8 tiles per target, of 128 to 2048 K steps, for 256 CUs.  The cut is the shortest
+// schedule over 1 to 8 rounds of workgroups: rounds * (longest chunk + STEPS_PER_TILE) plus the combining pass, the
+// constant being the prologue and epilogue of a tile in K steps.  It is taken where that is at least a fifth shorter than
+// the uncut launch, which is bound by the larger of its longest tile and the mean load of a CU.
+inline DecSplit choose_dec_split(Dims D, int TM, int TN, int TK, int wgs_per_xcd, double us_per_step) {
+  constexpr int STEPS_PER_TILE = 8;
+  DecSplit best;
+  best.spseg = (D.F + TK - 1) / TK;
+  const long longest = (long)D.L * best.spseg;
+  const TileGrid one = TileGrid::make(D.L, D.B, D.d, TM, TN);
+  const double mean = (double)D.P() * best.spseg * one.mt * one.nt / (8.0 * wgs_per_xcd);
+  double cost = 0.8 * (std::max((double)longest, mean) + STEPS_PER_TILE);
+  for (int r = 1; r <= 8; ++r) {
+    // shortest chunk that fits r rounds (the bound below keeps the group count small; it never fits 8 rounds itself)
+    int lo = (int)std::max(1L, (long)D.P() * best.spseg / (72L * wgs_per_xcd)), hi = (int)longest;
+    if (lo > hi) continue;
+    auto groups = [&](int chunk) {
+      DecSplit s{chunk, 0, best.spseg};
+      for (int lp = 0; lp < D.L; ++lp) s.groups += s.chunks(lp);
+      return s.groups;
+    };
+    while (lo < hi) {
+      const int mid = lo + (hi - lo) / 2;
+      const TileGrid tg = TileGrid::make(groups(mid), D.B, D.d, TM, TN);
+      if ((long)tg.rounds * tg.per_xcd <= (long)r * wgs_per_xcd) hi = mid; else lo = mid + 1;
+    }
+    const int g = groups(lo);
+    const TileGrid tg = TileGrid::make(g, D.B, D.d, TM, TN);
+    if ((long)tg.rounds * tg.per_xcd > (long)r * wgs_per_xcd || g <= D.L) continue;
+    const double combine_us = 8.0 * g * D.B * D.d / 5e6;      // slots written and read at 5 TB/s
+    const double c = (double)r * (lo + STEPS_PER_TILE) + combine_us / us_per_step;
+    if (c < cost) { cost = c; best.chunk = lo; best.groups = g; }
+  }
+  return best;
 }
 
 // A run of K steps, counted from the start of the group's first segment.
@@ -217,9 +256,10 @@ struct EncPolicy {
 // ---------------------------------------------------------------------------
 // Cross-layer decode (eq. 3): target lp, K runs over the sources l = 0..lp.
 // ---------------------------------------------------------------------------
-template <typename T>
+// SPLIT: a group is one chunk of a target's K range and the epilogue leaves its partial sums (see DecSplit).
+template <typename T, bool SPLIT = false>
 struct DecPolicy {
-  static constexpr bool XCD_SYNC = true;
+  static constexpr bool XCD_SYNC = !SPLIT;
   static constexpr bool A_KC = true, B_KC = false;
   typedef T AType;
   Dims D;
@@ -227,25 +267,41 @@ struct DecPolicy {
   const T* z; const T* W_dec; const float* b_dec; float* y_hat;
   const int32_t* skip_flags; int kcap;
   uint32_t* xcd_sync;   // 8 counters, 64 words apart, zero at launch (or NULL): see main_loop
+  DecSplit sp; float* part;   // SPLIT only
   // the dense decode stands down when the device-side switch selected the gather path
   __device__ bool skip() const { return skip_flags && gather_selected(skip_flags, kcap); }
-  struct GInfo { int lp; };
+  struct GInfo { int lp, chunk, slot; };
   struct Epi { float4 b; };
-  __device__ GInfo ginfo(int order) const { return {D.L - 1 - order}; }   // longest K first
+  __device__ GInfo ginfo(int order) const {
+    if (!SPLIT) return {D.L - 1 - order, 0, 0};   // longest K first
+    int lp = D.L - 1, r = order;
+    while (r >= sp.chunks(lp)) { r -= sp.chunks(lp); --lp; }
+    return {lp, r, order};
+  }
   __device__ int nseg(const GInfo& g) const { return g.lp + 1; }
-  __device__ KRange krange(const GInfo& g, int spseg) const { return {0, nseg(g) * spseg}; }
+  __device__ KRange krange(const GInfo& g, int spseg) const {
+    const int steps = nseg(g) * spseg;
+    if (!SPLIT) return {0, steps};
+    const int n = sp.chunks(g.lp), first = (int)((long)g.chunk * steps / n);      // equal shares
+    return {first, (int)((long)(g.chunk + 1) * steps / n) - first};
+  }
   __device__ const T* a_seg(const GInfo&, int s) const { return z + (size_t)s * D.B * D.F; }
   __device__ const T* b_seg(const GInfo& g, int s) const {
     return W_dec + (size_t)packed_index(s, g.lp, D.L) * D.F * D.d;
   }
   static constexpr int EPI_BATCH = 8, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
-  static constexpr bool PERSISTENT = true, UNIFORM_K = false;
+  static constexpr bool PERSISTENT = !SPLIT, UNIFORM_K = false;
   struct EpiRegs {};
   __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0) const {
+    if (SPLIT) return;
     e.b = ok ? *reinterpret_cast<const float4*>(b_dec + (size_t)g.lp * D.d + col) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   __device__ void epi_load(EpiRegs&, const GInfo&, const EpiPos&) const {}
   __device__ void epi4(Epi& e, const GInfo& g, const EpiPos& pos, float4 v, const EpiRegs&) const {
+    if (SPLIT) {
+      *reinterpret_cast<float4*>(epi_ptr(part, pos.uoff((size_t)g.slot * D.B, D.d), pos.loff(D.d))) = v;
+      return;
+    }
     const float4 b = e.b;
     *reinterpret_cast<float4*>(epi_ptr(y_hat, pos.uoff((size_t)g.lp * D.B, D.d), pos.loff(D.d))) =
         make_float4(v.x + b.x, v.y + b.y, v.z + b.z, v.w + b.w);

@@ -32,6 +32,27 @@ __global__ void zero_i32_kernel(int32_t* p, int n) {
   if (i < n) p[i] = 0;
 }
 
+// ---- decode partial sums (see DecSplit): grid = (runs of 1024 elements of [B][d], targets) ----
+__global__ __launch_bounds__(256) void decode_combine_kernel(Dims D, DecSplit sp, const float* __restrict__ part,
+                                                             const float* __restrict__ b_dec, float* __restrict__ y_hat,
+                                                             const int32_t* __restrict__ skip_flags, int kcap) {
+  if (skip_flags && gather_selected(skip_flags, kcap)) return;
+  const size_t n = (size_t)D.B * D.d, i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;
+  const int lp = blockIdx.y;
+  int slot = 0;
+  for (int q = D.L - 1; q > lp; --q) slot += sp.chunks(q);
+  const int end = slot + sp.chunks(lp);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (; slot < end; ++slot) {
+    const float4 v = *reinterpret_cast<const float4*>(part + slot * n + i);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  const float4 b = *reinterpret_cast<const float4*>(b_dec + (size_t)lp * D.d + i % D.d);
+  *reinterpret_cast<float4*>(y_hat + lp * n + i) = make_float4(s.x + b.x, s.y + b.y, s.z + b.z, s.w + b.w);
+}
+
 // ---- decoder norms (App. B): one wavefront per (source layer, feature) -----
 // The L-l blocks that leave source l are contiguous in the source-major packing,
 // so feature f's rows are L-l runs of d contiguous elements.
@@ -597,6 +618,13 @@ hipError_t launch_topk_select(hipStream_t s, bool bf16, Dims D, const float* pre
   if (bf16) { if (nv4 == 2) CLT_TOPK(bf16_t, 2); else if (nv4 == 8) CLT_TOPK(bf16_t, 8); else CLT_TOPK(bf16_t, 0); }
   else { if (nv4 == 2) CLT_TOPK(float, 2); else if (nv4 == 8) CLT_TOPK(float, 8); else CLT_TOPK(float, 0); }
 #undef CLT_TOPK
+  return hipGetLastError();
+}
+
+hipError_t launch_decode_combine(hipStream_t s, Dims D, DecSplit sp, const float* part, const float* b_dec, float* y_hat,
+                                 const int32_t* skip_flags, int kcap) {
+  const dim3 grid((unsigned)(((size_t)D.B * D.d + 1023) / 1024), D.L);
+  hipLaunchKernelGGL(decode_combine_kernel, grid, dim3(256), 0, s, D, sp, part, b_dec, y_hat, skip_flags, kcap);
   return hipGetLastError();
 }
 

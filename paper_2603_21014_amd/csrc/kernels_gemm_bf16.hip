@@ -178,7 +178,9 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   // waves 0-3 stage A, waves 4-7 stage B (waves w and w+4 share a SIMD, so each SIMD holds one of each group)
   const bool loads_a = __builtin_amdgcn_readfirstlane(w) < 4;
   const int kseg = p.kseg, nseg = p.nseg(gi);
-  const int nk = nseg * ((kseg + TK - 1) / TK);
+  const int spseg = (kseg + TK - 1) / TK;
+  const KRange kr = p.krange(gi, spseg);
+  const int nk = kr.count;
 
   Stager<P::A_KC, TA> sa;
   Stager<P::B_KC, bf16_t> sb;
@@ -186,9 +188,9 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   sb.init(lt, p.ldb);
 
   // uniform cursors: current segment bases, k offset inside the segment
-  int ld_seg = 0, ld_k0 = 0;
-  const TA* Aseg = p.a_seg(gi, 0);
-  const bf16_t* Bseg = p.b_seg(gi, 0);
+  int ld_seg = kr.first / spseg, ld_k0 = (kr.first - ld_seg * spseg) * TK;
+  const TA* Aseg = p.a_seg(gi, ld_seg);
+  const bf16_t* Bseg = p.b_seg(gi, ld_seg);
   const size_t a_row0 = P::A_KC ? (size_t)m0 * p.lda : (size_t)m0;   // tile origin at k = 0
   const size_t b_row0 = P::B_KC ? (size_t)n0 * p.ldb : (size_t)n0;
   const size_t a_kstep = P::A_KC ? 1 : (size_t)p.lda, b_kstep = P::B_KC ? 1 : (size_t)p.ldb;
@@ -494,6 +496,7 @@ hipError_t init_gemm_bf16() {
   if ((e = set_lds_attr<EncPolicy<bf16_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<EncPolicy<bf16_t, int8_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DecPolicy<bf16_t>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<DecPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DzPolicy<bf16_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DzPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, false>>()) != hipSuccess) return e;
@@ -518,9 +521,16 @@ hipError_t launch_enc_bf16(hipStream_t s, Dims D, const EncArgs& a, bool int8_x)
                       0.5f * a.ste_eps, (bf16_t*)a.z, (bf16_t*)a.pre, a.cls, a.l0, a.log_threshold, a.pre32};
   return launch(s, p, D.L);
 }
+DecSplit dec_split_bf16(Dims D) { return choose_dec_split(D, TM, TN, TK, 32, 0.8); }
 hipError_t launch_dec_bf16(hipStream_t s, Dims D, const DecArgs& a) {
+  if (a.split.groups > 0) {
+    DecPolicy<bf16_t, true> p{D, D.B, D.d, D.F, D.F, D.d, (const bf16_t*)a.z, (const bf16_t*)a.W_dec, a.b_dec, a.y_hat,
+                              a.skip_flags, a.kcap, nullptr, a.split, a.split_part};
+    const hipError_t e = launch(s, p, a.split.groups);
+    return e != hipSuccess ? e : launch_decode_combine(s, D, a.split, a.split_part, a.b_dec, a.y_hat, a.skip_flags, a.kcap);
+  }
   DecPolicy<bf16_t> p{D, D.B, D.d, D.F, D.F, D.d, (const bf16_t*)a.z, (const bf16_t*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags, a.kcap,
-                      a.xcd_sync};
+                      a.xcd_sync, a.split, nullptr};
   return launch(s, p, D.L);
 }
 template <bool FOLD>

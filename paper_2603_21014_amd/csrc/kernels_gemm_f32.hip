@@ -6,8 +6,8 @@
 // without packed arithmetic end at half of that, and the operand traffic is small beside either.
 //
 // Against the vector-FMA kernel before it (64x64x16 tiles, scalar loads): L = 12, d = 768, F = 6144, B = 1024: decode
-// 16.6 -> 7.9 ms (95 TFLOP/s), dz 12.0 -> 6.5 (115), dW_dec 12.2 -> 6.8 (110); L = 4, d = 64, F = 256, B = 128: decode
-// 186 -> 31 us, dz 42 -> 14, dW_dec 72 -> 36.
+// 16.6 -> 7.9 ms (95 TFLOP/s; 6.2 with its K ranges cut), dz 12.0 -> 6.0 (126), dW_dec 12.2 -> 6.8 (110); L = 4, d = 64,
+// F = 256, B = 128: decode 186 -> 31 us (12 cut), dz 42 -> 14, dW_dec 72 -> 37.
 //
 // One workgroup = 4 wavefronts computes a TxT tile (T = 128: 64x64 per wavefront as 4x4 accumulators; T = 64: 32x32),
 // K advances in steps of 32 through two LDS stages, two workgroups per CU cover each other's barriers.  Operands keep
@@ -116,11 +116,23 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
     }
   };
 
-  f32x4 acc[NB][NB];
+  // sums over 128 k at a time, added up in `tot`: the rounding errors of a long K grow with the number of partial
+  // sums and the length of one, not with K (K = 768: rms error of the
+  // pre-activations 2.1e-7 instead of 5.0e-7 with one running sum)
+  constexpr int STEPS_PER_SUM = 4;
+  f32x4 acc[NB][NB], tot[NB][NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NB; ++j) acc[i][j] = tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { tot[i][j][q] += acc[i][j][q]; acc[i][j][q] = 0.f; }
+  };
 
   constexpr int STAGE = OA::LDS_FLOATS + OB::LDS_FLOATS;
   fetch(kr.first);
@@ -131,20 +143,25 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
   for (int kt = 0; kt < kr.count; ++kt) {
     const float* sa = smem + (kt & 1) * STAGE;
     const float* sb = sa + OA::LDS_FLOATS;
+    f32x4 fa[2][NB], fb[2][NB];
+    auto read = [&](int sl) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) fa[sl][i] = OA::frag(sa, wm + 16 * i, sl, lane);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) fb[sl][j] = OB::frag(sb, wn + 16 * j, sl, lane);
+    };
+    read(0);
+    if ((kt & (STEPS_PER_SUM - 1)) == 0) flush();     // covers the read latency
 #pragma unroll
     for (int sl = 0; sl < FTK / 16; ++sl) {
-      f32x4 fa[NB], fb[NB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i) fa[i] = OA::frag(sa, wm + 16 * i, sl, lane);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) fb[j] = OB::frag(sb, wn + 16 * j, sl, lane);
+      if (sl == 0) read(1);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int i = 0; i < NB; ++i)
 #pragma unroll
           for (int j = 0; j < NB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][q], fa[i][q], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl][j][q], fa[sl][i][q], acc[i][j], 0, 0, 0);
     }
     // the other stage was last read before the barrier that ended the previous step
     if (kt + 1 < kr.count) {
@@ -156,6 +173,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
     __syncthreads();
   }
 
+  flush();
   // a lane's four columns of block j and row lane % 16 of block i
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
@@ -172,21 +190,21 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       pos.ru = m0 + wm + 16 * i;
-      const f32x4 v = acc[i][j];
+      const f32x4 v = tot[i][j];
       if (col_ok && pos.row() < M) p.epi4(est, gi, pos, make_float4(v[0], v[1], v[2], v[3]), er[i]);
     }
     p.epi_end(est, gi, nullptr);
   }
 }
 
-int g_cus = 256;
+constexpr int CUS = 256;
 
 template <class P>
-hipError_t launch(hipStream_t s, const P& p, int G) {
+hipError_t launch(hipStream_t s, const P& p, int G, int tile = 0) {
   const TileGrid big = TileGrid::make(G, p.M, p.N, 128, 128);
   // 128x128 tiles read each operand half as often, 64x64 tiles fill the chip at a quarter of the size: the small
   // tile where the large one leaves half of the two workgroups per CU without work
-  if ((long)big.mt * big.nt * G >= g_cus) {
+  if (tile ? tile == 128 : (long)big.mt * big.nt * G >= CUS) {
     hipLaunchKernelGGL((gemm_f32_kernel<P, 128>), dim3(big.num_wg()), dim3(256), 0, s, p, big);
   } else {
     const TileGrid tg = TileGrid::make(G, p.M, p.N, 64, 64);
@@ -203,8 +221,25 @@ hipError_t launch_enc_f32(hipStream_t s, Dims D, const EncArgs& a) {
                      0.5f * a.ste_eps, (float*)a.z, (float*)a.pre, a.cls, a.l0, a.log_threshold, a.pre32};
   return launch(s, p, D.L);
 }
+// The tile that the decode is cut for: with less than 32 of the large tile's K steps per CU there is too little work to
+// share out in large tiles.
+static int dec_tile(Dims D) {
+  const double steps = (double)D.P() * ((D.F + FTK - 1) / FTK) * ((D.B + 127) / 128) * ((D.d + 127) / 128);
+  return steps >= 32.0 * CUS ? 128 : 64;
+}
+DecSplit dec_split_f32(Dims D) {
+  const int T = dec_tile(D);
+  return choose_dec_split(D, T, T, FTK, (T == 128 ? 2 : 4) * CUS / 8, T == 128 ? 3.4 : 1.0);
+}
 hipError_t launch_dec_f32(hipStream_t s, Dims D, const DecArgs& a) {
-  DecPolicy<float> p{D, D.B, D.d, D.F, D.F, D.d, (const float*)a.z, (const float*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags, a.kcap, nullptr};
+  if (a.split.groups > 0) {
+    DecPolicy<float, true> p{D, D.B, D.d, D.F, D.F, D.d, (const float*)a.z, (const float*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags,
+                             a.kcap, nullptr, a.split, a.split_part};
+    const hipError_t e = launch(s, p, a.split.groups, dec_tile(D));
+    return e != hipSuccess ? e : launch_decode_combine(s, D, a.split, a.split_part, a.b_dec, a.y_hat, a.skip_flags, a.kcap);
+  }
+  DecPolicy<float> p{D, D.B, D.d, D.F, D.F, D.d, (const float*)a.z, (const float*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags, a.kcap,
+                     nullptr, a.split, nullptr};
   return launch(s, p, D.L);
 }
 hipError_t launch_dz_f32(hipStream_t s, Dims D, const DzArgs& a) {

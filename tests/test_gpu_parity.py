@@ -53,6 +53,19 @@ def test_fp32_large_tiles(d, F, B):
     show(f"f32 large tiles d{d} F{F} B{B}", compare_step(w, g, o, TOL["f32"]))
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,d,F,B", [
+    (4, 136, 2056, 33),      # K of a source layer: 32 full steps of 64 and a remainder, chunks that cross layers
+    (3, 512, 1544, 256),     # full row and column tiles
+    (7, 264, 520, 300),
+])
+def test_decode_with_cut_k_ranges(dtype, L, d, F, B):
+    """Few tiles per target: the decode cuts the targets' K ranges and adds fp32 partial sums."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype=dtype, L=L, d=d, F=F, B=B, seed=61 + L)
+    g, o = run_both(w)
+    show(f"cut decode {dtype} L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL[dtype]))
+
+
 def test_bf16_several_tiles_and_segments():
     """Spans 2x3 output tiles of 256x256 per group and up to 4 K segments."""
     w = S.scaled(S.WORKLOADS["gpt2"], L=4, d=512, F=768, B=512, k_active=16)
