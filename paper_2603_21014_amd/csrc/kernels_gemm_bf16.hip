@@ -71,6 +71,14 @@ template <> __device__ __forceinline__ u32x4 load8<int8_t>(const int8_t* p) {
   u32x4 r = {q[0], q[1], 0u, 0u};
   return r;
 }
+// the same through a buffer descriptor over the 4 GB from `base` on; a lane offset beyond them reads as zeros
+template <typename TE> __device__ __forceinline__ u32x4 buffer_load8(const char* base, uint32_t voff) {
+  const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0xffffff00u, 0x00027000);
+  if (sizeof(TE) == 2) return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)voff, 0, 0));
+  const u32x2 q = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(d, (int)voff, 0, 0));
+  u32x4 r = {q[0], q[1], 0u, 0u};
+  return r;
+}
 template <typename TE> __device__ __forceinline__ u32x4 cook8(u32x4 raw);
 template <> __device__ __forceinline__ u32x4 cook8<bf16_t>(u32x4 raw) { return raw; }
 template <> __device__ __forceinline__ u32x4 cook8<int8_t>(u32x4 raw) {
@@ -86,15 +94,19 @@ template <> __device__ __forceinline__ u32x4 cook8<int8_t>(u32x4 raw) {
 //                         and transposes it in registers before the LDS write.
 // Addresses are a wave-uniform base (tile origin, advanced along K by the
 // caller) plus one 32-bit per-lane byte offset that never changes, so a load
-// needs a single address register.  The EDGE variants predicate every chunk
-// and redirect out-of-range ones to the tensor base (always readable); those
-// chunks reach LDS as zeros.
+// needs a single address register.  The EDGE variants load through a buffer
+// descriptor at that base: a chunk outside the matrix gets a lane offset that
+// the descriptor does not cover and comes back as zeros, so nothing is kept or
+// selected between the load and the LDS write (with selects there, L = 6,
+// d = 2056, F = 8200, 4100 tokens: dW_dec 5.4 ms, decode 4.1; now 4.3 and 3.5.
+// One prompt of 100 tokens, d = 2048, F = 8192, L = 16: decode 1.36 -> 1.03 ms).
 // ---------------------------------------------------------------------------
 template <bool KC, typename TE>
 struct Stager {
   uint32_t voff;       // per-lane byte offset inside the tile
   uint32_t step;       // byte distance between the lane's consecutive chunks (uniform)
   int r_lane, k_lane;  // EDGE only: first row / k index of this lane inside the tile
+  static constexpr uint32_t OUT_OF_RANGE = 0xffffff00u;
 
   __device__ __forceinline__ void init(int lt, int ld) {
     if (KC) {
@@ -108,16 +120,9 @@ struct Stager {
     }
   }
   // tile_base = operand + tile origin (row r0, k index k0), uniform
-  // EDGE: chunks outside the matrix are read from the tensor base and must reach LDS as zeros.  A
-  // K-contiguous operand remembers which chunks lie inside (bit i of `inside`) and zeroes the others
-  // when the tile goes to LDS, so that nothing is computed on the loaded registers here; a
-  // K-strided one zeroes them at once (its transposition mixes all 8 registers, and keeping the
-  // predicates until then costs the predicated code more registers than it has).
   template <bool EDGE>
-  __device__ __forceinline__ void load(u32x4 (&r)[8], uint32_t& inside, const TE* seg_base, const TE* tile_base,
-                                       int rows_left, int k_left) const {
+  __device__ __forceinline__ void load(u32x4 (&r)[8], const TE* tile_base, int rows_left, int k_left) const {
     const char* b = reinterpret_cast<const char*>(tile_base);
-    uint32_t in = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const char* bi = b + (size_t)i * step;            // uniform
@@ -126,25 +131,17 @@ struct Stager {
       } else {
         const bool ok = KC ? (r_lane + 32 * i < rows_left && k_lane < k_left)
                            : (r_lane < rows_left && k_lane + i < k_left);
-        const TE* ptr = ok ? reinterpret_cast<const TE*>(bi + voff) : seg_base;
-        const u32x4 v = load8<TE>(ptr);
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        if (KC) { r[i] = v; in |= (ok ? 1u : 0u) << i; }
-        else r[i] = ok ? v : zero;
+        r[i] = buffer_load8<TE>(bi, ok ? voff : OUT_OF_RANGE);
       }
     }
-    if (EDGE && KC) inside = in;
   }
-  template <bool EDGE>
-  __device__ __forceinline__ void store(bf16_t* lds, const u32x4 (&r)[8], uint32_t inside, int lt) const {
+  __device__ __forceinline__ void store(bf16_t* lds, const u32x4 (&r)[8], int lt) const {
     if (KC) {
       const int c = lt & 7;
-      const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int row = (lt >> 3) + 32 * i;
-        const u32x4 v = cook8<TE>(r[i]);
-        *reinterpret_cast<u32x4*>(lds + lds_off(row, c)) = (!EDGE || ((inside >> i) & 1u)) ? v : zero;
+        *reinterpret_cast<u32x4*>(lds + lds_off(row, c)) = cook8<TE>(r[i]);
       }
     } else {
       const int nb = lt & 31, kb = lt >> 5;
@@ -195,11 +192,10 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   const size_t b_row0 = P::B_KC ? (size_t)n0 * p.ldb : (size_t)n0;
   const size_t a_kstep = P::A_KC ? 1 : (size_t)p.lda, b_kstep = P::B_KC ? 1 : (size_t)p.ldb;
   u32x4 rg[8];
-  uint32_t rg_inside = 0;   // EDGE, K-contiguous operand: which of the 8 chunks lie inside the matrix
 
   auto fetch = [&]() {
-    if (loads_a) sa.template load<EDGE>(rg, rg_inside, Aseg, Aseg + a_row0 + ld_k0 * a_kstep, p.M - m0, kseg - ld_k0);
-    else sb.template load<EDGE>(rg, rg_inside, Bseg, Bseg + b_row0 + ld_k0 * b_kstep, p.N - n0, kseg - ld_k0);
+    if (loads_a) sa.template load<EDGE>(rg, Aseg + a_row0 + ld_k0 * a_kstep, p.M - m0, kseg - ld_k0);
+    else sb.template load<EDGE>(rg, Bseg + b_row0 + ld_k0 * b_kstep, p.N - n0, kseg - ld_k0);
     ld_k0 += TK;
     if (ld_k0 >= kseg) {
       ld_k0 = 0;
@@ -232,8 +228,8 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   };
   auto stage = [&](int st) {
     bf16_t* base = smem + st * STAGE_ELEMS;
-    if (loads_a) sa.template store<EDGE>(base, rg, rg_inside, lt);
-    else sb.template store<EDGE>(base + 256 * TK, rg, rg_inside, lt);
+    if (loads_a) sa.store(base, rg, lt);
+    else sb.store(base + 256 * TK, rg, lt);
   };
 
   // v_mfma_f32_16x16x32_bf16: a lane's fragment is 8 consecutive k of row lane%16; lane group lane/16 takes
@@ -433,8 +429,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_bf16_kernel(P p, TileGrid tg, i
       epilogue<P, false>(p, gi, m0, n0, smem, acc, t);
     } else {
       const bool inside = (m0 + TM <= p.M) && (n0 + TN <= p.N);
-      if (inside && p.kseg % TK == 0) main_loop<P, false>(p, gi, m0, n0, smem, acc, t, sync_count);
-      else main_loop<P, true>(p, gi, m0, n0, smem, acc, t, sync_count);
+      main_loop<P, true>(p, gi, m0, n0, smem, acc, t, sync_count);
       if (inside) epilogue<P, false>(p, gi, m0, n0, smem, acc, t);
       else epilogue<P, true>(p, gi, m0, n0, smem, acc, t);
     }

@@ -28,10 +28,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int FTK = 32;
-constexpr uint32_t OUT_OF_RANGE = 0x80000000u;      // lane offset that no descriptor below covers
+constexpr uint32_t OUT_OF_RANGE = 0xffffff00u;      // lane offset that no descriptor below covers
 
 __device__ __forceinline__ f32x4 load_chunk(const float* base, uint32_t voff) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0x7fffffff, 0x00027000);
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0xffffff00u, 0x00027000);
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0));
 }
 
