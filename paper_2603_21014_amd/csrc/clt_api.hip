@@ -139,7 +139,7 @@ float backward_threshold(const clt_config* c) {
 Plan make_plan(const clt_config* c) {
   const size_t L = c->L, d = c->d, F = c->F, B = c->B;
   const size_t esz = c->dtype == CLT_DTYPE_BF16 ? 2 : 4;
-  // row blocks of the column-partial arrays: 32-row blocks of the reduction kernels, or the 128-row half
+  // row blocks of the column-partial arrays: at most 32-row blocks of the reduction kernels, or the 128-row half
   // tiles of the dz epilogue that folds the straight-through reductions in (whichever is more)
   const size_t rbs = row_blocks(c->B) > fold_row_blocks(c->B) ? row_blocks(c->B) : fold_row_blocks(c->B);
   const size_t wide = F > d ? F : d;
@@ -152,9 +152,12 @@ Plan make_plan(const clt_config* c) {
   p.part_cols = o;  o += align_up(rbs * L * wide * 4);
   p.part_cols2 = o; o += align_up(rbs * L * F * 4);
   p.part_cols3 = o; o += align_up(rbs * L * F * 4);
-  p.part_rec = o;   o += align_up(rbs * L * 8);
-  p.part_sp = o;    o += align_up(rbs * L * 8);
-  p.part_dead = o;  o += align_up(rbs * L * 8);
+  const Dims dims{c->L, c->d, c->F, c->B};
+  const bool bf16 = c->dtype == CLT_DTYPE_BF16;
+  // (part_rec also holds the L * row_blocks(B) partial sums of clt_norm_accumulate)
+  p.part_rec = o;   o += align_up(L * std::max<size_t>(reduce_grid(bf16, dims, c->d).blocks(), row_blocks(c->B)) * 8);
+  p.part_sp = o;    o += align_up(L * (size_t)reduce_grid(bf16, dims, c->F).blocks() * 8);
+  p.part_dead = o;  o += align_up(L * (size_t)reduce_grid(bf16, dims, c->F).blocks() * 8);
   p.l0 = o;         o += align_up(L * 4);
   p.flags = o;      o += align_up(4 * 4);
   p.xcd_sync = o;   o += align_up(8 * 64 * 4);   // pacing counters of the dense decode, one 256-byte line per XCD
@@ -572,7 +575,7 @@ int clt_loss(clt_handle* h, void* stream, const void* y, const float* y_scale, c
   if (h->stage < 1) { set_err(h->err, "clt_loss: call clt_forward first (decoder norms missing)"); return CLT_ERR_STATE; }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const Dims D = h->D;
-  const int rbs = row_blocks(D.B);
+  const ReduceGrid rgd = reduce_grid(h->bf16, D, D.d), rgf = reduce_grid(h->bf16, D, D.F);
   float* norms = reinterpret_cast<float*>(h->ws + h->plan.norms);
   float* G = reinterpret_cast<float*>(h->ws + h->plan.G);
   float* part = reinterpret_cast<float*>(h->ws + h->plan.part_cols);
@@ -586,11 +589,11 @@ int clt_loss(clt_handle* h, void* stream, const void* y, const float* y_scale, c
   // before the same partial buffer is reused for the db_dec partials of the reconstruction pass
   RUN(h, s, K_LOSS_SP, launch_loss_sparsity(s, h->bf16, D, z, norms, h->cfg.C, psp, part, dead ? pre : nullptr, theta,
                                             h->cfg.log_threshold != 0, pdead, part2));
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part, rbs, D.L * D.F, lambda0 / (float)D.B, nullptr, 0.f, G));
+  RUN(h, s, K_COLRED, launch_col_reduce(s, part, rgf.rbs, D.L * D.F, lambda0 / (float)D.B, nullptr, 0.f, G));
   if (dead)
-    RUN(h, s, K_COLRED, launch_col_reduce(s, part2, rbs, D.L * D.F, lambda1 / (float)D.B, nullptr, 0.f, G, true));
+    RUN(h, s, K_COLRED, launch_col_reduce(s, part2, rgf.rbs, D.L * D.F, lambda1 / (float)D.B, nullptr, 0.f, G, true));
   RUN(h, s, K_LOSS_REC, launch_loss_rec(s, h->bf16, h->int8, D, y_hat, y, y_scale, d_yhat, prec, part));
-  RUN(h, s, K_LOSS_FINAL, launch_loss_final(s, prec, rbs * D.L, psp, rbs * D.L, dead ? pdead : nullptr,
+  RUN(h, s, K_LOSS_FINAL, launch_loss_final(s, prec, rgd.blocks() * D.L, psp, rgf.blocks() * D.L, dead ? pdead : nullptr,
                                             1.0f / (float)D.B, lambda0, lambda1, loss_dev));
   h->lambda0 = lambda0;
   h->lambda1 = lambda1;
@@ -610,7 +613,7 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
                          float* gb_enc, float* gtheta, void* gW_dec, float* gb_dec, const AdamFuseArgs& fenc,
                          const AdamFuseArgs& fdec) {
   const Dims D = h->D;
-  const int rbs = row_blocks(D.B);
+  const int rbs = reduce_grid(h->bf16, D, D.F).rbs;
   float* norms = reinterpret_cast<float*>(h->ws + h->plan.norms);
   float* G = reinterpret_cast<float*>(h->ws + h->plan.G);
   float* part = reinterpret_cast<float*>(h->ws + h->plan.part_cols);
@@ -621,7 +624,7 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   const float lam1_over_b = h->lambda1 / (float)D.B;
 
   // db_dec from the column partials that clt_loss left behind
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part, rbs, D.L * D.d, 1.0f, nullptr, 0.f, gb_dec));
+  RUN(h, s, K_COLRED, launch_col_reduce(s, part, reduce_grid(h->bf16, D, D.d).rbs, D.L * D.d, 1.0f, nullptr, 0.f, gb_dec));
   // Backward through the decoder: dense GEMMs, or the gather kernels on the lists of the forward
   // pass when the device-side switch selected them (AUTO enqueues both; the one not selected
   // returns at once).

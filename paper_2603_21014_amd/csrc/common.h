@@ -211,6 +211,15 @@ hipError_t init_gemm_bf16();   // one-time function attributes (LDS size)
 // Elementwise / reduction kernels (kernels_elementwise.hip)
 constexpr int LOSS_ROWS_PER_BLOCK = 32;   // token rows per block of the row-blocked reductions
 inline int row_blocks(int B) { return (B + LOSS_ROWS_PER_BLOCK - 1) / LOSS_ROWS_PER_BLOCK; }
+// How the reductions over token rows cut [L][B][cols]: workgroups of `rows` rows x 16 bytes of columns per lane.  128
+// rows where that still gives every CU two workgroups: the column partials (4 bytes per column and row block, written and
+// read again) then cost a quarter.  32 rows elsewhere, for the chip's sake.
+struct ReduceGrid { int rows, rbs, chunks; int blocks() const { return rbs * chunks; } };
+inline ReduceGrid reduce_grid(bool bf16, Dims D, int cols) {
+  const int width = bf16 ? 512 : 256, chunks = (cols + width - 1) / width;
+  const int rows = (double)D.L * chunks * ((D.B + 127) / 128) >= 512.0 ? 128 : LOSS_ROWS_PER_BLOCK;
+  return {rows, (D.B + rows - 1) / rows, chunks};
+}
 
 hipError_t launch_zero_i32(hipStream_t s, int32_t* p, int n);
 // activation normalisation (Sec. 3.1): norm_sum[l] += sum over the B rows of ||a[l,b,:]||_2 (part: row_blocks(B)*L

@@ -110,90 +110,187 @@ __global__ __launch_bounds__(256) void norms_from_partials_kernel(Dims D, const 
   norms[i] = sqrtf(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
 }
 
-// ---- reconstruction loss: r = y_hat - y; partial sum r^2; d_yhat = 2 r / B;
-// column partial sums of d_yhat (for db_dec).  grid = (row blocks, L), each
-// thread owns 4 consecutive columns and walks the block's rows.
-template <typename T, bool INT8>
-__global__ __launch_bounds__(256) void loss_rec_kernel(Dims D, const float* __restrict__ y_hat, const void* yv,
-                                                       const float* __restrict__ y_scale, T* __restrict__ d_yhat,
-                                                       double* __restrict__ loss_part, float* __restrict__ col_part) {
-  const int rb = blockIdx.x, l = blockIdx.y;
-  const int r0 = rb * LOSS_ROWS_PER_BLOCK, r1 = min(D.B, r0 + LOSS_ROWS_PER_BLOCK);
-  const float two_over_b = 2.0f / (float)D.B;
-  double sq = 0.0;
-  for (int c = threadIdx.x * 4; c < D.d; c += 1024) {
-    float4 cs = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int r = r0; r < r1; ++r) {
-      const size_t o = ((size_t)l * D.B + r) * D.d + c;
-      const float4 yh = *reinterpret_cast<const float4*>(y_hat + o);
-      float4 y;
-      if (INT8) {
-        const uint32_t q = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const int8_t*>(yv) + o);
-        const float s = y_scale[(size_t)l * D.B + r];
-        y = make_float4(s * (float)(int8_t)q, s * (float)(int8_t)(q >> 8), s * (float)(int8_t)(q >> 16),
-                        s * (float)(int8_t)(q >> 24));
-      } else {
-        y = Elem<T>::load4(reinterpret_cast<const T*>(yv) + o);
-      }
-      const float4 rr = make_float4(yh.x - y.x, yh.y - y.y, yh.z - y.z, yh.w - y.w);
-      sq += (double)(rr.x * rr.x + rr.y * rr.y) + (double)(rr.z * rr.z + rr.w * rr.w);
-      const float4 g = make_float4(two_over_b * rr.x, two_over_b * rr.y, two_over_b * rr.z, two_over_b * rr.w);
-      Elem<T>::store4(d_yhat + o, g);
-      cs.x += g.x; cs.y += g.y; cs.z += g.z; cs.w += g.w;
-    }
-    *reinterpret_cast<float4*>(col_part + ((size_t)rb * D.L + l) * D.d + c) = cs;
+// ---- reductions over token rows (losses, straight-through terms) --------------------------
+// One workgroup takes `rows` token rows of one layer and 16 bytes of columns per lane (512 columns of bf16, 256 of
+// fp32); its four wavefronts take a quarter of the rows each, eight rows in flight, and add their column sums up in LDS
+// in a fixed order.  Walking one row after the other over all columns, with a workgroup per 32 rows only, left the small
+// shapes bound by the latency of one load per row (sparsity sum, L = 12, F = 6144, 300 tokens: 129 us; L = 4, F = 256, 128
+// tokens: 17) and wrote four times the partials for the large ones.
+constexpr int ROWS_IN_FLIGHT = 8;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <typename T> struct Row16 { static constexpr int N = 16 / sizeof(T); };      // columns per lane
+template <typename T> __device__ __forceinline__ u32x4 load16(const T* p) { return *reinterpret_cast<const u32x4*>(p); }
+__device__ __forceinline__ void widen16(u32x4 r, float (&f)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { f[2 * i] = __uint_as_float(r[i] << 16); f[2 * i + 1] = __uint_as_float(r[i] & 0xffff0000u); }
+}
+__device__ __forceinline__ void widen16(u32x4 r, float (&f)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[i] = __uint_as_float(r[i]);
+}
+__device__ __forceinline__ void store16(bf16_t* p, const float (&f)[8]) {
+  const u32x4 r = {pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7])};
+  *reinterpret_cast<u32x4*>(p) = r;
+}
+__device__ __forceinline__ void store16(float* p, const float (&f)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
+}
+template <int N> __device__ __forceinline__ void load_floats(const float* p, float (&f)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; i += 4) {
+    const float4 v = *reinterpret_cast<const float4*>(p + i);
+    f[i] = v.x; f[i + 1] = v.y; f[i + 2] = v.z; f[i + 3] = v.w;
   }
-  const double tot = block_sum_256(sq);
-  if (threadIdx.x == 0) loss_part[(size_t)l * gridDim.x + rb] = tot;
+}
+// the workgroup's part: rows [r0, r1) of the calling wavefront, first column c of the calling lane
+template <int N> struct RowPart {
+  int rb, l, r0, r1, c;
+  __device__ __forceinline__ RowPart(Dims D, int rows, int nchunks, int cols) {
+    const int chunk = blockIdx.x % nchunks;
+    rb = blockIdx.x / nchunks;
+    l = blockIdx.y;
+    const int w = threadIdx.x >> 6;
+    r0 = min(D.B, rb * rows + w * (rows / 4));
+    r1 = min(D.B, r0 + rows / 4);
+    c = (chunk * 64 + (threadIdx.x & 63)) * N;
+    if (c >= cols) r1 = r0;      // nothing to do, but the lane takes part in the barriers
+  }
+};
+// column sums of the four wavefronts, written by the first one (all threads of the workgroup call it)
+template <int N>
+__device__ __forceinline__ void add_column_sums(float (&s)[N], float* dst, bool in, float (&lds)[3][64 * N]) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __syncthreads();
+  if (w > 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) lds[w - 1][i * 64 + lane] = s[i];
+  }
+  __syncthreads();
+  if (w == 0 && in) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) s[i] = (s[i] + lds[0][i * 64 + lane]) + (lds[1][i * 64 + lane] + lds[2][i * 64 + lane]);
+#pragma unroll
+    for (int i = 0; i < N; i += 4) *reinterpret_cast<float4*>(dst + i) = make_float4(s[i], s[i + 1], s[i + 2], s[i + 3]);
+  }
 }
 
-// ---- sparsity loss: partial sum tanh(C z n); column partials of C z sech^2(C z n)
-// (both from one hardware exponential).
+// reconstruction loss: r = y_hat - y; partial sum r^2; d_yhat = 2 r / B; column partial sums of d_yhat (for db_dec)
+template <typename T, bool INT8>
+__global__ __launch_bounds__(256) void loss_rec_kernel(Dims D, int rows, int nchunks, const float* __restrict__ y_hat,
+                                                       const void* yv, const float* __restrict__ y_scale,
+                                                       T* __restrict__ d_yhat, double* __restrict__ loss_part,
+                                                       float* __restrict__ col_part) {
+  constexpr int N = Row16<T>::N, R = ROWS_IN_FLIGHT / 2;      // (two more loads per row than the other kernels)
+  __shared__ float lds[3][64 * N];
+  const RowPart<N> p(D, rows, nchunks, D.d);
+  const float two_over_b = 2.0f / (float)D.B;
+  float cs[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) cs[i] = 0.f;
+  double sq = 0.0;
+  for (int r = p.r0; r < p.r1; r += R) {
+    float yh[R][N], ys[R];
+    u32x4 raw[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const int rj = min(r + j, p.r1 - 1);
+      const size_t o = ((size_t)p.l * D.B + rj) * D.d + p.c;
+      load_floats(y_hat + o, yh[j]);
+      if (INT8) {
+        const uint2 q = *reinterpret_cast<const uint2*>(reinterpret_cast<const int8_t*>(yv) + o);
+        raw[j] = u32x4{q.x, q.y, 0u, 0u};
+        ys[j] = y_scale[(size_t)p.l * D.B + rj];
+      } else {
+        raw[j] = load16(reinterpret_cast<const T*>(yv) + o);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (r + j >= p.r1) break;
+      float y[N], g[N];
+      if (INT8) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) y[i] = ys[j] * (float)(int8_t)(raw[j][i / 4] >> (8 * (i & 3)));
+      } else {
+        widen16(raw[j], y);
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        y[i] = yh[j][i] - y[i];
+        g[i] = two_over_b * y[i];
+        cs[i] += g[i];
+      }
+#pragma unroll
+      for (int i = 0; i < N; i += 4)
+        sq += (double)(y[i] * y[i] + y[i + 1] * y[i + 1]) + (double)(y[i + 2] * y[i + 2] + y[i + 3] * y[i + 3]);
+      store16(d_yhat + ((size_t)p.l * D.B + r + j) * D.d + p.c, g);
+    }
+  }
+  add_column_sums(cs, col_part + ((size_t)p.rb * D.L + p.l) * D.d + p.c, p.c < D.d, lds);
+  const double tot = block_sum_256(sq);
+  if (threadIdx.x == 0) loss_part[(size_t)p.l * gridDim.x + blockIdx.x] = tot;
+}
+
+// sparsity loss: partial sum tanh(C z n); column partials of C z sech^2(C z n) (both from one hardware exponential).
 // With DEAD also the App. B dead-feature term: partial sum relu(theta - pre) n and the
 // column partials of relu(theta - pre) (its derivative w.r.t. the decoder norm).
 template <typename T, bool DEAD>
-__global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, const T* __restrict__ z,
+__global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, int rows, int nchunks, const T* __restrict__ z,
                                                             const float* __restrict__ norms, float C,
                                                             double* __restrict__ loss_part,
                                                             float* __restrict__ col_part, const T* __restrict__ pre,
                                                             const float* __restrict__ theta, bool log_threshold,
                                                             double* __restrict__ dead_part,
                                                             float* __restrict__ dead_col_part) {
-  const int rb = blockIdx.x, l = blockIdx.y;
-  const int r0 = rb * LOSS_ROWS_PER_BLOCK, r1 = min(D.B, r0 + LOSS_ROWS_PER_BLOCK);
-  double sp = 0.0, dead = 0.0;
-  for (int c = threadIdx.x * 4; c < D.F; c += 1024) {
-    const float4 n4 = *reinterpret_cast<const float4*>(norms + (size_t)l * D.F + c);
-    const float nn[4] = {n4.x, n4.y, n4.z, n4.w};
-    const float cn[4] = {C * n4.x, C * n4.y, C * n4.z, C * n4.w};
-    float th[4] = {0.f, 0.f, 0.f, 0.f};
-    if (DEAD) {
-      const float4 t4 = *reinterpret_cast<const float4*>(theta + (size_t)l * D.F + c);
-      th[0] = threshold_value(t4.x, log_threshold); th[1] = threshold_value(t4.y, log_threshold);
-      th[2] = threshold_value(t4.z, log_threshold); th[3] = threshold_value(t4.w, log_threshold);
-    }
-    float cs[4] = {0.f, 0.f, 0.f, 0.f}, ds[4] = {0.f, 0.f, 0.f, 0.f};
-    float ts = 0.f, dsum = 0.f;
-    for (int r = r0; r < r1; ++r) {
-      const size_t o = ((size_t)l * D.B + r) * D.F + c;
-      const float4 z4 = Elem<T>::load4(z + o);
-      const float zz[4] = {z4.x, z4.y, z4.z, z4.w};
+  constexpr int N = Row16<T>::N, R = DEAD ? ROWS_IN_FLIGHT / 2 : ROWS_IN_FLIGHT;
+  __shared__ float lds[3][64 * N];
+  const RowPart<N> p(D, rows, nchunks, D.F);
+  const bool in = p.c < D.F;
+  float ka[N], nn[N], th[N], cs[N], ds[N];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < N; ++i) ka[i] = nn[i] = th[i] = cs[i] = ds[i] = 0.f;
+  if (in) {
+    load_floats(norms + (size_t)p.l * D.F + p.c, nn);
+    if (DEAD) load_floats(theta + (size_t)p.l * D.F + p.c, th);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    ka[i] = -2.0f * 1.4426950408889634f * (C * nn[i]);
+    if (DEAD) th[i] = threshold_value(th[i], log_threshold);
+  }
+  double sp = 0.0, dead = 0.0;
+  for (int r = p.r0; r < p.r1; r += R) {
+    u32x4 zr[R], pr[DEAD ? R : 1];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const size_t o = ((size_t)p.l * D.B + min(r + j, p.r1 - 1)) * D.F + p.c;
+      zr[j] = load16(z + o);
+      if (DEAD) pr[j] = load16(pre + o);
+    }
+    float ts = 0.f, dsum = 0.f;      // at most 8 rows of a lane's columns in fp32
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (r + j >= p.r1) break;
+      float zz[N];
+      widen16(zr[j], zz);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
         if (zz[i] != 0.f) {
-          // e = exp(-2|u|): tanh|u| = (1 - e) / (1 + e), sech^2 u = 4 e / (1 + e)^2 (no cancellation for large u)
-          const float u = cn[i] * zz[i];
-          const float e = __builtin_amdgcn_exp2f(-2.0f * 1.4426950408889634f * fabsf(u));
-          const float r = __builtin_amdgcn_rcpf(1.0f + e);
-          ts += copysignf((1.0f - e) * r, u);
-          cs[i] += C * zz[i] * (4.0f * e * r * r);
+          // u = C n z, e = exp(-2|u|), q = e / (1 + e): tanh|u| = 1 - 2 q, sech^2 u = 4 q / (1 + e) (no cancellation
+          // for large u)
+          const float a = ka[i] * zz[i];      // -2 log2(e) u
+          const float e = __builtin_amdgcn_exp2f(-fabsf(a));
+          const float rc = __builtin_amdgcn_rcpf(1.0f + e);
+          const float q = e * rc;
+          ts -= copysignf(fmaf(-2.0f, q, 1.0f), a);
+          cs[i] = fmaf(zz[i], q * rc, cs[i]);
         }
       }
       if (DEAD) {
-        const float4 p4 = Elem<T>::load4(pre + o);
-        const float pp[4] = {p4.x, p4.y, p4.z, p4.w};
+        float pp[N];
+        widen16(pr[j], pp);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < N; ++i) {
           const float g = fmaxf(th[i] - pp[i], 0.f);
           ds[i] += g;
           dsum += g * nn[i];
@@ -202,16 +299,18 @@ __global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, const T* __r
     }
     sp += (double)ts;
     dead += (double)dsum;
-    const size_t po = ((size_t)rb * D.L + l) * D.F + c;
-    *reinterpret_cast<float4*>(col_part + po) = make_float4(cs[0], cs[1], cs[2], cs[3]);
-    if (DEAD) *reinterpret_cast<float4*>(dead_col_part + po) = make_float4(ds[0], ds[1], ds[2], ds[3]);
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i) cs[i] *= 4.0f * C;
+  const size_t po = ((size_t)p.rb * D.L + p.l) * D.F + p.c;
+  add_column_sums(cs, col_part + po, in, lds);
+  if (DEAD) add_column_sums(ds, dead_col_part + po, in, lds);
   const double tot = block_sum_256(sp);
-  if (threadIdx.x == 0) loss_part[(size_t)l * gridDim.x + rb] = tot;
+  if (threadIdx.x == 0) loss_part[(size_t)p.l * gridDim.x + blockIdx.x] = tot;
   if (DEAD) {
     __syncthreads();
     const double dt = block_sum_256(dead);
-    if (threadIdx.x == 0) dead_part[(size_t)l * gridDim.x + rb] = dt;
+    if (threadIdx.x == 0) dead_part[(size_t)p.l * gridDim.x + blockIdx.x] = dt;
   }
 }
 
@@ -219,10 +318,18 @@ __global__ __launch_bounds__(256) void loss_final_kernel(const double* part_rec,
                                                          int n_sp, const double* part_dead, float inv_B, float lambda0,
                                                          float lambda1, float* loss_dev) {
   double a = 0.0, b = 0.0, c = 0.0;
-  for (int i = threadIdx.x; i < n_rec; i += 256) a += part_rec[i];
-  for (int i = threadIdx.x; i < n_sp; i += 256) b += part_sp[i];
-  if (part_dead)
-    for (int i = threadIdx.x; i < n_sp; i += 256) c += part_dead[i];
+  auto sum = [](const double* p, int n) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};      // four chains keep four loads in flight
+    for (int i = threadIdx.x; i < n; i += 1024) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i + 256 * q < n) s[q] += p[i + 256 * q];
+    }
+    return (s[0] + s[1]) + (s[2] + s[3]);
+  };
+  a = sum(part_rec, n_rec);
+  b = sum(part_sp, n_sp);
+  if (part_dead) c = sum(part_dead, n_sp);
   a = block_sum_256(a);
   __syncthreads();
   b = block_sum_256(b);
@@ -238,14 +345,31 @@ __global__ __launch_bounds__(256) void loss_final_kernel(const double* part_rec,
   }
 }
 
+// Sum over the row partials of 64 columns by a workgroup: each wavefront adds a quarter of the partials, the quarters
+// are added in order.  Valid in the first wavefront.  (One thread per column and 128 partials: 34 us at 73728 columns,
+// bound by the chain of loads; quarters with eight loads in flight: see the callers.)
+__device__ __forceinline__ float sum_partials(const float* __restrict__ part, int nparts, int ncols, int c, float (&lds)[3][64]) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int per = (nparts + 3) / 4, r0 = min(nparts, w * per), r1 = min(nparts, r0 + per);
+  float s = 0.f;
+  if (c < ncols) {
+#pragma unroll 8
+    for (int r = r0; r < r1; ++r) s += part[(size_t)r * ncols + c];
+  }
+  __syncthreads();
+  if (w > 0) lds[w - 1][lane] = s;
+  __syncthreads();
+  return w == 0 ? (s + lds[0][lane]) + (lds[1][lane] + lds[2][lane]) : 0.f;
+}
+
 __global__ __launch_bounds__(256) void col_reduce_kernel(const float* __restrict__ part, int nparts, int ncols,
                                                          float alpha, const float* __restrict__ theta, float inv_eps,
                                                          float* __restrict__ out, bool accumulate, PartsSwitch sw) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= ncols) return;
+  __shared__ float lds[3][64];
+  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
   if (sw.flags && lists_backward_selected(sw.flags, sw.kcap)) nparts = sw.nparts_lists;
-  float s = 0.f;
-  for (int r = 0; r < nparts; ++r) s += part[(size_t)r * ncols + c];
+  float s = sum_partials(part, nparts, ncols, c, lds);
+  if (threadIdx.x >= 64 || c >= ncols) return;
   s *= alpha;
   if (theta) s = (s == 0.f) ? 0.f : s * -(theta[c] * inv_eps);   // empty window: exactly 0, also for theta = inf
   out[c] = accumulate ? out[c] + s : s;
@@ -259,13 +383,12 @@ __global__ __launch_bounds__(256) void dtheta_final_kernel(const float* __restri
                                                            bool log_threshold, const float* __restrict__ norms,
                                                            float inv_eps, float lam1_over_b,
                                                            float* __restrict__ out, PartsSwitch sw) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= ncols) return;
+  __shared__ float lds[3][64];
+  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
   if (sw.flags && lists_backward_selected(sw.flags, sw.kcap)) nparts = sw.nparts_lists;
-  float w = 0.f, nb = 0.f;
-  for (int r = 0; r < nparts; ++r) w += part_win[(size_t)r * ncols + c];
-  if (lam1_over_b != 0.f)
-    for (int r = 0; r < nparts; ++r) nb += part_below[(size_t)r * ncols + c];
+  const float w = sum_partials(part_win, nparts, ncols, c, lds);
+  const float nb = lam1_over_b != 0.f ? sum_partials(part_below, nparts, ncols, c, lds) : 0.f;
+  if (threadIdx.x >= 64 || c >= ncols) return;
   const float th = threshold_value(theta_param[c], log_threshold);
   float g = (w == 0.f) ? 0.f : w * -(th * inv_eps);   // empty window: exactly 0, also for theta = inf
   if (lam1_over_b != 0.f) g += lam1_over_b * norms[c] * nb;
@@ -281,7 +404,7 @@ __global__ __launch_bounds__(256) void dtheta_final_kernel(const float* __restri
 // multiplied by it, because the encoder-weight gradient contracts them with the
 // integer codes.
 template <typename T>
-__global__ __launch_bounds__(256) void ste_reduce_kernel(Dims D, T* __restrict__ dpre,
+__global__ __launch_bounds__(256) void ste_reduce_kernel(Dims D, int rows, int nchunks, T* __restrict__ dpre,
                                                          const uint8_t* __restrict__ cls,
                                                          const float* __restrict__ row_scale,
                                                          const float* __restrict__ norms, float lam1_over_b,
@@ -290,28 +413,48 @@ __global__ __launch_bounds__(256) void ste_reduce_kernel(Dims D, T* __restrict__
                                                          float* __restrict__ part_below,
                                                          const int32_t* __restrict__ only_if_lists, int kcap) {
   if (only_if_lists && !lists_backward_selected(only_if_lists, kcap)) return;
-  const int rb = blockIdx.x, l = blockIdx.y;
-  const int r0 = rb * LOSS_ROWS_PER_BLOCK, r1 = min(D.B, r0 + LOSS_ROWS_PER_BLOCK);
-  const bool dead = lam1_over_b != 0.f;
-  for (int c = threadIdx.x * 4; c < D.F; c += 1024) {
-    float st[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f}, nb[4] = {0.f, 0.f, 0.f, 0.f};
-    float dg[4] = {0.f, 0.f, 0.f, 0.f};
-    if (dead) {
-      const float4 n4 = *reinterpret_cast<const float4*>(norms + (size_t)l * D.F + c);
-      dg[0] = -lam1_over_b * n4.x; dg[1] = -lam1_over_b * n4.y; dg[2] = -lam1_over_b * n4.z; dg[3] = -lam1_over_b * n4.w;
-    }
-    for (int r = r0; r < r1; ++r) {
-      const size_t o = ((size_t)l * D.B + r) * D.F + c;
-      uint32_t c4 = *reinterpret_cast<const uint32_t*>(cls + o);
-      if (!dead) c4 &= 0x03030303u;       // without the dead-feature term only active / window entries matter
-      if (!c4) continue;
-      const float4 g4 = Elem<T>::load4(dpre + o);
-      float g[4] = {g4.x, g4.y, g4.z, g4.w};
-      bool rewrite = row_scale != nullptr;
-      const float s = row_scale ? row_scale[(size_t)l * D.B + r] : 1.0f;
+  constexpr int N = Row16<T>::N, W = N / 4, R = ROWS_IN_FLIGHT;      // W words of classes per row
+  __shared__ float lds[3][64 * N];
+  const RowPart<N> p(D, rows, nchunks, D.F);
+  const bool dead = lam1_over_b != 0.f, in = p.c < D.F;
+  float st[N], sb[N], nb[N], dg[N];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t ci = (c4 >> (8 * i)) & 7u;
+  for (int i = 0; i < N; ++i) st[i] = sb[i] = nb[i] = dg[i] = 0.f;
+  if (dead && in) {
+    load_floats(norms + (size_t)p.l * D.F + p.c, dg);
+#pragma unroll
+    for (int i = 0; i < N; ++i) dg[i] *= -lam1_over_b;
+  }
+  const uint32_t care = dead ? 0xffffffffu : 0x03030303u;   // without the dead-feature term only active / window entries matter
+  for (int r = p.r0; r < p.r1; r += R) {
+    uint32_t cw[R][W];
+    u32x4 raw[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const uint32_t* q = reinterpret_cast<const uint32_t*>(cls + ((size_t)p.l * D.B + min(r + j, p.r1 - 1)) * D.F + p.c);
+#pragma unroll
+      for (int k = 0; k < W; ++k) cw[j][k] = q[k];
+    }
+    uint32_t any[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      any[j] = 0u;
+#pragma unroll
+      for (int k = 0; k < W; ++k) any[j] |= (cw[j][k] &= care);
+      if (r + j >= p.r1) any[j] = 0u;
+      raw[j] = u32x4{0u, 0u, 0u, 0u};
+      if (any[j]) raw[j] = load16(dpre + ((size_t)p.l * D.B + r + j) * D.F + p.c);
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (!any[j]) continue;
+      float g[N];
+      widen16(raw[j], g);
+      bool rewrite = row_scale != nullptr;
+      const float s = row_scale ? row_scale[(size_t)p.l * D.B + r + j] : 1.0f;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const uint32_t ci = (cw[j][i / 4] >> (8 * (i & 3))) & 7u;
         if (ci & CLS_WINDOW) st[i] += g[i];
         if (ci & CLS_BELOW) nb[i] += 1.0f;
         if (!(ci & CLS_ACTIVE) && (ci & CLS_WINDOW)) {   // held dz for the threshold gradient only
@@ -323,13 +466,13 @@ __global__ __launch_bounds__(256) void ste_reduce_kernel(Dims D, T* __restrict__
           g[i] *= s;
         }
       }
-      if (rewrite) Elem<T>::store4(dpre + o, make_float4(g[0], g[1], g[2], g[3]));
+      if (rewrite) store16(dpre + ((size_t)p.l * D.B + r + j) * D.F + p.c, g);
     }
-    const size_t po = ((size_t)rb * D.L + l) * D.F + c;
-    *reinterpret_cast<float4*>(part_theta + po) = make_float4(st[0], st[1], st[2], st[3]);
-    *reinterpret_cast<float4*>(part_benc + po) = make_float4(sb[0], sb[1], sb[2], sb[3]);
-    if (dead) *reinterpret_cast<float4*>(part_below + po) = make_float4(nb[0], nb[1], nb[2], nb[3]);
   }
+  const size_t po = ((size_t)p.rb * D.L + p.l) * D.F + p.c;
+  add_column_sums(st, part_theta + po, in, lds);
+  add_column_sums(sb, part_benc + po, in, lds);
+  if (dead) add_column_sums(nb, part_below + po, in, lds);
 }
 
 // ---- Adam (App. C Table 1), 4 elements per lane --------------------------------
@@ -648,15 +791,16 @@ hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_par
 
 hipError_t launch_loss_rec(hipStream_t s, bool bf16, bool int8_y, Dims D, const float* y_hat, const void* y,
                            const float* y_scale, void* d_yhat, double* loss_part, float* col_part) {
-  const dim3 grid(row_blocks(D.B), D.L);
+  const ReduceGrid rg = reduce_grid(bf16, D, D.d);
+  const dim3 grid(rg.blocks(), D.L);
   if (!bf16)
-    hipLaunchKernelGGL((loss_rec_kernel<float, false>), grid, dim3(256), 0, s, D, y_hat, y, y_scale, (float*)d_yhat,
+    hipLaunchKernelGGL((loss_rec_kernel<float, false>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, y_hat, y, y_scale, (float*)d_yhat,
                        loss_part, col_part);
   else if (int8_y)
-    hipLaunchKernelGGL((loss_rec_kernel<bf16_t, true>), grid, dim3(256), 0, s, D, y_hat, y, y_scale,
+    hipLaunchKernelGGL((loss_rec_kernel<bf16_t, true>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, y_hat, y, y_scale,
                        (bf16_t*)d_yhat, loss_part, col_part);
   else
-    hipLaunchKernelGGL((loss_rec_kernel<bf16_t, false>), grid, dim3(256), 0, s, D, y_hat, y, y_scale,
+    hipLaunchKernelGGL((loss_rec_kernel<bf16_t, false>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, y_hat, y, y_scale,
                        (bf16_t*)d_yhat, loss_part, col_part);
   return hipGetLastError();
 }
@@ -664,10 +808,11 @@ hipError_t launch_loss_rec(hipStream_t s, bool bf16, bool int8_y, Dims D, const 
 hipError_t launch_loss_sparsity(hipStream_t s, bool bf16, Dims D, const void* z, const float* norms, float C,
                                 double* loss_part, float* col_part, const void* pre, const float* theta,
                                 bool log_threshold, double* dead_part, float* dead_col_part) {
-  const dim3 grid(row_blocks(D.B), D.L);
+  const ReduceGrid rg = reduce_grid(bf16, D, D.F);
+  const dim3 grid(rg.blocks(), D.L);
 #define CLT_LSP(T, DEAD)                                                                                      \
-  hipLaunchKernelGGL((loss_sparsity_kernel<T, DEAD>), grid, dim3(256), 0, s, D, (const T*)z, norms, C, loss_part, \
-                     col_part, (const T*)pre, theta, log_threshold, dead_part, dead_col_part)
+  hipLaunchKernelGGL((loss_sparsity_kernel<T, DEAD>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, (const T*)z, norms, \
+                     C, loss_part, col_part, (const T*)pre, theta, log_threshold, dead_part, dead_col_part)
   if (bf16) { if (pre) CLT_LSP(bf16_t, true); else CLT_LSP(bf16_t, false); }
   else { if (pre) CLT_LSP(float, true); else CLT_LSP(float, false); }
 #undef CLT_LSP
@@ -684,7 +829,7 @@ hipError_t launch_loss_final(hipStream_t s, const double* part_rec, int n_rec, c
 
 hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha,
                              const float* theta_or_null, float inv_eps, float* out, bool accumulate, PartsSwitch sw) {
-  hipLaunchKernelGGL(col_reduce_kernel, dim3((ncols + 255) / 256), dim3(256), 0, s, part, nparts, ncols, alpha,
+  hipLaunchKernelGGL(col_reduce_kernel, dim3((ncols + 63) / 64), dim3(256), 0, s, part, nparts, ncols, alpha,
                      theta_or_null, inv_eps, out, accumulate, sw);
   return hipGetLastError();
 }
@@ -692,7 +837,7 @@ hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int n
 hipError_t launch_dtheta_final(hipStream_t s, const float* part_win, const float* part_below, int nparts, int ncols,
                                const float* theta_param, bool log_threshold, const float* norms, float inv_eps,
                                float lam1_over_b, float* out, PartsSwitch sw) {
-  hipLaunchKernelGGL(dtheta_final_kernel, dim3((ncols + 255) / 256), dim3(256), 0, s, part_win, part_below, nparts,
+  hipLaunchKernelGGL(dtheta_final_kernel, dim3((ncols + 63) / 64), dim3(256), 0, s, part_win, part_below, nparts,
                      ncols, theta_param, log_threshold, norms, inv_eps, lam1_over_b, out, sw);
   return hipGetLastError();
 }
@@ -701,12 +846,13 @@ hipError_t launch_ste_reduce(hipStream_t s, bool bf16, Dims D, void* dpre, const
                              const float* row_scale_or_null, const float* norms, float lam1_over_b,
                              float* part_theta, float* part_benc, float* part_below,
                              const int32_t* only_if_lists, int kcap) {
-  const dim3 grid(row_blocks(D.B), D.L);
+  const ReduceGrid rg = reduce_grid(bf16, D, D.F);
+  const dim3 grid(rg.blocks(), D.L);
   if (bf16)
-    hipLaunchKernelGGL((ste_reduce_kernel<bf16_t>), grid, dim3(256), 0, s, D, (bf16_t*)dpre, cls, row_scale_or_null,
+    hipLaunchKernelGGL((ste_reduce_kernel<bf16_t>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, (bf16_t*)dpre, cls, row_scale_or_null,
                        norms, lam1_over_b, part_theta, part_benc, part_below, only_if_lists, kcap);
   else
-    hipLaunchKernelGGL((ste_reduce_kernel<float>), grid, dim3(256), 0, s, D, (float*)dpre, cls, row_scale_or_null,
+    hipLaunchKernelGGL((ste_reduce_kernel<float>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, (float*)dpre, cls, row_scale_or_null,
                        norms, lam1_over_b, part_theta, part_benc, part_below, only_if_lists, kcap);
   return hipGetLastError();
 }
