@@ -23,11 +23,12 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
-  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part,
+  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part, row_squares,
          fl_off, fl_cnt, fl_tok, fl_val, fl_seg, total;
   int kcap;
   int ecap;
   DecSplit split;
+  bool row_squares_on;      // the dense decode leaves the decoder rows' sums of squares
 };
 
 thread_local char g_err[256] = "";
@@ -202,6 +203,10 @@ Plan make_plan(const clt_config* c) {
     p.split = c->dtype == CLT_DTYPE_BF16 ? dec_split_bf16(D) : dec_split_f32(D);
   }
   p.split_part = o; o += align_up((size_t)p.split.groups * B * d * 4);
+  // (automatic mode: the dense decode may stand down, so the norms keep their own kernel)
+  const size_t squares = bf16 && c->decode_mode == CLT_DECODE_DENSE ? dec_row_squares_floats(dims) : 0;
+  p.row_squares_on = squares > 0;
+  p.row_squares = o; o += align_up(squares * 4);
   p.total = o;
   return p;
 }
@@ -516,10 +521,16 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
   float* norms = reinterpret_cast<float*>(h->ws + h->plan.norms);
   int32_t* l0 = l0_per_layer ? l0_per_layer : reinterpret_cast<int32_t*>(h->ws + h->plan.l0);
   int32_t* flags = reinterpret_cast<int32_t*>(h->ws + h->plan.flags);
+  const int mode = h->cfg.decode_mode;
+  DecArgs da{z, W_dec, b_dec, y_hat, mode == CLT_DECODE_AUTO ? flags : nullptr, h->plan.kcap,
+             reinterpret_cast<uint32_t*>(h->ws + h->plan.xcd_sync), h->plan.split,
+             reinterpret_cast<float*>(h->ws + h->plan.split_part)};
   RUN(h, s, K_ZERO, launch_zero_i32(s, l0, h->D.L));
   if (h->n2_for && h->n2_for == W_dec)   // the last fused update left the sums of squares of exactly these weights
-    RUN(h, s, K_NORMS_REUSE, launch_norms_from_partials(s, h->D, reinterpret_cast<const float*>(h->ws + h->plan.n2_part), norms,
+    RUN(h, s, K_NORMS_REUSE, launch_norms_from_partials(s, h->D, reinterpret_cast<const float*>(h->ws + h->plan.n2_part), h->D.d / 64, norms,
                                                             h->cfg.decode_mode == CLT_DECODE_DENSE ? nullptr : flags, h->plan.kcap));
+  else if (h->plan.row_squares_on)   // few tokens: the decode below reads every weight once and takes the squares along
+    da.row_squares = reinterpret_cast<float*>(h->ws + h->plan.row_squares);
   else
     RUN(h, s, K_NORMS, launch_decoder_norms(s, h->bf16, h->D, W_dec, norms));
   h->n2_for = nullptr;
@@ -527,10 +538,6 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
   float* pre32 = topk ? reinterpret_cast<float*>(h->ws + h->plan.pre32) : nullptr;
   EncArgs ea{x, x_scale, W_enc, b_enc, theta, h->cfg.ste_bandwidth, z, pre, act_class, l0,
              h->cfg.log_threshold != 0, pre32};
-  const int mode = h->cfg.decode_mode;
-  DecArgs da{z, W_dec, b_dec, y_hat, mode == CLT_DECODE_AUTO ? flags : nullptr, h->plan.kcap,
-             reinterpret_cast<uint32_t*>(h->ws + h->plan.xcd_sync), h->plan.split,
-             reinterpret_cast<float*>(h->ws + h->plan.split_part)};
   GatherLists gl{reinterpret_cast<int32_t*>(h->ws + h->plan.g_idx), reinterpret_cast<float*>(h->ws + h->plan.g_val),
                  reinterpret_cast<int32_t*>(h->ws + h->plan.g_counts),
                  reinterpret_cast<int32_t*>(h->ws + h->plan.g_counts_w), h->plan.kcap, list_stride(h->plan.kcap)};
@@ -554,6 +561,8 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
     if (h->bf16) RUN(h, s, K_DEC, launch_dec_bf16(s, h->D, da));
     else RUN(h, s, K_DEC, launch_dec_f32(s, h->D, da));
   }
+  if (da.row_squares)
+    RUN(h, s, K_NORMS, launch_norms_from_partials(s, h->D, da.row_squares, 2 * ((h->D.d + 255) / 256), norms, nullptr, 0));
   h->stage = 1;
   return CLT_OK;
 }

@@ -160,12 +160,16 @@ struct DecSplit {
 };
 DecSplit dec_split_f32(Dims D);      // the cut that the shape gets (see choose_dec_split)
 DecSplit dec_split_bf16(Dims D);
+size_t dec_row_squares_floats(Dims D);     // 0: the shape's decode does not take the row squares along
 struct DecArgs {       // y_hat[lp] = sum_{l<=lp} z[l] W_dec[p(l,lp)] + b_dec[lp]
   const void* z; const void* W_dec; const float* b_dec; float* y_hat;
   const int32_t* skip_flags;   // optional decode switch (see GatherLists); NULL = always run
   int kcap;
   uint32_t* xcd_sync = nullptr;   // bf16 kernel: 8 x 64 words of pacing counters (zeroed by the launch), or NULL
   DecSplit split; float* split_part = nullptr;   // split.groups > 0: that many slots of B * d floats
+  // bf16 kernel with few tokens: dec_row_squares_floats(D) floats for the sums of squares of W_dec's rows over runs of 128
+  // columns, [P][runs][F], or NULL (see launch_norms_from_partials)
+  float* row_squares = nullptr;
 };
 struct DzArgs {        // dz[l] = sum_{lp>=l} dyhat[lp] W_dec[p(l,lp)]^T + g_sp, kept where active|window
   const void* d_yhat; const void* W_dec; const void* z; const uint8_t* cls; const float* norms;
@@ -178,7 +182,7 @@ struct DzArgs {        // dz[l] = sum_{lp>=l} dyhat[lp] W_dec[p(l,lp)]^T + g_sp,
   // them: [half tile][L][F].  x_scale: the row scales of int8 inputs, or NULL.
   const float* x_scale = nullptr; float* part_theta = nullptr; float* part_benc = nullptr; float* part_below = nullptr;
 };
-inline int fold_row_blocks(int B) { return 2 * ((B + 255) / 256); }
+inline int fold_row_blocks(int B) { return 2 * ((B + 255) / 256); }      // (at most 128 tokens: 64-row halves, two as well)
 // Optional Adam fused into the two weight-gradient GEMMs (m == nullptr: plain gradient output)
 struct AdamFuseArgs { float* m; float* v; float* master; AdamScalars a; };
 struct DWdecArgs {     // dW_dec[p] = z[l]^T dyhat[lp] + (G/n)[l,f] W_dec[p][f,:]
@@ -242,9 +246,10 @@ hipError_t launch_decode_combine(hipStream_t s, Dims D, DecSplit sp, const float
 hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_dec, float* norms);
 // the same norms from the partial sums of squares a fused weight-gradient launch left behind:
 // n[l,f] = sqrt(sum over the blocks p(l, l..L-1) and their d / 64 column runs of n2_part[p][run][f]), in that order
-// (flags: the device-side decode switch of the step that left the sums, NULL when only the dense kernels run)
-hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_part, float* norms, const int32_t* flags,
-                                      int kcap);
+// (runs: column runs per row in the dense layout, d / 64 after an update, see DecArgs::row_squares for the decode's;
+//  flags: the device-side decode switch of the step that left the sums, NULL when only the dense kernels run)
+hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_part, int runs, float* norms,
+                                      const int32_t* flags, int kcap);
 // L_rec partials, d_yhat = 2 r / B, column partials for db_dec
 hipError_t launch_loss_rec(hipStream_t s, bool bf16, bool int8_y, Dims D, const float* y_hat, const void* y,
                            const float* y_scale, void* d_yhat, double* loss_part, float* col_part);

@@ -12,9 +12,10 @@
 //   ginfo(order) group visited at position `order` of the launch (longest K first)
 //   nseg(gi), a_seg(gi,s), b_seg(gi,s)   K segments of a group
 //   krange(gi, spseg)   the group's share of the K steps, counted through its segments at spseg steps each
-//   epi_begin(st, gi, col, ok, row0)   once per tile and lane: loads what depends on the lane's
+//   epi_begin(st, gi, col, ok, row0, part)   once per tile and lane: loads what depends on the lane's
 //                columns only (biases, thresholds, norms) when `ok` (col inside the matrix); row0 is the
-//                first row of the block whose rows this lane will see (wave-uniform in the bf16 kernel)
+//                first row of the block whose rows this lane will see (wave-uniform in the bf16 kernel) and
+//                part the number of that block
 //   epi_load(regs, gi, pos)       issues the global loads the epilogue of that 4-column
 //                group needs and keeps the results as loaded (no arithmetic on them here: that
 //                is where the wait for the load would land).  The bf16 kernel calls it ahead of
@@ -23,6 +24,8 @@
 //   epi4(st, gi, pos, v, regs)    consumes 4 accumulators of one row, columns col..col+3
 //   PERSISTENT   the bf16 kernel runs one workgroup per CU over many tiles (else one per tile)
 //   UNIFORM_K    every group of a launch has the same K length
+//   TILE_M       rows of the bf16 kernel's tile (256; 128 in the variants for few rows, see Few)
+//   ROW_SQUARES  the bf16 kernel's loop also leaves the sums of squares of B's rows (see row_squares)
 #pragma once
 #include "common.h"
 
@@ -179,6 +182,8 @@ __device__ __forceinline__ float4 adam_update4(const AdamFuse& f, T* w, size_t u
 // ---------------------------------------------------------------------------
 template <typename T, typename TA = T>
 struct EncPolicy {
+  static constexpr int TILE_M = 256;
+  static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = true, B_KC = false;
   typedef TA AType;
@@ -199,7 +204,7 @@ struct EncPolicy {
   static constexpr int EPI_BATCH = 8, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
   static constexpr bool PERSISTENT = true, UNIFORM_K = true;
   struct EpiRegs { float s; };
-  __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0) const {
+  __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0, int part) const {
     e.count = 0;
     e.b = e.th = make_float4(0.f, 0.f, 0.f, 0.f);
     if (ok) {
@@ -259,6 +264,8 @@ struct EncPolicy {
 // SPLIT: a group is one chunk of a target's K range and the epilogue leaves its partial sums (see DecSplit).
 template <typename T, bool SPLIT = false>
 struct DecPolicy {
+  static constexpr int TILE_M = 256;
+  static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = !SPLIT;
   static constexpr bool A_KC = true, B_KC = false;
   typedef T AType;
@@ -268,6 +275,7 @@ struct DecPolicy {
   const int32_t* skip_flags; int kcap;
   uint32_t* xcd_sync;   // 8 counters, 64 words apart, zero at launch (or NULL): see main_loop
   DecSplit sp; float* part;   // SPLIT only
+  float* n2_part;             // ROW_SQUARES only: [P][runs of 128 columns][F] sums of squares of W_dec
   // the dense decode stands down when the device-side switch selected the gather path
   __device__ bool skip() const { return skip_flags && gather_selected(skip_flags, kcap); }
   struct GInfo { int lp, chunk, slot; };
@@ -292,7 +300,7 @@ struct DecPolicy {
   static constexpr int EPI_BATCH = 8, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
   static constexpr bool PERSISTENT = !SPLIT, UNIFORM_K = false;
   struct EpiRegs {};
-  __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0) const {
+  __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0, int part) const {
     if (SPLIT) return;
     e.b = ok ? *reinterpret_cast<const float4*>(b_dec + (size_t)g.lp * D.d + col) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
@@ -324,6 +332,8 @@ struct DecPolicy {
 template <typename T, bool FOLD_ = false>
 struct DzPolicy {
   static constexpr bool FOLD = FOLD_;
+  static constexpr int TILE_M = 256;
+  static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = true, B_KC = true;
   typedef T AType;
@@ -349,7 +359,7 @@ struct DzPolicy {
   static constexpr int EPI_BATCH = 8, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
   static constexpr bool PERSISTENT = false, UNIFORM_K = false;   // measured: no faster as a tile loop (15.4 ms either way)
   struct EpiRegs { uint32_t c4; typename Elem<T>::Raw4 z4; float s; };
-  __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0) const {
+  __device__ void epi_begin(Epi& e, const GInfo& g, int col, bool ok, int row0, int part) const {
     float4 n4 = make_float4(0.f, 0.f, 0.f, 0.f);
     if (ok) n4 = *reinterpret_cast<const float4*>(norms + (size_t)g.l * D.F + col);
     const float ka = -2.0f * 1.4426950408889634f * C, kb = 4.0f * lam_c_over_b, kd = 0.0f - lam1_over_b;
@@ -360,7 +370,7 @@ struct DzPolicy {
       e.st = e.sb = e.nb = make_float4(0.f, 0.f, 0.f, 0.f);
       e.col = col;
       e.ok = ok;
-      e.prow = row0 >> 7;     // the wave's 128-row half tile
+      e.prow = part;     // the wave's half of the tile's rows
     }
   }
   __device__ void epi_load(EpiRegs& r, const GInfo& g, const EpiPos& pos) const {
@@ -441,6 +451,8 @@ struct DzPolicy {
 // the same reason as ADAM: one straight run of code).
 template <typename T, bool ADAM, bool N2 = false>
 struct DWdecPolicy {
+  static constexpr int TILE_M = 256;
+  static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = false, B_KC = false;
   typedef T AType;
@@ -470,7 +482,7 @@ struct DWdecPolicy {
   static constexpr int EPI_BATCH = N2 ? 3 : 4, EPI_BATCH_LATE = N2 ? 6 : 8, EPI_BATCH_LAST = N2 ? 7 : 8;
   static constexpr bool PERSISTENT = true, UNIFORM_K = true;
   struct EpiRegs { float Gf, nf; typename Elem<T>::Raw4 w; AdamRegs ad; };
-  __device__ void epi_begin(Epi& e, const GInfo&, int col, bool, int row0) const {
+  __device__ void epi_begin(Epi& e, const GInfo&, int col, bool, int row0, int part) const {
     e.row0 = row0;
     e.run = col >> 6;
   }
@@ -514,6 +526,8 @@ struct DWdecPolicy {
 // ---------------------------------------------------------------------------
 template <typename T, bool ADAM, typename TA = T>
 struct DWencPolicy {
+  static constexpr int TILE_M = 256;
+  static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = false, B_KC = false;
   typedef TA AType;
@@ -532,7 +546,7 @@ struct DWencPolicy {
   static constexpr int EPI_BATCH = 4, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
   static constexpr bool PERSISTENT = true, UNIFORM_K = true;
   struct EpiRegs { AdamRegs ad; typename Elem<T>::Raw4 w; };
-  __device__ void epi_begin(Epi&, const GInfo&, int, bool, int) const {}
+  __device__ void epi_begin(Epi&, const GInfo&, int, bool, int, int) const {}
   __device__ void epi_load(EpiRegs& r, const GInfo& g, const EpiPos& pos) const {
     if (!ADAM) return;
     const size_t uo = pos.uoff((size_t)g.l * D.d, D.F);
@@ -547,6 +561,13 @@ struct DWencPolicy {
     if (ADAM) adam_update4<T>(fuse, W_enc, uo, lo, r.ad, r.w, v);
   }
   __device__ void epi_end(Epi&, const GInfo&, float*) const {}
+};
+
+// The variants for at most 128 rows (tokens).
+template <class P, bool ROW_SQUARES_ = false>
+struct Few : P {
+  static constexpr int TILE_M = 128;
+  static constexpr bool ROW_SQUARES = ROW_SQUARES_, PERSISTENT = false, XCD_SYNC = false;
 };
 
 }  // namespace clt

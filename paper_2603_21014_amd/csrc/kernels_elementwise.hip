@@ -76,10 +76,10 @@ __global__ __launch_bounds__(256) void decoder_norms_kernel(Dims D, const T* __r
   if (lane == 0) norms[row] = sqrtf(acc);
 }
 
-// The same norms from sums of squares that the last fused update left, in a fixed order.  The dense kernel leaves
-// them per (block, 64-column run, feature), [P][d / 64][F]; the list-driven row kernel per (block, feature, slot),
+// The same norms from sums of squares that the last fused update (or the decode of few tokens) left, in a fixed order.  The dense kernel leaves
+// them per (block, column run, feature), [P][runs][F]; the list-driven row kernel per (block, feature, slot),
 // [P][F][8 ceil(d / 2048)].  Which of the two ran is what the device-side switch decided in that step (flags).
-__global__ __launch_bounds__(256) void norms_from_partials_kernel(Dims D, const float* __restrict__ n2_part,
+__global__ __launch_bounds__(256) void norms_from_partials_kernel(Dims D, const float* __restrict__ n2_part, int runs,
                                                                   float* __restrict__ norms,
                                                                   const int32_t* __restrict__ flags, int kcap) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;      // l * F + f
@@ -96,7 +96,6 @@ __global__ __launch_bounds__(256) void norms_from_partials_kernel(Dims D, const 
         a[0] += u.x; a[1] += u.y; a[2] += u.z; a[3] += u.w; a[4] += w.x; a[5] += w.y; a[6] += w.z; a[7] += w.w;
       }
   } else {
-    const int runs = D.d >> 6;
     const float* base = n2_part + (size_t)packed_index(l, l, D.L) * runs * D.F + f;
     // eight independent chains keep eight loads in flight per lane; the order of the sum stays fixed
     const int n = (D.L - l) * runs;
@@ -781,10 +780,10 @@ hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_
   return hipGetLastError();
 }
 
-hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_part, float* norms, const int32_t* flags,
-                                      int kcap) {
+hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_part, int runs, float* norms,
+                                      const int32_t* flags, int kcap) {
   const long rows = (long)D.L * D.F;
-  hipLaunchKernelGGL(norms_from_partials_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, D, n2_part, norms,
+  hipLaunchKernelGGL(norms_from_partials_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, D, n2_part, runs, norms,
                      flags, kcap);
   return hipGetLastError();
 }

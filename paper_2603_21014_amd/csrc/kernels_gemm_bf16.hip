@@ -32,14 +32,22 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef f32x4_t acc_t[8][4];   // a wave's 128x64 block as 8x4 accumulators of 16x16
+// a wave's block as accumulators of 16x16: half of the tile's rows by 64 columns
+template <class P> using acc_t = f32x4_t[P::TILE_M / 32][4];
 // native 16-byte register vector (HIP's uint4 is a class type; selects on it go through memory)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int TM = 256, TN = 256, TK = 64;
-constexpr int STAGE_ELEMS = 2 * 256 * TK;            // A tile + B tile, bf16 elements
-constexpr int LDS_BYTES = 2 * STAGE_ELEMS * 2;       // two stages = 128 KB
+template <class P> constexpr int stage_elems = (P::TILE_M + TN) * TK;             // A tile + B tile, bf16 elements
+template <class P> constexpr int lds_bytes = 2 * stage_elems<P> * 2;              // two stages = 128 KB (96 with 128 rows)
+
+// Tiles of 128 rows, for launches with at most 128 tokens: everything else alike, each wavefront half as many
+// accumulators.  Such a launch streams the weights once and is bound by that, not by the matrix cores, but 256-row tiles spend
+// 1.5 us of matrix time on a K step whose 32 KB of weights take 1.5 us to arrive.  The registers that are free here hold a
+// second K step of operands on its way, and the decode takes the squares for the decoder norms along instead of a second
+// pass over the weights.  One prompt of 100 tokens (L = 16, d = 2048, F = 8192: 4.6 GB of decoder): forward 1807 -> 1105 us,
+// of which decode 1073 -> 930 and norms 806 -> 20.
 
 // element offset of 16-byte chunk `c` (8 bf16) of tile row `row`
 __device__ __forceinline__ int lds_off(int row, int c) {
@@ -101,8 +109,11 @@ template <> __device__ __forceinline__ u32x4 cook8<int8_t>(u32x4 raw) {
 // d = 2056, F = 8200, 4100 tokens: dW_dec 5.4 ms, decode 4.1; now 4.3 and 3.5.
 // One prompt of 100 tokens, d = 2048, F = 8192, L = 16: decode 1.36 -> 1.03 ms).
 // ---------------------------------------------------------------------------
-template <bool KC, typename TE>
+// ROWS: rows of the tile; 128 (K-contiguous operands only) halves the chunks per lane.
+template <bool KC, typename TE, int ROWS>
 struct Stager {
+  static_assert(ROWS == 256 || KC, "128-row tiles: K-contiguous operand");
+  static constexpr int NCH = ROWS / 32;
   uint32_t voff;       // per-lane byte offset inside the tile
   uint32_t step;       // byte distance between the lane's consecutive chunks (uniform)
   int r_lane, k_lane;  // EDGE only: first row / k index of this lane inside the tile
@@ -124,7 +135,7 @@ struct Stager {
   __device__ __forceinline__ void load(u32x4 (&r)[8], const TE* tile_base, int rows_left, int k_left) const {
     const char* b = reinterpret_cast<const char*>(tile_base);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NCH; ++i) {
       const char* bi = b + (size_t)i * step;            // uniform
       if (!EDGE) {
         r[i] = load8<TE>(reinterpret_cast<const TE*>(bi + voff));
@@ -139,7 +150,7 @@ struct Stager {
     if (KC) {
       const int c = lt & 7;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < NCH; ++i) {
         const int row = (lt >> 3) + 32 * i;
         *reinterpret_cast<u32x4*>(lds + lds_off(row, c)) = cook8<TE>(r[i]);
       }
@@ -162,14 +173,46 @@ struct Stager {
   }
 };
 
+// Sums of squares of the 64 k rows of a staged K-strided tile over its 256 columns, as two runs of 128 columns: a lane
+// squares its 8 (k) x 8 block, and the 16 lanes that share the k rows of a run halve the values among them step by step,
+// which leaves value (lane / 2) % 8 of the run in each.  About 80 vector instructions per K step of a loop that waits for
+// memory.
+__device__ __forceinline__ float row_squares(const u32x4 (&r)[8], int lane) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  float s[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    s[i] = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      s[i] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)r[i][w]), __builtin_bit_cast(bf16x2, (uint32_t)r[i][w]), s[i], false);
+  }
+  // partner lanes: 15 - i, then i ^ 7, then i ^ 3, then i ^ 1 of a row of 16; each keeps its bit's half of the values
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float keep = (lane & 8) ? s[i + 4] : s[i], give = (lane & 8) ? s[i] : s[i + 4];
+    s[i] = keep + dpp_move<0x140>(give);      // row_mirror
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float keep = (lane & 4) ? s[i + 2] : s[i], give = (lane & 4) ? s[i] : s[i + 2];
+    s[i] = keep + dpp_move<0x141>(give);      // row_half_mirror
+  }
+  const float keep = (lane & 2) ? s[1] : s[0], give = (lane & 2) ? s[0] : s[1];
+  const float v = keep + dpp_move<0x1B>(give);      // quad_perm [3,2,1,0]
+  return v + dpp_move<0xB1>(v);                     // quad_perm [1,0,3,2]
+}
+
 constexpr int NTHREADS = 512;   // 8 wavefronts: two per SIMD, so one's memory phase hides under the other's MFMAs
 
 // K loop of one output tile.  EDGE = false assumes the tile lies fully inside the
 // matrices and kseg is a multiple of 64 (no predication at all).
 template <class P, bool EDGE>
 __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& gi, int m0, int n0, bf16_t* smem,
-                                          acc_t& acc, int t, uint32_t& sync_count) {
+                                          acc_t<P>& acc, int t, uint32_t& sync_count) {
   typedef typename P::AType TA;
+  constexpr int WROWS = P::TILE_M / 2, STAGE = stage_elems<P>, NQ = P::TILE_M / 128;   // NQ: groups of 4 A fragments per slice
+  constexpr int DEPTH = P::TILE_M == 128 ? 2 : 1;      // K steps of operands in registers
   const int lane = t & 63, w = t >> 6, wm = w >> 2, wn = w & 3;
   const int lt = t & 255;
   // waves 0-3 stage A, waves 4-7 stage B (waves w and w+4 share a SIMD, so each SIMD holds one of each group)
@@ -179,8 +222,8 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   const KRange kr = p.krange(gi, spseg);
   const int nk = kr.count;
 
-  Stager<P::A_KC, TA> sa;
-  Stager<P::B_KC, bf16_t> sb;
+  Stager<P::A_KC, TA, P::TILE_M> sa;
+  Stager<P::B_KC, bf16_t, TN> sb;
   sa.init(lt, p.lda);
   sb.init(lt, p.ldb);
 
@@ -191,11 +234,16 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   const size_t a_row0 = P::A_KC ? (size_t)m0 * p.lda : (size_t)m0;   // tile origin at k = 0
   const size_t b_row0 = P::B_KC ? (size_t)n0 * p.ldb : (size_t)n0;
   const size_t a_kstep = P::A_KC ? 1 : (size_t)p.lda, b_kstep = P::B_KC ? 1 : (size_t)p.ldb;
-  u32x4 rg[8];
+  u32x4 rg[DEPTH][8];
+  int rg_seg[DEPTH], rg_k0[DEPTH];      // ROW_SQUARES: where the fetched K step lies
 
-  auto fetch = [&]() {
-    if (loads_a) sa.template load<EDGE>(rg, Aseg + a_row0 + ld_k0 * a_kstep, p.M - m0, kseg - ld_k0);
-    else sb.template load<EDGE>(rg, Bseg + b_row0 + ld_k0 * b_kstep, p.N - n0, kseg - ld_k0);
+  auto fetch = [&](auto buf) {
+    if (loads_a) sa.template load<EDGE>(rg[buf], Aseg + a_row0 + ld_k0 * a_kstep, p.M - m0, kseg - ld_k0);
+    else sb.template load<EDGE>(rg[buf], Bseg + b_row0 + ld_k0 * b_kstep, p.N - n0, kseg - ld_k0);
+    if constexpr (P::ROW_SQUARES) {
+      rg_seg[buf] = ld_seg;
+      rg_k0[buf] = ld_k0;
+    }
     ld_k0 += TK;
     if (ld_k0 >= kseg) {
       ld_k0 = 0;
@@ -226,10 +274,21 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
       }
     }
   };
-  auto stage = [&](int st) {
-    bf16_t* base = smem + st * STAGE_ELEMS;
-    if (loads_a) sa.store(base, rg, lt);
-    else sb.store(base + 256 * TK, rg, lt);
+  auto stage = [&](int st, auto buf) {
+    bf16_t* base = smem + st * STAGE;
+    if (loads_a) {
+      sa.store(base, rg[buf], lt);
+    } else {
+      if constexpr (P::ROW_SQUARES) {
+        if (m0 == 0) {
+          const float s2 = row_squares(rg[buf], lane);
+          const int k = rg_k0[buf] + ((lt >> 5) << 3) + ((lane >> 1) & 7), run = (n0 >> 7) + ((lane >> 4) & 1);
+          if (!(lane & 1) && k < kseg)
+            p.n2_part[((size_t)packed_index(rg_seg[buf], gi.lp, p.D.L) * (2 * ((p.N + TN - 1) / TN)) + run) * kseg + k] = s2;
+        }
+      }
+      sb.store(base + P::TILE_M * TK, rg[buf], lt);
+    }
   };
 
   // v_mfma_f32_16x16x32_bf16: a lane's fragment is 8 consecutive k of row lane%16; lane group lane/16 takes
@@ -242,12 +301,12 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   u32x4 fa[2][4], fb[2][4];
   const int frow = lane & 15, fch = ((lane >> 3) & 2) | (lane >> 5);
   auto read_a = [&](int st, int sl, int q, int buf) {
-    const bf16_t* a = smem + st * STAGE_ELEMS;
+    const bf16_t* a = smem + st * STAGE;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fa[buf][i] = ld16(a + lds_off(wm * 128 + (4 * q + i) * 16 + frow, 4 * sl + fch));
+    for (int i = 0; i < 4; ++i) fa[buf][i] = ld16(a + lds_off(wm * WROWS + (4 * q + i) * 16 + frow, 4 * sl + fch));
   };
   auto read_b = [&](int st, int sl, int buf) {
-    const bf16_t* b = smem + st * STAGE_ELEMS + 256 * TK;
+    const bf16_t* b = smem + st * STAGE + P::TILE_M * TK;
 #pragma unroll
     for (int j = 0; j < 4; ++j) fb[buf][j] = ld16(b + lds_off(wn * 64 + j * 16 + frow, 4 * sl + fch));
   };
@@ -263,21 +322,27 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   // One K step = the 64 MFMAs of this wave on tile `kt`; the fragment reads of the next group overlap the
   // MFMAs of the current one, and the MFMAs of a tile's last group are held back until the first fragment
   // reads of the next tile are in flight (their operands stay in registers across the memory phase).
-  auto mfma = [&](int) { mfma_g(1, 1, 1); };   // the group held back at the end of a K step
+  auto mfma_held = [&]() { mfma_g(NQ - 1, 1, 1); };   // the group held back at the end of a K step
   const int first_kt = 0;
   auto compute = [&](int kt) {
     const int cur = kt & 1;
     __builtin_amdgcn_s_setprio(1);
     read_b(cur, 0, 0);
     read_a(cur, 0, 0, 0);
-    if (kt != first_kt) mfma_g(1, 1, 1);   // last group of the previous tile, deferred to cover this read latency
-    read_a(cur, 0, 1, 1);
-    mfma_g(0, 0, 0);
-    read_b(cur, 1, 1);
-    read_a(cur, 1, 0, 0);
-    mfma_g(1, 1, 0);
-    read_a(cur, 1, 1, 1);
-    mfma_g(0, 0, 1);
+    if (kt != first_kt) mfma_held();   // last group of the previous tile, deferred to cover this read latency
+    if constexpr (NQ == 2) {
+      read_a(cur, 0, 1, 1);
+      mfma_g(0, 0, 0);
+      read_b(cur, 1, 1);
+      read_a(cur, 1, 0, 0);
+      mfma_g(1, 1, 0);
+      read_a(cur, 1, 1, 1);
+      mfma_g(0, 0, 1);
+    } else {
+      read_b(cur, 1, 1);
+      read_a(cur, 1, 0, 1);
+      mfma_g(0, 0, 0);
+    }
     __builtin_amdgcn_s_setprio(0);
   };
 
@@ -293,35 +358,82 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   // and read by both from 2k+1 (A) / 2k+2 (B) on, after a barrier.
   // (the prologue is repeated inside each branch on purpose: every branch then only ever
   // touches its own operand, which keeps the other operand's addressing out of its registers)
-  if (loads_a) {
-    fetch();
-    stage(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt >= 1) stage(kt & 1);
-      if (kt + 1 < nk) {
-        if (ld_k0 == 0) xcd_sync();   // the fetch opens a new K segment
-        fetch();
+  const std::integral_constant<int, 0> b0;
+  if constexpr (DEPTH == 1) {
+    if (loads_a) {
+      fetch(b0);
+      stage(0, b0);
+      __syncthreads();
+      for (int kt = 0; kt < nk; ++kt) {
+        if (kt >= 1) stage(kt & 1, b0);
+        if (kt + 1 < nk) {
+          if (ld_k0 == 0) xcd_sync();   // the fetch opens a new K segment
+          fetch(b0);
+        }
+        __syncthreads();
+        compute(kt);
+        __syncthreads();
       }
+      mfma_held();
+    } else {
+      fetch(b0);
+      stage(0, b0);
+      if (nk > 1) fetch(b0);
       __syncthreads();
-      compute(kt);
-      __syncthreads();
+      for (int kt = 0; kt < nk; ++kt) {
+        if (kt >= 1) compute(kt - 1);
+        __syncthreads();
+        if (kt + 1 < nk) stage((kt + 1) & 1, b0);
+        if (kt + 2 < nk) fetch(b0);
+        __syncthreads();
+      }
+      compute(nk - 1);
+      mfma_held();
     }
-    mfma(1);
   } else {
-    fetch();
-    stage(0);
-    if (nk > 1) fetch();
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt >= 1) compute(kt - 1);
+    // The same phases with two K steps of operands in registers: step k's registers are fetched again for step k + 2 right
+    // after they went to LDS (buffer k & 1, hence the pairs of steps).
+    const std::integral_constant<int, 1> b1;
+    if (loads_a) {
+      fetch(b0);
+      if (nk > 1) fetch(b1);
+      stage(0, b0);
+      if (nk > 2) fetch(b0);
       __syncthreads();
-      if (kt + 1 < nk) stage((kt + 1) & 1);
-      if (kt + 2 < nk) fetch();
+      auto step = [&](int kt, auto buf) {
+        if (kt >= 1) {
+          stage(kt & 1, buf);
+          if (kt + 2 < nk) fetch(buf);
+        }
+        __syncthreads();
+        compute(kt);
+        __syncthreads();
+      };
+      for (int kt = 0; kt < nk; kt += 2) {
+        step(kt, b0);
+        if (kt + 1 < nk) step(kt + 1, b1);
+      }
+      mfma_held();
+    } else {
+      fetch(b0);
+      if (nk > 1) fetch(b1);
+      stage(0, b0);
+      if (nk > 2) fetch(b0);
       __syncthreads();
+      auto step = [&](int kt, auto buf) {      // buf: that of step kt + 1
+        if (kt >= 1) compute(kt - 1);
+        __syncthreads();
+        if (kt + 1 < nk) stage((kt + 1) & 1, buf);
+        if (kt + 3 < nk) fetch(buf);
+        __syncthreads();
+      };
+      for (int kt = 0; kt < nk; kt += 2) {
+        step(kt, b1);
+        if (kt + 1 < nk) step(kt + 1, b0);
+      }
+      compute(nk - 1);
+      mfma_held();
     }
-    compute(nk - 1);
-    mfma(1);
   }
 }
 
@@ -332,7 +444,8 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
 // inside the matrix, no predicates.
 template <class P, bool EDGE>
 __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi, int m0, int n0, bf16_t* smem,
-                                         acc_t& acc, int t) {
+                                         acc_t<P>& acc, int t) {
+  constexpr int WROWS = P::TILE_M / 2;
   const int lane = t & 63, w = t >> 6;
   const int wu = __builtin_amdgcn_readfirstlane(w), wm = wu >> 2, wn = wu & 3;
   const int M = p.M, N = p.N;
@@ -347,15 +460,15 @@ __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi
   pos.ru = 0;
   const bool col_ok = !EDGE || pos.col() < N;
   typename P::Epi est;
-  p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm * 128);
-  // The wave's block is 32 row groups of 4 rows (4 slabs of 8).  Each slab goes through the wave's
+  p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm * WROWS, (m0 / WROWS) + wm);
+  // The wave's block is 32 row groups of 4 rows (4 slabs of 8; 16 and 2 in 128-row tiles).  Each slab goes through the wave's
   // private LDS region (a wave's LDS accesses complete in issue order, so the transposition needs
   // no barrier).  The global loads the policy's epilogue needs run ahead of their use as a rolling
   // window: before group g is consumed the loads of all groups below g + depth have been issued, so
   // loads stay in flight while earlier groups are computed and stored.  The window deepens slab by
   // slab as the accumulators already written out stop occupying registers (predicated edge tiles
   // keep to 4: the predicates' registers come on top).
-  constexpr int NG = 32;
+  constexpr int NG = WROWS / 4;
   // look-ahead (in row groups) while group g is consumed
   auto depth = [](int g) constexpr {
     const int d = g < 8 ? P::EPI_BATCH : (g < 16 ? P::EPI_BATCH_LATE : P::EPI_BATCH_LAST);
@@ -363,7 +476,7 @@ __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi
   };
   typename P::EpiRegs er[NG];
   auto issue = [&](int g) {
-    pos.ru = m0 + wm * 128 + g * 4;
+    pos.ru = m0 + wm * WROWS + g * 4;
     if (!EDGE || (col_ok && pos.row() < M)) p.epi_load(er[g], gi, pos);
   };
 #pragma unroll
@@ -384,7 +497,7 @@ __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi
     const int want = g + depth(g);
 #pragma unroll
     for (int q = (done < NG ? done : NG); q < (want < NG ? want : NG); ++q) issue(q);
-    pos.ru = m0 + wm * 128 + g * 4;
+    pos.ru = m0 + wm * WROWS + g * 4;
     const float4 v = *reinterpret_cast<const float4*>(wl + ((g & 7) * 4 + pos.rl) * 64 + pos.cl);
     if (!EDGE || (col_ok && pos.row() < M)) p.epi4(est, gi, pos, v, er[g]);
   }
@@ -407,12 +520,12 @@ __global__ __launch_bounds__(NTHREADS) void gemm_bf16_kernel(P p, TileGrid tg, i
     int gorder, tm, tn;
     if (!tg.decode(vb, gorder, tm, tn)) continue;
     const typename P::GInfo gi = p.ginfo(gorder);
-    const int m0 = tm * TM, n0 = tn * TN;
+    const int m0 = tm * P::TILE_M, n0 = tn * TN;
 
-    // wave w owns output rows (w/4)*128.., columns (w%4)*64..
-    acc_t acc;
+    // wave w owns output rows (w/4)*TILE_M/2.., columns (w%4)*64..
+    acc_t<P> acc;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < P::TILE_M / 32; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -428,7 +541,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_bf16_kernel(P p, TileGrid tg, i
       main_loop<P, false>(p, gi, m0, n0, smem, acc, t, sync_count);
       epilogue<P, false>(p, gi, m0, n0, smem, acc, t);
     } else {
-      const bool inside = (m0 + TM <= p.M) && (n0 + TN <= p.N);
+      const bool inside = (m0 + P::TILE_M <= p.M) && (n0 + TN <= p.N);
       main_loop<P, true>(p, gi, m0, n0, smem, acc, t, sync_count);
       if (inside) epilogue<P, false>(p, gi, m0, n0, smem, acc, t);
       else epilogue<P, true>(p, gi, m0, n0, smem, acc, t);
@@ -441,10 +554,10 @@ int g_num_wg_slots = 0;   // workgroups of a persistent grid: the CU count, roun
 
 template <class P>
 hipError_t launch(hipStream_t s, const P& p, int G) {
-  const TileGrid tg = TileGrid::make(G, p.M, p.N, TM, TN);
+  const TileGrid tg = TileGrid::make(G, p.M, p.N, P::TILE_M, TN);
   const int nwg = tg.num_wg();
   if (g_num_wg_slots < 8) return hipErrorNotInitialized;
-  if (p.M % TM == 0 && p.N % TN == 0 && p.kseg % TK == 0) {
+  if (p.M % P::TILE_M == 0 && p.N % TN == 0 && p.kseg % TK == 0) {
     // The tile loop gives every workgroup a fixed share (tiles i, i + grid, ...).  The shares are equal when all
     // groups have the same K, or when every workgroup meets every round of groups equally often (the slots of
     // a round are a multiple of the slots one pass of the grid covers; the snake order evens out the teams).
@@ -461,12 +574,12 @@ hipError_t launch(hipStream_t s, const P& p, int G) {
         const hipError_t ez = launch_zero_i32(s, reinterpret_cast<int32_t*>(q.xcd_sync), 8 * 64);
         if (ez != hipSuccess) return ez;
       }
-      hipLaunchKernelGGL((gemm_bf16_kernel<P, true>), dim3(grid), dim3(NTHREADS), LDS_BYTES, s, q, tg, nwg);
+      hipLaunchKernelGGL((gemm_bf16_kernel<P, true>), dim3(grid), dim3(NTHREADS), lds_bytes<P>, s, q, tg, nwg);
       return hipGetLastError();
     }
-    hipLaunchKernelGGL((gemm_bf16_kernel<P, true>), dim3(grid), dim3(NTHREADS), LDS_BYTES, s, p, tg, nwg);
+    hipLaunchKernelGGL((gemm_bf16_kernel<P, true>), dim3(grid), dim3(NTHREADS), lds_bytes<P>, s, p, tg, nwg);
   } else {
-    hipLaunchKernelGGL((gemm_bf16_kernel<P, false>), dim3(nwg), dim3(NTHREADS), LDS_BYTES, s, p, tg, nwg);
+    hipLaunchKernelGGL((gemm_bf16_kernel<P, false>), dim3(nwg), dim3(NTHREADS), lds_bytes<P>, s, p, tg, nwg);
   }
   return hipGetLastError();
 }
@@ -474,10 +587,10 @@ hipError_t launch(hipStream_t s, const P& p, int G) {
 template <class P>
 hipError_t set_lds_attr() {
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<P, true>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<P>);
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<P, false>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<P>);
 }
 
 }  // namespace
@@ -494,6 +607,14 @@ hipError_t init_gemm_bf16() {
   if ((e = set_lds_attr<DecPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DzPolicy<bf16_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DzPolicy<bf16_t, true>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<EncPolicy<bf16_t>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<EncPolicy<bf16_t, int8_t>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<DecPolicy<bf16_t>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<DecPolicy<bf16_t>, true>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<DecPolicy<bf16_t, true>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<DecPolicy<bf16_t, true>, true>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<DzPolicy<bf16_t>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<Few<DzPolicy<bf16_t, true>>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, false>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, true, true>>()) != hipSuccess) return e;
@@ -504,29 +625,38 @@ hipError_t init_gemm_bf16() {
   return hipSuccess;
 }
 
+// 128-row tiles where all tokens fit one of them: two would read the weights twice for the same matrix time
+static bool few_rows(Dims D) { return D.B <= Few<EncPolicy<bf16_t>>::TILE_M; }
+template <class P>
+static hipError_t launch_rows(hipStream_t s, Dims D, const P& p, int G) {
+  return few_rows(D) ? launch(s, Few<P>{p}, G) : launch(s, p, G);
+}
+
 hipError_t launch_enc_bf16(hipStream_t s, Dims D, const EncArgs& a, bool int8_x) {
   if (int8_x) {
     EncPolicy<bf16_t, int8_t> p{D, D.B, D.F, D.d, D.d, D.F,
                                 (const int8_t*)a.x, (const bf16_t*)a.W_enc, a.b_enc, a.theta, a.x_scale,
                                 0.5f * a.ste_eps, (bf16_t*)a.z, (bf16_t*)a.pre, a.cls, a.l0, a.log_threshold, a.pre32};
-    return launch(s, p, D.L);
+    return launch_rows(s, D, p, D.L);
   }
   EncPolicy<bf16_t> p{D, D.B, D.F, D.d, D.d, D.F,
                       (const bf16_t*)a.x, (const bf16_t*)a.W_enc, a.b_enc, a.theta, nullptr,
                       0.5f * a.ste_eps, (bf16_t*)a.z, (bf16_t*)a.pre, a.cls, a.l0, a.log_threshold, a.pre32};
-  return launch(s, p, D.L);
+  return launch_rows(s, D, p, D.L);
 }
-DecSplit dec_split_bf16(Dims D) { return choose_dec_split(D, TM, TN, TK, 32, 0.8); }
+DecSplit dec_split_bf16(Dims D) { return choose_dec_split(D, few_rows(D) ? TM / 2 : TM, TN, TK, 32, 0.8); }
+size_t dec_row_squares_floats(Dims D) { return few_rows(D) ? (size_t)D.P() * 2 * ((D.d + TN - 1) / TN) * D.F : 0; }
 hipError_t launch_dec_bf16(hipStream_t s, Dims D, const DecArgs& a) {
   if (a.split.groups > 0) {
     DecPolicy<bf16_t, true> p{D, D.B, D.d, D.F, D.F, D.d, (const bf16_t*)a.z, (const bf16_t*)a.W_dec, a.b_dec, a.y_hat,
-                              a.skip_flags, a.kcap, nullptr, a.split, a.split_part};
-    const hipError_t e = launch(s, p, a.split.groups);
+                              a.skip_flags, a.kcap, nullptr, a.split, a.split_part, a.row_squares};
+    const hipError_t e = a.row_squares ? launch(s, Few<DecPolicy<bf16_t, true>, true>{p}, a.split.groups)
+                                       : launch_rows(s, D, p, a.split.groups);
     return e != hipSuccess ? e : launch_decode_combine(s, D, a.split, a.split_part, a.b_dec, a.y_hat, a.skip_flags, a.kcap);
   }
   DecPolicy<bf16_t> p{D, D.B, D.d, D.F, D.F, D.d, (const bf16_t*)a.z, (const bf16_t*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags, a.kcap,
-                      a.xcd_sync, a.split, nullptr};
-  return launch(s, p, D.L);
+                      a.xcd_sync, a.split, nullptr, a.row_squares};
+  return a.row_squares ? launch(s, Few<DecPolicy<bf16_t>, true>{p}, D.L) : launch_rows(s, D, p, D.L);
 }
 template <bool FOLD>
 static hipError_t launch_dz_mode(hipStream_t s, Dims D, const DzArgs& a) {
@@ -534,7 +664,7 @@ static hipError_t launch_dz_mode(hipStream_t s, Dims D, const DzArgs& a) {
                            (const bf16_t*)a.d_yhat, (const bf16_t*)a.W_dec, (const bf16_t*)a.z, a.cls, a.norms,
                            a.lam_c_over_b, a.C, (bf16_t*)a.dpre, a.lam1_over_b, a.skip_flags, a.kcap,
                            a.x_scale, a.part_theta, a.part_benc, a.part_below};
-  return launch(s, p, D.L);
+  return launch_rows(s, D, p, D.L);
 }
 hipError_t launch_dz_bf16(hipStream_t s, Dims D, const DzArgs& a) {
   return a.part_theta ? launch_dz_mode<true>(s, D, a) : launch_dz_mode<false>(s, D, a);

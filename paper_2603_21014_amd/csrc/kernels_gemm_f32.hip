@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
     typename P::Epi est;
     EpiPos pos{m0 + wm, n0 + wn + 16 * j, lane & 15, 4 * (lane >> 4)};
     const bool col_ok = pos.col() < N;
-    p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm);
+    p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm, 0);
     typename P::EpiRegs er[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -234,12 +234,12 @@ DecSplit dec_split_f32(Dims D) {
 hipError_t launch_dec_f32(hipStream_t s, Dims D, const DecArgs& a) {
   if (a.split.groups > 0) {
     DecPolicy<float, true> p{D, D.B, D.d, D.F, D.F, D.d, (const float*)a.z, (const float*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags,
-                             a.kcap, nullptr, a.split, a.split_part};
+                             a.kcap, nullptr, a.split, a.split_part, nullptr};
     const hipError_t e = launch(s, p, a.split.groups, dec_tile(D));
     return e != hipSuccess ? e : launch_decode_combine(s, D, a.split, a.split_part, a.b_dec, a.y_hat, a.skip_flags, a.kcap);
   }
   DecPolicy<float> p{D, D.B, D.d, D.F, D.F, D.d, (const float*)a.z, (const float*)a.W_dec, a.b_dec, a.y_hat, a.skip_flags, a.kcap,
-                     nullptr, a.split, nullptr};
+                     nullptr, a.split, nullptr, nullptr};
   return launch(s, p, D.L);
 }
 hipError_t launch_dz_f32(hipStream_t s, Dims D, const DzArgs& a) {

@@ -66,6 +66,21 @@ def test_decode_with_cut_k_ranges(dtype, L, d, F, B):
     show(f"cut decode {dtype} L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL[dtype]))
 
 
+@pytest.mark.parametrize("L,d,F,B,int8", [
+    (2, 40, 72, 1, False),
+    (3, 264, 520, 64, True),
+    (4, 512, 1024, 65, False),      # rows end just behind the first half of the tile, columns and K fill tiles
+    (3, 512, 512, 128, False),      # full tile
+    (2, 136, 264, 128, True),
+    (3, 264, 520, 129, False),      # first size with the large tiles
+])
+def test_few_tokens(L, d, F, B, int8):
+    """At most 128 tokens: tiles of 128 rows, decoder norms from the squares that the decode takes along."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=17 + B, int8_inputs=int8)
+    g, o = run_both(w)
+    show(f"few tokens L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
+
+
 def test_bf16_several_tiles_and_segments():
     """Spans 2x3 output tiles of 256x256 per group and up to 4 K segments."""
     w = S.scaled(S.WORKLOADS["gpt2"], L=4, d=512, F=768, B=512, k_active=16)
