@@ -140,9 +140,11 @@ float backward_threshold(const clt_config* c) {
 Plan make_plan(const clt_config* c) {
   const size_t L = c->L, d = c->d, F = c->F, B = c->B;
   const size_t esz = c->dtype == CLT_DTYPE_BF16 ? 2 : 4;
-  // row blocks of the column-partial arrays: at most 32-row blocks of the reduction kernels, or the 128-row half
-  // tiles of the dz epilogue that folds the straight-through reductions in (whichever is more)
-  const size_t rbs = row_blocks(c->B) > fold_row_blocks(c->B) ? row_blocks(c->B) : fold_row_blocks(c->B);
+  const Dims dims{c->L, c->d, c->F, c->B};
+  const bool bf16 = c->dtype == CLT_DTYPE_BF16;
+  // row blocks of the column-partial arrays: at most 32-row blocks of the reduction kernels, or the half tiles of
+  // the dz epilogue that folds the straight-through reductions in (whichever is more)
+  const size_t rbs = std::max(row_blocks(c->B), fold_row_blocks(dims));
   const size_t wide = F > d ? F : d;
   Plan p;
   size_t o = 0;
@@ -153,8 +155,6 @@ Plan make_plan(const clt_config* c) {
   p.part_cols = o;  o += align_up(rbs * L * wide * 4);
   p.part_cols2 = o; o += align_up(rbs * L * F * 4);
   p.part_cols3 = o; o += align_up(rbs * L * F * 4);
-  const Dims dims{c->L, c->d, c->F, c->B};
-  const bool bf16 = c->dtype == CLT_DTYPE_BF16;
   // (part_rec also holds the L * row_blocks(B) partial sums of clt_norm_accumulate)
   p.part_rec = o;   o += align_up(L * std::max<size_t>(reduce_grid(bf16, dims, c->d).blocks(), row_blocks(c->B)) * 8);
   p.part_sp = o;    o += align_up(L * (size_t)reduce_grid(bf16, dims, c->F).blocks() * 8);
@@ -648,7 +648,7 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   // another number of row blocks, and the kernels that sum them look at the switch.
   const bool fold = h->bf16 && mode != CLT_DECODE_GATHER;
   if (fold) { za.x_scale = h->int8 ? x_scale : nullptr; za.part_theta = part; za.part_benc = part2; za.part_below = part3; }
-  const int nparts = fold ? fold_row_blocks(D.B) : rbs;
+  const int nparts = fold ? fold_row_blocks(D) : rbs;
   PartsSwitch psw;
   if (fold && mode == CLT_DECODE_AUTO) psw = PartsSwitch{flags, kcap, rbs};
   DWdecArgs wa{z, d_yhat, W_dec, G, norms, gW_dec, fdec, skip, kcap};

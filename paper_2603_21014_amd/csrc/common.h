@@ -178,11 +178,20 @@ struct DzArgs {        // dz[l] = sum_{lp>=l} dyhat[lp] W_dec[p(l,lp)]^T + g_sp,
   const int32_t* skip_flags = nullptr;   // optional switch: stand down when the gather path is selected
   int kcap = 0;
   // bf16 kernel only, all four or none: the straight-through reductions folded into the epilogue (then dpre is
-  // final and launch_ste_reduce is not needed).  Column partials per 128-row half tile, fold_row_blocks(B) of
+  // final and launch_ste_reduce is not needed).  Column partials per half tile of rows, fold_row_blocks(D) of
   // them: [half tile][L][F].  x_scale: the row scales of int8 inputs, or NULL.
   const float* x_scale = nullptr; float* part_theta = nullptr; float* part_benc = nullptr; float* part_below = nullptr;
 };
-inline int fold_row_blocks(int B) { return 2 * ((B + 255) / 256); }      // (at most 128 tokens: 64-row halves, two as well)
+// Whether the bf16 contractions over tokens as rows run in tiles of 128 tokens instead of 256: up to 384 tokens, and where
+// 256-row tiles would be too few for the 256 CUs.  Both sides measured at 130 / 256 / 300 / 384 / 512 / 640 tokens: gradients
+// of L = 12, d = 768, F = 6144: 1108 / 1199 / 1455 / 1554 / 1878 / 2204 us with 128 rows, 1121 / 1208 / 1505 / 1584 / 1741 / 2121
+// with 256; forward of L = 8, d = 2048, F = 8192: 530 / 572 / 787 / 820 / 977 / 1697 and 566 / 612 / 838 / 878 / 914 / 1239;
+// gradients of L = 4, d = 512, F = 2048 (32 to 96 tiles of 256 rows): 142 / 151 / 159 / 166 / 182 / 194 and 177 / 187 / 187 / 197
+// / 207 / 223.
+inline bool few_rows(Dims D) {
+  return D.B <= 384 || (double)D.L * ((D.B + 255) / 256) * ((D.F + 255) / 256) < 256.0;
+}
+inline int fold_row_blocks(Dims D) { return few_rows(D) ? 2 * ((D.B + 127) / 128) : 2 * ((D.B + 255) / 256); }
 // Optional Adam fused into the two weight-gradient GEMMs (m == nullptr: plain gradient output)
 struct AdamFuseArgs { float* m; float* v; float* master; AdamScalars a; };
 struct DWdecArgs {     // dW_dec[p] = z[l]^T dyhat[lp] + (G/n)[l,f] W_dec[p][f,:]

@@ -563,7 +563,7 @@ struct DWencPolicy {
   __device__ void epi_end(Epi&, const GInfo&, float*) const {}
 };
 
-// The variants for at most 128 rows (tokens).
+// The variants for few rows (tokens), see few_rows.
 template <class P, bool ROW_SQUARES_ = false>
 struct Few : P {
   static constexpr int TILE_M = 128;

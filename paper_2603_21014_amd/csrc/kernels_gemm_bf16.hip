@@ -42,13 +42,12 @@ constexpr int TM = 256, TN = 256, TK = 64;
 template <class P> constexpr int stage_elems = (P::TILE_M + TN) * TK;             // A tile + B tile, bf16 elements
 template <class P> constexpr int lds_bytes = 2 * stage_elems<P> * 2;              // two stages = 128 KB (96 with 128 rows)
 
-// Tiles of 128 rows, for launches with at most 128 tokens: everything else alike, each wavefront half as many
-// accumulators.  Such a launch streams the weights once and is bound by that, not by the matrix cores, but 256-row tiles spend
+// Tiles of 128 rows, for launches with few tokens (few_rows): everything else alike, each wavefront half as many
+// accumulators.  Such a launch streams the weights and is bound by that, not by the matrix cores, but 256-row tiles spend
 // 1.5 us of matrix time on a K step whose 32 KB of weights take 1.5 us to arrive.  The registers that are free here hold a
 // second K step of operands on its way, and the decode takes the squares for the decoder norms along instead of a second
 // pass over the weights.  One prompt of 100 tokens (L = 16, d = 2048, F = 8192: 4.6 GB of decoder): forward 1807 -> 1105 us,
 // of which decode 1073 -> 930 and norms 806 -> 20.
-
 // element offset of 16-byte chunk `c` (8 bf16) of tile row `row`
 __device__ __forceinline__ int lds_off(int row, int c) {
   return row * TK + (((c ^ row ^ (row >> 3)) & 7) << 3);
@@ -625,8 +624,6 @@ hipError_t init_gemm_bf16() {
   return hipSuccess;
 }
 
-// 128-row tiles where all tokens fit one of them: two would read the weights twice for the same matrix time
-static bool few_rows(Dims D) { return D.B <= Few<EncPolicy<bf16_t>>::TILE_M; }
 template <class P>
 static hipError_t launch_rows(hipStream_t s, Dims D, const P& p, int G) {
   return few_rows(D) ? launch(s, Few<P>{p}, G) : launch(s, p, G);

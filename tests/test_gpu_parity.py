@@ -72,10 +72,13 @@ def test_decode_with_cut_k_ranges(dtype, L, d, F, B):
     (4, 512, 1024, 65, False),      # rows end just behind the first half of the tile, columns and K fill tiles
     (3, 512, 512, 128, False),      # full tile
     (2, 136, 264, 128, True),
-    (3, 264, 520, 129, False),      # first size with the large tiles
+    (3, 264, 520, 129, False),      # two row tiles, the squares from the first
+    (8, 136, 4104, 384, False),     # last and first size on either side of the tile rule: 8 x 2 x 17 tiles of 256 rows
+    (8, 136, 4104, 385, False),
+    (2, 264, 520, 700, False),      # many tokens, few tiles
 ])
 def test_few_tokens(L, d, F, B, int8):
-    """At most 128 tokens: tiles of 128 rows, decoder norms from the squares that the decode takes along."""
+    """Few tokens: tiles of 128 rows, decoder norms from the squares that the decode takes along."""
     w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=17 + B, int8_inputs=int8)
     g, o = run_both(w)
     show(f"few tokens L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
