@@ -438,72 +438,84 @@ __global__ __launch_bounds__(1024, 2) void gather_dz_lds_kernel(Dims D, GatherLi
 }
 
 // ---- feature lists: column scan of the class bytes in FL_SEGS token segments ----
-// Each thread owns 4 consecutive features of one layer and one token segment.
+// Each thread owns 8 consecutive features of one layer and one token segment (F is a multiple of 8), the class bytes of
+// eight tokens in flight.
 __global__ __launch_bounds__(256) void fl_count_kernel(Dims D, const uint8_t* __restrict__ cls, FeatureLists fl,
                                                        const int32_t* __restrict__ flags) {
   if (!lists_backward_selected(flags, fl.kcap)) return;
-  const int LF4 = D.L * D.F / 4;
+  const int LF8 = D.L * D.F / 8;
   const int q = blockIdx.x * 256 + threadIdx.x, sgm = blockIdx.y;
-  if (q >= LF4) return;
-  const int l = (q * 4) / D.F, f = (q * 4) % D.F;
+  if (q >= LF8) return;
+  const int l = (q * 8) / D.F, f = (q * 8) % D.F;
   const int seg_len = (D.B + FL_SEGS - 1) / FL_SEGS;
   const int b0 = sgm * seg_len, b1 = min(D.B, b0 + seg_len);
-  int c[4] = {0, 0, 0, 0};
+  int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll 8
   for (int b = b0; b < b1; ++b) {
-    const uint32_t a4 = *reinterpret_cast<const uint32_t*>(cls + ((size_t)l * D.B + b) * D.F + f);
-    const uint32_t listed = (a4 | (a4 >> 1)) & 0x01010101u;      // active, or inside the threshold window
+    const uint2 a8 = *reinterpret_cast<const uint2*>(cls + ((size_t)l * D.B + b) * D.F + f);
+    const uint32_t lo = (a8.x | (a8.x >> 1)) & 0x01010101u, hi = (a8.y | (a8.y >> 1)) & 0x01010101u;      // active, or inside the threshold window
 #pragma unroll
-    for (int i = 0; i < 4; ++i) c[i] += (int)((listed >> (8 * i)) & 1u);
+    for (int i = 0; i < 4; ++i) { c[i] += (int)((lo >> (8 * i)) & 1u); c[4 + i] += (int)((hi >> (8 * i)) & 1u); }
   }
-  int32_t* o = fl.seg + (size_t)sgm * D.L * D.F + (size_t)q * 4;
-  o[0] = c[0]; o[1] = c[1]; o[2] = c[2]; o[3] = c[3];
+  int4* o = reinterpret_cast<int4*>(fl.seg + (size_t)sgm * D.L * D.F + (size_t)q * 8);
+  o[0] = make_int4(c[0], c[1], c[2], c[3]);
+  o[1] = make_int4(c[4], c[5], c[6], c[7]);
 }
 
-// One workgroup of 1024 lanes per layer: layer-local exclusive scan over the features of the summed
-// segment counts; the segment counts are turned into each segment's first slot.  A lane owns a
-// run of consecutive features (8 at F = 8192, so neighbouring lanes share cache lines).
+// One workgroup of 1024 lanes per layer: layer-local exclusive scan over the features of the summed segment counts; the
+// segment counts are turned into each segment's first slot.  The lanes take 1024 consecutive features at a time, so that
+// every access is one run of memory (a lane with a run of 8 features of its own: 152 us at 16 x 8192 features, each access of
+// a wavefront spread over 2 KB).
 constexpr int FL_SCAN_THREADS = 1024;
 __global__ __launch_bounds__(FL_SCAN_THREADS) void fl_scan_kernel(Dims D, FeatureLists fl,
                                                                   int32_t* __restrict__ flags, int dense_beyond) {
   if (!lists_backward_selected(flags, fl.kcap)) return;
-  __shared__ int tot[FL_SCAN_THREADS];
-  const int l = blockIdx.x, tid = threadIdx.x;
-  const int per = (D.F + FL_SCAN_THREADS - 1) / FL_SCAN_THREADS;
-  const int f0 = min(D.F, tid * per), f1 = min(D.F, f0 + per);
+  constexpr int WAVES = FL_SCAN_THREADS / 64;
+  __shared__ int wtot[WAVES];
+  const int l = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const size_t LF = (size_t)D.L * D.F;
-  int sum = 0;
-  for (int f = f0; f < f1; ++f) {
-    int c = 0;
-    for (int sgm = 0; sgm < FL_SEGS; ++sgm) c += fl.seg[(size_t)sgm * LF + (size_t)l * D.F + f];
-    sum += c;
-  }
-  tot[tid] = sum;
-  __syncthreads();
-  for (int off = 1; off < FL_SCAN_THREADS; off <<= 1) {   // inclusive scan of the lane totals
-    const int v = tid >= off ? tot[tid - off] : 0;
+  int run = 0;      // entries of the features before this chunk
+  for (int f0 = 0; f0 < D.F; f0 += FL_SCAN_THREADS) {
+    const int f = f0 + threadIdx.x;
+    const bool in = f < D.F;
+    const size_t lf = (size_t)l * D.F + (in ? f : 0);
+    int v[FL_SEGS], c = 0;
+#pragma unroll
+    for (int sgm = 0; sgm < FL_SEGS; ++sgm) v[sgm] = in ? fl.seg[(size_t)sgm * LF + lf] : 0;
+#pragma unroll
+    for (int sgm = 0; sgm < FL_SEGS; ++sgm) c += v[sgm];
+    int incl = c;      // inclusive scan over the wavefront
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int u = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += u;
+    }
+    if (lane == 63) wtot[w] = incl;
     __syncthreads();
-    tot[tid] += v;
-    __syncthreads();
+    int before = run, total = 0;
+#pragma unroll
+    for (int q = 0; q < WAVES; ++q) {
+      if (q < w) before += wtot[q];
+      total += wtot[q];
+    }
+    __syncthreads();      // the next chunk writes wtot again
+    if (in) {
+      int pos = before + incl - c;
+      fl.off[lf] = pos;
+      fl.cnt[lf] = c;
+#pragma unroll
+      for (int sgm = 0; sgm < FL_SEGS; ++sgm) {
+        fl.seg[(size_t)sgm * LF + lf] = pos;
+        pos += v[sgm];
+      }
+    }
+    run += total;
   }
-  if (tid == FL_SCAN_THREADS - 1) {
-    atomicMax(&flags[3], tot[tid]);      // the longest layer decides whether the fused dz has room
+  if (threadIdx.x == 0) {
+    atomicMax(&flags[3], run);      // the longest layer decides whether the fused dz has room
     // Automatic mode: lists too long for the fused dz are long enough for the dense kernels to win, so the backward
     // is handed back to them (they run after this kernel and look at the same bit; so do the list kernels).
-    if (dense_beyond > 0 && tot[tid] > dense_beyond) atomicAnd(&flags[0], ~2);
-  }
-  int run = tot[tid] - sum;
-  for (int f = f0; f < f1; ++f) {
-    const size_t lf = (size_t)l * D.F + f;
-    fl.off[lf] = run;
-    int c = 0;
-    for (int sgm = 0; sgm < FL_SEGS; ++sgm) {
-      const int v = fl.seg[(size_t)sgm * LF + lf];
-      fl.seg[(size_t)sgm * LF + lf] = run + c;
-      c += v;
-    }
-    fl.cnt[lf] = c;
-    run += c;
+    if (dense_beyond > 0 && run > dense_beyond) atomicAnd(&flags[0], ~2);
   }
 }
 
@@ -983,10 +995,19 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
   const float* tv = fl.val + (size_t)l * D.B * fl.kcap + off;
   for (int j = sub; j < cnt; j += 16) {
     float acc = 0.f;
-    for (int lp = l; lp < D.L; ++lp) {
-      const float* q = fl.dz_part + (size_t)packed_index(l, lp, D.L) * 8 * fl.ecap + off + j;
+    const float* q = fl.dz_part + (size_t)packed_index(l, l, D.L) * 8 * fl.ecap + off + j;      // the targets' partials follow each other
+    const int n = (D.L - l) * 8;
+    int i = 0;
+    for (; i + 32 <= n; i += 32) {      // four targets' partials in flight
+      float p[32];
 #pragma unroll
-      for (int s8 = 0; s8 < 8; ++s8) acc += q[(size_t)s8 * fl.ecap];
+      for (int u = 0; u < 32; ++u) p[u] = q[(size_t)(i + u) * fl.ecap];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) acc += p[u];
+    }
+    for (; i < n; i += 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += q[(size_t)(i + u) * fl.ecap];
     }
     const float zv = tv[j];
     const float ex = __builtin_amdgcn_exp2f(-2.0f * 1.4426950408889634f * C * nn * fabsf(zv));
@@ -1086,8 +1107,8 @@ hipError_t init_gather() {
 hipError_t launch_feature_lists(hipStream_t s, bool bf16, Dims D, const uint8_t* cls, const void* z, FeatureLists fl,
                                 int32_t* flags, bool dense_when_too_long) {
   const int LF4 = D.L * D.F / 4;
-  const dim3 grid((LF4 + 255) / 256, FL_SEGS);
-  hipLaunchKernelGGL(fl_count_kernel, grid, dim3(256), 0, s, D, cls, fl, flags);
+  const dim3 grid((LF4 + 255) / 256, FL_SEGS), grid8((LF4 / 2 + 255) / 256, FL_SEGS);
+  hipLaunchKernelGGL(fl_count_kernel, grid8, dim3(256), 0, s, D, cls, fl, flags);
   hipLaunchKernelGGL(fl_scan_kernel, dim3(D.L), dim3(FL_SCAN_THREADS), 0, s, D, fl, flags,
                      dense_when_too_long && fl.dz_part ? fl.ecap : 0);
   if (bf16)
