@@ -313,28 +313,27 @@ __global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, int rows, in
   }
 }
 
-__global__ __launch_bounds__(256) void loss_final_kernel(const double* part_rec, int n_rec, const double* part_sp,
-                                                         int n_sp, const double* part_dead, float inv_B, float lambda0,
-                                                         float lambda1, float* loss_dev) {
-  double a = 0.0, b = 0.0, c = 0.0;
-  auto sum = [](const double* p, int n) {
+__global__ __launch_bounds__(1024) void loss_final_kernel(const double* part_rec, int n_rec, const double* part_sp,
+                                                          int n_sp, const double* part_dead, float inv_B, float lambda0,
+                                                          float lambda1, float* loss_dev) {
+  __shared__ double sh[3][16];
+  auto sum = [&](const double* p, int n, int slot) {
     double s[4] = {0.0, 0.0, 0.0, 0.0};      // four chains keep four loads in flight
-    for (int i = threadIdx.x; i < n; i += 1024) {
+    for (int i = threadIdx.x; i < n; i += 4096) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (i + 256 * q < n) s[q] += p[i + 256 * q];
+        if (i + 1024 * q < n) s[q] += p[i + 1024 * q];
     }
-    return (s[0] + s[1]) + (s[2] + s[3]);
+    const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+    if ((threadIdx.x & 63) == 0) sh[slot][threadIdx.x >> 6] = t;
   };
-  a = sum(part_rec, n_rec);
-  b = sum(part_sp, n_sp);
-  if (part_dead) c = sum(part_dead, n_sp);
-  a = block_sum_256(a);
+  sum(part_rec, n_rec, 0);
+  sum(part_sp, n_sp, 1);
+  sum(part_dead, part_dead ? n_sp : 0, 2);
   __syncthreads();
-  b = block_sum_256(b);
-  __syncthreads();
-  c = block_sum_256(c);
   if (threadIdx.x == 0) {
+    double a = 0.0, b = 0.0, c = 0.0;
+    for (int i = 0; i < 16; ++i) { a += sh[0][i]; b += sh[1][i]; c += sh[2][i]; }
     const double rec = a * (double)inv_B, sp = b * (double)inv_B * (double)lambda0;
     const double dead = c * (double)inv_B * (double)lambda1;
     loss_dev[0] = (float)(rec + sp + dead);
@@ -474,19 +473,36 @@ __global__ __launch_bounds__(256) void ste_reduce_kernel(Dims D, int rows, int n
   if (dead) add_column_sums(nb, part_below + po, in, lds);
 }
 
-// ---- Adam (App. C Table 1), 4 elements per lane --------------------------------
+// ---- Adam (App. C Table 1), ADAM_QUADS x 4 elements per lane, one workgroup per run ----
+constexpr int ADAM_QUADS = 2;
 template <typename T, bool MASTER>
 __global__ __launch_bounds__(256) void adam_kernel(size_t n4, T* __restrict__ p, const T* __restrict__ g,
                                                    float* __restrict__ m, float* __restrict__ v,
                                                    float* __restrict__ master, AdamScalars a) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    const size_t o = i * 4;
-    const float4 g4 = Elem<T>::load4(g + o);
-    float4 m4 = *reinterpret_cast<const float4*>(m + o);
-    float4 v4 = *reinterpret_cast<const float4*>(v + o);
-    float4 p4 = MASTER ? *reinterpret_cast<const float4*>(master + o) : Elem<T>::load4(p + o);
-    const float gg[4] = {g4.x, g4.y, g4.z, g4.w};
-    float mm[4] = {m4.x, m4.y, m4.z, m4.w}, vv[4] = {v4.x, v4.y, v4.z, v4.w}, pp[4] = {p4.x, p4.y, p4.z, p4.w};
+  typedef typename Elem<T>::Raw4 Raw4;
+  constexpr int R = ADAM_QUADS;      // quads of a lane, all their loads in flight
+  const size_t i0 = (size_t)blockIdx.x * (256 * R) + threadIdx.x;
+  Raw4 g4[R], w4[R];
+  float4 m4[R], v4[R], p4[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    if (i0 + 256 * j >= n4) break;
+    const size_t o = (i0 + 256 * j) * 4;
+    g4[j] = Elem<T>::load_raw4(g + o);
+    m4[j] = *reinterpret_cast<const float4*>(m + o);
+    v4[j] = *reinterpret_cast<const float4*>(v + o);
+    if (MASTER) p4[j] = *reinterpret_cast<const float4*>(master + o);
+    else w4[j] = Elem<T>::load_raw4(p + o);
+  }
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    if (i0 + 256 * j >= n4) break;
+    const size_t o = (i0 + 256 * j) * 4;
+    if (!MASTER) p4[j] = Elem<T>::widen4(w4[j]);
+    const float4 gw = Elem<T>::widen4(g4[j]);
+    const float gg[4] = {gw.x, gw.y, gw.z, gw.w};
+    float mm[4] = {m4[j].x, m4[j].y, m4[j].z, m4[j].w}, vv[4] = {v4[j].x, v4[j].y, v4[j].z, v4[j].w};
+    float pp[4] = {p4[j].x, p4[j].y, p4[j].z, p4[j].w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) adam_element(pp[k], mm[k], vv[k], gg[k], a);
     *reinterpret_cast<float4*>(m + o) = make_float4(mm[0], mm[1], mm[2], mm[3]);
@@ -665,29 +681,51 @@ __global__ __launch_bounds__(256) void topk_select_kernel(Dims D, const float* _
 // token vectors over the first batches.  Stage 1: grid = (row blocks, L), one wave per row, each
 // block leaves the sum of its rows' norms; stage 2 adds the blocks of a layer, in order, to the
 // running sum.  int8 rows: the norm of the codes times |row scale|.
+// A wave takes four rows at a time, 16 bytes (int8: 8) per lane and row in flight: L = 16, d = 2048, 4096 tokens of bf16,
+// 268 MB.
 template <typename T, bool INT8>
 __global__ __launch_bounds__(256) void row_norm_sum_kernel(Dims D, const void* __restrict__ av,
                                                            const float* __restrict__ a_scale,
                                                            double* __restrict__ part) {
+  constexpr int N = INT8 ? 8 : Row16<T>::N, R = 4;
   const int rb = blockIdx.x, l = blockIdx.y, lane = threadIdx.x & 63;
   const int r0 = rb * LOSS_ROWS_PER_BLOCK, r1 = min(D.B, r0 + LOSS_ROWS_PER_BLOCK);
   double s = 0.0;   // the same value in every lane of a wave
-  for (int r = r0 + (threadIdx.x >> 6); r < r1; r += 4) {
-    const size_t o = ((size_t)l * D.B + r) * D.d;
-    float acc = 0.f;
-    for (int j = lane * 4; j < D.d; j += 256) {
-      float4 v;
-      if (INT8) {
-        const uint32_t q = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const int8_t*>(av) + o + j);
-        v = make_float4((float)(int8_t)q, (float)(int8_t)(q >> 8), (float)(int8_t)(q >> 16), (float)(int8_t)(q >> 24));
-      } else {
-        v = Elem<T>::load4(reinterpret_cast<const T*>(av) + o + j);
+  for (int r = r0 + (threadIdx.x >> 6) * R; r < r1; r += 4 * R) {
+    float acc[R] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int c = lane * N; c < D.d; c += 64 * N) {
+      u32x4 raw[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const size_t o = ((size_t)l * D.B + min(r + j, r1 - 1)) * D.d + c;
+        if (INT8) {
+          const uint2 q = *reinterpret_cast<const uint2*>(reinterpret_cast<const int8_t*>(av) + o);
+          raw[j] = u32x4{q.x, q.y, 0u, 0u};
+        } else {
+          raw[j] = load16(reinterpret_cast<const T*>(av) + o);
+        }
       }
-      acc += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        float v[N];
+        if constexpr (INT8) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) v[i] = (float)(int8_t)(raw[j][i / 4] >> (8 * (i & 3)));
+        } else {
+          widen16(raw[j], v);
+        }
+#pragma unroll
+        for (int i = 0; i < N; i += 4) acc[j] += (v[i] * v[i] + v[i + 1] * v[i + 1]) + (v[i + 2] * v[i + 2] + v[i + 3] * v[i + 3]);
+      }
     }
-    float n = sqrtf(wave_sum(acc));
-    if (INT8) n *= fabsf(a_scale[(size_t)l * D.B + r]);
-    s += (double)n;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (r + j >= r1) break;
+      float n = sqrtf(wave_sum(acc[j]));
+      if (INT8) n *= fabsf(a_scale[(size_t)l * D.B + r + j]);
+      s += (double)n;
+    }
   }
   __shared__ double sh[4];
   if (lane == 0) sh[threadIdx.x >> 6] = s;
@@ -695,12 +733,14 @@ __global__ __launch_bounds__(256) void row_norm_sum_kernel(Dims D, const void* _
   if (threadIdx.x == 0) part[(size_t)l * gridDim.x + rb] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-__global__ void norm_sum_final_kernel(int L, int nrb, const double* __restrict__ part, double* __restrict__ norm_sum) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= L) return;
+// one wavefront per layer
+__global__ __launch_bounds__(64) void norm_sum_final_kernel(int nrb, const double* __restrict__ part, double* __restrict__ norm_sum) {
+  const int l = blockIdx.x;
   double s = 0.0;
-  for (int i = 0; i < nrb; ++i) s += part[(size_t)l * nrb + i];
-  norm_sum[l] += s;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < nrb; i += 64) s += part[(size_t)l * nrb + i];
+  s = wave_sum(s);
+  if (threadIdx.x == 0) norm_sum[l] += s;
 }
 
 // 1 / c[l] = n_tokens / norm_sum[l]; a layer that summed to zero has no scale and keeps factor 1
@@ -821,7 +861,7 @@ hipError_t launch_loss_sparsity(hipStream_t s, bool bf16, Dims D, const void* z,
 hipError_t launch_loss_final(hipStream_t s, const double* part_rec, int n_rec, const double* part_sp, int n_sp,
                              const double* part_dead_or_null, float inv_B, float lambda0, float lambda1,
                              float* loss_dev) {
-  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
+  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(1024), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
                      inv_B, lambda0, lambda1, loss_dev);
   return hipGetLastError();
 }
@@ -859,7 +899,7 @@ hipError_t launch_ste_reduce(hipStream_t s, bool bf16, Dims D, void* dpre, const
 hipError_t launch_adam_matrix(hipStream_t s, bool bf16, size_t n, void* p, const void* g, float* m, float* v,
                               float* master, AdamScalars a) {
   const size_t n4 = n / 4;   // matrices have a multiple of 64 elements (d, F multiples of 8)
-  const dim3 grid(grid_for(n4, 256, 256 * 32));
+  const dim3 grid((unsigned)((n4 + 256 * ADAM_QUADS - 1) / (256 * ADAM_QUADS)));
   if (bf16) {
     if (master)
       hipLaunchKernelGGL((adam_kernel<bf16_t, true>), grid, dim3(256), 0, s, n4, (bf16_t*)p, (const bf16_t*)g, m, v,
@@ -880,7 +920,7 @@ hipError_t launch_adam_matrix(hipStream_t s, bool bf16, size_t n, void* p, const
 
 hipError_t launch_adam_vector(hipStream_t s, size_t n, float* p, const float* g, float* m, float* v, AdamScalars a) {
   const size_t n4 = n / 4;   // vectors have L*F or L*d elements, multiples of 8
-  hipLaunchKernelGGL((adam_kernel<float, false>), dim3(grid_for(n4, 256, 256 * 32)), dim3(256), 0, s, n4, p, g, m, v,
+  hipLaunchKernelGGL((adam_kernel<float, false>), dim3((unsigned)((n4 + 256 * ADAM_QUADS - 1) / (256 * ADAM_QUADS))), dim3(256), 0, s, n4, p, g, m, v,
                      (float*)nullptr, a);
   return hipGetLastError();
 }
@@ -894,7 +934,7 @@ hipError_t launch_norm_accumulate(hipStream_t s, bool bf16, bool int8_a, Dims D,
     hipLaunchKernelGGL((row_norm_sum_kernel<bf16_t, true>), grid, dim3(256), 0, s, D, a, a_scale, part);
   else
     hipLaunchKernelGGL((row_norm_sum_kernel<bf16_t, false>), grid, dim3(256), 0, s, D, a, a_scale, part);
-  hipLaunchKernelGGL(norm_sum_final_kernel, dim3((D.L + 63) / 64), dim3(64), 0, s, D.L, (int)grid.x, part, norm_sum);
+  hipLaunchKernelGGL(norm_sum_final_kernel, dim3(D.L), dim3(64), 0, s, (int)grid.x, part, norm_sum);
   return hipGetLastError();
 }
 
