@@ -254,11 +254,17 @@ static hipError_t launch_dwdec_mode(hipStream_t s, Dims D, const DWdecArgs& a) {
   DWdecPolicy<float, ADAM> p{D, D.F, D.d, D.B, D.F, D.d,
                              (const float*)a.z, (const float*)a.d_yhat, (float*)a.W_dec, a.G, a.norms,
                              (float*)a.dW_dec, AdamFuse{a.fuse.m, a.fuse.v, a.fuse.master, a.fuse.a}, a.skip_flags, a.kcap, 0, nullptr};
-  // one launch per source layer, like the bf16 path
-  for (int l = 0; l < D.L; ++l) {
+  // launches of whole source layers, like the bf16 path, each of at least 8 rounds of tiles for the chip (L = 4, d = 64,
+  // F = 256, 128 tokens: one launch instead of four of 9 us)
+  const long tiles = (long)((D.F + 127) / 128) * ((D.d + 127) / 128), want = 8L * 2 * CUS;
+  for (int l = 0; l < D.L;) {
+    int l1 = l;
+    long blocks = 0;
+    do { blocks += D.L - l1; ++l1; } while (l1 < D.L && blocks * tiles < want);
     p.p0 = packed_index(l, l, D.L);
-    const hipError_t e = launch(s, p, D.L - l);
+    const hipError_t e = launch(s, p, (int)blocks);
     if (e != hipSuccess) return e;
+    l = l1;
   }
   return hipSuccess;
 }
