@@ -25,6 +25,7 @@
 //   PERSISTENT   the bf16 kernel runs one workgroup per CU over many tiles (else one per tile)
 //   UNIFORM_K    every group of a launch has the same K length
 //   TILE_M       rows of the bf16 kernel's tile (256; 128 in the variants for few rows, see Few)
+//   HALF_ROWS    the bf16 kernel treats tiles with at most half of their rows inside the matrix apart
 //   ROW_SQUARES  the bf16 kernel's loop also leaves the sums of squares of B's rows (see row_squares)
 #pragma once
 #include "common.h"
@@ -183,6 +184,7 @@ __device__ __forceinline__ float4 adam_update4(const AdamFuse& f, T* w, size_t u
 template <typename T, typename TA = T>
 struct EncPolicy {
   static constexpr int TILE_M = 256;
+  static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = true, B_KC = false;
@@ -265,6 +267,7 @@ struct EncPolicy {
 template <typename T, bool SPLIT = false>
 struct DecPolicy {
   static constexpr int TILE_M = 256;
+  static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = !SPLIT;
   static constexpr bool A_KC = true, B_KC = false;
@@ -333,6 +336,7 @@ template <typename T, bool FOLD_ = false>
 struct DzPolicy {
   static constexpr bool FOLD = FOLD_;
   static constexpr int TILE_M = 256;
+  static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = true, B_KC = true;
@@ -452,6 +456,7 @@ struct DzPolicy {
 template <typename T, bool ADAM, bool N2 = false>
 struct DWdecPolicy {
   static constexpr int TILE_M = 256;
+  static constexpr bool HALF_ROWS = !ADAM;      // (with the update it spills 29 registers)
   static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = false, B_KC = false;
@@ -527,6 +532,7 @@ struct DWdecPolicy {
 template <typename T, bool ADAM, typename TA = T>
 struct DWencPolicy {
   static constexpr int TILE_M = 256;
+  static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = false, B_KC = false;
@@ -567,6 +573,7 @@ struct DWencPolicy {
 template <class P, bool ROW_SQUARES_ = false>
 struct Few : P {
   static constexpr int TILE_M = 128;
+  static constexpr bool HALF_ROWS = false;
   static constexpr bool ROW_SQUARES = ROW_SQUARES_, PERSISTENT = false, XCD_SYNC = false;
 };
 

@@ -32,8 +32,8 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-// a wave's block as accumulators of 16x16: half of the tile's rows by 64 columns
-template <class P> using acc_t = f32x4_t[P::TILE_M / 32][4];
+// a wave's block as accumulators of 16x16: half of the tile's rows by 64 columns in a whole tile
+template <int NI, int NJ> using acc_t = f32x4_t[NI][NJ];
 // native 16-byte register vector (HIP's uint4 is a class type; selects on it go through memory)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -206,11 +206,17 @@ constexpr int NTHREADS = 512;   // 8 wavefronts: two per SIMD, so one's memory p
 
 // K loop of one output tile.  EDGE = false assumes the tile lies fully inside the
 // matrices and kseg is a multiple of 64 (no predication at all).
-template <class P, bool EDGE>
+// A wave computes NI x NJ blocks of 16x16: half of the tile's rows by 64 columns, or in a tile at a matrix edge that has at
+// most half of its rows or columns inside only that half, shared out among all eight waves (so every SIMD has the same
+// work): half the matrix instructions of a tile that is mostly padding.  What remains is the two barriers and the LDS
+// traffic of a K step, about two thirds of a whole tile's time.  Steps before -> after: L = 12, d = 768, F = 6144, 4100 tokens
+// 11.97 -> 11.19 ms, 4095 tokens 11.07 -> 10.55, F = 6152: 11.85 -> 11.11, d = 776: 13.27 -> 13.12 (4096 tokens and none of
+// them ragged: 10.44); L = 6, d = 2056, F = 8200, 4100 tokens 13.44 -> 13.03.
+template <class P, bool EDGE, int NI, int NJ>
 __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& gi, int m0, int n0, bf16_t* smem,
-                                          acc_t<P>& acc, int t, uint32_t& sync_count) {
+                                          acc_t<NI, NJ>& acc, int t, uint32_t& sync_count) {
   typedef typename P::AType TA;
-  constexpr int WROWS = P::TILE_M / 2, STAGE = stage_elems<P>, NQ = P::TILE_M / 128;   // NQ: groups of 4 A fragments per slice
+  constexpr int STAGE = stage_elems<P>, NQ = NI / 4;   // NQ: groups of 4 A fragments per slice
   constexpr int DEPTH = P::TILE_M == 128 ? 2 : 1;      // K steps of operands in registers
   const int lane = t & 63, w = t >> 6, wm = w >> 2, wn = w & 3;
   const int lt = t & 255;
@@ -260,7 +266,7 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   // 32 have done so (every workgroup of an XCD walks the same groups in the same order, so the n-th booking
   // of each belongs together).  Only a pacing aid: a wait that runs into its bound just goes on.
   auto xcd_sync = [&]() {
-    if constexpr (P::XCD_SYNC) {
+    if constexpr (P::XCD_SYNC && !EDGE) {
       ++sync_count;
       if (p.xcd_sync && t == 0) {
         uint32_t* ctr = p.xcd_sync + (blockIdx.x & 7) * 64;
@@ -297,23 +303,23 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
   // c^1 of the same 8 rows, which the swizzle puts on distinct banks (chunks in order: two-way conflicts on
   // every fragment read).  One K step = two slices; in each the four B fragments stay put while the A
   // fragments come four at a time: 4 groups of 16 MFMAs per K step.
-  u32x4 fa[2][4], fb[2][4];
+  u32x4 fa[2][4], fb[2][NJ];
   const int frow = lane & 15, fch = ((lane >> 3) & 2) | (lane >> 5);
   auto read_a = [&](int st, int sl, int q, int buf) {
     const bf16_t* a = smem + st * STAGE;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fa[buf][i] = ld16(a + lds_off(wm * WROWS + (4 * q + i) * 16 + frow, 4 * sl + fch));
+    for (int i = 0; i < 4; ++i) fa[buf][i] = ld16(a + lds_off(wm * (NI * 16) + (4 * q + i) * 16 + frow, 4 * sl + fch));
   };
   auto read_b = [&](int st, int sl, int buf) {
     const bf16_t* b = smem + st * STAGE + P::TILE_M * TK;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fb[buf][j] = ld16(b + lds_off(wn * 64 + j * 16 + frow, 4 * sl + fch));
+    for (int j = 0; j < NJ; ++j) fb[buf][j] = ld16(b + lds_off(wn * (NJ * 16) + j * 16 + frow, 4 * sl + fch));
   };
   auto mfma_g = [&](int q, int abuf, int bbuf) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
         acc[4 * q + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fa[abuf][i]),
                                                                     __builtin_bit_cast(bf16x8_t, fb[bbuf][j]),
                                                                     acc[4 * q + i][j], 0, 0, 0);
@@ -441,25 +447,38 @@ __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& g
 // group never changes and the group's origin is wave-uniform (EpiPos), so the policy's memory
 // accesses are a scalar base plus one fixed per-lane offset.  EDGE = false: the tile lies fully
 // inside the matrix, no predicates.
-template <class P, bool EDGE>
+// NJ = 2 (see main_loop): the wave's 32 columns and its neighbour's make up one run of 64, which the even wave takes
+// through the policy's epilogue.
+template <class P, bool EDGE, int NI, int NJ>
 __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi, int m0, int n0, bf16_t* smem,
-                                         acc_t<P>& acc, int t) {
-  constexpr int WROWS = P::TILE_M / 2;
+                                         acc_t<NI, NJ>& acc, int t) {
+  constexpr int WROWS = NI * 16;
   const int lane = t & 63, w = t >> 6;
   const int wu = __builtin_amdgcn_readfirstlane(w), wm = wu >> 2, wn = wu & 3;
   const int M = p.M, N = p.N;
   __syncthreads();
-  float* wl = reinterpret_cast<float*>(smem) + wu * (32 * 64);
+  float* wl = reinterpret_cast<float*>(smem) + (NJ == 4 ? wu * (32 * 64) : (wm * 2 + (wn >> 1)) * (WROWS * 64));
+  if (NJ == 2) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          wl[(16 * i + 4 * (lane >> 4) + r) * 64 + (wn & 1) * 32 + j * 16 + (lane & 15)] = acc[i][j][r];
+    __syncthreads();
+    if (wn & 1) return;
+  }
   EpiPos pos;
   // (the transposition uses the first 64 KB of LDS, 8 KB per wave; the policy's scratch lies behind it)
   pos.lds = reinterpret_cast<float*>(smem) + 8 * (32 * 64) + wu * 128;
-  pos.cu = n0 + wn * 64;
+  pos.cu = n0 + (NJ == 4 ? wn : wn >> 1) * 64;
   pos.cl = (lane & 15) << 2;
   pos.rl = lane >> 4;
   pos.ru = 0;
   const bool col_ok = !EDGE || pos.col() < N;
   typename P::Epi est;
-  p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm * WROWS, (m0 / WROWS) + wm);
+  p.epi_begin(est, gi, pos.col(), col_ok, m0 + wm * WROWS, m0 / (P::TILE_M / 2) + wm);
   // The wave's block is 32 row groups of 4 rows (4 slabs of 8; 16 and 2 in 128-row tiles).  Each slab goes through the wave's
   // private LDS region (a wave's LDS accesses complete in issue order, so the transposition needs
   // no barrier).  The global loads the policy's epilogue needs run ahead of their use as a rolling
@@ -482,12 +501,12 @@ __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi
   for (int g = 0; g < depth(0); ++g) issue(g);
 #pragma unroll
   for (int g = 0; g < NG; ++g) {
-    if ((g & 7) == 0) {
+    if (NJ == 4 && (g & 7) == 0) {
       const int i = g >> 3;
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             wl[(16 * ii + 4 * (lane >> 4) + r) * 64 + j * 16 + (lane & 15)] = acc[2 * i + ii][j][r];
@@ -497,10 +516,20 @@ __device__ __forceinline__ void epilogue(const P& p, const typename P::GInfo& gi
 #pragma unroll
     for (int q = (done < NG ? done : NG); q < (want < NG ? want : NG); ++q) issue(q);
     pos.ru = m0 + wm * WROWS + g * 4;
-    const float4 v = *reinterpret_cast<const float4*>(wl + ((g & 7) * 4 + pos.rl) * 64 + pos.cl);
+    const float4 v = *reinterpret_cast<const float4*>(wl + ((NJ == 4 ? g & 7 : g) * 4 + pos.rl) * 64 + pos.cl);
     if (!EDGE || (col_ok && pos.row() < M)) p.epi4(est, gi, pos, v, er[g]);
   }
   p.epi_end(est, gi, pos.lds);
+}
+
+template <int NI, int NJ>
+__device__ __forceinline__ void zero_acc(acc_t<NI, NJ>& acc) {
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 }
 
 // P::PERSISTENT: the grid is one workgroup per CU and workgroup i runs tiles i, i + gridDim.x, ...
@@ -521,29 +550,37 @@ __global__ __launch_bounds__(NTHREADS) void gemm_bf16_kernel(P p, TileGrid tg, i
     const typename P::GInfo gi = p.ginfo(gorder);
     const int m0 = tm * P::TILE_M, n0 = tn * TN;
 
-    // wave w owns output rows (w/4)*TILE_M/2.., columns (w%4)*64..
-    acc_t<P> acc;
-#pragma unroll
-    for (int i = 0; i < P::TILE_M / 32; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-
     // The thread index is made opaque once per tile: everything a lane derives from it (LDS
     // addresses, operand offsets, epilogue positions) is then recomputed per tile instead of
     // being hoisted out of this loop, where it would stay live across both phases of every tile
     // and push the kernel over its 256 registers.
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
+    constexpr int NI = P::TILE_M / 32;      // wave w owns output rows (w/4)*TILE_M/2.., columns (w%4)*64..
     if (INTERIOR) {   // no tile of this launch touches an edge
-      main_loop<P, false>(p, gi, m0, n0, smem, acc, t, sync_count);
-      epilogue<P, false>(p, gi, m0, n0, smem, acc, t);
+      acc_t<NI, 4> acc;
+      zero_acc(acc);
+      main_loop<P, false, NI, 4>(p, gi, m0, n0, smem, acc, t, sync_count);
+      epilogue<P, false, NI, 4>(p, gi, m0, n0, smem, acc, t);
+    } else if (p.N - n0 <= TN / 2) {
+      acc_t<NI, 2> acc;
+      zero_acc(acc);
+      main_loop<P, true, NI, 2>(p, gi, m0, n0, smem, acc, t, sync_count);
+      epilogue<P, true, NI, 2>(p, gi, m0, n0, smem, acc, t);
+    } else if (P::HALF_ROWS && p.M - m0 <= P::TILE_M / 2) {
+      if constexpr (P::HALF_ROWS) {
+        acc_t<4, 4> acc;
+        zero_acc(acc);
+        main_loop<P, true, 4, 4>(p, gi, m0, n0, smem, acc, t, sync_count);
+        epilogue<P, true, 4, 4>(p, gi, m0, n0, smem, acc, t);
+      }
     } else {
       const bool inside = (m0 + P::TILE_M <= p.M) && (n0 + TN <= p.N);
-      main_loop<P, true>(p, gi, m0, n0, smem, acc, t, sync_count);
-      if (inside) epilogue<P, false>(p, gi, m0, n0, smem, acc, t);
-      else epilogue<P, true>(p, gi, m0, n0, smem, acc, t);
+      acc_t<NI, 4> acc;
+      zero_acc(acc);
+      main_loop<P, true, NI, 4>(p, gi, m0, n0, smem, acc, t, sync_count);
+      if (inside) epilogue<P, false, NI, 4>(p, gi, m0, n0, smem, acc, t);
+      else epilogue<P, true, NI, 4>(p, gi, m0, n0, smem, acc, t);
     }
     if (LOOP) __syncthreads();   // the next tile stages its operands in the LDS the epilogue transposed through
   } while (LOOP && (vb += gridDim.x) < nwg);

@@ -84,6 +84,18 @@ def test_few_tokens(L, d, F, B, int8):
     show(f"few tokens L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
 
 
+@pytest.mark.parametrize("L,d,F,B", [
+    (8, 136, 2824, 640),      # last tile: 128 of 256 rows of tokens, 8 of 256 features
+    (8, 392, 2944, 641),      # 129 rows, 128 features, 136 columns: one side of the rule and the other
+    (8, 264, 2952, 516),      # 4 rows, 136 features, 8 columns
+])
+def test_tiles_half_outside_the_matrix(L, d, F, B):
+    """Tiles at a matrix edge with at most half of their rows or columns inside, 256-row tiles (more than 256 of them)."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=31 + B)
+    g, o = run_both(w)
+    show(f"edge tiles L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
+
+
 def test_bf16_several_tiles_and_segments():
     """Spans 2x3 output tiles of 256x256 per group and up to 4 K segments."""
     w = S.scaled(S.WORKLOADS["gpt2"], L=4, d=512, F=768, B=512, k_active=16)
