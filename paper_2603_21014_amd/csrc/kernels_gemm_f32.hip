@@ -6,8 +6,8 @@
 // without packed arithmetic end at half of that, and the operand traffic is small beside either.
 //
 // Against the vector-FMA kernel before it (64x64x16 tiles, scalar loads): L = 12, d = 768, F = 6144, B = 1024: decode
-// 16.6 -> 7.9 ms (95 TFLOP/s; 6.2 with its K ranges cut), dz 12.0 -> 6.0 (126), dW_dec 12.2 -> 6.8 (110); L = 4, d = 64,
-// F = 256, B = 128: decode 186 -> 31 us (12 cut), dz 42 -> 14, dW_dec 72 -> 37.
+// 16.6 -> 6.0 ms (126 TFLOP/s; 7.9 without its K ranges cut), dz 12.0 -> 5.6 (135), dW_dec 12.2 -> 6.2 (121); L = 4, d = 64,
+// F = 256, B = 128: decode 186 -> 5 us, dz 42 -> 12, dW_dec 72 -> 10.
 //
 // One workgroup = 4 wavefronts computes a TxT tile (T = 128: 64x64 per wavefront as 4x4 accumulators; T = 64: 32x32),
 // K advances in steps of 32 through two LDS stages, two workgroups per CU cover each other's barriers.  Operands keep
@@ -140,10 +140,24 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
   ob.store(smem + OA::LDS_FLOATS, rb);
   if (kr.count > 1) fetch(kr.first + 1);
   __syncthreads();
+  // A K step: the MFMAs on the last four k of the step before (held back, their operands stay in registers) cover the latency
+  // of the first fragment reads; the next tile goes to LDS and the one after it is fetched between the two slices, so
+  // that only the barrier itself stands between two steps' MFMAs.  (With the stores right before the barrier and nothing
+  // held back the matrix cores were busy 76 to 82 % of the time, at full clock; decode 6.19 -> 6.01 ms, dz 5.93 -> 5.60,
+  // dW_dec 6.39 -> 6.21 at the sizes above.)
+  constexpr int NSL = FTK / 16;
+  static_assert(NSL == 2, "two slices");
+  f32x4 fa[NSL][NB], fb[NSL][NB];
+  auto mfma = [&](int sl, int q) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl][j][q], fa[sl][i][q], acc[i][j], 0, 0, 0);
+  };
   for (int kt = 0; kt < kr.count; ++kt) {
     const float* sa = smem + (kt & 1) * STAGE;
     const float* sb = sa + OA::LDS_FLOATS;
-    f32x4 fa[2][NB], fb[2][NB];
     auto read = [&](int sl) {
 #pragma unroll
       for (int i = 0; i < NB; ++i) fa[sl][i] = OA::frag(sa, wm + 16 * i, sl, lane);
@@ -151,18 +165,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
       for (int j = 0; j < NB; ++j) fb[sl][j] = OB::frag(sb, wn + 16 * j, sl, lane);
     };
     read(0);
-    if ((kt & (STEPS_PER_SUM - 1)) == 0) flush();     // covers the read latency
+    if (kt > 0) mfma(1, 3);
+    if ((kt & (STEPS_PER_SUM - 1)) == 0) flush();
+    read(1);
 #pragma unroll
-    for (int sl = 0; sl < FTK / 16; ++sl) {
-      if (sl == 0) read(1);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[sl][j][q], fa[sl][i][q], acc[i][j], 0, 0, 0);
-    }
+    for (int q = 0; q < 4; ++q) mfma(0, q);
     // the other stage was last read before the barrier that ended the previous step
     if (kt + 1 < kr.count) {
       float* s = smem + ((kt + 1) & 1) * STAGE;
@@ -170,8 +177,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
       ob.store(s + OA::LDS_FLOATS, rb);
       if (kt + 2 < kr.count) fetch(kr.first + kt + 2);
     }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) mfma(1, q);
     __syncthreads();
   }
+  if (kr.count > 0) mfma(1, 3);
 
   flush();
   // a lane's four columns of block j and row lane % 16 of block i
