@@ -22,7 +22,8 @@
  *          straight-through window |pre - theta| < ste_bandwidth/2, bit 2 = below
  *          the threshold (pre < theta strictly: where the dead-feature penalty of
  *          App. B has a gradient); all three decided on the fp32 accumulator
- *          before any rounding.  With the TopK activation only bit 0 is used.
+ *          before any rounding (fp32 storage: pre is one chain of fused multiply-adds
+ *          in the order of d, then + b_enc).  With the TopK activation only bit 0 is used.
  * Packed decoder: block p(l,l') = l*L - l(l-1)/2 + (l'-l), 0 <= l <= l' < L
  * (source-major: all decoders that leave source layer l are contiguous, which
  * is the "concatenation" whose row norm the sparsity term uses); each block is

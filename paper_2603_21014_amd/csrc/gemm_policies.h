@@ -26,6 +26,7 @@
 //   UNIFORM_K    every group of a launch has the same K length
 //   TILE_M       rows of the bf16 kernel's tile (256; 128 in the variants for few rows, see Few)
 //   HALF_ROWS    the bf16 kernel treats tiles with at most half of their rows inside the matrix apart
+//   IN_ORDER     the fp32 kernel adds the products of an entry up one after the other in the order of K
 //   ROW_SQUARES  the bf16 kernel's loop also leaves the sums of squares of B's rows (see row_squares)
 #pragma once
 #include "common.h"
@@ -186,6 +187,7 @@ struct EncPolicy {
   static constexpr int TILE_M = 256;
   static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
+  static constexpr bool IN_ORDER = true;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = true, B_KC = false;
   typedef TA AType;
@@ -269,6 +271,7 @@ struct DecPolicy {
   static constexpr int TILE_M = 256;
   static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
+  static constexpr bool IN_ORDER = false;
   static constexpr bool XCD_SYNC = !SPLIT;
   static constexpr bool A_KC = true, B_KC = false;
   typedef T AType;
@@ -338,6 +341,7 @@ struct DzPolicy {
   static constexpr int TILE_M = 256;
   static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
+  static constexpr bool IN_ORDER = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = true, B_KC = true;
   typedef T AType;
@@ -458,6 +462,7 @@ struct DWdecPolicy {
   static constexpr int TILE_M = 256;
   static constexpr bool HALF_ROWS = !ADAM;      // (with the update it spills 29 registers)
   static constexpr bool ROW_SQUARES = false;
+  static constexpr bool IN_ORDER = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = false, B_KC = false;
   typedef T AType;
@@ -534,6 +539,7 @@ struct DWencPolicy {
   static constexpr int TILE_M = 256;
   static constexpr bool HALF_ROWS = true;
   static constexpr bool ROW_SQUARES = false;
+  static constexpr bool IN_ORDER = false;
   static constexpr bool XCD_SYNC = false;
   static constexpr bool A_KC = false, B_KC = false;
   typedef TA AType;

@@ -16,6 +16,11 @@
 // / 16) + q for MFMA q of a 16-wide slice, so any pair of layouts agrees and nothing is transposed.
 // Loads go through buffer descriptors: a chunk outside the matrix gets an offset beyond the descriptor's range and
 // reads as zero, so sizes that fit no tile run the same code as those that do.
+// IN_ORDER (the encoder): one running sum per entry, in the order of K.  The MFMA adds its four products one after the other,
+// each with one rounding, so the pre-activations are exactly a chain of FMAs over k = 0, 1, 2, ...  The active set, the window
+// and the TopK selection are decided on them and jump where one lies within rounding of its threshold: another order of
+// the sum would give a trained model another set for some inputs.  A lane then reads k = 4 q + lane / 16 for MFMA q,
+// four single reads in both layouts; no slower (L = 12, d = 768, F = 6144, B = 1024: step 22.68 and 22.70 ms).
 // The MFMA's operands are swapped (D = B^T A^T): a lane then holds four consecutive columns of one row, which is what
 // the policies' epilogues take.
 #include "common.h"
@@ -36,10 +41,11 @@ __device__ __forceinline__ f32x4 load_chunk(const float* base, uint32_t voff) {
 }
 
 // One operand's T x 32 tile: staging by 256 lanes (T / 32 chunks of 16 bytes each) and fragment reads.
-template <bool KC, int T>
+template <bool KC, int T, bool IN_ORDER>
 struct Operand {
   static constexpr int NCH = T / 32;                       // chunks per lane
-  static constexpr int PITCH = KC ? FTK + 4 : T + 4;       // floats; +4 spreads the fragment reads over all banks
+  // floats; the padding spreads the fragment reads over all banks (16 lanes' rows of four k, 4 apart or next to each other)
+  static constexpr int PITCH = KC ? FTK + 4 : IN_ORDER ? T + 16 : T + 4;
   static constexpr int LDS_FLOATS = KC ? T * PITCH : FTK * PITCH;
   static constexpr int RSTEP = KC ? 32 : 1024 / T;         // rows (KC) or k (strided) between a lane's chunks
   uint32_t voff, ok;      // lane byte offset inside the tile; bit i: chunk i's row lies inside the matrix
@@ -67,13 +73,17 @@ struct Operand {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) *reinterpret_cast<f32x4*>(s + lds + i * RSTEP * PITCH) = r[i];
   }
-  // fragment of the 16 rows from `row0` on for k slice `sl` (16 wide): element q is k = 16 sl + 4 (lane / 16) + q
+  // fragment of the 16 rows from `row0` on for k slice `sl` (16 wide): element q is k = 16 sl + 4 (lane / 16) + q, or
+  // 16 sl + 4 q + lane / 16 where the products are added in the order of k
   __device__ __forceinline__ static f32x4 frag(const float* s, int row0, int sl, int lane) {
-    const int row = row0 + (lane & 15), k = 16 * sl + 4 * (lane >> 4);
-    if (KC) return *reinterpret_cast<const f32x4*>(s + row * PITCH + k);
+    const int row = row0 + (lane & 15), k = 16 * sl + (IN_ORDER ? lane >> 4 : 4 * (lane >> 4));
+    if (KC && !IN_ORDER) return *reinterpret_cast<const f32x4*>(s + row * PITCH + k);
     f32x4 v;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = s[(k + q) * PITCH + row];
+    for (int q = 0; q < 4; ++q) {
+      const int kq = k + (IN_ORDER ? 4 * q : q);
+      v[q] = s[KC ? row * PITCH + kq : kq * PITCH + row];
+    }
     return v;
   }
 };
@@ -81,8 +91,8 @@ struct Operand {
 template <class P, int T>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
   constexpr int NB = T / 32, W = T / 2;      // 16-blocks per wavefront and direction, wavefront block edge
-  typedef Operand<P::A_KC, T> OA;
-  typedef Operand<P::B_KC, T> OB;
+  typedef Operand<P::A_KC, T, P::IN_ORDER> OA;
+  typedef Operand<P::B_KC, T, P::IN_ORDER> OB;
   __shared__ __align__(16) float smem[2 * (OA::LDS_FLOATS + OB::LDS_FLOATS)];
   int gorder, tm, tn;
   if (!tg.decode(blockIdx.x, gorder, tm, tn) || p.skip()) return;
@@ -117,8 +127,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
   };
 
   // sums over 128 k at a time, added up in `tot`: the rounding errors of a long K grow with the number of partial
-  // sums and the length of one, not with K (K = 768: rms error of the
-  // pre-activations 2.1e-7 instead of 5.0e-7 with one running sum)
+  // sums and the length of one, not with K (K = 768: rms error 2.1e-7 instead of 5.0e-7 with one running sum)
   constexpr int STEPS_PER_SUM = 4;
   f32x4 acc[NB][NB], tot[NB][NB];
 #pragma unroll
@@ -166,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
     };
     read(0);
     if (kt > 0) mfma(1, 3);
-    if ((kt & (STEPS_PER_SUM - 1)) == 0) flush();
+    if (!P::IN_ORDER && (kt & (STEPS_PER_SUM - 1)) == 0) flush();
     read(1);
 #pragma unroll
     for (int q = 0; q < 4; ++q) mfma(0, q);

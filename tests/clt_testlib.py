@@ -79,6 +79,22 @@ def theta_for_density(x, W_enc, b_enc, rho):
     return out
 
 
+def fma_chain(a, b):
+    """a [m, K] times b [K, n] in fp32 as one chain of fused multiply-adds per entry, in the order of K: acc = fma(a[:, k],
+    b[k], acc).  The product of two fp32 numbers is exact in 64 bits; its sum with acc is rounded to odd there (the
+    two-sum's error says whether and to which side it was inexact), so that rounding it to fp32 rounds once."""
+    acc = np.zeros((a.shape[0], b.shape[1]), np.float32)
+    for k in range(a.shape[1]):
+        p, c = np.multiply.outer(a[:, k].astype(np.float64), b[k].astype(np.float64)), acc.astype(np.float64)
+        s = p + c
+        t = s - p
+        err = (p - (s - t)) + (c - t)
+        odd = (s.view(np.int64) & 1).astype(bool)
+        s = np.where((err != 0) & ~odd, np.nextafter(s, np.where(err > 0, np.inf, -np.inf)), s)
+        acc = s.astype(np.float32)
+    return acc
+
+
 def to_np(t):
     return t.detach().float().cpu().numpy().astype(np.float64)
 

@@ -9,7 +9,7 @@ import torch
 from oracle import clt_oracle as O
 from workloads import clt_synth as S
 
-from clt_testlib import GpuRun, OracleRun, compare_step, rel_l2, run_both, theta_for_density, to_np
+from clt_testlib import GpuRun, OracleRun, compare_step, fma_chain, rel_l2, run_both, theta_for_density, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -51,6 +51,29 @@ def test_fp32_large_tiles(d, F, B):
     w = S.scaled(S.WORKLOADS["tiny"], L=2, d=d, F=F, B=B, seed=51 + d)
     g, o = run_both(w)
     show(f"f32 large tiles d{d} F{F} B{B}", compare_step(w, g, o, TOL["f32"]))
+
+
+@pytest.mark.parametrize("L,d,F,B", [
+    (2, 776, 264, 77),       # 64x64 tiles, remainders everywhere
+    (2, 136, 4104, 509),     # 2 x 4 x 33 tiles of 128x128
+    (2, 128, 4096, 512),     # the same without remainders
+])
+def test_fp32_preactivations_are_one_fma_chain_in_order(L, d, F, B):
+    """Which features are active is decided on the fp32 pre-activation, so its rounding is part of the result: one chain
+    of fused multiply-adds in the order of d, bit for bit, at the rows where tiles and wavefronts begin and end."""
+    w = S.scaled(S.WORKLOADS["tiny"], L=L, d=d, F=F, B=B, seed=71 + d)
+    params = S.make_params(w)
+    params["b_enc"] = 0.01 * torch.randn((L, F), generator=torch.Generator().manual_seed(5))
+    x, y = S.make_inputs(w)
+    g = GpuRun(w, params, x, y)
+    rows = sorted({r % B for r in (0, 1, 31, 32, 63, 64, 127, 128, 255, 256, -2, -1)})
+    for l in range(L):
+        want = fma_chain(x[l, rows].numpy(), params["W_enc"][l].numpy()) + params["b_enc"][l].numpy()
+        theta = params["theta"][l].numpy()
+        assert (g.pre[l, rows] == want).all()
+        assert (g.z[l, rows] == np.where(want > theta, want, 0)).all()
+        assert (g.active[l, rows] == (want > theta)).all() and (g.below[l, rows] == (want < theta)).all()
+        assert (g.window[l, rows] == (np.abs(want - theta) < np.float32(0.5 * w.ste_eps))).all()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
