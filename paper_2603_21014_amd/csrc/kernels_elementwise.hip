@@ -275,14 +275,14 @@ __global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, int rows, in
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         if (zz[i] != 0.f) {
-          // u = C n z, e = exp(-2|u|), q = e / (1 + e): tanh|u| = 1 - 2 q, sech^2 u = 4 q / (1 + e) (no cancellation
-          // for large u)
+          // u = C n z, e = exp(-2|u|): tanh|u| = (1 - e) / (1 + e), sech^2 u = 4 e / (1 + e)^2 (no cancellation for large u;
+          // 1 - e is exact for e >= 1/2, so that small u keep their digits: 1 - 2 e / (1 + e) subtracts a rounded quotient and
+          // is 4 times further off at |u| < 0.1)
           const float a = ka[i] * zz[i];      // -2 log2(e) u
           const float e = __builtin_amdgcn_exp2f(-fabsf(a));
           const float rc = __builtin_amdgcn_rcpf(1.0f + e);
-          const float q = e * rc;
-          ts -= copysignf(fmaf(-2.0f, q, 1.0f), a);
-          cs[i] = fmaf(zz[i], q * rc, cs[i]);
+          ts -= copysignf((1.0f - e) * rc, a);
+          cs[i] = fmaf(zz[i], e * rc * rc, cs[i]);
         }
       }
       if (DEAD) {

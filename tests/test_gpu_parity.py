@@ -159,6 +159,31 @@ def test_master_weights_bf16():
     show("bf16 master", compare_step(w, g, o, TOL["bf16"]))
 
 
+def test_sparsity_of_small_features_keeps_its_digits():
+    """tanh(C z n) for small arguments: one token, eight features with the same z, decoder rows of norm 1, C = 1, so that
+    L_sp = 8 lambda0 tanh(z).  With e = exp(-2 z) as the hardware gives it (one unit of 2^-24 off for e in [1/2, 1)) and 1 - e
+    exact, (1 - e) / (1 + e) is off by at most 2^-25 plus a few relative roundings of 2^-24 (argument, reciprocal, product,
+    sum of four, result)."""
+    from paper_2603_21014_amd import binding as K
+    dev, F = "cuda:0", 8
+    params = {"W_enc": torch.zeros(1, 8, F), "b_enc": torch.zeros(1, F), "theta": torch.full((1, F), 1e-4),
+              "W_dec": torch.zeros(1, F, 8), "b_dec": torch.zeros(1, 8)}
+    params["W_dec"][..., 0] = 1.0
+    params = {k: v.to(dev) for k, v in params.items()}
+    step = K.CLTStep(1, 8, F, 1, dtype="f32", C_=1.0, device=dev)
+    x = torch.zeros(1, 1, 8, device=dev)
+    worst = 0.0
+    for i in range(64):
+        z = np.float32(0.004 * 1.05 ** i)
+        params["b_enc"].fill_(float(z))
+        step.forward(x, params)
+        got = step.loss(x, 1.0, to_host=True)[2] / F
+        want = np.tanh(np.float64(z))
+        worst = max(worst, abs(got - want) / (2.0 ** -25 + 12 * 2.0 ** -24 * want))
+    print(f"worst error of tanh in units of its bound: {worst:.2f}", flush=True)
+    assert worst <= 1.0
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_infinite_threshold_gives_bias_only(dtype):
     w = S.scaled(S.WORKLOADS["tiny"], dtype=dtype)
