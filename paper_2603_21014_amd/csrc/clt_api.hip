@@ -598,9 +598,9 @@ int clt_loss(clt_handle* h, void* stream, const void* y, const float* y_scale, c
   // before the same partial buffer is reused for the db_dec partials of the reconstruction pass
   RUN(h, s, K_LOSS_SP, launch_loss_sparsity(s, h->bf16, D, z, norms, h->cfg.C, psp, part, dead ? pre : nullptr, theta,
                                             h->cfg.log_threshold != 0, pdead, part2));
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part, rgf.rbs, D.L * D.F, lambda0 / (float)D.B, nullptr, 0.f, G));
+  RUN(h, s, K_COLRED, launch_col_reduce(s, part, rgf.rbs, D.L * D.F, lambda0 / (float)D.B, G));
   if (dead)
-    RUN(h, s, K_COLRED, launch_col_reduce(s, part2, rgf.rbs, D.L * D.F, lambda1 / (float)D.B, nullptr, 0.f, G, true));
+    RUN(h, s, K_COLRED, launch_col_reduce(s, part2, rgf.rbs, D.L * D.F, lambda1 / (float)D.B, G, true));
   RUN(h, s, K_LOSS_REC, launch_loss_rec(s, h->bf16, h->int8, D, y_hat, y, y_scale, d_yhat, prec, part));
   RUN(h, s, K_LOSS_FINAL, launch_loss_final(s, prec, rgd.blocks() * D.L, psp, rgf.blocks() * D.L, dead ? pdead : nullptr,
                                             1.0f / (float)D.B, lambda0, lambda1, loss_dev));
@@ -633,7 +633,7 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   const float lam1_over_b = h->lambda1 / (float)D.B;
 
   // db_dec from the column partials that clt_loss left behind
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part, reduce_grid(h->bf16, D, D.d).rbs, D.L * D.d, 1.0f, nullptr, 0.f, gb_dec));
+  RUN(h, s, K_COLRED, launch_col_reduce(s, part, reduce_grid(h->bf16, D, D.d).rbs, D.L * D.d, 1.0f, gb_dec));
   // Backward through the decoder: dense GEMMs, or the gather kernels on the lists of the forward
   // pass when the device-side switch selected them (AUTO enqueues both; the one not selected
   // returns at once).
@@ -683,11 +683,11 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
     RUN(h, s, K_STE, launch_ste_reduce(s, h->bf16, D, dpre, act_class, h->int8 ? x_scale : nullptr, norms, lam1_over_b,
                                        part, part2, part3, fold ? flags : nullptr, kcap));
   if (h->cfg.activation == CLT_ACT_TOPK)     // no threshold: the window partials are all zero, and so is the gradient
-    RUN(h, s, K_COLRED, launch_col_reduce(s, part, nparts, D.L * D.F, 1.0f, nullptr, 0.f, gtheta, false, psw));
+    RUN(h, s, K_COLRED, launch_col_reduce(s, part, nparts, D.L * D.F, 1.0f, gtheta, false, psw));
   else
     RUN(h, s, K_COLRED, launch_dtheta_final(s, part, part3, nparts, D.L * D.F, theta, h->cfg.log_threshold != 0, norms,
                                             1.0f / h->cfg.ste_bandwidth, lam1_over_b, gtheta, psw));
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part2, nparts, D.L * D.F, 1.0f, nullptr, 0.f, gb_enc, false, psw));
+  RUN(h, s, K_COLRED, launch_col_reduce(s, part2, nparts, D.L * D.F, 1.0f, gb_enc, false, psw));
   if (h->bf16) RUN(h, s, K_DWENC, launch_dwenc_bf16(s, D, ea, h->int8));
   else RUN(h, s, K_DWENC, launch_dwenc_f32(s, D, ea));
   if (mode != CLT_DECODE_GATHER) {

@@ -177,8 +177,8 @@ struct DzArgs {        // dz[l] = sum_{lp>=l} dyhat[lp] W_dec[p(l,lp)]^T + g_sp,
   float lam1_over_b;      // dead-feature coefficient lambda1 / B (0 = term off)
   const int32_t* skip_flags = nullptr;   // optional switch: stand down when the gather path is selected
   int kcap = 0;
-  // bf16 kernel only, all four or none: the straight-through reductions folded into the epilogue (then dpre is
-  // final and launch_ste_reduce is not needed).  Column partials per half tile of rows, fold_row_blocks(D) of
+  // bf16 kernel only: the straight-through reductions are folded into the epilogue (dpre is final and
+  // launch_ste_reduce is not needed).  Column partials per half tile of rows, fold_row_blocks(D) of
   // them: [half tile][L][F].  x_scale: the row scales of int8 inputs, or NULL.
   const float* x_scale = nullptr; float* part_theta = nullptr; float* part_benc = nullptr; float* part_below = nullptr;
 };
@@ -275,10 +275,9 @@ hipError_t launch_loss_final(hipStream_t s, const double* part_rec, int n_rec, c
 // Automatic mode: the column partials of the backward come in nparts row blocks when the dense dz epilogue wrote
 // them and in nparts_lists when the list-driven backward ran (launch_ste_reduce); which, the device-side switch says.
 struct PartsSwitch { const int32_t* flags = nullptr; int kcap = 0; int nparts_lists = 0; };
-// out[c] = alpha * sum_r part[r][c] (fixed order), optionally times -(theta[c]/eps)
-hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha,
-                             const float* theta_or_null, float inv_eps, float* out, bool accumulate = false,
-                             PartsSwitch sw = PartsSwitch{});
+// out[c] = alpha * sum_r part[r][c] (fixed order)
+hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha, float* out,
+                             bool accumulate = false, PartsSwitch sw = PartsSwitch{});
 // dtheta[c] = -(theta/eps) sum_r part_win[r][c] + lam1_over_b * norms[c] * sum_r part_below[r][c], times theta
 // when the parameter is log(theta)
 hipError_t launch_dtheta_final(hipStream_t s, const float* part_win, const float* part_below, int nparts, int ncols,

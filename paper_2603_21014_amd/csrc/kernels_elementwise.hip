@@ -361,15 +361,14 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ part, in
 }
 
 __global__ __launch_bounds__(256) void col_reduce_kernel(const float* __restrict__ part, int nparts, int ncols,
-                                                         float alpha, const float* __restrict__ theta, float inv_eps,
-                                                         float* __restrict__ out, bool accumulate, PartsSwitch sw) {
+                                                         float alpha, float* __restrict__ out, bool accumulate,
+                                                         PartsSwitch sw) {
   __shared__ float lds[3][64];
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
   if (sw.flags && lists_backward_selected(sw.flags, sw.kcap)) nparts = sw.nparts_lists;
   float s = sum_partials(part, nparts, ncols, c, lds);
   if (threadIdx.x >= 64 || c >= ncols) return;
   s *= alpha;
-  if (theta) s = (s == 0.f) ? 0.f : s * -(theta[c] * inv_eps);   // empty window: exactly 0, also for theta = inf
   out[c] = accumulate ? out[c] + s : s;
 }
 
@@ -868,10 +867,10 @@ hipError_t launch_loss_final(hipStream_t s, const double* part_rec, int n_rec, c
   return hipGetLastError();
 }
 
-hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha,
-                             const float* theta_or_null, float inv_eps, float* out, bool accumulate, PartsSwitch sw) {
-  hipLaunchKernelGGL(col_reduce_kernel, dim3((ncols + 63) / 64), dim3(256), 0, s, part, nparts, ncols, alpha,
-                     theta_or_null, inv_eps, out, accumulate, sw);
+hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha, float* out,
+                             bool accumulate, PartsSwitch sw) {
+  hipLaunchKernelGGL(col_reduce_kernel, dim3((ncols + 63) / 64), dim3(256), 0, s, part, nparts, ncols, alpha, out,
+                     accumulate, sw);
   return hipGetLastError();
 }
 

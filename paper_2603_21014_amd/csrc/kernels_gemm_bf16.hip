@@ -641,7 +641,6 @@ hipError_t init_gemm_bf16() {
   if ((e = set_lds_attr<EncPolicy<bf16_t, int8_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DecPolicy<bf16_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DecPolicy<bf16_t, true>>()) != hipSuccess) return e;
-  if ((e = set_lds_attr<DzPolicy<bf16_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DzPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<Few<EncPolicy<bf16_t>>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<Few<EncPolicy<bf16_t, int8_t>>>()) != hipSuccess) return e;
@@ -649,7 +648,6 @@ hipError_t init_gemm_bf16() {
   if ((e = set_lds_attr<Few<DecPolicy<bf16_t>, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<Few<DecPolicy<bf16_t, true>>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<Few<DecPolicy<bf16_t, true>, true>>()) != hipSuccess) return e;
-  if ((e = set_lds_attr<Few<DzPolicy<bf16_t>>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<Few<DzPolicy<bf16_t, true>>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, false>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, true>>()) != hipSuccess) return e;
@@ -692,16 +690,12 @@ hipError_t launch_dec_bf16(hipStream_t s, Dims D, const DecArgs& a) {
                       a.xcd_sync, a.split, nullptr, a.row_squares};
   return a.row_squares ? launch(s, Few<DecPolicy<bf16_t>, true>{p}, D.L) : launch_rows(s, D, p, D.L);
 }
-template <bool FOLD>
-static hipError_t launch_dz_mode(hipStream_t s, Dims D, const DzArgs& a) {
-  DzPolicy<bf16_t, FOLD> p{D, D.B, D.F, D.d, D.d, D.d,
+hipError_t launch_dz_bf16(hipStream_t s, Dims D, const DzArgs& a) {
+  DzPolicy<bf16_t, true> p{D, D.B, D.F, D.d, D.d, D.d,
                            (const bf16_t*)a.d_yhat, (const bf16_t*)a.W_dec, (const bf16_t*)a.z, a.cls, a.norms,
                            a.lam_c_over_b, a.C, (bf16_t*)a.dpre, a.lam1_over_b, a.skip_flags, a.kcap,
                            a.x_scale, a.part_theta, a.part_benc, a.part_below};
   return launch_rows(s, D, p, D.L);
-}
-hipError_t launch_dz_bf16(hipStream_t s, Dims D, const DzArgs& a) {
-  return a.part_theta ? launch_dz_mode<true>(s, D, a) : launch_dz_mode<false>(s, D, a);
 }
 template <bool ADAM, bool N2>
 static hipError_t launch_dwdec_mode(hipStream_t s, Dims D, const DWdecArgs& a) {

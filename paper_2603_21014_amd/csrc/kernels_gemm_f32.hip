@@ -30,7 +30,6 @@ namespace clt {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int FTK = 32;
 constexpr uint32_t OUT_OF_RANGE = 0xffffff00u;      // lane offset that no descriptor below covers
