@@ -188,6 +188,10 @@ struct DzArgs {        // dz[l] = sum_{lp>=l} dyhat[lp] W_dec[p(l,lp)]^T + g_sp,
 // with 256; forward of L = 8, d = 2048, F = 8192: 530 / 572 / 787 / 820 / 977 / 1697 and 566 / 612 / 838 / 878 / 914 / 1239;
 // gradients of L = 4, d = 512, F = 2048 (32 to 96 tiles of 256 rows): 142 / 151 / 159 / 166 / 182 / 194 and 177 / 187 / 187 / 197
 // / 207 / 223.
+// One rule for the encoder, the decode and dz: the decode has d columns instead of F and then fewer tiles still, but where
+// they are few its K ranges are cut as well (choose_dec_split).
+// (256 is the MI355X's CU count and a literal here, as in the other rules on tile counts: the workspace is sized by them,
+// also on a host without a GPU.  With fewer CUs the results are the same and the choice is less good.)
 inline bool few_rows(Dims D) {
   return D.B <= 384 || (double)D.L * ((D.B + 255) / 256) * ((D.F + 255) / 256) < 256.0;
 }

@@ -1,8 +1,8 @@
 // The five contractions of a CLT train step, each described as a "policy":
 // operand addressing (which memory dimension is the contraction index K), the
 // K segments of the triangular sums, and the fused epilogue.  The same policies
-// drive the fp32 FMA kernel (kernels_gemm_f32.hip) and the bf16 MFMA kernel
-// (kernels_gemm_bf16.hip).
+// drive the fp32 (kernels_gemm_f32.hip) and the bf16 (kernels_gemm_bf16.hip)
+// MFMA kernels.
 //
 // A policy exposes
 //   A_KC / B_KC  true when the operand is contiguous along K in memory
@@ -330,11 +330,13 @@ struct DecPolicy {
 // 4 e / (1 + e)^2 with e = exp(-2 |C z n|): no cancellation for large arguments
 // and one hardware exponential per element.
 // ---------------------------------------------------------------------------
-// FOLD (bf16 kernel, dense mode): the epilogue also does what ste_reduce_kernel does after the plain
+// FOLD (bf16 kernel): the epilogue also does what ste_reduce_kernel does after the plain
 // variant -- it writes the final d pre (an inactive entry inside the threshold window only lends its dz
-// to the threshold gradient; rows times the x scale for int8 inputs) and leaves, per 128-row half tile,
-// the column sums of dz over the window (-> d theta), of d pre (-> d b_enc) and of the below-threshold
-// count, summed in a fixed order: a lane over its 32 rows, then the 4 lanes that share its columns.
+// to the threshold gradient; rows times the x scale for int8 inputs) and leaves, per half of the tile's rows
+// (128; 64 in a 128-row tile and in one with at most half of its rows inside the matrix, where the two parts
+// are the halves of those rows), the column sums of dz over the window (-> d theta), of d pre (-> d b_enc) and of
+// the below-threshold count, summed in a fixed order: a lane over its 32 (16) rows, then the 4 lanes that share
+// its columns.
 template <typename T, bool FOLD_ = false>
 struct DzPolicy {
   static constexpr bool FOLD = FOLD_;

@@ -46,8 +46,10 @@ template <class P> constexpr int lds_bytes = 2 * stage_elems<P> * 2;            
 // accumulators.  Such a launch streams the weights and is bound by that, not by the matrix cores, but 256-row tiles spend
 // 1.5 us of matrix time on a K step whose 32 KB of weights take 1.5 us to arrive.  The registers that are free here hold a
 // second K step of operands on its way, and the decode takes the squares for the decoder norms along instead of a second
-// pass over the weights.  One prompt of 100 tokens (L = 16, d = 2048, F = 8192: 4.6 GB of decoder): forward 1807 -> 1105 us,
-// of which decode 1073 -> 930 and norms 806 -> 20.
+// pass over the weights (dense mode).  One prompt of 100 tokens (L = 16, d = 2048, F = 8192: 4.6 GB of decoder), pass after
+// pass: forward 1807 -> 1092 us, of which decode with its combining pass 1073 -> 931 and norms 806 -> 21.  (The first passes
+// after other work take up to 15 % longer.)
+
 // element offset of 16-byte chunk `c` (8 bf16) of tile row `row`
 __device__ __forceinline__ int lds_off(int row, int c) {
   return row * TK + (((c ^ row ^ (row >> 3)) & 7) << 3);
@@ -104,9 +106,10 @@ template <> __device__ __forceinline__ u32x4 cook8<int8_t>(u32x4 raw) {
 // needs a single address register.  The EDGE variants load through a buffer
 // descriptor at that base: a chunk outside the matrix gets a lane offset that
 // the descriptor does not cover and comes back as zeros, so nothing is kept or
-// selected between the load and the LDS write (with selects there, L = 6,
-// d = 2056, F = 8200, 4100 tokens: dW_dec 5.4 ms, decode 4.1; now 4.3 and 3.5.
-// One prompt of 100 tokens, d = 2048, F = 8192, L = 16: decode 1.36 -> 1.03 ms).
+// selected between the load and the LDS write (L = 6, d = 2056, F = 8200, 4100
+// tokens: dW_dec 5.4 ms with selects there, 4.3 without, decode 4.1 and 3.5; one
+// prompt of 100 tokens, d = 2048, F = 8192, L = 16, still in 256-row tiles:
+// decode 1.36 and 1.03 ms).
 // ---------------------------------------------------------------------------
 // ROWS: rows of the tile; 128 (K-contiguous operands only) halves the chunks per lane.
 template <bool KC, typename TE, int ROWS>
@@ -209,9 +212,10 @@ constexpr int NTHREADS = 512;   // 8 wavefronts: two per SIMD, so one's memory p
 // A wave computes NI x NJ blocks of 16x16: half of the tile's rows by 64 columns, or in a tile at a matrix edge that has at
 // most half of its rows or columns inside only that half, shared out among all eight waves (so every SIMD has the same
 // work): half the matrix instructions of a tile that is mostly padding.  What remains is the two barriers and the LDS
-// traffic of a K step, about two thirds of a whole tile's time.  Steps before -> after: L = 12, d = 768, F = 6144, 4100 tokens
-// 11.97 -> 11.19 ms, 4095 tokens 11.07 -> 10.55, F = 6152: 11.85 -> 11.11, d = 776: 13.27 -> 13.12 (4096 tokens and none of
-// them ragged: 10.44); L = 6, d = 2056, F = 8200, 4100 tokens 13.44 -> 13.03.
+// traffic of a K step, about two thirds of a whole tile's time.  Training steps (JumpReLU, fused Adam) before -> after:
+// L = 12, d = 768, F = 6144, 4100 tokens 11.72 -> 10.83 ms, 4095 tokens 10.64 -> 10.35, F = 6152: 11.33 -> 10.81, d = 776:
+// 13.19 -> 12.48 (4096 tokens and none of them ragged: 10.27); L = 6, d = 2056, F = 8200, 4100 tokens 13.28 -> 13.01, with the
+// dead-feature term, the log threshold and heavy-tailed inputs 13.25 -> 13.11.
 template <class P, bool EDGE, int NI, int NJ>
 __device__ __forceinline__ void main_loop(const P& p, const typename P::GInfo& gi, int m0, int n0, bf16_t* smem,
                                           acc_t<NI, NJ>& acc, int t, uint32_t& sync_count) {
@@ -676,6 +680,7 @@ hipError_t launch_enc_bf16(hipStream_t s, Dims D, const EncArgs& a, bool int8_x)
                       0.5f * a.ste_eps, (bf16_t*)a.z, (bf16_t*)a.pre, a.cls, a.l0, a.log_threshold, a.pre32};
   return launch_rows(s, D, p, D.L);
 }
+// (32: CUs of an XCD, one workgroup each; see few_rows for why these are literals)
 DecSplit dec_split_bf16(Dims D) { return choose_dec_split(D, few_rows(D) ? TM / 2 : TM, TN, TK, 32, 0.8); }
 size_t dec_row_squares_floats(Dims D) { return few_rows(D) ? (size_t)D.P() * 2 * ((D.d + TN - 1) / TN) * D.F : 0; }
 hipError_t launch_dec_bf16(hipStream_t s, Dims D, const DecArgs& a) {

@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P p, TileGrid tg) {
   }
 }
 
-constexpr int CUS = 256;
+constexpr int CUS = 256;      // a literal like the one in few_rows
 
 template <class P>
 hipError_t launch(hipStream_t s, const P& p, int G, int tile = 0) {
