@@ -46,11 +46,34 @@ def test_ragged_shapes_full_step(dtype, L, d, F, B):
 
 @pytest.mark.parametrize("d,F,B", [(136, 8200, 516), (128, 8192, 512), (264, 4104, 513)])
 def test_fp32_large_tiles(d, F, B):
-    """Enough tiles for the 128x128 fp32 kernel in the encoder, dz and weight-gradient launches, with and without
-    remainders in rows, columns and K (steps of 32)."""
+    """Enough tiles for the 128x128 fp32 kernel in the encoder and dz, at the first and last shape also in dW_dec, with and
+    without remainders in rows, columns and K (steps of 32)."""
     w = S.scaled(S.WORKLOADS["tiny"], L=2, d=d, F=F, B=B, seed=51 + d)
     g, o = run_both(w)
     show(f"f32 large tiles d{d} F{F} B{B}", compare_step(w, g, o, TOL["f32"]))
+
+
+@pytest.mark.parametrize("d,F,B", [
+    (1024, 2048, 128),       # 384 tiles of 128x128 in dW_dec, 256 in dW_enc, no remainders
+    (1032, 2056, 130),       # 459 and 306, remainders everywhere
+])
+def test_fp32_large_weight_gradient_tiles(d, F, B):
+    w = S.scaled(S.WORKLOADS["tiny"], L=2, d=d, F=F, B=B, seed=53 + d)
+    for fused in (False, True):
+        g, o = run_both(w, fused=fused)
+        show(f"f32 large gradient tiles d{d} F{F} B{B} fused={fused}", compare_step(w, g, o, TOL["f32"]))
+
+
+@pytest.mark.parametrize("L,d,F,B", [
+    (8, 136, 2824, 640),     # K ranges cut into 48 chunks
+    (4, 2056, 264, 641),     # one tile per target, remainders in rows, columns and K
+    (2, 2048, 512, 1536),    # the same without remainders
+])
+def test_fp32_large_decode_tiles(L, d, F, B):
+    """At least 8192 K steps of 128x128 tiles in the fp32 decode: the large tile, with its K ranges cut and whole."""
+    w = S.scaled(S.WORKLOADS["tiny"], L=L, d=d, F=F, B=B, seed=55 + L)
+    g, o = run_both(w)
+    show(f"f32 large decode tiles L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["f32"]))
 
 
 @pytest.mark.parametrize("L,d,F,B", [
@@ -113,14 +136,51 @@ def test_few_tokens(L, d, F, B, int8):
     (8, 264, 2952, 516),      # 4 rows, 136 features, 8 columns
 ])
 def test_tiles_half_outside_the_matrix(L, d, F, B):
-    """Tiles at a matrix edge with at most half of their rows or columns inside, 256-row tiles (more than 256 of them)."""
+    """Tiles at a matrix edge with at most half of their rows or columns inside, 256-row tiles (more than 256 of them).  The
+    decode of these shapes has its K ranges cut."""
     w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=31 + B)
     g, o = run_both(w)
     show(f"edge tiles L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
 
 
+@pytest.mark.parametrize("L,d,F,B,int8,lambda1", [
+    (8, 136, 2824, 640, True, 5.0),
+    (8, 392, 2944, 641, False, 5.0),
+    (8, 264, 2952, 516, True, 0.0),
+])
+def test_edge_tiles_with_int8_inputs_and_dead_features(L, d, F, B, int8, lambda1):
+    """256-row edge tiles whose loads convert int8 codes, and whose dz epilogue counts the entries below the threshold."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=37 + B, int8_inputs=int8, lambda1=lambda1,
+                 log_threshold=lambda1 > 0)
+    g, o = run_both(w, fused=int8)
+    if lambda1:
+        dead_term_matters(w, o, TOL["bf16"])
+    show(f"edge tiles int8={int8} lambda1={lambda1} L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
+
+
+@pytest.mark.parametrize("L,d,F,B", [
+    (10, 264, 520, 2052),    # 256-row tiles; the last ones hold 4 rows, 8 columns
+    (10, 424, 776, 2216),    # 168 rows, 168 columns
+    (10, 424, 520, 1960),    # too few tiles for 256 rows: 128-row tiles
+])
+def test_edge_tiles_of_the_uncut_decode(L, d, F, B):
+    """Edge tiles of a decode that sums over a target's whole K range in one tile."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=39 + B)
+    g, o = run_both(w)
+    show(f"uncut decode L{L} d{d} F{F} B{B}", compare_step(w, g, o, TOL["bf16"]))
+
+
+def test_tile_loop_of_the_uncut_decode():
+    """8 targets x 64 tiles, all inside the matrix: the decode walks two tiles per CU, the workgroups of an XCD paced at
+    every K segment."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=8, d=1024, F=512, B=4096, seed=45)
+    g, o = run_both(w)
+    show("decode tile loop", compare_step(w, g, o, TOL["bf16"]))
+
+
 def test_bf16_several_tiles_and_segments():
-    """Spans 2x3 output tiles of 256x256 per group and up to 4 K segments."""
+    """No remainders, up to 4 K segments: 2 x 3 tiles of 256x256 per block in dW_dec, 128-row tiles in the encoder and dz, K
+    ranges of the decode cut."""
     w = S.scaled(S.WORKLOADS["gpt2"], L=4, d=512, F=768, B=512, k_active=16)
     g, o = run_both(w)
     show("bf16 multi-tile", compare_step(w, g, o, TOL["bf16"]))
@@ -129,8 +189,9 @@ def test_bf16_several_tiles_and_segments():
 @pytest.mark.parametrize("fused", [False, True])
 def test_bf16_more_interior_tiles_than_cus(fused):
     """Every matrix extent is a multiple of the 256-tile and the launches hold more workgroup slots than the GPU has
-    CUs, empty slots included (encoder 5 groups x 72 tiles in 432 slots, decode 5 x 8, dW_dec up to 5 blocks x 36
-    tiles in 288 slots): the kernels without edge code walk their tiles in a loop, one workgroup per CU."""
+    CUs, empty slots included (encoder 5 groups x 72 tiles in 432 slots, dW_dec up to 5 blocks x 36 tiles in 288
+    slots): the kernels without edge code walk their tiles in a loop, one workgroup per CU.  (The decode has 5 x 8 tiles and its
+    K ranges cut into 30 chunks.)"""
     w = S.scaled(S.WORKLOADS["gpt2"], L=5, d=512, F=4608, B=1024, k_active=32, seed=77)
     g, o = run_both(w, fused=fused)
     show(f"bf16 tile loop fused={fused}", compare_step(w, g, o, TOL["bf16"]))
