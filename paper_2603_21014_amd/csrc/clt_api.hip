@@ -552,7 +552,7 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
     //  alone, so a row longer than the per-token lists hold does not stop it)
     RUN(h, s, K_DECIDE, launch_decode_decide(s, h->D, l0, h->cfg.gather_density_threshold, backward_threshold(&h->cfg),
                                              mode == CLT_DECODE_GATHER,
-                                             mode == CLT_DECODE_AUTO && sparse_dwdec_takes_dz(h->D) && h->plan.ecap > 0,
+                                             mode == CLT_DECODE_AUTO && sparse_dwdec_takes_dz(h->bf16, h->D) && h->plan.ecap > 0,
                                              flags));
     RUN(h, s, K_COMPACT, launch_compact_active(s, h->bf16, h->D, z, act_class, gl, flags));
     RUN(h, s, K_GATHER, launch_gather_decode(s, h->bf16, h->D, gl, W_dec, b_dec, y_hat, flags));
@@ -660,7 +660,7 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   FeatureLists fl{reinterpret_cast<int32_t*>(h->ws + h->plan.fl_off), reinterpret_cast<int32_t*>(h->ws + h->plan.fl_cnt),
                   reinterpret_cast<int32_t*>(h->ws + h->plan.fl_tok), reinterpret_cast<float*>(h->ws + h->plan.fl_val),
                   reinterpret_cast<int32_t*>(h->ws + h->plan.fl_seg), kcap,
-                  sparse_dwdec_takes_dz(D) && h->plan.ecap ? reinterpret_cast<float*>(h->ws + h->plan.dz_part) : nullptr,
+                  sparse_dwdec_takes_dz(h->bf16, D) && h->plan.ecap ? reinterpret_cast<float*>(h->ws + h->plan.dz_part) : nullptr,
                   h->plan.ecap};
   if (mode != CLT_DECODE_DENSE) {
     // The row kernel of dW_dec runs before the rest of the backward: when the lists are short enough it also takes

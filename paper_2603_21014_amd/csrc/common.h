@@ -367,7 +367,7 @@ __host__ __device__ inline bool fused_dz_selected(const int32_t* flags, const Fe
 }
 constexpr int FUSED_DZ_ENTRIES_PER_TOKEN = 128;      // forced gather mode: ecap = B * min(kcap, this)
 constexpr int FUSED_DZ_ENTRIES_PER_TOKEN_MAX = 320;  // automatic mode: sized from the backward threshold, up to this
-bool sparse_dwdec_takes_dz(Dims D);                  // whether launch_sparse_dwdec will use the kernel that can (else: dz_part = NULL)
+bool sparse_dwdec_takes_dz(bool bf16, Dims D);                  // whether launch_sparse_dwdec will use the kernel that can (else: dz_part = NULL)
 // dz at the listed entries only: sum_{lp>=l} <d_yhat[lp,b,:], W_dec[p(l,lp)][f,:]> + sparsity gradient -> dpre[l,b,f]
 hipError_t launch_gather_dz(hipStream_t s, bool bf16, Dims D, GatherLists g, const void* d_yhat, const void* W_dec,
                             const float* norms, float lam_c_over_b, float C, void* dpre, const int32_t* flags,

@@ -15,9 +15,9 @@
 //             features' decoder rows with the token's d y_hat rows;
 //   feature lists   transpose of the row lists: per (layer, feature) the tokens on
 //             which it is active, built by a column scan in token order;
-//   sparse dW_dec   one workgroup per (layer, feature, 8 targets): sums the few
-//             d y_hat rows of the feature's tokens, adds the norm term and runs
-//             the fused Adam update of the row.
+//   sparse dW_dec   one wavefront per (source, target, feature, slice of columns): sums
+//             the d y_hat rows of the feature's tokens, adds the norm term and runs
+//             the fused Adam update of the row; takes the partial dot products of dz along.
 // Every order of summation is fixed, so the results are bitwise reproducible
 // (no floating-point atomics).  Decode and dz read B * k * P * d * sizeof(T)
 // bytes of decoder rows (HBM/L2-bound); sparse dW_dec streams the optimizer
@@ -217,6 +217,14 @@ __global__ __launch_bounds__(64) void gather_decode_kernel(Dims D, GatherLists g
     for (; j < cnt; ++j) gather_rows<T, 1>(acc, Wp, D.d, (uint32_t)col, ii, vv, j);
   }
   *reinterpret_cast<float4*>(y_hat + ((size_t)lp * D.B + b) * D.d + col) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+}
+
+typedef unsigned int u32x4_lds __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_mfma __attribute__((ext_vector_type(8)));
+typedef float f32x4_mfma __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void wave_lds_order() {      // a wave's LDS accesses complete in order; this keeps the compiler to it
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // ---------------------------------------------------------------------------
@@ -780,25 +788,21 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
 
 // The same rows cut into eight column slices, one per XCD (workgroups go round-robin to the XCDs, so blockIdx & 7
 // names the slice): an XCD's L2 then only ever sees its d/8 columns of d y_hat, and with the (source, target) pairs
-// walked target-major that is B * d/8 elements at a time (2 MB at L=16 d=2048 B=4096), so the gathered d y_hat rows
-// come out of the L2.  One wave per (pair, feature, slice), four consecutive features per workgroup, lanes own 4
-// columns per pass of 256; 44-48 registers with bf16 storage, eight waves per SIMD.  The weights and optimizer state,
-// touched once, are streamed with non-temporal accesses so that they do not displace the slice (plain accesses: 10 %
-// slower).  The sums run over the feature's tokens in list order; with fp32 storage exactly as in the kernel above
-// (same gradient and update, bit for bit).  At more than a few tokens per feature the kernel is bound by vector
-// instruction issue, hence the bf16 token loop below.  This is the kernel the library uses whenever d is a
-// multiple of 32.
-#ifndef SD_ITEMS_PER_WG
-#define SD_ITEMS_PER_WG 2
-#endif
-template <typename T, bool MASTER>
-__global__ __launch_bounds__(256, sizeof(T) == 2 ? 8 : 6) void sparse_dwdec_sliced_kernel(Dims D, FeatureLists fl, const T* __restrict__ d_yhat,
-                                                                     T* __restrict__ W_dec, const float* __restrict__ G,
-                                                                     const float* __restrict__ norms, T* __restrict__ dW_dec,
+// walked target-major that is B * d/8 elements at a time (2 MB of bf16 at L=16 d=2048 B=4096), so the gathered d y_hat rows
+// come out of the L2.  One wave per (pair, feature, slice), four consecutive features per workgroup.  The weights and optimizer
+// state, touched once, are streamed with non-temporal accesses so that they do not displace the slice (plain accesses: 10 %
+// slower).  The sums run over the feature's tokens in list order.
+// fp32 storage: lanes own 4 columns per pass of 256; sums exactly as in the kernel above (same gradient and update, bit for
+// bit).  Used whenever d is a multiple of 32.
+constexpr int SD_ITEMS_PER_WG = 2;
+template <bool MASTER>
+__global__ __launch_bounds__(256, MASTER ? 5 : 6) void sparse_dwdec_sliced_kernel(Dims D, FeatureLists fl, const float* __restrict__ d_yhat,
+                                                                     float* __restrict__ W_dec, const float* __restrict__ G,
+                                                                     const float* __restrict__ norms, float* __restrict__ dW_dec,
                                                                      AdamFuseArgs fuse, const int32_t* __restrict__ flags,
-                                                                     float* __restrict__ n2_part,
                                                                      const int32_t* __restrict__ fl_tok,
                                                                      const float* __restrict__ fl_val) {
+  typedef float T;
   // (fl_tok, fl_val: fl.tok and fl.val once more, as parameters of their own that nothing else aliases: the wave-uniform
   //  reads of the token lists can then go through the scalar unit)
   if (!lists_backward_selected(flags, fl.kcap)) return;
@@ -863,44 +867,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 8 : 6) void sparse_dwdec_slic
             }
           }
         };
-        if constexpr (sizeof(T) == 2) {
-          // bf16 storage.  The rows come through buffer loads (descriptor of the target's d y_hat, the lane's column
-          // offset in a register, the token's row offset as the scalar operand: no vector arithmetic per token) and
-          // stay packed: z * row enters the gradient two tokens at a time as a packed dot product (the two tokens'
-          // values of a column brought into one register by a byte permute, (z_a, z_b) as the scalar operand; z is a
-          // bf16 value, so nothing is rounded), the dz product two columns at a time.
-          const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
-              const_cast<T*>(dyt), 0, (int)((size_t)D.B * D.d * 2), 0x00020000);
-          const uint32_t voff = col * 2, row_bytes = (uint32_t)D.d * 2;
-          const uint32_t wzx = on ? wr[0] : 0u, wzy = on ? wr[1] : 0u;
-          for (int j = 0; j < cur.cnt; j += 4) {
-            const int nval = cur.cnt - j < 4 ? cur.cnt - j : 4;
-            nt_u32x2 q[4];
-            uint32_t zb[4], bt[4];
-            // (four list entries at once whatever nval is: past the feature's own entries lie other lists or, at the
-            //  very end, the arrays that follow in the workspace; what is read there is replaced by token 0 with z = 0)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { bt[u] = (uint32_t)tk[j + u]; zb[u] = __float_as_uint(tv[j + u]); }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              if (u >= nval) { bt[u] = 0u; zb[u] = 0u; }
-              q[u] = __builtin_amdgcn_raw_buffer_load_b64(rows, voff, bt[u] * row_bytes, 0);
-            }
-            float pd[4];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const uint32_t zp = (zb[2 * h] >> 16) | (zb[2 * h + 1] & 0xffff0000u);
-              const nt_u32x2 qa = q[2 * h], qb = q[2 * h + 1];
-              acc[0] = dot2_bf16(__builtin_amdgcn_perm(qb[0], qa[0], 0x05040100u), zp, acc[0]);
-              acc[1] = dot2_bf16(__builtin_amdgcn_perm(qb[0], qa[0], 0x07060302u), zp, acc[1]);
-              acc[2] = dot2_bf16(__builtin_amdgcn_perm(qb[1], qa[1], 0x05040100u), zp, acc[2]);
-              acc[3] = dot2_bf16(__builtin_amdgcn_perm(qb[1], qa[1], 0x07060302u), zp, acc[3]);
-              pd[2 * h] = dot2_bf16(qa[0], wzx, dot2_bf16(qa[1], wzy, 0.f));
-              pd[2 * h + 1] = dot2_bf16(qb[0], wzx, dot2_bf16(qb[1], wzy, 0.f));
-            }
-            if (dz_out) dz_group(j, nval, pd);
-          }
-        } else {
+        {
           const float4 wz = on ? wl : make_float4(0.f, 0.f, 0.f, 0.f);
           int j = 0;
           for (; j + 4 <= cur.cnt; j += 4) {
@@ -963,17 +930,259 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 8 : 6) void sparse_dwdec_slic
             if (MASTER) nt_store_f4(lane_ptr(fuse.master + o, col), pn);
             Elem<T>::nt_store_raw4(lane_ptr(W_dec + o, col), stored);
           }
-          if (n2_part) {      // sum of squares of the pass's weights as stored, for the next step's norms: slot (slice, pass)
-            const float4 wn = Elem<T>::widen4(stored);
-            const float sq = on ? (wn.x * wn.x + wn.y * wn.y) + (wn.z * wn.z + wn.w * wn.w) : 0.f;
-            const int b16 = __float_as_int(row16_sum(sq));
-            const float tot = (__int_as_float(__builtin_amdgcn_readlane(b16, 0)) + __int_as_float(__builtin_amdgcn_readlane(b16, 16))) +
-                              (__int_as_float(__builtin_amdgcn_readlane(b16, 32)) + __int_as_float(__builtin_amdgcn_readlane(b16, 48)));
-            if (lane == 0)
-              n2_part[((size_t)packed_index(cur.l, cur.lp, D.L) * D.F + cur.f) * (8 * passes) + slice * passes + ps] = tot;
-          }
         }
       }
+    }
+  }
+}
+
+// columns of a slice: an eighth of d, whole runs of 8
+__host__ __device__ inline int slice_cols(int d) { return (d + 63) / 64 * 8; }
+
+// Streaming accesses of a wavefront to `bytes` bytes from a uniform address on: base and bounds in scalar registers, the lane's
+// 32-bit offset as it is; lanes beyond the end load zeros and store nothing.  (With pointers, base + lane of every array was hoisted
+// out of the item loop, two registers per lane each, and spilled.)
+struct UniformRun {
+  __amdgpu_buffer_rsrc_t d;
+  static constexpr int NT = 2;      // cache policy: non-temporal
+  __device__ __forceinline__ UniformRun(const void* p, int bytes) : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000)) {}
+  __device__ __forceinline__ nt_f32x4 load_f4(uint32_t o) const { return __builtin_bit_cast(nt_f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)o, 0, NT)); }
+  __device__ __forceinline__ nt_u32x2 load8(uint32_t o) const { return __builtin_bit_cast(nt_u32x2, __builtin_amdgcn_raw_buffer_load_b64(d, (int)o, 0, NT)); }
+  __device__ __forceinline__ uint32_t load4(uint32_t o) const { return __builtin_amdgcn_raw_buffer_load_b32(d, (int)o, 0, 0); }
+  __device__ __forceinline__ void store_f4(uint32_t o, nt_f32x4 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((__vector_size__(16))) unsigned int, v), d, (int)o, 0, NT);
+  }
+  __device__ __forceinline__ void store8(uint32_t o, nt_u32x2 v, int policy) const {
+    const __attribute__((__vector_size__(8))) unsigned int t = {v[0], v[1]};
+    if (policy) __builtin_amdgcn_raw_buffer_store_b64(t, d, (int)o, 0, NT); else __builtin_amdgcn_raw_buffer_store_b64(t, d, (int)o, 0, 0);
+  }
+  __device__ __forceinline__ void store4(uint32_t o, uint32_t v) const { __builtin_amdgcn_raw_buffer_store_b32(v, d, (int)o, 0, 0); }
+};
+
+// bf16 storage.  What bounds it: the bytes that come back through the vector caches, state and gathered rows added up (a wavefront's
+// loads return in order, so rows that wait in the L2 do not overtake state on its way from HBM), and below a few tokens per
+// feature the state alone at 6 TB/s.  Hence 16 bytes per lane and load for the rows (rows that lie in the L2 come at 18 TB/s with 8 bytes
+// per lane, at 28 to 31 with 16, whatever their stride), and every weight loaded once: as quads of columns for the update,
+// turned into runs of 8 through LDS for the dot products.
+// A load takes 4 entries of the feature's list at a time, one per row of 16 lanes, 128 columns each.  The sum z * row
+// goes to the matrix cores: as A operand of v_mfma_f32_16x16x32 the load's registers are a 16 x 32 matrix whose row m is column run m
+// (8 columns) and whose k = 8 t + c is column c of entry t's run; with B[8 t + c][n] = z_t where c = n, else 0, entry (m, n) of
+// the product is column 8 m + n of the sum over the 4 entries: products exact, sums fp32.  The dot products for dz stay on the
+// vector unit (packed, 16 lanes per entry, four entries per cross-lane sum).  z is a bf16 value: nothing is rounded.
+// L = 16, d = 2048, F = 8192, 4096 tokens with the update, against one entry at a time with 8 bytes per lane: 82 active features per
+// token 19.1 -> 15.0 ms, 16: 9.05 -> 8.35, 2.5: 7.4 either way.  Whole steps at L = 12, d = 768, F = 6144: 12.2 -> 8.7 ms at
+// 1 % active, 8.3 -> 6.9 at 0.4 %.  More rows or the next feature's state in flight per wavefront: no faster (16.4 to 18.3 ms).
+// NH: runs of 128 columns per pass.  ADAM: 0 gradient only, 1 with the update, 2 with fp32 master weights.
+constexpr int SDM_ITEMS = 4;      // quads of features per workgroup; 2: 1.5 % slower, 8: 3 %
+template <int NH, int ADAM>
+__global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ? 1 : 0)) void sparse_dwdec_mfma_kernel(
+    Dims D, FeatureLists fl, const bf16_t* __restrict__ d_yhat, bf16_t* __restrict__ W_dec, const float* __restrict__ G,
+    const float* __restrict__ norms, bf16_t* __restrict__ dW_dec, AdamFuseArgs fuse, const int32_t* __restrict__ flags,
+    float* __restrict__ n2_part, const int32_t* __restrict__ fl_tok, const float* __restrict__ fl_val,
+    const int32_t* __restrict__ fl_cnt, const int32_t* __restrict__ fl_off) {
+  if (!lists_backward_selected(flags, fl.kcap)) return;
+  typedef Elem<bf16_t> E;
+  constexpr int IT = SDM_ITEMS, R = NH > 2 ? 2 : 1;      // column quads per lane in the update
+  constexpr int COLS = 128 * NH;
+  __shared__ __align__(16) unsigned char smem[4][3072];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = lane >> 4, i16 = lane & 15;
+  float* const sums = reinterpret_cast<float*>(smem[wv]);                       // [COLS] after the token loop
+  nt_u32x2* const win = reinterpret_cast<nt_u32x2*>(smem[wv]);                  // [64] list window during it
+  const u32x4_lds* const wts = reinterpret_cast<const u32x4_lds*>(smem[wv] + 2048);      // [COLS] weights, by runs of 8
+  nt_u32x2* const wts8 = reinterpret_cast<nt_u32x2*>(smem[wv] + 2048);                   // and as the lanes load them
+  // the B operand's diagonal: lane (t, n) holds z_t at k = n of its run of 8
+  const uint32_t half = i16 >= 8 ? 0u : (i16 & 1) ? 0xffff0000u : 0x0000ffffu;
+  const int slice = blockIdx.x & 7, wg = blockIdx.x >> 3, nwg = gridDim.x >> 3;      // (gridDim.x is a multiple of 8)
+  const int sw = slice_cols(D.d), slots = (sw + 255) / 256, passes = NH == 4 ? (sw + COLS - 1) / COLS : 1;
+  const int F4 = (D.F + 3) / 4;
+  const bool dz_on = fused_dz_selected(flags, fl);
+  const uint32_t row_bytes = (uint32_t)D.d * 2;
+  const int pq = blockIdx.y;                               // pair ordinal, target-major: (0,0) (0,1) (1,1) (0,2) ...
+  int lp = __builtin_amdgcn_readfirstlane((int)((__builtin_amdgcn_sqrtf(8.0f * (float)pq + 1.0f) - 1.0f) * 0.5f));
+  while ((lp + 1) * (lp + 2) / 2 <= pq) ++lp;
+  while (lp * (lp + 1) / 2 > pq) --lp;
+  const int l = pq - lp * (lp + 1) / 2;
+  const int pair = packed_index(l, lp, D.L);
+  const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16_t*>(d_yhat + (size_t)lp * D.B * D.d), 0, (int)((size_t)D.B * D.d * 2), 0x00020000);
+  const int32_t* const tkl = fl_tok + (size_t)l * D.B * fl.kcap;
+  const float* const tvl = fl_val + (size_t)l * D.B * fl.kcap;
+  const size_t lF = (size_t)l * D.F;
+  for (int q0 = wg * IT; q0 < F4; q0 += nwg * IT) {
+    const int f_first = q0 * 4 + wv;
+    if (f_first >= D.F) break;
+    const int f_end = min(D.F, (q0 + IT) * 4);
+    // the list heads of an item are requested one item ahead
+    int cnt = fl_cnt[lF + f_first], off = fl_off[lF + f_first];
+    uint32_t tok = UniformRun(tkl + off, cnt * 4).load4(lane * 4u), val = UniformRun(tvl + off, cnt * 4).load4(lane * 4u);
+#pragma unroll 1
+    for (int fi = f_first; fi < f_end; fi += 4) {
+      int f = fi;      // (opaque: addresses are formed from it anew instead of being carried along per lane)
+      asm volatile("" : "+s"(f));
+      const bool more = f + 4 < f_end;
+      const int fn = more ? f + 4 : f;
+      const int cnt_n = fl_cnt[lF + fn], off_n = fl_off[lF + fn];
+      const float Gf = G[lF + f], nf = norms[lF + f];
+      const size_t o = ((size_t)pair * D.F + f) * D.d;
+      float* dz_out = dz_on ? fl.dz_part + ((size_t)pair * 8 + slice) * fl.ecap + off : nullptr;
+      uint32_t tok_n = 0, val_n = 0;
+      for (int ps = 0; ps < passes; ++ps) {
+        const int c0 = slice * sw + ps * COLS;
+        const int cols = __builtin_amdgcn_readfirstlane(max(min(min(sw - ps * COLS, COLS), D.d - c0), 0));
+        const UniformRun pw(W_dec + o + c0, cols * 2);
+        E::Raw4 wq[R];      // a lane's quads of columns: the weights, then the optimizer state
+        nt_f32x4 m4[R], v4[R], p4[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) wq[r] = pw.load8((uint32_t)(r * 64 + lane) * 8u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (ADAM) {
+            m4[r] = UniformRun(fuse.m + o + c0, cols * 4).load_f4((uint32_t)(r * 64 + lane) * 16u);
+            v4[r] = UniformRun(fuse.v + o + c0, cols * 4).load_f4((uint32_t)(r * 64 + lane) * 16u);
+            if (ADAM == 2) p4[r] = UniformRun(fuse.master + o + c0, cols * 4).load_f4((uint32_t)(r * 64 + lane) * 16u);
+          }
+        }
+        tok_n = UniformRun(tkl + off_n, cnt_n * 4).load4(lane * 4u);
+        val_n = UniformRun(tvl + off_n, cnt_n * 4).load4(lane * 4u);
+        float4 a4[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) a4[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (cnt > 0) {
+          wave_lds_order();
+#pragma unroll
+          for (int r = 0; r < R; ++r) wts8[r * 64 + lane] = wq[r];
+          wave_lds_order();
+          uint32_t voff[NH];
+          u32x4_lds w8[NH];
+          f32x4_mfma acc[NH];
+#pragma unroll
+          for (int h = 0; h < NH; ++h) {      // (lanes past the slice: zeros, no descriptor covers their offset)
+            voff[h] = h * 128 + i16 * 8 < cols ? (uint32_t)(c0 + h * 128 + i16 * 8) * 2u : 0x7ffffff0u;
+            w8[h] = wts[h * 16 + i16];
+            acc[h] = f32x4_mfma{0.f, 0.f, 0.f, 0.f};
+          }
+          for (int w0 = 0; w0 < cnt; w0 += 64) {
+            const int n = __builtin_amdgcn_readfirstlane(min(64, cnt - w0));
+            if (w0 > 0 || (NH == 4 && ps > 0)) {      // (the head came with the item; a later pass has another window in its place)
+              tok = UniformRun(tkl + off + w0, n * 4).load4(lane * 4u);
+              val = UniformRun(tvl + off + w0, n * 4).load4(lane * 4u);
+            }
+            wave_lds_order();
+            win[lane] = nt_u32x2{lane < n ? tok * row_bytes : 0x80000000u, __builtin_amdgcn_perm(val, val, 0x07060706u)};
+            wave_lds_order();
+            float dz_keep = 0.f;
+            for (int j = 0; j < n; j += 16) {
+              float pd[4] = {0.f, 0.f, 0.f, 0.f};
+              auto sets = [&](auto first) {      // two sets of 4 entries, one entry per row of 16 lanes
+                constexpr int u0 = decltype(first)::value;
+                nt_u32x2 en[2];
+                u32x4_lds q[2][NH];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) en[u] = win[j + 4 * (u0 + u) + grp];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                  for (int h = 0; h < NH; ++h)
+                    q[u][h] = __builtin_bit_cast(u32x4_lds, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(en[u][0] + voff[h]), 0, 0));
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                  const uint32_t zs = en[u][1] & half;
+                  const u32x4_lds zd = {(i16 >> 1) == 0 ? zs : 0u, (i16 >> 1) == 1 ? zs : 0u, (i16 >> 1) == 2 ? zs : 0u, (i16 >> 1) == 3 ? zs : 0u};
+#pragma unroll
+                  for (int h = 0; h < NH; ++h) {
+                    acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_mfma, q[u][h]), __builtin_bit_cast(bf16x8_mfma, zd), acc[h], 0, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) pd[u0 + u] = dot2_bf16(q[u][h][k], w8[h][k], pd[u0 + u]);
+                  }
+                }
+              };
+              sets(std::integral_constant<int, 0>{});
+              if (j + 8 < n) sets(std::integral_constant<int, 2>{});
+              const bool o1 = lane & 1, o2 = lane & 2;
+              const float r1 = (o1 ? pd[1] : pd[0]) + dpp_move<0xB1>(o1 ? pd[0] : pd[1]);
+              const float r2 = (o1 ? pd[3] : pd[2]) + dpp_move<0xB1>(o1 ? pd[2] : pd[3]);
+              float r = (o2 ? r2 : r1) + dpp_move<0x4E>(o2 ? r1 : r2);
+              r += dpp_move<0x128>(r);      // row_ror:8
+              r += dpp_move<0x124>(r);      // row_ror:4
+              if ((i16 >> 2) == (j >> 4)) dz_keep = r;
+            }
+            const int td = (i16 >> 2) * 16 + (i16 & 3) * 4 + grp;      // the entry whose sum the lane kept
+            if (dz_out) {
+              const UniformRun out(dz_out + w0, n * 4);
+              if (NH == 4 && ps > 0) dz_keep += __uint_as_float(out.load4(td * 4u));      // (a slice wider than a pass: one after the other)
+              out.store4(td * 4u, __float_as_uint(dz_keep));
+            }
+          }
+          wave_lds_order();
+#pragma unroll
+          for (int h = 0; h < NH; ++h)
+            if (i16 < 8) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) sums[h * 128 + (4 * grp + r) * 8 + i16] = acc[h][r];
+            }
+          wave_lds_order();
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            a4[r] = *reinterpret_cast<const float4*>(sums + (r * 64 + lane) * 4);
+            wq[r] = wts8[r * 64 + lane];      // (not held through the loop)
+          }
+          // The zeros beside z in the B operand meet the other seven columns of a run, so an infinity or a NaN in one column of
+          // d y_hat would reach them.  Where a sum is not finite the columns are summed up one by one.
+          float nan = 0.f;
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            if ((r * 64 + lane) * 4 < cols) nan = fmaf(a4[r].x, 0.f, fmaf(a4[r].y, 0.f, fmaf(a4[r].z, 0.f, fmaf(a4[r].w, 0.f, nan))));
+          if (__builtin_amdgcn_ballot_w64(nan != nan)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              a4[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+              for (int e = 0; e < cnt; ++e) {
+                const uint32_t at = (r * 64 + lane) * 4 < cols ? (uint32_t)tkl[off + e] * row_bytes + (uint32_t)(c0 + (r * 64 + lane) * 4) * 2u : 0x80000000u;
+                const nt_u32x2 raw = __builtin_bit_cast(nt_u32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, (int)at, 0, 0));
+                const float4 y = E::widen4(raw);
+                const float z = tvl[off + e];
+                a4[r] = make_float4(fmaf(z, y.x, a4[r].x), fmaf(z, y.y, a4[r].y), fmaf(z, y.z, a4[r].z), fmaf(z, y.w, a4[r].w));
+              }
+            }
+          }
+        }
+        const float coef = Gf * __builtin_amdgcn_rcpf(fmaxf(nf, 1e-30f));
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int qd = r * 64 + lane;
+          const bool on = qd * 4 < cols;
+          const float4 wl = E::widen4(wq[r]);
+          const float w4[4] = {wl.x, wl.y, wl.z, wl.w};
+          const float g4[4] = {fmaf(coef, w4[0], a4[r].x), fmaf(coef, w4[1], a4[r].y), fmaf(coef, w4[2], a4[r].z), fmaf(coef, w4[3], a4[r].w)};
+          if (dW_dec) UniformRun(dW_dec + o + c0, cols * 2).store8((uint32_t)qd * 8u, E::narrow4(make_float4(g4[0], g4[1], g4[2], g4[3])), 0);
+          if (ADAM) {
+            float mm[4] = {m4[r][0], m4[r][1], m4[r][2], m4[r][3]};
+            float vv[4] = {v4[r][0], v4[r][1], v4[r][2], v4[r][3]};
+            float pp[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pp[k] = ADAM == 2 ? p4[r][k] : w4[k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) adam_element(pp[k], mm[k], vv[k], g4[k], fuse.a);
+            const float4 pn = make_float4(pp[0], pp[1], pp[2], pp[3]);
+            const E::Raw4 stored = E::narrow4(pn);
+            UniformRun(fuse.m + o + c0, cols * 4).store_f4((uint32_t)qd * 16u, nt_f32x4{mm[0], mm[1], mm[2], mm[3]});
+            UniformRun(fuse.v + o + c0, cols * 4).store_f4((uint32_t)qd * 16u, nt_f32x4{vv[0], vv[1], vv[2], vv[3]});
+            if (ADAM == 2) UniformRun(fuse.master + o + c0, cols * 4).store_f4((uint32_t)qd * 16u, nt_f32x4{pp[0], pp[1], pp[2], pp[3]});
+            pw.store8((uint32_t)qd * 8u, stored, 1);
+            if (n2_part && ps * R + r < slots) {      // sum of squares of 256 weights as stored, for the next step's norms
+              const float4 wn = E::widen4(stored);
+              const float sq = on ? (wn.x * wn.x + wn.y * wn.y) + (wn.z * wn.z + wn.w * wn.w) : 0.f;
+              const int b16 = __float_as_int(row16_sum(sq));
+              const float tot = (__int_as_float(__builtin_amdgcn_readlane(b16, 0)) + __int_as_float(__builtin_amdgcn_readlane(b16, 16))) +
+                                (__int_as_float(__builtin_amdgcn_readlane(b16, 32)) + __int_as_float(__builtin_amdgcn_readlane(b16, 48)));
+              if (lane == 0) n2_part[((size_t)pair * D.F + f) * (8 * slots) + slice * slots + ps * R + r] = tot;
+            }
+          }
+        }
+        wave_lds_order();
+      }
+      cnt = cnt_n; off = off_n; tok = tok_n; val = val_n;
     }
   }
 }
@@ -1118,11 +1327,11 @@ hipError_t launch_feature_lists(hipStream_t s, bool bf16, Dims D, const uint8_t*
   return hipGetLastError();
 }
 
-// The sliced kernel: d in eight slices of whole lane quads, and one target's d y_hat within reach of a 32-bit byte offset
-static bool sparse_dwdec_sliced(Dims D) {
-  return D.d % 32 == 0 && (size_t)D.B * D.d * 2 < ((size_t)1 << 31) && !getenv("CLT_SD_ROWS");
+// The sliced kernels: d in eight slices (fp32: of whole lane quads), and one target's d y_hat within reach of a 32-bit byte offset
+static bool sparse_dwdec_sliced(bool bf16, Dims D) {
+  return (bf16 || D.d % 32 == 0) && (size_t)D.B * D.d * 2 < ((size_t)1 << 31) && !getenv("CLT_SD_ROWS");
 }
-bool sparse_dwdec_takes_dz(Dims D) { return sparse_dwdec_sliced(D) && !getenv("CLT_NO_FUSED_DZ"); }
+bool sparse_dwdec_takes_dz(bool bf16, Dims D) { return sparse_dwdec_sliced(bf16, D) && !getenv("CLT_NO_FUSED_DZ"); }
 
 hipError_t launch_dz_from_partials(hipStream_t s, bool bf16, Dims D, FeatureLists fl, const float* norms,
                                    float lam_c_over_b, float C, void* dpre, const int32_t* flags) {
@@ -1137,24 +1346,41 @@ hipError_t launch_dz_from_partials(hipStream_t s, bool bf16, Dims D, FeatureList
   return hipGetLastError();
 }
 
+template <int NH>
+static hipError_t launch_sparse_dwdec_mfma(hipStream_t s, Dims D, const FeatureLists& fl, const DWdecArgs& a, float* n2,
+                                           const int32_t* flags) {
+  // (every workgroup takes SDM_ITEMS quads of features while the grid allows it)
+  const size_t wgs = ((D.F + 3) / 4 + SDM_ITEMS - 1) / SDM_ITEMS, most = (size_t)1 << 19;
+  const dim3 grid(8 * (unsigned)(wgs < most ? wgs : most), D.P());
+#define CLT_SDM(ADAM)                                                                                                 \
+  hipLaunchKernelGGL((sparse_dwdec_mfma_kernel<NH, ADAM>), grid, dim3(256), 0, s, D, fl, (const bf16_t*)a.d_yhat,     \
+                     (bf16_t*)a.W_dec, a.G, a.norms, (bf16_t*)a.dW_dec, a.fuse, flags, n2, fl.tok, fl.val, fl.cnt, fl.off)
+  if (!a.fuse.m) CLT_SDM(0); else if (!a.fuse.master) CLT_SDM(1); else CLT_SDM(2);
+#undef CLT_SDM
+  return hipGetLastError();
+}
+
 hipError_t launch_sparse_dwdec(hipStream_t s, bool bf16, Dims D, FeatureLists fl, const DWdecArgs& a,
                                const int32_t* flags) {
   const bool master = a.fuse.m && a.fuse.master;
   float* n2 = (bf16 && a.fuse.m && D.d % 256 == 0) ? a.n2_part : nullptr;
-  // Both kernels get one workgroup per item while the grid allows it (see the comment in the sliced kernel).
-  if (sparse_dwdec_sliced(D)) {
+  if (sparse_dwdec_sliced(bf16, D)) {
+    if (bf16) {
+      const int runs = (slice_cols(D.d) + 127) / 128;
+      return runs <= 1 ? launch_sparse_dwdec_mfma<1>(s, D, fl, a, n2, flags) : runs == 2 ? launch_sparse_dwdec_mfma<2>(s, D, fl, a, n2, flags)
+             : runs == 3 ? launch_sparse_dwdec_mfma<3>(s, D, fl, a, n2, flags) : launch_sparse_dwdec_mfma<4>(s, D, fl, a, n2, flags);
+    }
     const size_t per_xcd = ((size_t)(D.L * (D.L + 1) / 2) * ((D.F + 3) / 4) + SD_ITEMS_PER_WG - 1) / SD_ITEMS_PER_WG,
                  gx = (size_t)1 << 27;
     const dim3 grid((unsigned)(8 * (per_xcd < gx ? per_xcd : gx)));
-#define CLT_SDS(T, M)                                                                                              \
-  hipLaunchKernelGGL((sparse_dwdec_sliced_kernel<T, M>), grid, dim3(256), 0, s, D, fl, (const T*)a.d_yhat,         \
-                     (T*)a.W_dec, a.G, a.norms, (T*)a.dW_dec, a.fuse, flags, n2, fl.tok, fl.val)
-    if (bf16) { if (master) CLT_SDS(bf16_t, true); else CLT_SDS(bf16_t, false); }
-    else { if (master) CLT_SDS(float, true); else CLT_SDS(float, false); }
+#define CLT_SDS(M)                                                                                                 \
+  hipLaunchKernelGGL((sparse_dwdec_sliced_kernel<M>), grid, dim3(256), 0, s, D, fl, (const float*)a.d_yhat,        \
+                     (float*)a.W_dec, a.G, a.norms, (float*)a.dW_dec, a.fuse, flags, fl.tok, fl.val)
+    if (master) CLT_SDS(true); else CLT_SDS(false);
 #undef CLT_SDS
     return hipGetLastError();
   }
-  // d not a multiple of 32 (or CLT_SD_ROWS set, for comparison runs): whole rows per workgroup
+  // fp32 with d not a multiple of 32, a batch beyond that reach (or CLT_SD_ROWS set, for comparison runs): whole rows per workgroup
   const size_t items = (size_t)D.L * D.F * ((D.L + SD_TCH - 1) / SD_TCH), gcap = (size_t)1 << 30;
   const dim3 grid((unsigned)(items < gcap ? items : gcap));
 #define CLT_SD(T, M)                                                                                              \

@@ -792,6 +792,43 @@ def test_dz_inside_the_row_kernel_long_feature_lists(dtype):
     show(f"fused dz, long feature lists {dtype}", compare_step(w, g, o, TOL[dtype]))
 
 
+@pytest.mark.parametrize("d,B,rho,master", [(8, 33, 0.3, False), (72, 130, 0.5, True), (136, 66, 0.05, False), (776, 90, 0.3, True),
+                                            (1032, 90, 0.3, False), (2056, 70, 0.3, True), (3080, 40, 0.3, False),
+                                            (4168, 70, 0.95, True)])
+def test_row_kernel_of_dw_dec_slice_widths(d, B, rho, master):
+    """bf16 storage: slices of one run of 8 columns (and empty ones) up to two passes of 512 columns, the last run and the last
+    slice ragged; lists of none to all tokens of the batch, more than one window of 64 among them; dz inside the kernel."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=3, d=d, F=72 if rho < 0.5 else 40, B=B, seed=90, master_weights=master)
+    theta = sparse_theta(w, rho)
+    for fused in (False, True):
+        g, o = run_both(w, theta=theta, decode_mode=GATHER, fused=fused)
+        assert g.decode_switch[2] == 2
+        show(f"row kernel d={d} fused={fused}", compare_step(w, g, o, TOL["bf16"]))
+
+
+def test_row_kernel_of_dw_dec_keeps_infinities_in_their_column():
+    """An infinite target makes one column of a token's d y_hat row infinite: in dW_dec it reaches that column of the features
+    that are active on the token, no other column (of the same run of 8 or elsewhere) and no other feature."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=2, d=136, F=264, B=90, seed=91)
+    theta = sparse_theta(w, 0.1)
+    params = S.make_params(w)
+    x, y = S.make_inputs(w)
+    a = GpuRun(w, params, x, y, theta=theta, decode_mode=GATHER)
+    y = y.clone()
+    lp, b, c = 1, 17, 43
+    y[lp, b, c] = float("inf")
+    g = GpuRun(w, params, x, y, theta=theta, decode_mode=GATHER)
+    assert (a.active == g.active).all() and a.active[:, b].any()
+    for p, l in ((0, 0), (1, 0), (2, 1)):
+        hit = np.zeros(a.grads["W_dec"][p].shape, bool)
+        if p > 0:
+            hit[a.active[l, b] | a.window[l, b], c] = True
+        assert (~np.isfinite(g.grads["W_dec"][p]) == hit).all()
+        ok = ~hit     # the same products and fp32 sums in another order: at most one unit of the stored bf16
+        d_, r_ = np.abs(g.grads["W_dec"][p] - a.grads["W_dec"][p])[ok], np.abs(a.grads["W_dec"][p])[ok]
+        assert (d_ <= 2.0 ** -7 * r_ + 1e-6 * r_.max()).all()
+
+
 def test_sparse_backward_many_layers():
     """More than 8 targets per source: the row kernel walks them in two chunks."""
     w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=11, d=64, F=256, B=48, seed=82)
