@@ -160,8 +160,8 @@ Plan make_plan(const clt_config* c) {
   p.part_sp = o;    o += align_up(L * (size_t)reduce_grid(bf16, dims, c->F).blocks() * 8);
   p.part_dead = o;  o += align_up(L * (size_t)reduce_grid(bf16, dims, c->F).blocks() * 8);
   p.l0 = o;         o += align_up(L * 4);
-  p.flags = o;      o += align_up(4 * 4);
-  p.xcd_sync = o;   o += align_up(8 * 64 * 4);   // pacing counters of the dense decode, one 256-byte line per XCD
+  p.flags = o;      o += align_up(5 * 4);
+  p.xcd_sync = o;   o += align_up(8 * 64 * 4);   // pacing counters of the decode, one 256-byte line per XCD
   // row sums of squares of the updated decoder weights, [P][d / 64][F] (reuse_decoder_norms, eligible shapes only)
   const bool n2 = c->reuse_decoder_norms && c->dtype == CLT_DTYPE_BF16 && F % 256 == 0 && d % 256 == 0;
   // (per block and feature: d / 64 runs in the dense kernel's layout, 8 slots per 2048 columns in the row kernel's)
@@ -550,12 +550,13 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
   if (mode != CLT_DECODE_DENSE) {   // Sec. 3.2: density monitor, then the gather path where it pays
     // (automatic mode with dz taken inside the row kernel of dW_dec: the backward works from the per-feature lists
     //  alone, so a row longer than the per-token lists hold does not stop it)
-    RUN(h, s, K_DECIDE, launch_decode_decide(s, h->D, l0, h->cfg.gather_density_threshold, backward_threshold(&h->cfg),
+    RUN(h, s, K_DECIDE, launch_decode_decide(s, h->bf16, h->D, l0, h->cfg.gather_density_threshold, backward_threshold(&h->cfg),
                                              mode == CLT_DECODE_GATHER,
                                              mode == CLT_DECODE_AUTO && sparse_dwdec_takes_dz(h->bf16, h->D) && h->plan.ecap > 0,
-                                             flags));
+                                             flags, da.xcd_sync));
     RUN(h, s, K_COMPACT, launch_compact_active(s, h->bf16, h->D, z, act_class, gl, flags));
-    RUN(h, s, K_GATHER, launch_gather_decode(s, h->bf16, h->D, gl, W_dec, b_dec, y_hat, flags));
+    RUN(h, s, K_GATHER, launch_gather_decode(s, h->bf16, h->D, gl, W_dec, b_dec, y_hat, flags, da.xcd_sync,
+                                                mode == CLT_DECODE_GATHER ? 1.0 : (double)h->cfg.gather_density_threshold));
   }
   if (mode != CLT_DECODE_GATHER) {
     if (h->bf16) RUN(h, s, K_DEC, launch_dec_bf16(s, h->D, da));

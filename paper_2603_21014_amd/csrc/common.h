@@ -313,17 +313,20 @@ hipError_t launch_mfma_loop(hipStream_t s, int workgroups, int iters, int mode, 
 hipError_t launch_diag_fill(hipStream_t s, void* buf, size_t bytes, int random_data);
 
 // ---- active-feature gather paths (kernels_gather.hip) -------------------------
-// Device-side switch, 4 ints in the workspace:
+// Device-side switch, 5 ints in the workspace:
 //   [0] bit 0: the measured density allows the gather decode (or it is forced); bit 1: it allows the list-driven
 //       backward through the decoder (or it is forced); bit 2: that backward does not need the row lists
 //   [1] longest per-(layer, token) list seen by the compaction (active + window-only entries)
 //   [2] path taken by the last forward: 1 dense, 2 gather
 //   [3] longest per-layer total of the feature lists (see fused_dz_selected)
+//   [4] longest row list with which the gather decode goes through the blocks in step, -1: never (see stepped_decode_selected)
 // The list-driven kernels run only when their bit of flags[0] is set and flags[1] <= kcap; the dense kernels that
 // carry the same flags stand down in exactly that case.
 __host__ __device__ inline bool gather_selected(const int32_t* flags, int kcap) {
   return (flags[0] & 1) != 0 && flags[1] <= kcap;
 }
+// Which of the two gather decodes runs when the lists are used.
+__host__ __device__ inline bool stepped_decode_selected(const int32_t* flags) { return flags[1] <= flags[4]; }
 // The backward through the decoder (dz, dW_dec) has a switch of its own, flags[0] bit 1: its list-driven kernels pay
 // up to a higher density than the gather decode does.
 // Bit 2 says that this backward does not touch the per-(layer, token) lists (dz is taken inside the row kernel of
@@ -338,15 +341,15 @@ __host__ __device__ inline bool lists_backward_selected(const int32_t* flags, in
 // (list_stride(kcap): never a multiple of 4 KB, or the heads of all rows would share one L2 channel).
 struct GatherLists { int32_t* idx; float* val; int32_t* counts; int32_t* counts_w; int kcap; int stride; };
 __host__ __device__ inline int list_stride(int kcap) { return kcap + 32; }
-// flags[0] = (sum l0 <= threshold * L*B*F) or forced; flags[1] = 0
-hipError_t launch_decode_decide(hipStream_t s, Dims D, const int32_t* l0, float density_threshold,
+// flags[0] = (sum l0 <= threshold * L*B*F) or forced; flags[1] = 0; step_ctr: 8 x 64 words, cleared
+hipError_t launch_decode_decide(hipStream_t s, bool bf16, Dims D, const int32_t* l0, float density_threshold,
                                 float backward_density_threshold, int forced, bool backward_without_row_lists,
-                                int32_t* flags);
+                                int32_t* flags, uint32_t* step_ctr);
 hipError_t launch_compact_active(hipStream_t s, bool bf16, Dims D, const void* z, const uint8_t* cls, GatherLists g,
                                  int32_t* flags);
 // y_hat[lp, b, :] = b_dec[lp] + sum_{l<=lp} sum_{active f} z[l,b,f] W_dec[p(l,lp)][f, :]; records the path in flags[2]
 hipError_t launch_gather_decode(hipStream_t s, bool bf16, Dims D, GatherLists g, const void* W_dec,
-                                const float* b_dec, float* y_hat, int32_t* flags);
+                                const float* b_dec, float* y_hat, int32_t* flags, uint32_t* step_ctr, double max_density);
 
 // Sparse backward through the decoder (same switch).
 // dpre := 0, or the dead-feature gradient -(lambda1/B) n where pre < theta and the entry is not listed

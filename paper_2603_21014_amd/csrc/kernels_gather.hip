@@ -31,9 +31,13 @@
 namespace clt {
 namespace {
 
-__global__ void decode_decide_kernel(Dims D, const int32_t* __restrict__ l0, float thr, float thr_bwd, int forced,
-                                     int rows_free, int32_t* __restrict__ flags) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+constexpr double STEP_MIN_REUSE = 6.0;      // tokens per feature, see stepped_gather_decode_kernel
+
+__global__ __launch_bounds__(512) void decode_decide_kernel(Dims D, const int32_t* __restrict__ l0, float thr, float thr_bwd, int forced,
+                                                            int rows_free, int can_step, int32_t* __restrict__ flags,
+                                                            uint32_t* __restrict__ step_ctr) {
+  step_ctr[threadIdx.x] = 0u;      // pacing of the stepped decode: 8 lines of 64 words
+  if (threadIdx.x != 0) return;
   long long tot = 0;
   for (int l = 0; l < D.L; ++l) tot += l0[l];
   const double dens = (double)tot / ((double)D.L * D.B * D.F);
@@ -42,6 +46,7 @@ __global__ void decode_decide_kernel(Dims D, const int32_t* __restrict__ l0, flo
   flags[1] = 0;
   flags[2] = 1;
   flags[3] = 0;
+  flags[4] = can_step && dens * D.B >= STEP_MIN_REUSE ? (int)(4.0 * dens * D.F) + 64 : -1;
 }
 
 // One wavefront per (layer, token) row; lanes take 16 consecutive features per pass (two 8-byte
@@ -189,18 +194,20 @@ __device__ __forceinline__ void gather_rows(float (&acc)[4], const T* __restrict
 }
 
 constexpr int GD_COLS = 256;      // columns per wavefront
+// (four wavefronts, of consecutive tokens, per workgroup: a launch that stands down costs a quarter of the empty workgroups)
 template <typename T>
-__global__ __launch_bounds__(64) void gather_decode_kernel(Dims D, GatherLists g, const T* __restrict__ W_dec,
+__global__ __launch_bounds__(256) void gather_decode_kernel(Dims D, GatherLists g, const T* __restrict__ W_dec,
                                                           const float* __restrict__ b_dec,
                                                           float* __restrict__ y_hat, int32_t* __restrict__ flags) {
-  if (!gather_selected(flags, g.kcap)) return;
-  const int ncs = (D.d + GD_COLS - 1) / GD_COLS;
+  if (!gather_selected(flags, g.kcap) || stepped_decode_selected(flags)) return;
+  const int ncs = (D.d + GD_COLS - 1) / GD_COLS, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cs = (int)(blockIdx.x % ncs);
-  const size_t bt = blockIdx.x / ncs;
+  const size_t bt = (size_t)(blockIdx.x / ncs) * 4 + wv;
+  if (blockIdx.x == 0 && threadIdx.x == 0) flags[2] = 2;
+  if (bt >= (size_t)D.L * D.B) return;
   const int lp = D.L - 1 - (int)(bt / D.B);   // heaviest targets first
   const int b = (int)(bt % D.B);
-  if (blockIdx.x == 0 && threadIdx.x == 0) flags[2] = 2;
-  const int col = cs * GD_COLS + threadIdx.x * 4;
+  const int col = cs * GD_COLS + (threadIdx.x & 63) * 4;
   if (col >= D.d) return;
   float acc[4];
 #pragma unroll
@@ -225,6 +232,188 @@ typedef float f32x4_mfma __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void wave_lds_order() {      // a wave's LDS accesses complete in order; this keeps the compiler to it
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// Streaming accesses of a wavefront to `bytes` bytes from a uniform address on: base and bounds in scalar registers, the lane's
+// 32-bit offset as it is; lanes beyond the end load zeros and store nothing.  (With pointers, base + lane of every array was hoisted
+// out of the item loop, two registers per lane each, and spilled.)
+struct UniformRun {
+  __amdgpu_buffer_rsrc_t d;
+  static constexpr int NT = 2;      // cache policy: non-temporal
+  __device__ __forceinline__ UniformRun(const void* p, int bytes) : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000)) {}
+  __device__ __forceinline__ nt_f32x4 load_f4(uint32_t o) const { return __builtin_bit_cast(nt_f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)o, 0, NT)); }
+  __device__ __forceinline__ nt_u32x2 load8(uint32_t o) const { return __builtin_bit_cast(nt_u32x2, __builtin_amdgcn_raw_buffer_load_b64(d, (int)o, 0, NT)); }
+  __device__ __forceinline__ uint32_t load4(uint32_t o) const { return __builtin_amdgcn_raw_buffer_load_b32(d, (int)o, 0, 0); }
+  __device__ __forceinline__ void store_f4(uint32_t o, nt_f32x4 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((__vector_size__(16))) unsigned int, v), d, (int)o, 0, NT);
+  }
+  __device__ __forceinline__ void store8(uint32_t o, nt_u32x2 v, int policy) const {
+    const __attribute__((__vector_size__(8))) unsigned int t = {v[0], v[1]};
+    if (policy) __builtin_amdgcn_raw_buffer_store_b64(t, d, (int)o, 0, NT); else __builtin_amdgcn_raw_buffer_store_b64(t, d, (int)o, 0, 0);
+  }
+  __device__ __forceinline__ void store4(uint32_t o, uint32_t v) const { __builtin_amdgcn_raw_buffer_store_b32(v, d, (int)o, 0, 0); }
+};
+
+// The decode of a batch whose features are active on several tokens each, bf16 storage: all tokens of the batch go through the
+// (source, target) blocks in step, so that a block's rows come out of the L2 from the second token on.
+// An XCD works on one target and 128 columns at a time: the slice of a block is F x 256 bytes (2 MB at F = 8192, half of its L2), all
+// 4096 tokens of a batch are spread over its wavefronts and keep their sums in LDS across the sources.  At every source the
+// workgroup books itself on its XCD's counter and waits, for a bounded time, until all of the XCD have begun the source before:
+// a pacing aid that no result depends on.  (The counter is only touched from one XCD, in its L2; an atomic that has to be seen by
+// the whole device takes ten times as long here.)  The sums are taken as in the row kernel of dW_dec below: four entries and 128
+// columns per load and MFMA.
+// What bounds it: a step takes about 7 us for the pacing, the latency of lists and rows and the 2 MB per XCD that come from memory, the
+// entries come on top at 20 to 25 TB/s of rows.  L = 16, d = 2048, F = 8192, 4096 tokens, against the kernel above: 4 active
+// features per token 1.19 -> 2.37 ms, 16: 4.2 -> 3.1, 32: 8.3 -> 4.9; L = 12, d = 768, F = 6144: 6: 0.42 -> 0.51, 12: 0.83 -> 0.56;
+// 1024 tokens (a fourth of the reuse): 0.22 -> 0.28; long-tailed lists (25 on average, 300 at most): 2.36 -> 2.59, one wavefront
+// holds up its XCD; 72 MB of decoder in all (9 per XCD, L = 5, d = 776, F = 3080, 3001 tokens): forward and loss 388 -> 414 us, 226 MB: 1962 ->
+// 1824.  Hence the rule: STEP_MIN_REUSE tokens per feature, no list longer than four times the mean + 64, a slice that fits half an
+// L2 and a decoder of several L2s.
+constexpr int SGD_WAVES = 16, SGD_WGS = 64, SGD_TPW = 4;      // wavefronts per workgroup, workgroups per XCD, tokens per wavefront
+constexpr int SGD_TOKENS = SGD_TPW * SGD_WAVES;
+__global__ __launch_bounds__(64 * SGD_WAVES, 8) void stepped_gather_decode_kernel(
+    Dims D, int kcap, int stride, const int32_t* __restrict__ counts, const int32_t* __restrict__ idx, const float* __restrict__ val,
+    const bf16_t* __restrict__ W_dec, const float* __restrict__ b_dec, float* __restrict__ y_hat, int32_t* __restrict__ flags,
+    uint32_t* __restrict__ ctr0, int nw) {
+  if (!gather_selected(flags, kcap) || !stepped_decode_selected(flags)) return;
+  __shared__ __align__(16) float acc_s[SGD_TOKENS][128];
+  __shared__ __align__(16) nt_u32x2 win_s[SGD_WAVES][64];
+  if (blockIdx.x == 0 && threadIdx.x == 0) flags[2] = 2;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = lane >> 4, i16 = lane & 15;
+  const int xcd = blockIdx.x & 7, wg = blockIdx.x >> 3;
+  const uint32_t half = i16 >= 8 ? 0u : (i16 & 1) ? 0xffff0000u : 0x0000ffffu;
+  nt_u32x2* const win = win_s[wv];
+  const int ns = (D.d + 127) / 128, units = D.L * ns;
+  const uint32_t row_bytes = (uint32_t)D.d * 2;
+  const int per_batch = nw * SGD_TOKENS;
+  uint32_t step = 0;
+  bool pace = true;
+  uint32_t* const ctr = ctr0 + xcd * 64;
+  for (int r = 0; r * 8 < units; ++r) {
+    const int u = r * 8 + ((r & 1) ? 7 - xcd : xcd);
+    if (u >= units) continue;
+    const int lp = D.L - 1 - u / ns, c0 = (u % ns) * 128;
+    const uint32_t voff = c0 + i16 * 8 < D.d ? (uint32_t)(c0 + i16 * 8) * 2u : 0x7ffffff0u;
+    for (int tb = 0; tb < D.B; tb += per_batch) {
+      const int t0 = tb + wv * nw + wg;      // the wavefront's tokens: t0, t0 + SGD_WAVES * nw, ...
+      int cn[SGD_TPW];
+#pragma unroll
+      for (int i = 0; i < SGD_TPW; ++i) {
+        *reinterpret_cast<float2*>(&acc_s[wv * SGD_TPW + i][lane * 2]) = make_float2(0.f, 0.f);
+        const int t = t0 + i * SGD_WAVES * nw;
+        cn[i] = counts[t < D.B ? t : 0];
+        if (t >= D.B) cn[i] = 0;
+      }
+      uint32_t fn = UniformRun(idx + (size_t)t0 * stride, cn[0] * 4).load4(lane * 4u), zn = UniformRun(val + (size_t)t0 * stride, cn[0] * 4).load4(lane * 4u);
+      for (int l = 0; l <= lp; ++l) {
+        int cc[SGD_TPW];
+        const int ln = l < lp ? l + 1 : l;
+#pragma unroll
+        for (int i = 0; i < SGD_TPW; ++i) {
+          cc[i] = cn[i];
+          const int t = t0 + i * SGD_WAVES * nw;
+          cn[i] = counts[(size_t)ln * D.B + (t < D.B ? t : 0)];
+          if (t >= D.B) cn[i] = 0;
+        }
+        {
+          ++step;
+          __syncthreads();
+          if (threadIdx.x == 0) {
+            uint32_t seen = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + 1u;
+            const uint32_t want = (step - 1u) * (uint32_t)nw;      // (the count in the low 20 bits; the polls go into the rest)
+#pragma unroll 1
+            for (int spin = 0; pace && (int)((seen - want) << 12) < 0; ++spin) {
+              __builtin_amdgcn_s_sleep(2);
+              seen = __hip_atomic_fetch_add(ctr, 1u << 20, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              pace = spin < 400;      // (after one wait in vain -- fewer CUs, another partition -- none any more)
+            }
+          }
+          __syncthreads();
+        }
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<bf16_t*>(W_dec + (size_t)packed_index(l, lp, D.L) * D.F * D.d), 0, (int)((size_t)D.F * D.d * 2), 0x00020000);
+#pragma unroll
+        for (int i = 0; i < SGD_TPW; ++i) {
+          const size_t row = (size_t)l * D.B + (t0 + i * SGD_WAVES * nw);
+          const uint32_t f0 = fn, z0 = zn;
+          {
+            const size_t next = i + 1 < SGD_TPW ? row + SGD_WAVES * nw : (size_t)ln * D.B + t0;
+            const int cnext = i + 1 < SGD_TPW ? cc[i + 1 < SGD_TPW ? i + 1 : 0] : cn[0];
+            fn = UniformRun(idx + next * stride, cnext * 4).load4(lane * 4u);
+            zn = UniformRun(val + next * stride, cnext * 4).load4(lane * 4u);
+          }
+          const int cnt = cc[i];
+          if (cnt == 0) continue;
+          f32x4_mfma acc = {0.f, 0.f, 0.f, 0.f};
+          float* const as = &acc_s[wv * SGD_TPW + i][(4 * grp) * 8 + (i16 & 7)];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[k] = as[8 * k];
+          uint32_t f = f0, zb = z0;
+#pragma unroll 1
+          for (int w0 = 0; w0 < cnt; w0 += 64) {
+            const int n = __builtin_amdgcn_readfirstlane(min(64, cnt - w0));
+            if (w0 > 0) {
+              f = UniformRun(idx + row * stride + w0, n * 4).load4(lane * 4u);
+              zb = UniformRun(val + row * stride + w0, n * 4).load4(lane * 4u);
+            }
+            wave_lds_order();
+            win[lane] = nt_u32x2{lane < n ? f * row_bytes : 0x80000000u, __builtin_amdgcn_perm(zb, zb, 0x07060706u)};
+            wave_lds_order();
+#pragma unroll 1
+            for (int j = 0; j < n; j += 16) {
+              nt_u32x2 en[4];
+              u32x4_lds q[4];
+#pragma unroll
+              for (int s4 = 0; s4 < 4; ++s4) en[s4] = win[j + 4 * s4 + grp];
+#pragma unroll
+              for (int s4 = 0; s4 < 4; ++s4)
+                q[s4] = __builtin_bit_cast(u32x4_lds, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(en[s4][0] + voff), 0, 0));
+#pragma unroll
+              for (int s4 = 0; s4 < 4; ++s4) {
+                const uint32_t zs = en[s4][1] & half;
+                const u32x4_lds zd = {(i16 >> 1) == 0 ? zs : 0u, (i16 >> 1) == 1 ? zs : 0u, (i16 >> 1) == 2 ? zs : 0u, (i16 >> 1) == 3 ? zs : 0u};
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_mfma, q[s4]), __builtin_bit_cast(bf16x8_mfma, zd), acc, 0, 0, 0);
+              }
+            }
+          }
+          wave_lds_order();
+          if (i16 < 8) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) as[8 * k] = acc[k];
+          }
+          wave_lds_order();
+        }
+      }
+      wave_lds_order();
+      const int col = c0 + lane * 2;
+      if (col < D.d) {
+        const float2 b = *reinterpret_cast<const float2*>(b_dec + (size_t)lp * D.d + col);
+#pragma unroll
+        for (int i = 0; i < SGD_TPW; ++i) {
+          const int t = t0 + i * SGD_WAVES * nw;
+          if (t >= D.B) break;
+          float2 a = *reinterpret_cast<const float2*>(&acc_s[wv * SGD_TPW + i][lane * 2]);
+          // (an infinity or a NaN in one weight reaches the sums of the other seven columns of its run through the zeros beside
+          //  z: where a sum is not finite the token's columns are summed up one by one)
+          if (__builtin_amdgcn_ballot_w64(!(fabsf(a.x) + fabsf(a.y) < __builtin_inff()))) {
+            a = make_float2(0.f, 0.f);
+            for (int l = 0; l <= lp; ++l) {
+              const size_t row = (size_t)l * D.B + t;
+              const bf16_t* w = W_dec + (size_t)packed_index(l, lp, D.L) * D.F * D.d + col;
+              for (int e = 0; e < counts[row]; ++e) {
+                const uint32_t w2 = *reinterpret_cast<const uint32_t*>(w + (size_t)idx[row * stride + e] * D.d);
+                const float z = val[row * stride + e];
+                a = make_float2(fmaf(z, __uint_as_float(w2 << 16), a.x), fmaf(z, __uint_as_float(w2 & 0xffff0000u), a.y));
+              }
+            }
+          }
+          *reinterpret_cast<float2*>(y_hat + ((size_t)lp * D.B + t) * D.d + col) = make_float2(a.x + b.x, a.y + b.y);
+        }
+      }
+      wave_lds_order();
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -939,26 +1128,6 @@ __global__ __launch_bounds__(256, MASTER ? 5 : 6) void sparse_dwdec_sliced_kerne
 // columns of a slice: an eighth of d, whole runs of 8
 __host__ __device__ inline int slice_cols(int d) { return (d + 63) / 64 * 8; }
 
-// Streaming accesses of a wavefront to `bytes` bytes from a uniform address on: base and bounds in scalar registers, the lane's
-// 32-bit offset as it is; lanes beyond the end load zeros and store nothing.  (With pointers, base + lane of every array was hoisted
-// out of the item loop, two registers per lane each, and spilled.)
-struct UniformRun {
-  __amdgpu_buffer_rsrc_t d;
-  static constexpr int NT = 2;      // cache policy: non-temporal
-  __device__ __forceinline__ UniformRun(const void* p, int bytes) : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000)) {}
-  __device__ __forceinline__ nt_f32x4 load_f4(uint32_t o) const { return __builtin_bit_cast(nt_f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)o, 0, NT)); }
-  __device__ __forceinline__ nt_u32x2 load8(uint32_t o) const { return __builtin_bit_cast(nt_u32x2, __builtin_amdgcn_raw_buffer_load_b64(d, (int)o, 0, NT)); }
-  __device__ __forceinline__ uint32_t load4(uint32_t o) const { return __builtin_amdgcn_raw_buffer_load_b32(d, (int)o, 0, 0); }
-  __device__ __forceinline__ void store_f4(uint32_t o, nt_f32x4 v) const {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(__attribute__((__vector_size__(16))) unsigned int, v), d, (int)o, 0, NT);
-  }
-  __device__ __forceinline__ void store8(uint32_t o, nt_u32x2 v, int policy) const {
-    const __attribute__((__vector_size__(8))) unsigned int t = {v[0], v[1]};
-    if (policy) __builtin_amdgcn_raw_buffer_store_b64(t, d, (int)o, 0, NT); else __builtin_amdgcn_raw_buffer_store_b64(t, d, (int)o, 0, 0);
-  }
-  __device__ __forceinline__ void store4(uint32_t o, uint32_t v) const { __builtin_amdgcn_raw_buffer_store_b32(v, d, (int)o, 0, 0); }
-};
-
 // bf16 storage.  What bounds it: the bytes that come back through the vector caches, state and gathered rows added up (a wavefront's
 // loads return in order, so rows that wait in the L2 do not overtake state on its way from HBM), and below a few tokens per
 // feature the state alone at 6 TB/s.  Hence 16 bytes per lane and load for the rows (rows that lie in the L2 come at 18 TB/s with 8 bytes
@@ -1228,11 +1397,19 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
 
 }  // namespace
 
-hipError_t launch_decode_decide(hipStream_t s, Dims D, const int32_t* l0, float density_threshold,
+// Whether the decode may go in step: what the host knows of the rule at stepped_gather_decode_kernel (max_density: up to which the
+// lists are used at all)
+static bool stepped_decode_possible(bool bf16, Dims D, double max_density) {
+  return bf16 && D.F <= 8192 && D.B * max_density >= STEP_MIN_REUSE && (double)D.P() * D.F * D.d * 2.0 >= 128e6 &&
+         (size_t)D.F * D.d * 2 < ((size_t)1 << 31);
+}
+
+hipError_t launch_decode_decide(hipStream_t s, bool bf16, Dims D, const int32_t* l0, float density_threshold,
                                 float backward_density_threshold, int forced, bool backward_without_row_lists,
-                                int32_t* flags) {
-  hipLaunchKernelGGL(decode_decide_kernel, dim3(1), dim3(64), 0, s, D, l0, density_threshold,
-                     backward_density_threshold, forced, backward_without_row_lists ? 1 : 0, flags);
+                                int32_t* flags, uint32_t* step_ctr) {
+  hipLaunchKernelGGL(decode_decide_kernel, dim3(1), dim3(512), 0, s, D, l0, density_threshold,
+                     backward_density_threshold, forced, backward_without_row_lists ? 1 : 0,
+                     stepped_decode_possible(bf16, D, forced ? 1.0 : (double)density_threshold) ? 1 : 0, flags, step_ctr);
   return hipGetLastError();
 }
 
@@ -1248,15 +1425,19 @@ hipError_t launch_compact_active(hipStream_t s, bool bf16, Dims D, const void* z
 }
 
 hipError_t launch_gather_decode(hipStream_t s, bool bf16, Dims D, GatherLists g, const void* W_dec,
-                                const float* b_dec, float* y_hat, int32_t* flags) {
+                                const float* b_dec, float* y_hat, int32_t* flags, uint32_t* step_ctr, double max_density) {
   const size_t ncs = ((size_t)D.d + GD_COLS - 1) / GD_COLS;
-  const dim3 grid((unsigned)((size_t)D.L * D.B * ncs));
+  const dim3 grid((unsigned)(((size_t)D.L * D.B + 3) / 4 * ncs));
   if (bf16)
-    hipLaunchKernelGGL((gather_decode_kernel<bf16_t>), grid, dim3(64), 0, s, D, g, (const bf16_t*)W_dec, b_dec, y_hat,
+    hipLaunchKernelGGL((gather_decode_kernel<bf16_t>), grid, dim3(256), 0, s, D, g, (const bf16_t*)W_dec, b_dec, y_hat,
                        flags);
   else
-    hipLaunchKernelGGL((gather_decode_kernel<float>), grid, dim3(64), 0, s, D, g, (const float*)W_dec, b_dec, y_hat,
+    hipLaunchKernelGGL((gather_decode_kernel<float>), grid, dim3(256), 0, s, D, g, (const float*)W_dec, b_dec, y_hat,
                        flags);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !stepped_decode_possible(bf16, D, max_density)) return e;
+  hipLaunchKernelGGL(stepped_gather_decode_kernel, dim3(8 * SGD_WGS), dim3(64 * SGD_WAVES), 0, s, D, g.kcap, g.stride, g.counts,
+                     g.idx, g.val, (const bf16_t*)W_dec, b_dec, y_hat, flags, step_ctr, SGD_WGS);
   return hipGetLastError();
 }
 

@@ -670,6 +670,42 @@ def test_gather_wide_model_dim_and_empty_rows():
         assert (g.y_hat[lp] == params["b_dec"][lp].numpy()[None, :]).all()
 
 
+@pytest.mark.parametrize("L,d,F,B,rho", [(12, 136, 6144, 70, 0.15), (5, 520, 8192, 4100, 0.002), (3, 1288, 8192, 300, 0.03)])
+def test_stepped_gather_decode(L, d, F, B, rho):
+    """The gather decode that goes through the (source, target) blocks in step (decoders of several L2s, features active on
+    several tokens): a last column slice of 8 columns, lists of several windows of 64, more tokens than one pass holds; against
+    sums over the listed entries in 64 bits (fp32 sums of about rho F L products: 1e-6), twice the same bits, and an infinite weight
+    that reaches only its column of the tokens that list its feature."""
+    from paper_2603_21014_amd import binding as K
+    g = torch.Generator(device="cuda").manual_seed(5)
+    P, T = L * (L + 1) // 2, torch.bfloat16
+    par = {"W_enc": (torch.randn(L, d, F, generator=g, device="cuda") / d ** 0.5).to(T), "b_enc": torch.zeros(L, F, device="cuda"),
+           "W_dec": (torch.randn(P, F, d, generator=g, device="cuda") / d ** 0.5).to(T), "b_dec": torch.randn(L, d, generator=g, device="cuda")}
+    x = torch.randn(L, B, d, generator=g, device="cuda").to(T)
+    par["theta"] = theta_for_density(x.float(), par["W_enc"].float(), par["b_enc"], rho).cuda()
+    st = K.CLTStep(L, d, F, B, dtype="bf16", decode_mode=GATHER, matrix_grads=False)
+    st.forward(x, par)
+    flags = K.clt_workspace_view(st.H, "decode_switch")
+    z, first = st.z.clone(), st.y_hat.clone()
+    assert flags[2] == 2 and (z != 0).sum() / (L * F) >= 6 and flags[1] <= 4 * (z != 0).sum() / (L * B) + 64
+    want = par["b_dec"].double()[:, None, :].repeat(1, B, 1)
+    p = 0
+    for l in range(L):
+        for lp in range(l, L):
+            want[lp] += z[l].double() @ par["W_dec"][p].double()
+            p += 1
+    assert ((first.double() - want).norm() / want.norm()).item() < 1e-6
+    st.forward(x, par)
+    assert torch.equal(st.y_hat, first)
+    f, c = int((z[0] != 0).sum(0).argmax()), d - 3
+    par["W_dec"][1, f, c] = float("inf")      # block (0, 1)
+    st.forward(x, par)
+    hit = torch.zeros_like(first, dtype=torch.bool)
+    hit[1, :, c] = z[0][:, f] != 0
+    assert hit.any() and torch.equal(~torch.isfinite(st.y_hat), hit)
+    assert (st.y_hat - first)[~hit].abs().max() < 1e-5 * first.abs().max()
+
+
 def test_gather_dz_lds_chunks_and_fallback(monkeypatch):
     """Backward through the lists when a token's d y_hat rows exceed 64 KB of LDS (fp32, d=2048: eight targets per
     chunk, nine targets from layer 0, so a second chunk of one), and the one-wave-per-entry kernel, which otherwise
