@@ -23,7 +23,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
-  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part, row_squares,
+  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_bdec, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part, row_squares,
          fl_off, fl_cnt, fl_tok, fl_val, fl_seg, total;
   int kcap;
   int ecap;
@@ -43,13 +43,13 @@ void set_err(char* dst, const char* fmt, ...) {
 }  // namespace
 
 enum KernelId {
-  K_NORMS, K_ENC, K_DEC, K_LOSS_SP, K_LOSS_REC, K_LOSS_FINAL, K_COLRED, K_DZ, K_STE, K_DWENC, K_DWDEC,
+  K_NORMS, K_ENC, K_DEC, K_LOSS, K_LOSS_FINISH, K_VECTORS, K_DZ, K_STE, K_DWENC, K_DWDEC,
   K_ADAM_WDEC, K_ADAM_WENC, K_ADAM_VEC, K_ZERO, K_DECIDE, K_COMPACT, K_GATHER, K_SP_FILL, K_GATHER_DZ, K_FLISTS,
   K_SP_DWDEC, K_TOPK, K_NORM_SUM, K_NORMALISE, K_NORMS_REUSE, K_COUNT
 };
 static const char* const kKernelNames[K_COUNT] = {
-  "decoder_norms", "encoder_jumprelu_gemm", "decode_gemm", "loss_sparsity", "loss_reconstruction", "loss_final",
-  "column_reduce", "dz_gemm", "ste_reduce", "dW_enc_gemm", "dW_dec_gemm", "adam_W_dec", "adam_W_enc",
+  "decoder_norms", "encoder_jumprelu_gemm", "decode_gemm", "losses", "loss_finish",
+  "vector_gradients", "dz_gemm", "ste_reduce", "dW_enc_gemm", "dW_dec_gemm", "adam_W_dec", "adam_W_enc",
   "adam_vectors", "zero_counters", "decode_decide", "compact_active", "gather_decode", "sparse_dpre_fill",
   "gather_dz", "feature_lists", "sparse_dW_dec", "topk_select", "activation_norm_sum", "normalise_activations",
   "decoder_norms_from_update"};
@@ -145,16 +145,16 @@ Plan make_plan(const clt_config* c) {
   // row blocks of the column-partial arrays: at most 32-row blocks of the reduction kernels, or the half tiles of
   // the dz epilogue that folds the straight-through reductions in (whichever is more)
   const size_t rbs = std::max(row_blocks(c->B), fold_row_blocks(dims));
-  const size_t wide = F > d ? F : d;
   Plan p;
   size_t o = 0;
   p.norms = o;      o += align_up(L * F * 4);
   p.G = o;          o += align_up(L * F * 4);
   p.d_yhat = o;     o += align_up(L * B * d * esz);
   p.dpre = o;       o += align_up(L * B * F * esz);
-  p.part_cols = o;  o += align_up(rbs * L * wide * 4);
+  p.part_cols = o;  o += align_up(rbs * L * F * 4);
   p.part_cols2 = o; o += align_up(rbs * L * F * 4);
   p.part_cols3 = o; o += align_up(rbs * L * F * 4);
+  p.part_bdec = o;  o += align_up(L * (size_t)reduce_grid(bf16, dims, c->d).rbs * d * 4);
   // (part_rec also holds the L * row_blocks(B) partial sums of clt_norm_accumulate)
   p.part_rec = o;   o += align_up(L * std::max<size_t>(reduce_grid(bf16, dims, c->d).blocks(), row_blocks(c->B)) * 8);
   p.part_sp = o;    o += align_up(L * (size_t)reduce_grid(bf16, dims, c->F).blocks() * 8);
@@ -525,14 +525,15 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
   DecArgs da{z, W_dec, b_dec, y_hat, mode == CLT_DECODE_AUTO ? flags : nullptr, h->plan.kcap,
              reinterpret_cast<uint32_t*>(h->ws + h->plan.xcd_sync), h->plan.split,
              reinterpret_cast<float*>(h->ws + h->plan.split_part)};
-  RUN(h, s, K_ZERO, launch_zero_i32(s, l0, h->D.L));
+  // (the encoder's counters are cleared by the kernel that forms the norms, where one runs before the encoder)
   if (h->n2_for && h->n2_for == W_dec)   // the last fused update left the sums of squares of exactly these weights
     RUN(h, s, K_NORMS_REUSE, launch_norms_from_partials(s, h->D, reinterpret_cast<const float*>(h->ws + h->plan.n2_part), h->D.d / 64, norms,
-                                                            h->cfg.decode_mode == CLT_DECODE_DENSE ? nullptr : flags, h->plan.kcap));
-  else if (h->plan.row_squares_on)   // few tokens: the decode below reads every weight once and takes the squares along
+                                                            h->cfg.decode_mode == CLT_DECODE_DENSE ? nullptr : flags, h->plan.kcap, l0));
+  else if (h->plan.row_squares_on) {   // few tokens: the decode below reads every weight once and takes the squares along
+    RUN(h, s, K_ZERO, launch_zero_i32(s, l0, h->D.L));
     da.row_squares = reinterpret_cast<float*>(h->ws + h->plan.row_squares);
-  else
-    RUN(h, s, K_NORMS, launch_decoder_norms(s, h->bf16, h->D, W_dec, norms));
+  } else
+    RUN(h, s, K_NORMS, launch_decoder_norms(s, h->bf16, h->D, W_dec, norms, l0));
   h->n2_for = nullptr;
   const bool topk = h->cfg.activation == CLT_ACT_TOPK;
   float* pre32 = topk ? reinterpret_cast<float*>(h->ws + h->plan.pre32) : nullptr;
@@ -563,7 +564,7 @@ int clt_forward(clt_handle* h, void* stream, const void* x, const float* x_scale
     else RUN(h, s, K_DEC, launch_dec_f32(s, h->D, da));
   }
   if (da.row_squares)
-    RUN(h, s, K_NORMS, launch_norms_from_partials(s, h->D, da.row_squares, 2 * ((h->D.d + 255) / 256), norms, nullptr, 0));
+    RUN(h, s, K_NORMS, launch_norms_from_partials(s, h->D, da.row_squares, 2 * ((h->D.d + 255) / 256), norms, nullptr, 0, nullptr));
   h->stage = 1;
   return CLT_OK;
 }
@@ -595,16 +596,11 @@ int clt_loss(clt_handle* h, void* stream, const void* y, const float* y_scale, c
   double* pdead = reinterpret_cast<double*>(h->ws + h->plan.part_dead);
   void* d_yhat = h->ws + h->plan.d_yhat;
   h->stage = 1;
-  // sparsity (and dead-feature) terms first: their column partials are folded into G
-  // before the same partial buffer is reused for the db_dec partials of the reconstruction pass
-  RUN(h, s, K_LOSS_SP, launch_loss_sparsity(s, h->bf16, D, z, norms, h->cfg.C, psp, part, dead ? pre : nullptr, theta,
-                                            h->cfg.log_threshold != 0, pdead, part2));
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part, rgf.rbs, D.L * D.F, lambda0 / (float)D.B, G));
-  if (dead)
-    RUN(h, s, K_COLRED, launch_col_reduce(s, part2, rgf.rbs, D.L * D.F, lambda1 / (float)D.B, G, true));
-  RUN(h, s, K_LOSS_REC, launch_loss_rec(s, h->bf16, h->int8, D, y_hat, y, y_scale, d_yhat, prec, part));
-  RUN(h, s, K_LOSS_FINAL, launch_loss_final(s, prec, rgd.blocks() * D.L, psp, rgf.blocks() * D.L, dead ? pdead : nullptr,
-                                            1.0f / (float)D.B, lambda0, lambda1, loss_dev));
+  float* rec_cols = reinterpret_cast<float*>(h->ws + h->plan.part_bdec);
+  RUN(h, s, K_LOSS, launch_loss(s, h->bf16, h->int8, D, z, norms, h->cfg.C, dead ? pre : nullptr, theta, h->cfg.log_threshold != 0, psp,
+                                part, pdead, part2, y_hat, y, y_scale, d_yhat, prec, rec_cols));
+  RUN(h, s, K_LOSS_FINISH, launch_loss_finish(s, D, prec, rgd.blocks() * D.L, psp, rgf.blocks() * D.L, dead ? pdead : nullptr,
+                                              1.0f / (float)D.B, lambda0, lambda1, loss_dev, part, part2, rgf.rbs, G));
   h->lambda0 = lambda0;
   h->lambda1 = lambda1;
   h->stage = 2;
@@ -621,7 +617,7 @@ int clt_loss(clt_handle* h, void* stream, const void* y, const float* y_scale, c
 static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const float* x_scale, const float* theta,
                          void* W_dec, void* W_enc, const void* z, const uint8_t* act_class, void* gW_enc,
                          float* gb_enc, float* gtheta, void* gW_dec, float* gb_dec, const AdamFuseArgs& fenc,
-                         const AdamFuseArgs& fdec) {
+                         const AdamFuseArgs& fdec, const VectorAdam& vth, const VectorAdam& vb_enc, const VectorAdam& vb_dec) {
   const Dims D = h->D;
   const int rbs = reduce_grid(h->bf16, D, D.F).rbs;
   float* norms = reinterpret_cast<float*>(h->ws + h->plan.norms);
@@ -633,8 +629,6 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   void* dpre = h->ws + h->plan.dpre;
   const float lam1_over_b = h->lambda1 / (float)D.B;
 
-  // db_dec from the column partials that clt_loss left behind
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part, reduce_grid(h->bf16, D, D.d).rbs, D.L * D.d, 1.0f, gb_dec));
   // Backward through the decoder: dense GEMMs, or the gather kernels on the lists of the forward
   // pass when the device-side switch selected them (AUTO enqueues both; the one not selected
   // returns at once).
@@ -683,12 +677,11 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   if (!fold || mode == CLT_DECODE_AUTO)
     RUN(h, s, K_STE, launch_ste_reduce(s, h->bf16, D, dpre, act_class, h->int8 ? x_scale : nullptr, norms, lam1_over_b,
                                        part, part2, part3, fold ? flags : nullptr, kcap));
-  if (h->cfg.activation == CLT_ACT_TOPK)     // no threshold: the window partials are all zero, and so is the gradient
-    RUN(h, s, K_COLRED, launch_col_reduce(s, part, nparts, D.L * D.F, 1.0f, gtheta, false, psw));
-  else
-    RUN(h, s, K_COLRED, launch_dtheta_final(s, part, part3, nparts, D.L * D.F, theta, h->cfg.log_threshold != 0, norms,
-                                            1.0f / h->cfg.ste_bandwidth, lam1_over_b, gtheta, psw));
-  RUN(h, s, K_COLRED, launch_col_reduce(s, part2, nparts, D.L * D.F, 1.0f, gb_enc, false, psw));
+  // (db_dec from the column partials that clt_loss left behind)
+  RUN(h, s, K_VECTORS, launch_vector_gradients(s, VectorGradArgs{
+      part, part3, part2, nparts, psw, D.L * D.F, reinterpret_cast<const float*>(h->ws + h->plan.part_bdec),
+      reduce_grid(h->bf16, D, D.d).rbs, D.L * D.d, theta, h->cfg.log_threshold != 0, h->cfg.activation == CLT_ACT_TOPK, norms,
+      1.0f / h->cfg.ste_bandwidth, lam1_over_b, gtheta, gb_enc, gb_dec, vth, vb_enc, vb_dec, fdec.a}));
   if (h->bf16) RUN(h, s, K_DWENC, launch_dwenc_bf16(s, D, ea, h->int8));
   else RUN(h, s, K_DWENC, launch_dwenc_f32(s, D, ea));
   if (mode != CLT_DECODE_GATHER) {
@@ -720,7 +713,8 @@ int clt_backward(clt_handle* h, void* stream, const void* x, const float* x_scal
   if (h->stage < 2) { set_err(h->err, "clt_backward: call clt_forward and clt_loss first"); return CLT_ERR_STATE; }
   const AdamFuseArgs none{nullptr, nullptr, nullptr, AdamScalars{}};
   return backward_impl(h, static_cast<hipStream_t>(stream), x, x_scale, theta, const_cast<void*>(W_dec), nullptr, z,
-                       act_class, grads->W_enc, grads->b_enc, grads->theta, grads->W_dec, grads->b_dec, none, none);
+                       act_class, grads->W_enc, grads->b_enc, grads->theta, grads->W_dec, grads->b_dec, none, none, VectorAdam{},
+                       VectorAdam{}, VectorAdam{});
 }
 
 int clt_backward_adam_step(clt_handle* h, void* stream, const void* x, const float* x_scale, const void* z,
@@ -754,20 +748,17 @@ int clt_backward_adam_step(clt_handle* h, void* stream, const void* x, const flo
   }
   if (h->stage < 2) { set_err(h->err, "clt_backward_adam_step: call clt_forward and clt_loss first"); return CLT_ERR_STATE; }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const Dims D = h->D;
   const AdamScalars a = adam_scalars(h, t, lr);
   const AdamFuseArgs fenc{(float*)m->W_enc, (float*)v->W_enc, master ? (float*)master->W_enc : nullptr, a};
   const AdamFuseArgs fdec{(float*)m->W_dec, (float*)v->W_dec, master ? (float*)master->W_dec : nullptr, a};
   h->n2_for = nullptr;
   rc = backward_impl(h, s, x, x_scale, params->theta, params->W_dec, params->W_enc, z, act_class, grads->W_enc,
-                     grads->b_enc, grads->theta, grads->W_dec, grads->b_dec, fenc, fdec);
+                     grads->b_enc, grads->theta, grads->W_dec, grads->b_dec, fenc, fdec, VectorAdam{params->theta, m->theta, v->theta},
+                     VectorAdam{params->b_enc, m->b_enc, v->b_enc}, VectorAdam{params->b_dec, m->b_dec, v->b_dec});
   if (rc != CLT_OK) return rc;
   // the weight-gradient kernel that ran (dense GEMM or row kernel) has updated W_dec and left the row sums of
   // squares of the new weights
   if (h->n2_eligible) h->n2_for = params->W_dec;
-  RUN(h, s, K_ADAM_VEC, launch_adam_vector(s, (size_t)D.L * D.F, params->b_enc, grads->b_enc, m->b_enc, v->b_enc, a));
-  RUN(h, s, K_ADAM_VEC, launch_adam_vector(s, (size_t)D.L * D.F, params->theta, grads->theta, m->theta, v->theta, a));
-  RUN(h, s, K_ADAM_VEC, launch_adam_vector(s, (size_t)D.L * D.d, params->b_dec, grads->b_dec, m->b_dec, v->b_dec, a));
   return CLT_OK;
 }
 
@@ -796,9 +787,9 @@ int clt_adam_step(clt_handle* h, void* stream, int64_t t, float lr, const clt_te
                                master ? (float*)master->W_dec : nullptr, a));
   RUN(h, s, K_ADAM_WENC, launch_adam_matrix(s, h->bf16, n_enc, params->W_enc, grads->W_enc, (float*)m->W_enc, (float*)v->W_enc,
                                master ? (float*)master->W_enc : nullptr, a));
-  RUN(h, s, K_ADAM_VEC, launch_adam_vector(s, (size_t)D.L * D.F, params->b_enc, grads->b_enc, m->b_enc, v->b_enc, a));
-  RUN(h, s, K_ADAM_VEC, launch_adam_vector(s, (size_t)D.L * D.F, params->theta, grads->theta, m->theta, v->theta, a));
-  RUN(h, s, K_ADAM_VEC, launch_adam_vector(s, (size_t)D.L * D.d, params->b_dec, grads->b_dec, m->b_dec, v->b_dec, a));
+  RUN(h, s, K_ADAM_VEC, launch_adam_vectors(s, AdamVectors{{D.L * D.F, D.L * D.F, D.L * D.d},
+      {params->b_enc, params->theta, params->b_dec}, {grads->b_enc, grads->theta, grads->b_dec},
+      {m->b_enc, m->theta, m->b_dec}, {v->b_enc, v->theta, v->b_dec}}, a));
   return CLT_OK;
 }
 

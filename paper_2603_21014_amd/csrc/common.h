@@ -256,37 +256,39 @@ hipError_t launch_topk_select(hipStream_t s, bool bf16, Dims D, const float* pre
 // dense decode (skip_flags).
 hipError_t launch_decode_combine(hipStream_t s, Dims D, DecSplit sp, const float* part, const float* b_dec, float* y_hat,
                                  const int32_t* skip_flags, int kcap);
-hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_dec, float* norms);
+// (l0: the encoder's L counters, cleared along the way, or NULL)
+hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_dec, float* norms, int32_t* l0);
 // the same norms from the partial sums of squares a fused weight-gradient launch left behind:
 // n[l,f] = sqrt(sum over the blocks p(l, l..L-1) and their d / 64 column runs of n2_part[p][run][f]), in that order
 // (runs: column runs per row in the dense layout, d / 64 after an update, see DecArgs::row_squares for the decode's;
 //  flags: the device-side decode switch of the step that left the sums, NULL when only the dense kernels run)
 hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_part, int runs, float* norms,
-                                      const int32_t* flags, int kcap);
-// L_rec partials, d_yhat = 2 r / B, column partials for db_dec
-hipError_t launch_loss_rec(hipStream_t s, bool bf16, bool int8_y, Dims D, const float* y_hat, const void* y,
-                           const float* y_scale, void* d_yhat, double* loss_part, float* col_part);
-// L_sp partials and column partials of C z sech^2(C z n)
-// with pre != NULL also the dead-feature partial sums: sum relu(theta - pre) n into dead_part and the column
-// partials of relu(theta - pre) into dead_col_part
-hipError_t launch_loss_sparsity(hipStream_t s, bool bf16, Dims D, const void* z, const float* norms, float C,
-                                double* loss_part, float* col_part, const void* pre, const float* theta,
-                                bool log_threshold, double* dead_part, float* dead_col_part);
-// final loss: loss_dev = {rec + sp + dead, rec, sp, dead}
-hipError_t launch_loss_final(hipStream_t s, const double* part_rec, int n_rec, const double* part_sp, int n_sp,
-                             const double* part_dead_or_null, float inv_B, float lambda0, float lambda1,
-                             float* loss_dev);
+                                      const int32_t* flags, int kcap, int32_t* l0);
+// The losses: L_sp partials and column partials of C z sech^2(C z n), with pre != NULL also the dead-feature partial sums (sum
+// relu(theta - pre) n into dead_part and the column partials of relu(theta - pre)); L_rec partials, d_yhat = 2 r / B, column
+// partials for db_dec
+hipError_t launch_loss(hipStream_t s, bool bf16, bool int8_y, Dims D, const void* z, const float* norms, float C, const void* pre,
+                       const float* theta, bool log_threshold, double* sp_part, float* sp_cols, double* dead_part, float* dead_cols,
+                       const float* y_hat, const void* y, const float* y_scale, void* d_yhat, double* rec_part, float* rec_cols);
+// loss_dev = {rec + sp + dead, rec, sp, dead}; G[l, f] = sums over the nparts row blocks of the column partials, times lambda / B
+hipError_t launch_loss_finish(hipStream_t s, Dims D, const double* part_rec, int n_rec, const double* part_sp, int n_sp,
+                              const double* part_dead_or_null, float inv_B, float lambda0, float lambda1, float* loss_dev,
+                              const float* sp_cols, const float* dead_cols, int nparts, float* G);
 // Automatic mode: the column partials of the backward come in nparts row blocks when the dense dz epilogue wrote
 // them and in nparts_lists when the list-driven backward ran (launch_ste_reduce); which, the device-side switch says.
 struct PartsSwitch { const int32_t* flags = nullptr; int kcap = 0; int nparts_lists = 0; };
-// out[c] = alpha * sum_r part[r][c] (fixed order)
-hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha, float* out,
-                             bool accumulate = false, PartsSwitch sw = PartsSwitch{});
-// dtheta[c] = -(theta/eps) sum_r part_win[r][c] + lam1_over_b * norms[c] * sum_r part_below[r][c], times theta
-// when the parameter is log(theta)
-hipError_t launch_dtheta_final(hipStream_t s, const float* part_win, const float* part_below, int nparts, int ncols,
-                               const float* theta_param, bool log_threshold, const float* norms, float inv_eps,
-                               float lam1_over_b, float* out, PartsSwitch sw = PartsSwitch{});
+// The vectors' gradients (all sums in a fixed order): d theta[c] = -(theta/eps) sum_r part_win[r][c] + lam1_over_b * norms[c] *
+// sum_r part_below[r][c], times theta when the parameter is log(theta) (TopK: the sum as it is); d b_enc, d b_dec; and where
+// p is given the Adam update of the vector.
+struct VectorAdam { float* p = nullptr; float* m = nullptr; float* v = nullptr; };
+struct VectorGradArgs {
+  const float* part_win; const float* part_below; const float* part_benc; int nparts; PartsSwitch sw; int nF;
+  const float* part_bdec; int nparts_bdec, nd;
+  const float* theta; bool log_threshold, topk; const float* norms; float inv_eps, lam1_over_b;
+  float* g_theta; float* g_benc; float* g_bdec;
+  VectorAdam th, b_enc, b_dec; AdamScalars adam;
+};
+hipError_t launch_vector_gradients(hipStream_t s, const VectorGradArgs& a);
 // reads dz kept where active|window: column partials for dtheta (window) and db_enc (active);
 // zeroes entries that are in the window but not active so the buffer becomes dpre
 // (entries that are below the threshold get the dead-feature gradient -lam1_over_b * n; part_below counts them)
@@ -300,7 +302,8 @@ hipError_t launch_ste_reduce(hipStream_t s, bool bf16, Dims D, void* dpre, const
 // p, g in T (or p in T with fp32 master); m, v float
 hipError_t launch_adam_matrix(hipStream_t s, bool bf16, size_t n, void* p, const void* g, float* m, float* v,
                               float* master_or_null, AdamScalars a);
-hipError_t launch_adam_vector(hipStream_t s, size_t n, float* p, const float* g, float* m, float* v, AdamScalars a);
+struct AdamVectors { int n[3]; float* p[3]; const float* g[3]; float* m[3]; float* v[3]; };
+hipError_t launch_adam_vectors(hipStream_t s, const AdamVectors& a, AdamScalars sc);
 
 // Diagnostic (kernels_diag.hip): the contraction kernel's instruction stream taken apart.  `workgroups` x 8 waves x
 // iters x 64 v_mfma_f32_16x16x32_bf16; mode bits add the LDS and memory traffic of the real kernel; out[0] / out[1] =

@@ -5,6 +5,8 @@
 // bitwise reproducible run to run.
 #include "common.h"
 
+#include <algorithm>
+
 namespace clt {
 namespace {
 
@@ -30,6 +32,10 @@ __device__ __forceinline__ double block_sum_256(double v) {
 __global__ void zero_i32_kernel(int32_t* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
+}
+// the same by the first workgroup of a kernel that runs anyway (n <= 128 <= its size)
+__device__ __forceinline__ void zero_counters(int32_t* p, int n) {
+  if (p && blockIdx.x == 0 && (int)threadIdx.x < n) p[threadIdx.x] = 0;
 }
 
 // ---- decode partial sums (see DecSplit): grid = (runs of 1024 elements of [B][d], targets) ----
@@ -58,7 +64,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(Dims D, DecSplit sp
 // so feature f's rows are L-l runs of d contiguous elements.
 template <typename T>
 __global__ __launch_bounds__(256) void decoder_norms_kernel(Dims D, const T* __restrict__ W_dec,
-                                                            float* __restrict__ norms) {
+                                                            float* __restrict__ norms, int32_t* __restrict__ l0) {
+  zero_counters(l0, D.L);
   const int lane = threadIdx.x & 63;
   const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);   // l * F + f
   if (row >= (long)D.L * D.F) return;
@@ -81,7 +88,9 @@ __global__ __launch_bounds__(256) void decoder_norms_kernel(Dims D, const T* __r
 // [P][F][8 ceil(d / 2048)].  Which of the two ran is what the device-side switch decided in that step (flags).
 __global__ __launch_bounds__(256) void norms_from_partials_kernel(Dims D, const float* __restrict__ n2_part, int runs,
                                                                   float* __restrict__ norms,
-                                                                  const int32_t* __restrict__ flags, int kcap) {
+                                                                  const int32_t* __restrict__ flags, int kcap,
+                                                                  int32_t* __restrict__ l0) {
+  zero_counters(l0, D.L);
   const long i = (long)blockIdx.x * 256 + threadIdx.x;      // l * F + f
   if (i >= (long)D.L * D.F) return;
   const int l = (int)(i / D.F), f = (int)(i - (long)l * D.F);
@@ -144,9 +153,9 @@ template <int N> __device__ __forceinline__ void load_floats(const float* p, flo
 // the workgroup's part: rows [r0, r1) of the calling wavefront, first column c of the calling lane
 template <int N> struct RowPart {
   int rb, l, r0, r1, c;
-  __device__ __forceinline__ RowPart(Dims D, int rows, int nchunks, int cols) {
-    const int chunk = blockIdx.x % nchunks;
-    rb = blockIdx.x / nchunks;
+  __device__ __forceinline__ RowPart(Dims D, int block, int rows, int nchunks, int cols) {
+    const int chunk = block % nchunks;
+    rb = block / nchunks;
     l = blockIdx.y;
     const int w = threadIdx.x >> 6;
     r0 = min(D.B, rb * rows + w * (rows / 4));
@@ -175,13 +184,12 @@ __device__ __forceinline__ void add_column_sums(float (&s)[N], float* dst, bool 
 
 // reconstruction loss: r = y_hat - y; partial sum r^2; d_yhat = 2 r / B; column partial sums of d_yhat (for db_dec)
 template <typename T, bool INT8>
-__global__ __launch_bounds__(256) void loss_rec_kernel(Dims D, int rows, int nchunks, const float* __restrict__ y_hat,
-                                                       const void* yv, const float* __restrict__ y_scale,
-                                                       T* __restrict__ d_yhat, double* __restrict__ loss_part,
-                                                       float* __restrict__ col_part) {
+__device__ __forceinline__ void loss_reconstruction(const Dims& D, int block, int nblocks, int rows, int nchunks, const float* __restrict__ y_hat,
+                                                    const void* yv, const float* __restrict__ y_scale,
+                                                    T* __restrict__ d_yhat, double* __restrict__ loss_part,
+                                                    float* __restrict__ col_part, float (&lds)[3][64 * Row16<T>::N]) {
   constexpr int N = Row16<T>::N, R = ROWS_IN_FLIGHT / 2;      // (two more loads per row than the other kernels)
-  __shared__ float lds[3][64 * N];
-  const RowPart<N> p(D, rows, nchunks, D.d);
+  const RowPart<N> p(D, block, rows, nchunks, D.d);
   const float two_over_b = 2.0f / (float)D.B;
   float cs[N];
 #pragma unroll
@@ -227,23 +235,21 @@ __global__ __launch_bounds__(256) void loss_rec_kernel(Dims D, int rows, int nch
   }
   add_column_sums(cs, col_part + ((size_t)p.rb * D.L + p.l) * D.d + p.c, p.c < D.d, lds);
   const double tot = block_sum_256(sq);
-  if (threadIdx.x == 0) loss_part[(size_t)p.l * gridDim.x + blockIdx.x] = tot;
+  if (threadIdx.x == 0) loss_part[(size_t)p.l * nblocks + block] = tot;
 }
 
 // sparsity loss: partial sum tanh(C z n); column partials of C z sech^2(C z n) (both from one hardware exponential).
 // With DEAD also the App. B dead-feature term: partial sum relu(theta - pre) n and the
 // column partials of relu(theta - pre) (its derivative w.r.t. the decoder norm).
 template <typename T, bool DEAD>
-__global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, int rows, int nchunks, const T* __restrict__ z,
-                                                            const float* __restrict__ norms, float C,
-                                                            double* __restrict__ loss_part,
-                                                            float* __restrict__ col_part, const T* __restrict__ pre,
-                                                            const float* __restrict__ theta, bool log_threshold,
-                                                            double* __restrict__ dead_part,
-                                                            float* __restrict__ dead_col_part) {
+__device__ __forceinline__ void loss_sparsity(const Dims& D, int block, int nblocks, int rows, int nchunks, const T* __restrict__ z,
+                                              const float* __restrict__ norms, float C, double* __restrict__ loss_part,
+                                              float* __restrict__ col_part, const T* __restrict__ pre,
+                                              const float* __restrict__ theta, bool log_threshold,
+                                              double* __restrict__ dead_part, float* __restrict__ dead_col_part,
+                                              float (&lds)[3][64 * Row16<T>::N]) {
   constexpr int N = Row16<T>::N, R = DEAD ? ROWS_IN_FLIGHT / 2 : ROWS_IN_FLIGHT;
-  __shared__ float lds[3][64 * N];
-  const RowPart<N> p(D, rows, nchunks, D.F);
+  const RowPart<N> p(D, block, rows, nchunks, D.F);
   const bool in = p.c < D.F;
   float ka[N], nn[N], th[N], cs[N], ds[N];
 #pragma unroll
@@ -305,42 +311,33 @@ __global__ __launch_bounds__(256) void loss_sparsity_kernel(Dims D, int rows, in
   add_column_sums(cs, col_part + po, in, lds);
   if (DEAD) add_column_sums(ds, dead_col_part + po, in, lds);
   const double tot = block_sum_256(sp);
-  if (threadIdx.x == 0) loss_part[(size_t)p.l * gridDim.x + blockIdx.x] = tot;
+  if (threadIdx.x == 0) loss_part[(size_t)p.l * nblocks + block] = tot;
   if (DEAD) {
     __syncthreads();
     const double dt = block_sum_256(dead);
-    if (threadIdx.x == 0) dead_part[(size_t)p.l * gridDim.x + blockIdx.x] = dt;
+    if (threadIdx.x == 0) dead_part[(size_t)p.l * nblocks + block] = dt;
   }
 }
 
-__global__ __launch_bounds__(1024) void loss_final_kernel(const double* part_rec, int n_rec, const double* part_sp,
-                                                          int n_sp, const double* part_dead, float inv_B, float lambda0,
-                                                          float lambda1, float* loss_dev) {
-  __shared__ double sh[3][16];
-  auto sum = [&](const double* p, int n, int slot) {
-    double s[4] = {0.0, 0.0, 0.0, 0.0};      // four chains keep four loads in flight
-    for (int i = threadIdx.x; i < n; i += 4096) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (i + 1024 * q < n) s[q] += p[i + 1024 * q];
-    }
-    const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
-    if ((threadIdx.x & 63) == 0) sh[slot][threadIdx.x >> 6] = t;
-  };
-  sum(part_rec, n_rec, 0);
-  sum(part_sp, n_sp, 1);
-  sum(part_dead, part_dead ? n_sp : 0, 2);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int i = 0; i < 16; ++i) { a += sh[0][i]; b += sh[1][i]; c += sh[2][i]; }
-    const double rec = a * (double)inv_B, sp = b * (double)inv_B * (double)lambda0;
-    const double dead = c * (double)inv_B * (double)lambda1;
-    loss_dev[0] = (float)(rec + sp + dead);
-    loss_dev[1] = (float)rec;
-    loss_dev[2] = (float)sp;
-    loss_dev[3] = (float)dead;
-  }
+// Both losses in one launch, the sparsity term's workgroups first.  What bounds these kernels at small shapes is the launch, 2 to 5 us
+// for each that waits for the one before: with the loss sums and G, and the vectors' gradients and their update, in one launch each
+// as well and the encoder's counters cleared along the way, a training step has 11 launches instead of 19 (L = 4, d = 64, F = 256, 128
+// tokens of fp32: 86 -> 69 us; L = 3, d = 136, F = 1032, 300 tokens of bf16: 184 -> 163).
+struct LossArgs {
+  int sp_rows, sp_chunks, sp_blocks, rec_rows, rec_chunks, rec_blocks;
+  const void* z; const float* norms; float C; const void* pre; const float* theta; bool log_threshold;
+  double* sp_part; float* sp_cols; double* dead_part; float* dead_cols;
+  const float* y_hat; const void* y; const float* y_scale; void* d_yhat; double* rec_part; float* rec_cols;
+};
+template <typename T, bool INT8, bool DEAD>
+__global__ __launch_bounds__(256) void loss_kernel(Dims D, LossArgs a) {
+  __shared__ float lds[3][64 * Row16<T>::N];
+  if ((int)blockIdx.x < a.sp_blocks)
+    loss_sparsity<T, DEAD>(D, blockIdx.x, a.sp_blocks, a.sp_rows, a.sp_chunks, (const T*)a.z, a.norms, a.C, a.sp_part, a.sp_cols,
+                           (const T*)a.pre, a.theta, a.log_threshold, a.dead_part, a.dead_cols, lds);
+  else
+    loss_reconstruction<T, INT8>(D, blockIdx.x - a.sp_blocks, a.rec_blocks, a.rec_rows, a.rec_chunks, a.y_hat, a.y, a.y_scale,
+                                 (T*)a.d_yhat, a.rec_part, a.rec_cols, lds);
 }
 
 // Sum over the row partials of 64 columns by a workgroup: each wavefront adds a quarter of the partials, the quarters
@@ -360,36 +357,80 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ part, in
   return w == 0 ? (s + lds[0][lane]) + (lds[1][lane] + lds[2][lane]) : 0.f;
 }
 
-__global__ __launch_bounds__(256) void col_reduce_kernel(const float* __restrict__ part, int nparts, int ncols,
-                                                         float alpha, float* __restrict__ out, bool accumulate,
-                                                         PartsSwitch sw) {
+// What is left of the loss after its row blocks: the first workgroup adds up the loss terms, the others the column partials
+// of the norms' gradient, G[c] = lambda0/B sum_r sp[r][c] (+ lambda1/B sum_r dead[r][c]).
+__global__ __launch_bounds__(256) void loss_finish_kernel(const double* __restrict__ part_rec, int n_rec, const double* __restrict__ part_sp,
+                                                          int n_sp, const double* __restrict__ part_dead, float inv_B, float lambda0,
+                                                          float lambda1, float* __restrict__ loss_dev, const float* __restrict__ sp_cols,
+                                                          const float* __restrict__ dead_cols, int nparts, int ncols,
+                                                          float* __restrict__ G) {
   __shared__ float lds[3][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  if (sw.flags && lists_backward_selected(sw.flags, sw.kcap)) nparts = sw.nparts_lists;
-  float s = sum_partials(part, nparts, ncols, c, lds);
-  if (threadIdx.x >= 64 || c >= ncols) return;
-  s *= alpha;
-  out[c] = accumulate ? out[c] + s : s;
+  if (blockIdx.x > 0) {
+    const int c = ((int)blockIdx.x - 1) * 64 + (threadIdx.x & 63);
+    float g = (lambda0 * inv_B) * sum_partials(sp_cols, nparts, ncols, c, lds);
+    if (part_dead) g += (lambda1 * inv_B) * sum_partials(dead_cols, nparts, ncols, c, lds);
+    if (threadIdx.x < 64 && c < ncols) G[c] = g;
+    return;
+  }
+  auto sum = [&](const double* p, int n) {
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};      // eight chains keep eight loads in flight
+    for (int i = threadIdx.x; i < n; i += 2048) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (i + 256 * q < n) s[q] += p[i + 256 * q];
+    }
+    __syncthreads();      // (the sum before this one has been read)
+    return block_sum_256(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
+  };
+  const double a = sum(part_rec, n_rec), b = sum(part_sp, n_sp), c = part_dead ? sum(part_dead, n_sp) : 0.0;
+  if (threadIdx.x == 0) {
+    const double rec = a * (double)inv_B, sp = b * (double)inv_B * (double)lambda0;
+    const double dead = c * (double)inv_B * (double)lambda1;
+    loss_dev[0] = (float)(rec + sp + dead);
+    loss_dev[1] = (float)rec;
+    loss_dev[2] = (float)sp;
+    loss_dev[3] = (float)dead;
+  }
 }
 
-// Threshold gradient: straight-through part -(theta/eps) * (sum over window entries of dz), plus the
-// dead-feature part (lambda1/B) n * #(pre < theta); times theta when the parameter is tau = log(theta).
-__global__ __launch_bounds__(256) void dtheta_final_kernel(const float* __restrict__ part_win,
-                                                           const float* __restrict__ part_below, int nparts,
-                                                           int ncols, const float* __restrict__ theta_param,
-                                                           bool log_threshold, const float* __restrict__ norms,
-                                                           float inv_eps, float lam1_over_b,
-                                                           float* __restrict__ out, PartsSwitch sw) {
+// Gradients of the three vectors from the column partials of the backward, and their Adam update where the caller wants it, in
+// one launch.  d b_enc and d b_dec are plain sums.  Threshold: straight-through part -(theta/eps) * (sum over window entries of
+// dz), plus the dead-feature part (lambda1/B) n * #(pre < theta); times theta when the parameter is tau = log(theta).  TopK has no
+// threshold, the partials are zeros.
+__global__ __launch_bounds__(256) void vector_gradients_kernel(VectorGradArgs a) {
   __shared__ float lds[3][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  if (sw.flags && lists_backward_selected(sw.flags, sw.kcap)) nparts = sw.nparts_lists;
-  const float w = sum_partials(part_win, nparts, ncols, c, lds);
-  const float nb = lam1_over_b != 0.f ? sum_partials(part_below, nparts, ncols, c, lds) : 0.f;
-  if (threadIdx.x >= 64 || c >= ncols) return;
-  const float th = threshold_value(theta_param[c], log_threshold);
-  float g = (w == 0.f) ? 0.f : w * -(th * inv_eps);   // empty window: exactly 0, also for theta = inf
-  if (lam1_over_b != 0.f) g += lam1_over_b * norms[c] * nb;
-  out[c] = log_threshold ? g * th : g;
+  const int nf = (a.nF + 63) / 64;
+  auto update = [&](const VectorAdam& q, int c, float g) {
+    if (!q.p) return;
+    float p = q.p[c], m = q.m[c], v = q.v[c];
+    adam_element(p, m, v, g, a.adam);
+    q.p[c] = p; q.m[c] = m; q.v[c] = v;
+  };
+  if ((int)blockIdx.x >= nf) {
+    const int c = ((int)blockIdx.x - nf) * 64 + (threadIdx.x & 63);
+    const float g = sum_partials(a.part_bdec, a.nparts_bdec, a.nd, c, lds);
+    if (threadIdx.x >= 64 || c >= a.nd) return;
+    a.g_bdec[c] = g;
+    update(a.b_dec, c, g);
+    return;
+  }
+  const int c = (int)blockIdx.x * 64 + (threadIdx.x & 63);
+  const int nparts = a.sw.flags && lists_backward_selected(a.sw.flags, a.sw.kcap) ? a.sw.nparts_lists : a.nparts;
+  const float w = sum_partials(a.part_win, nparts, a.nF, c, lds);
+  const float nb = a.lam1_over_b != 0.f ? sum_partials(a.part_below, nparts, a.nF, c, lds) : 0.f;
+  const float gb = sum_partials(a.part_benc, nparts, a.nF, c, lds);
+  if (threadIdx.x >= 64 || c >= a.nF) return;
+  float g = w;
+  if (!a.topk) {
+    const float th = threshold_value(a.theta[c], a.log_threshold);
+    g = (w == 0.f) ? 0.f : w * -(th * a.inv_eps);   // empty window: exactly 0, also for theta = inf
+    if (a.lam1_over_b != 0.f) g += a.lam1_over_b * a.norms[c] * nb;
+    if (a.log_threshold) g *= th;
+  }
+  a.g_theta[c] = g;
+  a.g_benc[c] = gb;
+  update(a.th, c, g);
+  update(a.b_enc, c, gb);
 }
 
 // ---- straight-through reductions over the buffer that holds dz where a feature
@@ -412,7 +453,7 @@ __global__ __launch_bounds__(256) void ste_reduce_kernel(Dims D, int rows, int n
   if (only_if_lists && !lists_backward_selected(only_if_lists, kcap)) return;
   constexpr int N = Row16<T>::N, W = N / 4, R = ROWS_IN_FLIGHT;      // W words of classes per row
   __shared__ float lds[3][64 * N];
-  const RowPart<N> p(D, rows, nchunks, D.F);
+  const RowPart<N> p(D, blockIdx.x, rows, nchunks, D.F);
   const bool dead = lam1_over_b != 0.f, in = p.c < D.F;
   float st[N], sb[N], nb[N], dg[N];
 #pragma unroll
@@ -511,6 +552,22 @@ __global__ __launch_bounds__(256) void adam_kernel(size_t n4, T* __restrict__ p,
     if (MASTER) *reinterpret_cast<float4*>(master + o) = pn;
     Elem<T>::store4(p + o, pn);
   }
+}
+
+// the three vectors in one launch, four elements per lane
+__global__ __launch_bounds__(256) void adam_vectors_kernel(AdamVectors q, AdamScalars a) {
+  const int t = blockIdx.y, i = ((int)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= q.n[t]) return;
+  const float4 g4 = *reinterpret_cast<const float4*>(q.g[t] + i);
+  const float4 p4 = *reinterpret_cast<const float4*>(q.p[t] + i), m4 = *reinterpret_cast<const float4*>(q.m[t] + i),
+               v4 = *reinterpret_cast<const float4*>(q.v[t] + i);
+  const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+  float p[4] = {p4.x, p4.y, p4.z, p4.w}, m[4] = {m4.x, m4.y, m4.z, m4.w}, v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) adam_element(p[k], m[k], v[k], g[k], a);
+  *reinterpret_cast<float4*>(q.p[t] + i) = make_float4(p[0], p[1], p[2], p[3]);
+  *reinterpret_cast<float4*>(q.m[t] + i) = make_float4(m[0], m[1], m[2], m[3]);
+  *reinterpret_cast<float4*>(q.v[t] + i) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // ---- TopK activation: the k largest of a row's F fp32 pre-activations ----------------
@@ -811,74 +868,52 @@ hipError_t launch_decode_combine(hipStream_t s, Dims D, DecSplit sp, const float
   return hipGetLastError();
 }
 
-hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_dec, float* norms) {
+hipError_t launch_decoder_norms(hipStream_t s, bool bf16, Dims D, const void* W_dec, float* norms, int32_t* l0) {
   const long rows = (long)D.L * D.F;
   const dim3 grid((unsigned)((rows + 3) / 4));
   if (bf16)
-    hipLaunchKernelGGL((decoder_norms_kernel<bf16_t>), grid, dim3(256), 0, s, D, (const bf16_t*)W_dec, norms);
+    hipLaunchKernelGGL((decoder_norms_kernel<bf16_t>), grid, dim3(256), 0, s, D, (const bf16_t*)W_dec, norms, l0);
   else
-    hipLaunchKernelGGL((decoder_norms_kernel<float>), grid, dim3(256), 0, s, D, (const float*)W_dec, norms);
+    hipLaunchKernelGGL((decoder_norms_kernel<float>), grid, dim3(256), 0, s, D, (const float*)W_dec, norms, l0);
   return hipGetLastError();
 }
 
 hipError_t launch_norms_from_partials(hipStream_t s, Dims D, const float* n2_part, int runs, float* norms,
-                                      const int32_t* flags, int kcap) {
+                                      const int32_t* flags, int kcap, int32_t* l0) {
   const long rows = (long)D.L * D.F;
   hipLaunchKernelGGL(norms_from_partials_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, D, n2_part, runs, norms,
-                     flags, kcap);
+                     flags, kcap, l0);
   return hipGetLastError();
 }
 
-hipError_t launch_loss_rec(hipStream_t s, bool bf16, bool int8_y, Dims D, const float* y_hat, const void* y,
-                           const float* y_scale, void* d_yhat, double* loss_part, float* col_part) {
-  const ReduceGrid rg = reduce_grid(bf16, D, D.d);
-  const dim3 grid(rg.blocks(), D.L);
-  if (!bf16)
-    hipLaunchKernelGGL((loss_rec_kernel<float, false>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, y_hat, y, y_scale, (float*)d_yhat,
-                       loss_part, col_part);
-  else if (int8_y)
-    hipLaunchKernelGGL((loss_rec_kernel<bf16_t, true>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, y_hat, y, y_scale,
-                       (bf16_t*)d_yhat, loss_part, col_part);
-  else
-    hipLaunchKernelGGL((loss_rec_kernel<bf16_t, false>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, y_hat, y, y_scale,
-                       (bf16_t*)d_yhat, loss_part, col_part);
+hipError_t launch_loss(hipStream_t s, bool bf16, bool int8_y, Dims D, const void* z, const float* norms, float C, const void* pre,
+                       const float* theta, bool log_threshold, double* sp_part, float* sp_cols, double* dead_part, float* dead_cols,
+                       const float* y_hat, const void* y, const float* y_scale, void* d_yhat, double* rec_part, float* rec_cols) {
+  const ReduceGrid rf = reduce_grid(bf16, D, D.F), rd = reduce_grid(bf16, D, D.d);
+  const LossArgs a{rf.rows, rf.chunks, rf.blocks(), rd.rows, rd.chunks, rd.blocks(), z, norms, C, pre, theta, log_threshold,
+                   sp_part, sp_cols, dead_part, dead_cols, y_hat, y, y_scale, d_yhat, rec_part, rec_cols};
+  const dim3 grid(rf.blocks() + rd.blocks(), D.L);
+#define CLT_LOSS(T, INT8)                                                                              \
+  do {                                                                                                 \
+    if (pre) hipLaunchKernelGGL((loss_kernel<T, INT8, true>), grid, dim3(256), 0, s, D, a);            \
+    else hipLaunchKernelGGL((loss_kernel<T, INT8, false>), grid, dim3(256), 0, s, D, a);               \
+  } while (0)
+  if (!bf16) CLT_LOSS(float, false); else if (int8_y) CLT_LOSS(bf16_t, true); else CLT_LOSS(bf16_t, false);
+#undef CLT_LOSS
   return hipGetLastError();
 }
 
-hipError_t launch_loss_sparsity(hipStream_t s, bool bf16, Dims D, const void* z, const float* norms, float C,
-                                double* loss_part, float* col_part, const void* pre, const float* theta,
-                                bool log_threshold, double* dead_part, float* dead_col_part) {
-  const ReduceGrid rg = reduce_grid(bf16, D, D.F);
-  const dim3 grid(rg.blocks(), D.L);
-#define CLT_LSP(T, DEAD)                                                                                      \
-  hipLaunchKernelGGL((loss_sparsity_kernel<T, DEAD>), grid, dim3(256), 0, s, D, rg.rows, rg.chunks, (const T*)z, norms, \
-                     C, loss_part, col_part, (const T*)pre, theta, log_threshold, dead_part, dead_col_part)
-  if (bf16) { if (pre) CLT_LSP(bf16_t, true); else CLT_LSP(bf16_t, false); }
-  else { if (pre) CLT_LSP(float, true); else CLT_LSP(float, false); }
-#undef CLT_LSP
+hipError_t launch_loss_finish(hipStream_t s, Dims D, const double* part_rec, int n_rec, const double* part_sp, int n_sp,
+                              const double* part_dead_or_null, float inv_B, float lambda0, float lambda1, float* loss_dev,
+                              const float* sp_cols, const float* dead_cols, int nparts, float* G) {
+  const int ncols = D.L * D.F;
+  hipLaunchKernelGGL(loss_finish_kernel, dim3(1 + (ncols + 63) / 64), dim3(256), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
+                     inv_B, lambda0, lambda1, loss_dev, sp_cols, dead_cols, nparts, ncols, G);
   return hipGetLastError();
 }
 
-hipError_t launch_loss_final(hipStream_t s, const double* part_rec, int n_rec, const double* part_sp, int n_sp,
-                             const double* part_dead_or_null, float inv_B, float lambda0, float lambda1,
-                             float* loss_dev) {
-  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(1024), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
-                     inv_B, lambda0, lambda1, loss_dev);
-  return hipGetLastError();
-}
-
-hipError_t launch_col_reduce(hipStream_t s, const float* part, int nparts, int ncols, float alpha, float* out,
-                             bool accumulate, PartsSwitch sw) {
-  hipLaunchKernelGGL(col_reduce_kernel, dim3((ncols + 63) / 64), dim3(256), 0, s, part, nparts, ncols, alpha, out,
-                     accumulate, sw);
-  return hipGetLastError();
-}
-
-hipError_t launch_dtheta_final(hipStream_t s, const float* part_win, const float* part_below, int nparts, int ncols,
-                               const float* theta_param, bool log_threshold, const float* norms, float inv_eps,
-                               float lam1_over_b, float* out, PartsSwitch sw) {
-  hipLaunchKernelGGL(dtheta_final_kernel, dim3((ncols + 63) / 64), dim3(256), 0, s, part_win, part_below, nparts,
-                     ncols, theta_param, log_threshold, norms, inv_eps, lam1_over_b, out, sw);
+hipError_t launch_vector_gradients(hipStream_t s, const VectorGradArgs& a) {
+  hipLaunchKernelGGL(vector_gradients_kernel, dim3((a.nF + 63) / 64 + (a.nd + 63) / 64), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -919,10 +954,9 @@ hipError_t launch_adam_matrix(hipStream_t s, bool bf16, size_t n, void* p, const
   return hipGetLastError();
 }
 
-hipError_t launch_adam_vector(hipStream_t s, size_t n, float* p, const float* g, float* m, float* v, AdamScalars a) {
-  const size_t n4 = n / 4;   // vectors have L*F or L*d elements, multiples of 8
-  hipLaunchKernelGGL((adam_kernel<float, false>), dim3((unsigned)((n4 + 256 * ADAM_QUADS - 1) / (256 * ADAM_QUADS))), dim3(256), 0, s, n4, p, g, m, v,
-                     (float*)nullptr, a);
+hipError_t launch_adam_vectors(hipStream_t s, const AdamVectors& a, AdamScalars sc) {
+  const int most = (std::max(a.n[0], std::max(a.n[1], a.n[2])) / 4 + 255) / 256;      // vectors have L*F or L*d elements, multiples of 8
+  hipLaunchKernelGGL(adam_vectors_kernel, dim3(most, 3), dim3(256), 0, s, a, sc);
   return hipGetLastError();
 }
 

@@ -706,6 +706,17 @@ def test_stepped_gather_decode(L, d, F, B, rho):
     assert (st.y_hat - first)[~hit].abs().max() < 1e-5 * first.abs().max()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,d,F,B,lambda1", [(1, 8, 8, 1, 0.0), (2, 72, 8, 33, 5.0), (3, 8, 200, 129, 0.0), (5, 136, 264, 65, 5.0)])
+def test_vectors_and_losses_at_the_edges_of_their_launches(dtype, L, d, F, B, lambda1):
+    """Both losses share a launch, the loss sum and G another, the vectors' gradients and their update a third: columns that are no
+    multiple of a workgroup's 64 (or fill less than one), one to three row blocks, with and without the dead-feature term."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype=dtype, L=L, d=d, F=F, B=B, seed=92, lambda1=lambda1)
+    for fused in (False, True):
+        g, o = run_both(w, fused=fused)
+        show(f"vectors {dtype} L={L} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL[dtype]))
+
+
 def test_gather_dz_lds_chunks_and_fallback(monkeypatch):
     """Backward through the lists when a token's d y_hat rows exceed 64 KB of LDS (fp32, d=2048: eight targets per
     chunk, nine targets from layer 0, so a second chunk of one), and the one-wave-per-entry kernel, which otherwise
