@@ -143,6 +143,11 @@ __device__ __forceinline__ void store16(bf16_t* p, const float (&f)[8]) {
 __device__ __forceinline__ void store16(float* p, const float (&f)[4]) {
   *reinterpret_cast<float4*>(p) = make_float4(f[0], f[1], f[2], f[3]);
 }
+__device__ __forceinline__ void nt_store16(bf16_t* p, const float (&f)[8]) {
+  const u32x4 r = {pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7])};
+  CLT_NT_STORE(r, reinterpret_cast<u32x4*>(p));
+}
+__device__ __forceinline__ void nt_store16(float* p, const float (&f)[4]) { nt_store_f4(p, make_float4(f[0], f[1], f[2], f[3])); }
 template <int N> __device__ __forceinline__ void load_floats(const float* p, float (&f)[N]) {
 #pragma unroll
   for (int i = 0; i < N; i += 4) {
@@ -739,8 +744,7 @@ __global__ __launch_bounds__(256) void topk_select_kernel(Dims D, const float* _
 // block leaves the sum of its rows' norms; stage 2 adds the blocks of a layer, in order, to the
 // running sum.  int8 rows: the norm of the codes times |row scale|.
 // A wave takes four rows at a time, 16 bytes (int8: 8) per lane and row in flight.  L = 16, d = 2048, 4096 tokens of bf16: the
-// kernel reads 268 MB in 71 us while what the division wrote before is still on its way to memory; sum and division
-// 182 -> 160 us together, most of it from the second stage (one chain of loads per layer before, 12 us).
+// kernel reads 268 MB in 71 us; its second stage was one chain of loads per layer before, 12 us.
 template <typename T, bool INT8>
 __global__ __launch_bounds__(256) void row_norm_sum_kernel(Dims D, const void* __restrict__ av,
                                                            const float* __restrict__ a_scale,
@@ -815,16 +819,30 @@ __global__ void normalise_scale_kernel(Dims D, const double* __restrict__ norm_s
   scale_out[i] = scale_in[i] * inv_norm_factor(norm_sum, (int)(i / D.B), n_tokens);
 }
 
-// native rows: a_out = a_in / c[l] (a_out may be a_in); grid = (chunks of a layer, L)
-template <typename T>
+// native rows: a_out = a_in / c[l] (a_out may be a_in); grid = (chunks of a layer, L).  Bound by memory.  STREAM: non-temporal stores,
+// for batches that do not fit the 256 MB Infinity Cache together with the result: plain ones push out what is still to be read
+// (L = 16, d = 2048, 4096 tokens of bf16, sum and division: 155.5 -> 123.8 us; in fp32 with L = 8 142 -> 128; 75 MB: 41 either way,
+// and the forward pass that follows may find the result there).
+constexpr int NORM_LOADS = 4;      // 16-byte pieces per lane
+template <typename T, bool STREAM>
 __global__ __launch_bounds__(256) void normalise_rows_kernel(Dims D, const double* __restrict__ norm_sum,
                                                              double n_tokens, const T* a_in, T* a_out) {
+  constexpr int N = Row16<T>::N, R = NORM_LOADS;
   const int l = blockIdx.y;
   const float k = inv_norm_factor(norm_sum, l, n_tokens);
-  const size_t n4 = (size_t)D.B * D.d / 4, base = (size_t)l * D.B * D.d;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-    const float4 v = Elem<T>::load4(a_in + base + 4 * i);
-    Elem<T>::store4(a_out + base + 4 * i, make_float4(k * v.x, k * v.y, k * v.z, k * v.w));
+  const size_t n = (size_t)D.B * D.d / N, base = (size_t)l * D.B * D.d, i0 = (size_t)blockIdx.x * (256 * R) + threadIdx.x;
+  u32x4 raw[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+    if (i0 + 256 * j < n) raw[j] = load16(a_in + base + (i0 + 256 * j) * N);
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    if (i0 + 256 * j >= n) break;
+    float v[N];
+    widen16(raw[j], v);
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] *= k;
+    if (STREAM) nt_store16(a_out + base + (i0 + 256 * j) * N, v); else store16(a_out + base + (i0 + 256 * j) * N, v);
   }
 }
 
@@ -834,13 +852,6 @@ __global__ __launch_bounds__(256) void normalise_rows_kernel(Dims D, const doubl
 static __device__ __align__(256) double scratch[STATIC_SCRATCH_DOUBLES];
 constexpr int MAX_DEVICES = 64;
 double* g_scratch_ptr[MAX_DEVICES] = {};   // device address of `scratch` on each GPU, resolved once
-
-inline int grid_for(size_t n, int per_block, int cap) {
-  size_t b = (n + per_block - 1) / per_block;
-  if (b < 1) b = 1;
-  if (b > (size_t)cap) b = cap;
-  return (int)b;
-}
 
 }  // namespace
 
@@ -999,13 +1010,14 @@ hipError_t launch_normalise(hipStream_t s, bool bf16, bool int8_a, Dims D, const
     hipLaunchKernelGGL(normalise_scale_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, D, norm_sum,
                        n_tokens, scale_in, scale_out);
   } else {
-    const dim3 grid(grid_for((size_t)D.B * D.d / 4, 256 * 4, 2048), D.L);
-    if (bf16)
-      hipLaunchKernelGGL((normalise_rows_kernel<bf16_t>), grid, dim3(256), 0, s, D, norm_sum, n_tokens,
-                         (const bf16_t*)a_in, (bf16_t*)a_out);
-    else
-      hipLaunchKernelGGL((normalise_rows_kernel<float>), grid, dim3(256), 0, s, D, norm_sum, n_tokens,
-                         (const float*)a_in, (float*)a_out);
+    const size_t per_wg = 256 * NORM_LOADS * (bf16 ? 8 : 4), n = (size_t)D.B * D.d;      // elements (rows are multiples of 8 elements)
+    const dim3 grid((unsigned)((n + per_wg - 1) / per_wg), D.L);
+    const bool stream = (double)D.L * n * (bf16 ? 2 : 4) > 128e6;
+#define CLT_NORM(T, STREAM) \
+  hipLaunchKernelGGL((normalise_rows_kernel<T, STREAM>), grid, dim3(256), 0, s, D, norm_sum, n_tokens, (const T*)a_in, (T*)a_out)
+    if (bf16) { if (stream) CLT_NORM(bf16_t, true); else CLT_NORM(bf16_t, false); }
+    else { if (stream) CLT_NORM(float, true); else CLT_NORM(float, false); }
+#undef CLT_NORM
   }
   return hipGetLastError();
 }

@@ -152,3 +152,20 @@ def test_normalisation_argument_errors():
     with pytest.raises(K.CLTError):
         K.clt_normalise(sn.H, sums, 40, scale_in=sc, scale_out=sc)
     assert torch.all(xf == 1.0) and torch.all(sc == 1.0)
+
+
+@pytest.mark.parametrize("dtype,L,B,d", [("bf16", 2, 16401, 2048), ("f32", 1, 4099, 8200), ("bf16", 3, 5, 8), ("f32", 2, 33, 264)])
+def test_division_of_batches_beyond_and_within_the_cache(dtype, L, B, d):
+    """The division streams batches of more than 128 MB past the cache and leaves smaller ones in it; the last pieces of a layer
+    are ragged either way.  One fp32 product per element, rounded to the storage type: exact."""
+    from paper_2603_21014_amd import binding as K
+    T = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cfg = K.make_config(L, d, 8, B, K.DTYPE_BF16 if dtype == "bf16" else K.DTYPE_F32)
+    H = K.clt_init(cfg, torch.empty(K.clt_workspace_bytes(cfg), dtype=torch.uint8, device="cuda:0"))
+    a = torch.randn((L, B, d), generator=torch.Generator(device="cuda:0").manual_seed(7), device="cuda:0").to(T)
+    s = torch.tensor([3.0 + l for l in range(L)], dtype=torch.float64, device="cuda:0")
+    out = torch.full_like(a, float("nan"))
+    K.clt_normalise(H, s, 2 * B, a_in=a, a_out=out)
+    k = (2.0 * B / s).float()
+    for l in range(L):
+        assert torch.equal(out[l], (a[l].float() * k[l]).to(T))
