@@ -645,7 +645,6 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   if (fold) { za.x_scale = h->int8 ? x_scale : nullptr; za.part_theta = part; za.part_benc = part2; za.part_below = part3; }
   const int nparts = fold ? fold_row_blocks(D) : rbs;
   PartsSwitch psw;
-  if (fold && mode == CLT_DECODE_AUTO) psw = PartsSwitch{flags, kcap, rbs};
   DWdecArgs wa{z, d_yhat, W_dec, G, norms, gW_dec, fdec, skip, kcap};
   if (h->n2_eligible && fdec.m) wa.n2_part = reinterpret_cast<float*>(h->ws + h->plan.n2_part);
   DWencArgs ea{x, dpre, gW_enc, W_enc, fenc};
@@ -657,6 +656,10 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
                   reinterpret_cast<int32_t*>(h->ws + h->plan.fl_seg), kcap,
                   sparse_dwdec_takes_dz(h->bf16, D) && h->plan.ecap ? reinterpret_cast<float*>(h->ws + h->plan.dz_part) : nullptr,
                   h->plan.ecap};
+  // Automatic mode: a list-driven backward always takes dz inside the row kernel of dW_dec (longer lists go back to the dense
+  // kernels), so without the dead-feature term, whose entries are not listed, the kernel that sums the partials does the rest.
+  const bool lists_final = fold && mode == CLT_DECODE_AUTO && fl.dz_part && lam1_over_b == 0.f;
+  if (fold && mode == CLT_DECODE_AUTO) psw = PartsSwitch{flags, kcap, lists_final ? 1 : rbs};
   if (mode != CLT_DECODE_DENSE) {
     // The row kernel of dW_dec runs before the rest of the backward: when the lists are short enough it also takes
     // the dot products that make up dz at the listed entries, and the separate gather kernel stands down.  (It
@@ -669,12 +672,13 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
       RUN(h, s, K_GATHER_DZ, launch_gather_dz(s, h->bf16, D, gl, d_yhat, W_dec, norms, lam_c_over_b, h->cfg.C, dpre,
                                               flags, &fl));
     RUN(h, s, K_SP_DWDEC, launch_sparse_dwdec(s, h->bf16, D, fl, wa, flags));
-    RUN(h, s, K_GATHER_DZ, launch_dz_from_partials(s, h->bf16, D, fl, norms, lam_c_over_b, h->cfg.C, dpre, flags));
+    RUN(h, s, K_GATHER_DZ, launch_dz_from_partials(s, h->bf16, D, fl, norms, lam_c_over_b, h->cfg.C, dpre, flags, lists_final,
+                                                   h->int8 ? x_scale : nullptr, part, part2));
   }
   if (mode != CLT_DECODE_GATHER) {
     if (h->bf16) RUN(h, s, K_DZ, launch_dz_bf16(s, D, za)); else RUN(h, s, K_DZ, launch_dz_f32(s, D, za));
   }
-  if (!fold || mode == CLT_DECODE_AUTO)
+  if (!fold || (mode == CLT_DECODE_AUTO && !lists_final))
     RUN(h, s, K_STE, launch_ste_reduce(s, h->bf16, D, dpre, act_class, h->int8 ? x_scale : nullptr, norms, lam1_over_b,
                                        part, part2, part3, fold ? flags : nullptr, kcap));
   // (db_dec from the column partials that clt_loss left behind)

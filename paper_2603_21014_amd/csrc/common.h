@@ -360,7 +360,7 @@ hipError_t launch_sparse_dpre_fill(hipStream_t s, bool bf16, Dims D, const uint8
                                    float lam1_over_b, void* dpre, const int32_t* flags, int kcap);
 hipError_t init_gather();   // once per process, after the device is chosen
 // Per (layer, feature): tokens on which the feature is active or inside the threshold window, ascending, with z
-// (0 for the window-only ones; transpose of the row lists).
+// (0 for the window-only ones; transpose of the row lists; with bf16 storage the active and window bits in the value's low bits).
 // Layer l's entries start at l * B * kcap; off is layer-local.  seg holds FL_SEGS x L*F partial counts.
 constexpr int FL_SEGS = 16;
 // dz_part / ecap: room for the partial dot products of the fused dz (see fused_dz_selected), P x 8 x ecap floats.
@@ -382,9 +382,11 @@ hipError_t launch_gather_dz(hipStream_t s, bool bf16, Dims D, GatherLists g, con
 // through the decoder back to the dense kernels.
 hipError_t launch_feature_lists(hipStream_t s, bool bf16, Dims D, const uint8_t* cls, const void* z, FeatureLists fl,
                                 int32_t* flags, bool dense_when_too_long);
-// d pre at the listed entries from the partial dot products the row kernel of dW_dec left (fused_dz_selected only)
+// d pre at the listed entries from the partial dot products the row kernel of dW_dec left (fused_dz_selected only).  final (bf16,
+// no dead-feature term): d pre in its final form, and the column sums of dz over the window and of d pre, one row of [L, F] each.
 hipError_t launch_dz_from_partials(hipStream_t s, bool bf16, Dims D, FeatureLists fl, const float* norms,
-                                   float lam_c_over_b, float C, void* dpre, const int32_t* flags);
+                                   float lam_c_over_b, float C, void* dpre, const int32_t* flags, bool final, const float* x_scale,
+                                   float* sum_theta, float* sum_benc);
 // dW_dec[p(l,lp)][f,:] = sum_{b in list(l,f)} z[l,b,f] d_yhat[lp,b,:] + (G/n)[l,f] W_dec[p][f,:], with the optional
 // fused Adam update of the row (every row is visited: Adam also moves rows without gradient)
 // (a.n2_part, bf16 with the fused update and d a multiple of 64: the row kernel leaves the same sums of squares of the

@@ -745,11 +745,17 @@ __global__ __launch_bounds__(256) void fl_fill_kernel(Dims D, const uint8_t* __r
       for (int i = 0; i < 4; ++i)
         if ((a4 >> (8 * i)) & 1u) {
           fl.tok[base + pos[i]] = b;
-          fl.val[base + pos[i]] = zz[i];
+          // (bf16 storage: the class travels in the low bits that a bf16 value leaves free)
+          fl.val[base + pos[i]] = sizeof(T) == 2 ? __uint_as_float(__float_as_uint(zz[i]) | ((c8[u] >> (8 * i)) & 3u)) : zz[i];
           ++pos[i];
         }
     }
   }
+}
+
+// z of a feature-list entry (see fl_fill_kernel)
+template <typename T> __device__ __forceinline__ float list_z(float v) {
+  return sizeof(T) == 2 ? __uint_as_float(__float_as_uint(v) & 0xffff0000u) : v;
 }
 
 // One item = (layer l, feature f, pair of targets): a workgroup of 256 lanes, 8 columns each,
@@ -804,7 +810,7 @@ __device__ __forceinline__ void sparse_dwdec_rows(const Dims& D, int l, int f, i
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int b = __builtin_amdgcn_readfirstlane(tk[j + u]);
-      zv[u] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tv[j + u])));
+      zv[u] = list_z<T>(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tv[j + u]))));
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const T* row = d_yhat + ((size_t)(lp0 + t) * D.B + b) * D.d;
@@ -827,7 +833,7 @@ __device__ __forceinline__ void sparse_dwdec_rows(const Dims& D, int l, int f, i
   }
   for (; j < cnt; ++j) {
     const int b = __builtin_amdgcn_readfirstlane(tk[j]);
-    const float zv = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tv[j])));
+    const float zv = list_z<T>(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tv[j]))));
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const T* row = d_yhat + ((size_t)(lp0 + t) * D.B + b) * D.d;
@@ -1310,7 +1316,7 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
                 const uint32_t at = (r * 64 + lane) * 4 < cols ? (uint32_t)tkl[off + e] * row_bytes + (uint32_t)(c0 + (r * 64 + lane) * 4) * 2u : 0x80000000u;
                 const nt_u32x2 raw = __builtin_bit_cast(nt_u32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, (int)at, 0, 0));
                 const float4 y = E::widen4(raw);
-                const float z = tvl[off + e];
+                const float z = list_z<bf16_t>(tvl[off + e]);
                 a4[r] = make_float4(fmaf(z, y.x, a4[r].x), fmaf(z, y.y, a4[r].y), fmaf(z, y.z, a4[r].z), fmaf(z, y.w, a4[r].w));
               }
             }
@@ -1356,25 +1362,36 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
   }
 }
 
-// Fused dz, second half: 16 lanes per (layer, feature) sum the partial dot products of each listed entry over the
-// targets and the eight column slices, always in that order, add the gradient of the sparsity term and write d pre.
-template <typename T>
+// Fused dz, second half: an entry's partial dot products summed over the targets and the eight column slices, always in that
+// order, plus the gradient of the sparsity term.  Bound by the partials, 8 floats per entry and target: a workgroup takes the
+// entries of 64 consecutive features one per lane, which reads them in whole lines (16 lanes per feature, in pieces of 64 bytes at
+// 4 KB and more from each other: 0.80 ms at L = 16, 41 entries per feature and layer; 0.40 now).
+// FINAL (bf16 storage, no dead-feature term): what ste_reduce_kernel does elsewhere in a scan of the dense arrays (0.43 ms there): the
+// final d pre (times the x scale for int8 inputs) and the column sums for d theta and d b_enc, an entry's dz going through its first
+// partial's place.
+template <typename T, bool FINAL>
 __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLists fl, const float* __restrict__ norms,
                                                                float lam_c_over_b, float C, T* __restrict__ dpre,
-                                                               const int32_t* __restrict__ flags) {
+                                                               const int32_t* __restrict__ flags, const float* __restrict__ x_scale,
+                                                               float* __restrict__ sum_theta, float* __restrict__ sum_benc) {
   if (!fused_dz_selected(flags, fl)) return;
-  const int sub = threadIdx.x & 15;
-  const long lf = (long)blockIdx.x * 16 + (threadIdx.x >> 4);
-  if (lf >= (long)D.L * D.F) return;
-  const int l = (int)(lf / D.F), f = (int)(lf % D.F);
-  const int cnt = fl.cnt[lf], off = fl.off[lf];
-  const float nn = norms[lf];
-  const int32_t* tk = fl.tok + (size_t)l * D.B * fl.kcap + off;
-  const float* tv = fl.val + (size_t)l * D.B * fl.kcap + off;
-  for (int j = sub; j < cnt; j += 16) {
+  __shared__ int off_s[64], cnt_s[64];
+  __shared__ float nn_s[64];
+  const int groups = (D.F + 63) / 64, l = (int)(blockIdx.x / groups), f0 = (int)(blockIdx.x % groups) * 64, nf = min(64, D.F - f0);
+  if (threadIdx.x < 64) {
+    const size_t lf = (size_t)l * D.F + f0 + min((int)threadIdx.x, nf - 1);
+    off_s[threadIdx.x] = fl.off[lf];
+    cnt_s[threadIdx.x] = (int)threadIdx.x < nf ? fl.cnt[lf] : 0;
+    nn_s[threadIdx.x] = norms[lf];
+  }
+  __syncthreads();
+  const int e0 = off_s[0], e1 = off_s[nf - 1] + cnt_s[nf - 1];
+  const size_t lists = (size_t)l * D.B * fl.kcap;
+  float* const part = fl.dz_part + (size_t)packed_index(l, l, D.L) * 8 * fl.ecap;      // the targets' partials follow each other
+  const int n = (D.L - l) * 8;
+  for (int e = e0 + threadIdx.x; e < e1; e += 256) {
     float acc = 0.f;
-    const float* q = fl.dz_part + (size_t)packed_index(l, l, D.L) * 8 * fl.ecap + off + j;      // the targets' partials follow each other
-    const int n = (D.L - l) * 8;
+    const float* q = part + e;
     int i = 0;
     for (; i + 32 <= n; i += 32) {      // four targets' partials in flight
       float p[32];
@@ -1387,11 +1404,41 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc += q[(size_t)(i + u) * fl.ecap];
     }
-    const float zv = tv[j];
+    int k = 0;      // the last feature that starts at or before e (empty ones before it start there too)
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1)
+      if (k + step < nf && off_s[k + step] <= e) k += step;
+    const float v = fl.val[lists + e], zv = list_z<T>(v), nn = nn_s[k];
+    const int b = fl.tok[lists + e];
     const float ex = __builtin_amdgcn_exp2f(-2.0f * 1.4426950408889634f * C * nn * fabsf(zv));
     const float sden = 1.0f + ex;
     const float gsp = 4.0f * lam_c_over_b * nn * ex * __builtin_amdgcn_rcpf(sden * sden);
-    Elem<T>::store(dpre + ((size_t)l * D.B + tk[j]) * D.F + f, acc + gsp);
+    const float dz = acc + gsp;
+    T* const out = dpre + ((size_t)l * D.B + b) * D.F + f0 + k;
+    if (!FINAL) {
+      Elem<T>::store(out, dz);
+    } else {
+      part[e] = dz;
+      if (__float_as_uint(v) & CLS_ACTIVE) Elem<T>::store(out, x_scale ? dz * x_scale[(size_t)l * D.B + b] : dz);
+    }
+  }
+  if (!FINAL) return;
+  __threadfence_block();
+  __syncthreads();
+  for (int k = threadIdx.x >> 4; k < nf; k += 16) {      // 16 lanes per feature
+    float st = 0.f, sb = 0.f;
+    for (int j = threadIdx.x & 15; j < cnt_s[k]; j += 16) {
+      const float dz = part[off_s[k] + j];
+      const uint32_t c = __float_as_uint(fl.val[lists + off_s[k] + j]);
+      st += (c & CLS_WINDOW) ? dz : 0.f;
+      sb += (c & CLS_ACTIVE) ? dz : 0.f;
+    }
+    st = row16_sum(st);
+    sb = row16_sum(sb);
+    if ((threadIdx.x & 15) == 0) {
+      sum_theta[(size_t)l * D.F + f0 + k] = st;
+      sum_benc[(size_t)l * D.F + f0 + k] = sb;
+    }
   }
 }
 
@@ -1515,15 +1562,15 @@ static bool sparse_dwdec_sliced(bool bf16, Dims D) {
 bool sparse_dwdec_takes_dz(bool bf16, Dims D) { return sparse_dwdec_sliced(bf16, D) && !getenv("CLT_NO_FUSED_DZ"); }
 
 hipError_t launch_dz_from_partials(hipStream_t s, bool bf16, Dims D, FeatureLists fl, const float* norms,
-                                   float lam_c_over_b, float C, void* dpre, const int32_t* flags) {
+                                   float lam_c_over_b, float C, void* dpre, const int32_t* flags, bool final, const float* x_scale,
+                                   float* sum_theta, float* sum_benc) {
   if (!fl.dz_part) return hipSuccess;
-  const dim3 grid((unsigned)(((size_t)D.L * D.F + 15) / 16));
-  if (bf16)
-    hipLaunchKernelGGL((dz_from_partials_kernel<bf16_t>), grid, dim3(256), 0, s, D, fl, norms, lam_c_over_b, C,
-                       (bf16_t*)dpre, flags);
-  else
-    hipLaunchKernelGGL((dz_from_partials_kernel<float>), grid, dim3(256), 0, s, D, fl, norms, lam_c_over_b, C,
-                       (float*)dpre, flags);
+  const dim3 grid((unsigned)((size_t)D.L * ((D.F + 63) / 64)));
+#define CLT_DZP(T, FINAL)                                                                                             \
+  hipLaunchKernelGGL((dz_from_partials_kernel<T, FINAL>), grid, dim3(256), 0, s, D, fl, norms, lam_c_over_b, C, (T*)dpre, flags, \
+                     x_scale, sum_theta, sum_benc)
+  if (!bf16) CLT_DZP(float, false); else if (final) CLT_DZP(bf16_t, true); else CLT_DZP(bf16_t, false);
+#undef CLT_DZP
   return hipGetLastError();
 }
 

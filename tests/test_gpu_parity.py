@@ -717,6 +717,22 @@ def test_vectors_and_losses_at_the_edges_of_their_launches(dtype, L, d, F, B, la
         show(f"vectors {dtype} L={L} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL[dtype]))
 
 
+@pytest.mark.parametrize("workload,d,F,B,topk", [("tiny", 72, 520, 130, 0), ("llama1b_int8", 264, 328, 300, 0), ("tiny", 256, 72, 66, 0),
+                                                 ("tiny", 136, 264, 90, 6)])
+def test_list_backward_finished_from_the_lists(workload, d, F, B, topk):
+    """Automatic mode, bf16 storage, no dead-feature term: the kernel that sums the dz partials writes the final d pre and the sums
+    for d theta and d b_enc, 64 features per workgroup (the last group ragged; features without a token, entries that are only in
+    the window), with and without row scales of x."""
+    w = S.scaled(S.WORKLOADS[workload], dtype="bf16", L=3, d=d, F=F, B=B, seed=93, topk=topk, **({"lambda0": 0.0} if topk else {}))
+    theta = None if topk else sparse_theta(w, 0.02)
+    for fused in (False, True):
+        g, o = run_both(w, theta=theta, decode_mode=AUTO, gather_density_threshold=0.2, list_backward_density_threshold=0.3, fused=fused)
+        assert g.decode_switch[0] & 2 and int(g.decode_switch[3]) > 0 and "ste_reduce" not in g.kernel_launches
+        assert topk or (g.window & ~g.active).any()
+        assert (~(g.active | g.window).any(axis=1)).any() or B > 250
+        show(f"finished from the lists {workload} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL["bf16"]))
+
+
 def test_gather_dz_lds_chunks_and_fallback(monkeypatch):
     """Backward through the lists when a token's d y_hat rows exceed 64 KB of LDS (fp32, d=2048: eight targets per
     chunk, nine targets from layer 0, so a second chunk of one), and the one-wave-per-entry kernel, which otherwise
