@@ -363,7 +363,9 @@ hipError_t init_gather();   // once per process, after the device is chosen
 // (0 for the window-only ones; transpose of the row lists; with bf16 storage the active and window bits in the value's low bits).
 // Layer l's entries start at l * B * kcap; off is layer-local.  seg holds FL_SEGS x L*F partial counts.
 constexpr int FL_SEGS = 16;
-// dz_part / ecap: room for the partial dot products of the fused dz (see fused_dz_selected), P x 8 x ecap floats.
+// Column slices that the row kernel of dW_dec cuts the rows into, and so partial dot products of dz per entry and target
+__host__ __device__ inline int dz_slices(bool bf16, int d) { return !bf16 || d > 1024 ? 8 : d > 512 ? 4 : d > 256 ? 2 : 1; }
+// dz_part / ecap: room for the partial dot products of the fused dz (see fused_dz_selected), P x dz_slices x ecap floats.
 struct FeatureLists { int32_t* off; int32_t* cnt; int32_t* tok; float* val; int32_t* seg; int kcap; float* dz_part; int ecap; };
 // flags[3] = longest per-layer total of the feature lists (raised by launch_feature_lists, cleared by
 // launch_decode_decide).  While it fits ecap, the row kernel of dW_dec also takes the dot products d y_hat . W_dec of

@@ -1131,8 +1131,9 @@ __global__ __launch_bounds__(256, MASTER ? 5 : 6) void sparse_dwdec_sliced_kerne
   }
 }
 
-// columns of a slice: an eighth of d, whole runs of 8
-__host__ __device__ inline int slice_cols(int d) { return (d + 63) / 64 * 8; }
+// bf16 storage: slices of at most 256 columns where eight of them make up d, fewer slices for smaller d (with eight of 32 columns at d =
+// 256 a wavefront's 64 lanes held 8 quads of columns): slices, and columns of a slice in whole runs of 8.
+__host__ __device__ inline int slice_cols(int d) { const int S = dz_slices(true, d); return (d + 8 * S - 1) / (8 * S) * 8; }
 
 // bf16 storage.  What bounds it: the bytes that come back through the vector caches, state and gathered rows added up (a wavefront's
 // loads return in order, so rows that wait in the L2 do not overtake state on its way from HBM), and below a few tokens per
@@ -1145,8 +1146,9 @@ __host__ __device__ inline int slice_cols(int d) { return (d + 63) / 64 * 8; }
 // the product is column 8 m + n of the sum over the 4 entries: products exact, sums fp32.  The dot products for dz stay on the
 // vector unit (packed, 16 lanes per entry, four entries per cross-lane sum).  z is a bf16 value: nothing is rounded.
 // L = 16, d = 2048, F = 8192, 4096 tokens with the update, against one entry at a time with 8 bytes per lane: 82 active features per
-// token 19.1 -> 15.0 ms, 16: 9.05 -> 8.35, 2.5: 7.4 either way.  Whole steps at L = 12, d = 768, F = 6144: 12.2 -> 8.7 ms at
-// 1 % active, 8.3 -> 6.9 at 0.4 %.  More rows or the next feature's state in flight per wavefront: no faster (16.4 to 18.3 ms).
+// token 19.1 -> 15.0 ms, 16: 9.05 -> 8.35, 2.5: 7.4 either way.  Whole steps (with the other changes to the list-driven path) at L = 12,
+// d = 768, F = 6144: 12.2 -> 7.5 ms at 1 % active, 8.4 -> 5.0 at 0.4 %; of that from four slices instead of eight: 8.5 -> 7.5, 5.7 -> 5.0.
+// L = 8, d = 200, F = 2000, 1000 tokens, 1 %: 725 -> 361 us, 555 with eight slices.  More rows or the next feature's state in flight per wavefront: no faster (16.4 to 18.3 ms).
 // NH: runs of 128 columns per pass.  ADAM: 0 gradient only, 1 with the update, 2 with fp32 master weights.
 constexpr int SDM_ITEMS = 4;      // quads of features per workgroup; 2: 1.5 % slower, 8: 3 %
 template <int NH, int ADAM>
@@ -1168,8 +1170,9 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
   nt_u32x2* const wts8 = reinterpret_cast<nt_u32x2*>(smem[wv] + 2048);                   // and as the lanes load them
   // the B operand's diagonal: lane (t, n) holds z_t at k = n of its run of 8
   const uint32_t half = i16 >= 8 ? 0u : (i16 & 1) ? 0xffff0000u : 0x0000ffffu;
-  const int slice = blockIdx.x & 7, wg = blockIdx.x >> 3, nwg = gridDim.x >> 3;      // (gridDim.x is a multiple of 8)
-  const int sw = slice_cols(D.d), slots = (sw + 255) / 256, passes = NH == 4 ? (sw + COLS - 1) / COLS : 1;
+  // (gridDim.x is a multiple of 8.  With fewer slices than XCDs 8 / S of them take the same slice, each its share of the features)
+  const int S = dz_slices(true, D.d), slice = blockIdx.x & (S - 1), wg = blockIdx.x / S, nwg = gridDim.x / S;
+  const int sw = slice_cols(D.d), slots = 8 * ((D.d + 2047) / 2048) / S, passes = NH == 4 ? (sw + COLS - 1) / COLS : 1;
   const int F4 = (D.F + 3) / 4;
   const bool dz_on = fused_dz_selected(flags, fl);
   const uint32_t row_bytes = (uint32_t)D.d * 2;
@@ -1181,6 +1184,7 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
   const int pair = packed_index(l, lp, D.L);
   const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(d_yhat + (size_t)lp * D.B * D.d), 0, (int)((size_t)D.B * D.d * 2), 0x00020000);
+  const size_t pairF = (size_t)pair * D.F;
   const int32_t* const tkl = fl_tok + (size_t)l * D.B * fl.kcap;
   const float* const tvl = fl_val + (size_t)l * D.B * fl.kcap;
   const size_t lF = (size_t)l * D.F;
@@ -1200,7 +1204,7 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
       const int cnt_n = fl_cnt[lF + fn], off_n = fl_off[lF + fn];
       const float Gf = G[lF + f], nf = norms[lF + f];
       const size_t o = ((size_t)pair * D.F + f) * D.d;
-      float* dz_out = dz_on ? fl.dz_part + ((size_t)pair * 8 + slice) * fl.ecap + off : nullptr;
+      float* dz_out = dz_on ? fl.dz_part + ((size_t)pair * S + slice) * fl.ecap + off : nullptr;
       uint32_t tok_n = 0, val_n = 0;
       for (int ps = 0; ps < passes; ++ps) {
         const int c0 = slice * sw + ps * COLS;
@@ -1248,9 +1252,9 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
             wave_lds_order();
             float dz_keep = 0.f;
             for (int j = 0; j < n; j += 16) {
-              float pd[4] = {0.f, 0.f, 0.f, 0.f};
-              auto sets = [&](auto first) {      // two sets of 4 entries, one entry per row of 16 lanes
-                constexpr int u0 = decltype(first)::value;
+              const bool o1 = lane & 1, o2 = lane & 2;
+              auto sets = [&](int u0) -> float {      // two sets of 4 entries, one entry per row of 16 lanes; their dot products in turn
+                float pd[2] = {0.f, 0.f};
                 nt_u32x2 en[2];
                 u32x4_lds q[2][NH];
 #pragma unroll
@@ -1268,15 +1272,13 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
                   for (int h = 0; h < NH; ++h) {
                     acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_mfma, q[u][h]), __builtin_bit_cast(bf16x8_mfma, zd), acc[h], 0, 0, 0);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) pd[u0 + u] = dot2_bf16(q[u][h][k], w8[h][k], pd[u0 + u]);
+                    for (int k = 0; k < 4; ++k) pd[u] = dot2_bf16(q[u][h][k], w8[h][k], pd[u]);
                   }
                 }
+                return (o1 ? pd[1] : pd[0]) + dpp_move<0xB1>(o1 ? pd[0] : pd[1]);
               };
-              sets(std::integral_constant<int, 0>{});
-              if (j + 8 < n) sets(std::integral_constant<int, 2>{});
-              const bool o1 = lane & 1, o2 = lane & 2;
-              const float r1 = (o1 ? pd[1] : pd[0]) + dpp_move<0xB1>(o1 ? pd[0] : pd[1]);
-              const float r2 = (o1 ? pd[3] : pd[2]) + dpp_move<0xB1>(o1 ? pd[2] : pd[3]);
+              const float r1 = sets(0);
+              const float r2 = j + 8 < n ? sets(2) : 0.f;
               float r = (o2 ? r2 : r1) + dpp_move<0x4E>(o2 ? r1 : r2);
               r += dpp_move<0x128>(r);      // row_ror:8
               r += dpp_move<0x124>(r);      // row_ror:4
@@ -1351,7 +1353,9 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
               const int b16 = __float_as_int(row16_sum(sq));
               const float tot = (__int_as_float(__builtin_amdgcn_readlane(b16, 0)) + __int_as_float(__builtin_amdgcn_readlane(b16, 16))) +
                                 (__int_as_float(__builtin_amdgcn_readlane(b16, 32)) + __int_as_float(__builtin_amdgcn_readlane(b16, 48)));
-              if (lane == 0) n2_part[((size_t)pair * D.F + f) * (8 * slots) + slice * slots + ps * R + r] = tot;
+              // (the slice's slots are written by its last sums: those that no columns belong to with zeros)
+              const int at = ps * R + r, end = ps + 1 == passes && r + 1 == R ? slots : at + 1;
+              if (lane < end - at) n2_part[(pairF + f) * (S * slots) + slice * slots + at + lane] = lane == 0 ? tot : 0.f;
             }
           }
         }
@@ -1387,8 +1391,9 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
   __syncthreads();
   const int e0 = off_s[0], e1 = off_s[nf - 1] + cnt_s[nf - 1];
   const size_t lists = (size_t)l * D.B * fl.kcap;
-  float* const part = fl.dz_part + (size_t)packed_index(l, l, D.L) * 8 * fl.ecap;      // the targets' partials follow each other
-  const int n = (D.L - l) * 8;
+  const int S = dz_slices(sizeof(T) == 2, D.d);
+  float* const part = fl.dz_part + (size_t)packed_index(l, l, D.L) * S * fl.ecap;      // the targets' partials follow each other
+  const int n = (D.L - l) * S;
   for (int e = e0 + threadIdx.x; e < e1; e += 256) {
     float acc = 0.f;
     const float* q = part + e;
@@ -1400,10 +1405,14 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
 #pragma unroll
       for (int u = 0; u < 32; ++u) acc += p[u];
     }
-    for (; i < n; i += 8) {
+    for (; i + 8 <= n; i += 8) {
+      float p[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc += q[(size_t)(i + u) * fl.ecap];
+      for (int u = 0; u < 8; ++u) p[u] = q[(size_t)(i + u) * fl.ecap];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += p[u];
     }
+    for (; i < n; ++i) acc += q[(size_t)i * fl.ecap];
     int k = 0;      // the last feature that starts at or before e (empty ones before it start there too)
 #pragma unroll
     for (int step = 32; step > 0; step >>= 1)
@@ -1578,7 +1587,7 @@ template <int NH>
 static hipError_t launch_sparse_dwdec_mfma(hipStream_t s, Dims D, const FeatureLists& fl, const DWdecArgs& a, float* n2,
                                            const int32_t* flags) {
   // (every workgroup takes SDM_ITEMS quads of features while the grid allows it)
-  const size_t wgs = ((D.F + 3) / 4 + SDM_ITEMS - 1) / SDM_ITEMS, most = (size_t)1 << 19;
+  const size_t wgs = (((D.F + 3) / 4 + SDM_ITEMS - 1) / SDM_ITEMS * dz_slices(true, D.d) + 7) / 8, most = (size_t)1 << 19;
   const dim3 grid(8 * (unsigned)(wgs < most ? wgs : most), D.P());
 #define CLT_SDM(ADAM)                                                                                                 \
   hipLaunchKernelGGL((sparse_dwdec_mfma_kernel<NH, ADAM>), grid, dim3(256), 0, s, D, fl, (const bf16_t*)a.d_yhat,     \

@@ -733,6 +733,20 @@ def test_list_backward_finished_from_the_lists(workload, d, F, B, topk):
         show(f"finished from the lists {workload} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL["bf16"]))
 
 
+@pytest.mark.parametrize("d", [256, 768, 1024, 1280, 2304])
+def test_row_sums_left_by_the_row_kernel_for_every_number_of_slices(d):
+    """The row kernel of dW_dec cuts rows of bf16 into 1 to 8 slices; the sums of squares that it leaves for the next step's norms
+    come in one layout all the same."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=2, d=d, F=256, B=70, seed=94)
+    params = S.make_params(w)
+    x, y = S.make_inputs(w)
+    theta = sparse_theta(w, 0.1)
+    a = GpuRun(w, params, x, y, theta=theta, fused=True, pre_steps=1, reuse_decoder_norms=True, decode_mode=GATHER)
+    b = GpuRun(w, params, x, y, theta=theta, fused=True, pre_steps=1, decode_mode=GATHER)
+    assert a.kernel_launches.get("decoder_norms_from_update") == 1 and b.kernel_launches.get("decoder_norms") == 1
+    assert rel_l2(a.norms, b.norms) < 1e-6
+
+
 def test_gather_dz_lds_chunks_and_fallback(monkeypatch):
     """Backward through the lists when a token's d y_hat rows exceed 64 KB of LDS (fp32, d=2048: eight targets per
     chunk, nine targets from layer 0, so a second chunk of one), and the one-wave-per-entry kernel, which otherwise
