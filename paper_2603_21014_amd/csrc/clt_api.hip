@@ -23,7 +23,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
-  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_bdec, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part, row_squares,
+  size_t norms, G, d_yhat, dpre, part_cols, part_cols2, part_cols3, part_bdec, part_rec, part_sp, part_dead, l0, flags, xcd_sync, n2_part, pre32, g_idx, g_val, g_counts, g_counts_w, dz_part, split_part, wg_part, row_squares,
          fl_off, fl_cnt, fl_tok, fl_val, fl_seg, total;
   int kcap;
   int ecap;
@@ -202,6 +202,7 @@ Plan make_plan(const clt_config* c) {
     const Dims D{c->L, c->d, c->F, c->B};
     p.split = c->dtype == CLT_DTYPE_BF16 ? dec_split_bf16(D) : dec_split_f32(D);
   }
+  p.wg_part = o;    o += align_up(bf16 ? wg_split_floats(dims) * 4 : 0);
   p.split_part = o; o += align_up((size_t)p.split.groups * B * d * 4);
   // (automatic mode: the dense decode may stand down, so the norms keep their own kernel)
   const size_t squares = bf16 && c->decode_mode == CLT_DECODE_DENSE ? dec_row_squares_floats(dims) : 0;
@@ -648,6 +649,7 @@ static int backward_impl(clt_handle* h, hipStream_t s, const void* x, const floa
   DWdecArgs wa{z, d_yhat, W_dec, G, norms, gW_dec, fdec, skip, kcap};
   if (h->n2_eligible && fdec.m) wa.n2_part = reinterpret_cast<float*>(h->ws + h->plan.n2_part);
   DWencArgs ea{x, dpre, gW_enc, W_enc, fenc};
+  wa.split_part = ea.split_part = reinterpret_cast<float*>(h->ws + h->plan.wg_part);
   GatherLists gl{reinterpret_cast<int32_t*>(h->ws + h->plan.g_idx), reinterpret_cast<float*>(h->ws + h->plan.g_val),
                  reinterpret_cast<int32_t*>(h->ws + h->plan.g_counts),
                  reinterpret_cast<int32_t*>(h->ws + h->plan.g_counts_w), kcap, list_stride(kcap)};

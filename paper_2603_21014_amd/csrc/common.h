@@ -206,11 +206,16 @@ struct DWdecArgs {     // dW_dec[p] = z[l]^T dyhat[lp] + (G/n)[l,f] W_dec[p][f,:
   // optional, bf16 kernel with the fused update and F, d multiples of 256: [P][d / 64][F] sums of squares of the
   // updated weights (see launch_norms_from_partials)
   float* n2_part = nullptr;
+  float* split_part = nullptr;   // bf16 kernel: wg_split_floats(D) floats
 };
 struct DWencArgs {     // dW_enc[l] = x[l]^T dpre[l]
   const void* x; const void* dpre; void* dW_enc; void* W_enc;
   AdamFuseArgs fuse;
+  float* split_part = nullptr;   // bf16 kernel: wg_split_floats(D) floats
 };
+size_t wg_split_floats(Dims D);      // room for the partial sums of weight gradients whose tokens are cut into chunks (0: none are)
+hipError_t launch_combine_dwdec(hipStream_t s, Dims D, int chunks, const DWdecArgs& a);
+hipError_t launch_combine_dwenc(hipStream_t s, Dims D, int chunks, const DWencArgs& a);
 
 hipError_t launch_enc_f32(hipStream_t s, Dims D, const EncArgs& a);
 hipError_t launch_dec_f32(hipStream_t s, Dims D, const DecArgs& a);

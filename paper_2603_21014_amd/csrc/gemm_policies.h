@@ -585,4 +585,33 @@ struct Few : P {
   static constexpr bool ROW_SQUARES = ROW_SQUARES_, PERSISTENT = false, XCD_SYNC = false;
 };
 
+// Weight gradients whose tiles leave CUs idle: every tile's K range (the tokens) cut into `chunks`, each a group of tiles of its own
+// that leaves fp32 partial sums [group][chunk][M][N]; launch_combine_dwdec / _dwenc add them up and do the rest (see choose_wg_chunks).
+template <class P>
+struct SplitTokens : P {
+  static constexpr bool PERSISTENT = false, HALF_ROWS = true;
+  static constexpr int EPI_BATCH = 8, EPI_BATCH_LATE = 8, EPI_BATCH_LAST = 8;
+  int chunks; float* part;
+  struct GInfo : P::GInfo { int chunk, slot; };
+  struct Epi {};
+  struct EpiRegs {};
+  __device__ GInfo ginfo(int order) const {
+    GInfo g;
+    static_cast<typename P::GInfo&>(g) = P::ginfo(order / chunks);
+    g.chunk = order % chunks;
+    g.slot = order;
+    return g;
+  }
+  __device__ KRange krange(const GInfo& g, int spseg) const {      // (one segment; equal shares)
+    const int first = (int)((long)g.chunk * spseg / chunks);
+    return {first, (int)((long)(g.chunk + 1) * spseg / chunks) - first};
+  }
+  __device__ void epi_begin(Epi&, const GInfo&, int, bool, int, int) const {}
+  __device__ void epi_load(EpiRegs&, const GInfo&, const EpiPos&) const {}
+  __device__ void epi4(Epi&, const GInfo& g, const EpiPos& pos, float4 v, const EpiRegs&) const {
+    *reinterpret_cast<float4*>(epi_ptr(part, pos.uoff((size_t)g.slot * this->M, this->N), pos.loff(this->N))) = v;
+  }
+  __device__ void epi_end(Epi&, const GInfo&, float*) const {}
+};
+
 }  // namespace clt

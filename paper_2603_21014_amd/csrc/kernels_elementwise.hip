@@ -559,6 +559,58 @@ __global__ __launch_bounds__(256) void adam_kernel(size_t n4, T* __restrict__ p,
   }
 }
 
+// ---- weight gradients whose tokens were cut into chunks (see SplitTokens): the chunks' partial sums in order, then what the
+// contraction's epilogue does otherwise.  grid = (runs of 1024 elements of [M][N], groups); DEC: groups are decoder blocks, rows
+// features, with the norm term and, for the next step's norms, the sums of squares of runs of 64 updated weights.  Bound by its launch
+// and its traffic (16 bytes per lane, everything fp32 but the weights); 15 blocks of 2048 x 512 features with the update: 9 us.
+struct CombineArgs {
+  int chunks, M, N; const float* part; bf16_t* w; bf16_t* grad; AdamFuseArgs fuse;
+  const float* G; const float* norms; float* n2_part; const int32_t* skip_flags; int kcap;
+};
+template <bool DEC>
+__global__ __launch_bounds__(256) void combine_weight_gradient_kernel(Dims D, CombineArgs a) {
+  if (DEC && a.skip_flags && lists_backward_selected(a.skip_flags, a.kcap)) return;
+  typedef Elem<bf16_t> E;
+  const size_t n = (size_t)a.M * a.N, i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;      // (with n2_part n is a multiple of a workgroup's 1024)
+  const int g = blockIdx.y;
+  const size_t o = g * n + i;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int c = 0; c < a.chunks; ++c) {
+    const float4 q = *reinterpret_cast<const float4*>(a.part + ((size_t)g * a.chunks + c) * n + i);
+    v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+  }
+  float4 w4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (DEC || (a.fuse.m && !a.fuse.master)) w4 = E::load4(a.w + o);
+  const int f = (int)(i / a.N);
+  if (DEC) {
+    int l = 0, q = g;
+    while (q >= D.L - l) { q -= D.L - l; ++l; }
+    const float coef = a.G[(size_t)l * D.F + f] * __builtin_amdgcn_rcpf(fmaxf(a.norms[(size_t)l * D.F + f], 1e-30f));
+    v = make_float4(fmaf(coef, w4.x, v.x), fmaf(coef, w4.y, v.y), fmaf(coef, w4.z, v.z), fmaf(coef, w4.w, v.w));
+  }
+  if (a.grad) E::store4(a.grad + o, v);
+  if (!a.fuse.m) return;
+  const float4 m4 = *reinterpret_cast<const float4*>(a.fuse.m + o), v4 = *reinterpret_cast<const float4*>(a.fuse.v + o),
+               p4 = a.fuse.master ? *reinterpret_cast<const float4*>(a.fuse.master + o) : w4;
+  const float gg[4] = {v.x, v.y, v.z, v.w};
+  float mm[4] = {m4.x, m4.y, m4.z, m4.w}, vv[4] = {v4.x, v4.y, v4.z, v4.w}, pp[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) adam_element(pp[k], mm[k], vv[k], gg[k], a.fuse.a);
+  *reinterpret_cast<float4*>(a.fuse.m + o) = make_float4(mm[0], mm[1], mm[2], mm[3]);
+  *reinterpret_cast<float4*>(a.fuse.v + o) = make_float4(vv[0], vv[1], vv[2], vv[3]);
+  const float4 pn = make_float4(pp[0], pp[1], pp[2], pp[3]);
+  if (a.fuse.master) *reinterpret_cast<float4*>(a.fuse.master + o) = pn;
+  const E::Raw4 stored = E::narrow4(pn);
+  *reinterpret_cast<E::Raw4*>(a.w + o) = stored;
+  if (DEC && a.n2_part) {      // 16 lanes hold a run of 64 columns
+    const float4 wn = E::widen4(stored);
+    const float s2 = row16_sum((wn.x * wn.x + wn.y * wn.y) + (wn.z * wn.z + wn.w * wn.w));
+    if ((threadIdx.x & 15) == 0) a.n2_part[((size_t)g * (a.N >> 6) + (i % a.N >> 6)) * a.M + f] = s2;
+  }
+}
+
 // the three vectors in one launch, four elements per lane
 __global__ __launch_bounds__(256) void adam_vectors_kernel(AdamVectors q, AdamScalars a) {
   const int t = blockIdx.y, i = ((int)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -962,6 +1014,20 @@ hipError_t launch_adam_matrix(hipStream_t s, bool bf16, size_t n, void* p, const
       hipLaunchKernelGGL((adam_kernel<float, false>), grid, dim3(256), 0, s, n4, (float*)p, (const float*)g, m, v,
                          master, a);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_combine_dwdec(hipStream_t s, Dims D, int chunks, const DWdecArgs& a) {
+  const CombineArgs c{chunks, D.F, D.d, a.split_part, (bf16_t*)a.W_dec, (bf16_t*)a.dW_dec, a.fuse, a.G, a.norms,
+                      a.fuse.m && D.F % 256 == 0 && D.d % 256 == 0 ? a.n2_part : nullptr, a.skip_flags, a.kcap};
+  const dim3 grid((unsigned)(((size_t)D.F * D.d + 1023) / 1024), D.P());
+  hipLaunchKernelGGL((combine_weight_gradient_kernel<true>), grid, dim3(256), 0, s, D, c);
+  return hipGetLastError();
+}
+hipError_t launch_combine_dwenc(hipStream_t s, Dims D, int chunks, const DWencArgs& a) {
+  const CombineArgs c{chunks, D.d, D.F, a.split_part, (bf16_t*)a.W_enc, (bf16_t*)a.dW_enc, a.fuse, nullptr, nullptr, nullptr, nullptr, 0};
+  const dim3 grid((unsigned)(((size_t)D.F * D.d + 1023) / 1024), D.L);
+  hipLaunchKernelGGL((combine_weight_gradient_kernel<false>), grid, dim3(256), 0, s, D, c);
   return hipGetLastError();
 }
 

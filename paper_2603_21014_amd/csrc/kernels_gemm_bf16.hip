@@ -657,6 +657,9 @@ hipError_t init_gemm_bf16() {
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWdecPolicy<bf16_t, true, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWencPolicy<bf16_t, false>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<SplitTokens<DWdecPolicy<bf16_t, false>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<SplitTokens<DWencPolicy<bf16_t, false>>>()) != hipSuccess) return e;
+  if ((e = set_lds_attr<SplitTokens<DWencPolicy<bf16_t, false, int8_t>>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWencPolicy<bf16_t, true>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWencPolicy<bf16_t, false, int8_t>>()) != hipSuccess) return e;
   if ((e = set_lds_attr<DWencPolicy<bf16_t, true, int8_t>>()) != hipSuccess) return e;
@@ -725,7 +728,45 @@ static hipError_t launch_dwdec_mode(hipStream_t s, Dims D, const DWdecArgs& a) {
   }
   return hipSuccess;
 }
+// Weight gradients with few tiles (up to half the CUs): chunks of tokens that their K range is cut into, 0: not cut, and the
+// contraction's own epilogue does the rest.  One tile of 256 x 256 keeps one CU busy through all the tokens, and then through the
+// update: 1.3 MB and more of weights and moments at the 45 GB/s or so that a CU moves, while most of the chip waits.  Cut (one
+// chunk: the update alone is moved out), the partial sums and the second launch cost traffic but run on every CU.
+// The costs, us: a K step of 32 tokens 1.6; the epilogue 8, with the update 30; cut: the epilogue of partial sums and the second launch
+// 13, their traffic at 7 TB/s (it stays in the Infinity Cache).  Cut where the model says 15 % less or better.  Whole steps, uncut -> cut (us):
+// 4 layers of width 80, 768 features: 500 tokens 147 -> 102, 1920 tokens 218 -> 135; width 256, 1024 features: 400 tokens 162 -> 131,
+// 4096 tokens 387 -> 256; 6 layers of width 136, 264 features, 130 tokens 145 -> 109; 2 layers of width 1024, 2048 features, 4096
+// tokens 552 -> 452.  Over 23 sizes the nearest calls of the rule lie between 5 % gained and 1 % lost (5 TB/s in its place leaves 20 us of
+// the third of these; 10 TB/s loses 4 % at 5 layers of width 328, 2536 features, 1792 tokens, gradients only).
+static int choose_wg_chunks(int groups, int M, int N, int B, bool adam, bool master) {
+  const int tiles = groups * ((M + TM - 1) / TM) * ((N + TN - 1) / TN), steps = (B + TK - 1) / TK;
+  const double n = (double)groups * M * N;
+  int best = 0;
+  double cost = 0.85 * (1.6 * steps + (adam ? 30.0 : 8.0));
+  for (int c = 1; c <= 16 && c * tiles <= 256 && tiles <= 128 && (c == 1 || 2 * c <= steps); ++c) {
+    const double t = 1.6 * ((steps + c - 1) / c) + 13.0 + n * (8.0 * c + (adam ? (master ? 30.0 : 22.0) : 2.0)) / 7e6;
+    if (t < cost) { best = c; cost = t; }
+  }
+  return best;
+}
+size_t wg_split_floats(Dims D) {
+  size_t most = 0;
+  for (int mode = 0; mode < 3; ++mode) {
+    const size_t dec = (size_t)choose_wg_chunks(D.P(), D.F, D.d, D.B, mode > 0, mode > 1) * D.P();
+    const size_t enc = (size_t)choose_wg_chunks(D.L, D.d, D.F, D.B, mode > 0, mode > 1) * D.L;
+    most = std::max(most, std::max(dec, enc) * D.F * D.d);
+  }
+  return most;
+}
 hipError_t launch_dwdec_bf16(hipStream_t s, Dims D, const DWdecArgs& a) {
+  const int chunks = choose_wg_chunks(D.P(), D.F, D.d, D.B, a.fuse.m, a.fuse.master);
+  if (chunks > 0) {
+    typedef DWdecPolicy<bf16_t, false> P;
+    SplitTokens<P> p{P{D, D.F, D.d, D.B, D.F, D.d, (const bf16_t*)a.z, (const bf16_t*)a.d_yhat, (bf16_t*)a.W_dec, a.G, a.norms, nullptr,
+                       AdamFuse{}, a.skip_flags, a.kcap, 0, nullptr}, chunks, a.split_part};
+    const hipError_t e = launch(s, p, D.P() * chunks);
+    return e != hipSuccess ? e : launch_combine_dwdec(s, D, chunks, a);
+  }
   if (!a.fuse.m) return launch_dwdec_mode<false, false>(s, D, a);
   // the row sums of squares need every tile to take the unpredicated epilogue (all 16 lanes of a row at work)
   if (a.n2_part && D.F % TM == 0 && D.d % TN == 0) return launch_dwdec_mode<true, true>(s, D, a);
@@ -737,7 +778,16 @@ static hipError_t launch_dwenc_mode(hipStream_t s, Dims D, const DWencArgs& a) {
                                   (bf16_t*)a.dW_enc, (bf16_t*)a.W_enc, AdamFuse{a.fuse.m, a.fuse.v, a.fuse.master, a.fuse.a}};
   return launch(s, p, D.L);
 }
+template <typename TA>
+static hipError_t launch_dwenc_split(hipStream_t s, Dims D, const DWencArgs& a, int chunks) {
+  typedef DWencPolicy<bf16_t, false, TA> P;
+  SplitTokens<P> p{P{D, D.d, D.F, D.B, D.d, D.F, (const TA*)a.x, (const bf16_t*)a.dpre, nullptr, nullptr, AdamFuse{}}, chunks, a.split_part};
+  const hipError_t e = launch(s, p, D.L * chunks);
+  return e != hipSuccess ? e : launch_combine_dwenc(s, D, chunks, a);
+}
 hipError_t launch_dwenc_bf16(hipStream_t s, Dims D, const DWencArgs& a, bool int8_x) {
+  const int chunks = choose_wg_chunks(D.L, D.d, D.F, D.B, a.fuse.m, a.fuse.master);
+  if (chunks > 0) return int8_x ? launch_dwenc_split<int8_t>(s, D, a, chunks) : launch_dwenc_split<bf16_t>(s, D, a, chunks);
   if (int8_x) return a.fuse.m ? launch_dwenc_mode<true, int8_t>(s, D, a) : launch_dwenc_mode<false, int8_t>(s, D, a);
   return a.fuse.m ? launch_dwenc_mode<true, bf16_t>(s, D, a) : launch_dwenc_mode<false, bf16_t>(s, D, a);
 }

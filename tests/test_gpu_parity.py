@@ -747,6 +747,39 @@ def test_row_sums_left_by_the_row_kernel_for_every_number_of_slices(d):
     assert rel_l2(a.norms, b.norms) < 1e-6
 
 
+@pytest.mark.parametrize("L,d,F,B,master,int8", [
+    (1, 8, 8, 1, False, False),            # one chunk of one step: the update alone is moved out
+    (3, 80, 264, 130, True, False),        # ragged tiles and tokens
+    (2, 256, 512, 1999, False, False),     # several chunks, the last token step ragged
+    (2, 72, 520, 1500, False, True),
+])
+def test_weight_gradients_cut_over_tokens(L, d, F, B, master, int8):
+    """Weight gradients of few tiles leave their partial sums to a second kernel, with and without the update."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=L, d=d, F=F, B=B, seed=95, int8_inputs=int8, lambda1=0.1, master_weights=master)
+    for fused in (False, True):
+        g, o = run_both(w, decode_mode=DENSE, fused=fused)
+        show(f"cut over tokens L={L} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL["bf16"]))
+
+
+def test_weight_gradients_cut_over_tokens_leave_the_next_norms():
+    """The second kernel's sums of squares of updated weights, and its standing down where the lists went backward."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=2, d=256, F=512, B=300, seed=96)
+    params = S.make_params(w)
+    x, y = S.make_inputs(w)
+    for theta, mode in ((None, DENSE), (sparse_theta(w, 0.05), AUTO)):
+        kw = dict(theta=theta, fused=True, pre_steps=1, decode_mode=mode)
+        if mode == AUTO:
+            kw.update(gather_density_threshold=0.2, list_backward_density_threshold=0.3)
+        a = GpuRun(w, params, x, y, reuse_decoder_norms=True, **kw)
+        b = GpuRun(w, params, x, y, **kw)
+        assert a.kernel_launches.get("decoder_norms_from_update") == 1 and b.kernel_launches.get("decoder_norms") == 1
+        assert rel_l2(a.norms, b.norms) < 1e-6
+    g, o = run_both(w, theta=sparse_theta(w, 0.05), fused=True, decode_mode=AUTO, gather_density_threshold=0.2,
+                    list_backward_density_threshold=0.3)
+    assert g.decode_switch[0] & 2
+    show("cut over tokens, lists backward", compare_step(w, g, o, TOL["bf16"]))
+
+
 def test_gather_dz_lds_chunks_and_fallback(monkeypatch):
     """Backward through the lists when a token's d y_hat rows exceed 64 KB of LDS (fp32, d=2048: eight targets per
     chunk, nine targets from layer 0, so a second chunk of one), and the one-wave-per-entry kernel, which otherwise
