@@ -1,9 +1,12 @@
 """Builds libclt.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
 from __future__ import annotations
 
+import glob
 import os
+import re
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -19,10 +22,47 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Wall", "-Wno-unused-function"]
 
 
+def vector_work_without_lanes(asm: str) -> list:
+    """(kernel, instruction) of every vector instruction that an assembly listing has between the end of a loop over
+    lanes and the instruction that gives the wavefront its lanes back.
+
+    A loop that leaves its lanes one by one ends with EXEC empty.  The compiler writes such a loop around every buffer
+    access whose descriptor it cannot prove to be the same in all lanes, and its register allocator has put the store
+    of a spilled register right behind the loop, in front of the restoring move: nothing is stored, and the reload
+    brings whatever the scratch memory held.  (Seen on the row kernel of dW_dec with a descriptor held in vector
+    registers and a limit of 72 registers: wrong updates of the weights.)  Reads and writes of single lanes do not look
+    at EXEC."""
+    found, kernel, empty, last = [], "", False, ""
+    for line in asm.splitlines():
+        line = line.split(";")[0].strip()
+        if not line or line.startswith("."):
+            continue
+        label = re.match(r"(\S+):$", line)
+        if label:
+            kernel, empty = label.group(1), False
+            continue
+        if line.startswith("s_cbranch_execnz"):
+            empty = re.match(r"s_\w+ exec,", last) is not None
+        elif empty:
+            if re.match(r"s_\w+ exec,|s_\w+saveexec|s_branch|s_endpgm", line):
+                empty = False
+            elif re.match(r"(v_|ds_|buffer_|global_|flat_|scratch_)", line) and not re.match(r"v_(readlane|readfirstlane|writelane)", line):
+                found.append((kernel, line))
+        last = line
+    return found
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, src.replace(".hip", ".o"))
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-    r = subprocess.run(cmd, capture_output=True, text=True)
+    with tempfile.TemporaryDirectory() as tmp:          # -save-temps: the device code's assembly on its way to the object
+        cmd = [HIPCC, *FLAGS, "-save-temps", "-c", os.path.join(CSRC, src), "-o", obj]
+        r = subprocess.run(cmd, capture_output=True, text=True, cwd=tmp)
+        for f in glob.glob(os.path.join(tmp, "*gfx950.s")) if r.returncode == 0 else ():
+            with open(f) as h:
+                lost = vector_work_without_lanes(h.read())
+            if lost:
+                raise RuntimeError(f"{src}: vector instructions with no lane at work, behind a loop over lanes:\n" +
+                                   "\n".join(f"  {k}: {i}" for k, i in lost))
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
     if r.returncode != 0:

@@ -237,10 +237,18 @@ __device__ __forceinline__ void wave_lds_order() {      // a wave's LDS accesses
 // Streaming accesses of a wavefront to `bytes` bytes from a uniform address on: base and bounds in scalar registers, the lane's
 // 32-bit offset as it is; lanes beyond the end load zeros and store nothing.  (With pointers, base + lane of every array was hoisted
 // out of the item loop, two registers per lane each, and spilled.)
+// The descriptor is put into scalar registers here, whatever the compiler makes of its parts.  A descriptor that it takes for
+// different from lane to lane costs a loop over the lanes around every access, which ends with no lane at work; the register
+// allocator then puts copies and spill stores behind such a loop before the lanes come back, and their values are lost (a row kernel of
+// dW_dec like that, limited to 80 or 72 registers, gave wrong updates).  build.py refuses a listing that shows it.
 struct UniformRun {
   __amdgpu_buffer_rsrc_t d;
   static constexpr int NT = 2;      // cache policy: non-temporal
-  __device__ __forceinline__ UniformRun(const void* p, int bytes) : d(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000)) {}
+  __device__ __forceinline__ UniformRun(const void* p, int bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    d = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((uint64_t)hi << 32 | lo), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+  }
   __device__ __forceinline__ nt_f32x4 load_f4(uint32_t o) const { return __builtin_bit_cast(nt_f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, (int)o, 0, NT)); }
   __device__ __forceinline__ nt_u32x2 load8(uint32_t o) const { return __builtin_bit_cast(nt_u32x2, __builtin_amdgcn_raw_buffer_load_b64(d, (int)o, 0, NT)); }
   __device__ __forceinline__ uint32_t load4(uint32_t o) const { return __builtin_amdgcn_raw_buffer_load_b32(d, (int)o, 0, 0); }
