@@ -276,7 +276,7 @@ def clt_backward_adam_step(H: Handle, x, z, act_class, t: int, lr: float, params
 
 _VIEWS = {"norms": (0, torch.float32, lambda c: (c.L, c.F)), "d_yhat": (1, None, lambda c: (c.L, c.B, c.d)),
           "dpre": (2, None, lambda c: (c.L, c.B, c.F)), "G": (3, torch.float32, lambda c: (c.L, c.F)),
-          "decode_switch": (4, torch.int32, lambda c: (4,))}
+          "decode_switch": (4, torch.int32, lambda c: (5,))}
 
 
 def clt_workspace_view(H: Handle, which: str) -> torch.Tensor:

@@ -427,7 +427,7 @@ int clt_workspace_view(const clt_handle* h, int which, void** ptr, size_t* bytes
     case 1: *ptr = h->ws + h->plan.d_yhat; *bytes = L * B * d * h->esz; break;
     case 2: *ptr = h->ws + h->plan.dpre; *bytes = L * B * F * h->esz; break;
     case 3: *ptr = h->ws + h->plan.G; *bytes = L * F * 4; break;
-    case 4: *ptr = h->ws + h->plan.flags; *bytes = 16; break;
+    case 4: *ptr = h->ws + h->plan.flags; *bytes = 5 * 4; break;
     default: return CLT_ERR_INVALID_ARG;
   }
   return CLT_OK;

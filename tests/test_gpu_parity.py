@@ -670,10 +670,11 @@ def test_gather_wide_model_dim_and_empty_rows():
         assert (g.y_hat[lp] == params["b_dec"][lp].numpy()[None, :]).all()
 
 
-@pytest.mark.parametrize("L,d,F,B,rho", [(12, 136, 6144, 70, 0.15), (5, 520, 8192, 4100, 0.002), (3, 1288, 8192, 300, 0.03)])
+@pytest.mark.parametrize("L,d,F,B,rho", [(9, 264, 8192, 700, 0.03), (5, 552, 8192, 4100, 0.004), (3, 1320, 8192, 300, 0.03)])
 def test_stepped_gather_decode(L, d, F, B, rho):
     """The gather decode that goes through the (source, target) blocks in step (decoders of several L2s, features active on
-    several tokens): a last column slice of 8 columns, lists of several windows of 64, more tokens than one pass holds; against
+    several tokens): last column slices of 8 and 40 columns, numbers of (target, slice) units that leave XCDs out of the last round,
+    lists of several windows of 64, more tokens than one pass holds; against
     sums over the listed entries in 64 bits (fp32 sums of about rho F L products: 1e-6), twice the same bits, and an infinite weight
     that reaches only its column of the tokens that list its feature."""
     from paper_2603_21014_amd import binding as K
@@ -687,7 +688,7 @@ def test_stepped_gather_decode(L, d, F, B, rho):
     st.forward(x, par)
     flags = K.clt_workspace_view(st.H, "decode_switch")
     z, first = st.z.clone(), st.y_hat.clone()
-    assert flags[2] == 2 and (z != 0).sum() / (L * F) >= 6 and flags[1] <= 4 * (z != 0).sum() / (L * B) + 64
+    assert flags[2] == 2 and 0 < flags[1] <= flags[4], "the decode did not go in step"
     want = par["b_dec"].double()[:, None, :].repeat(1, B, 1)
     p = 0
     for l in range(L):
