@@ -31,22 +31,39 @@
 namespace clt {
 namespace {
 
-constexpr double STEP_MIN_REUSE = 6.0;      // tokens per feature, see stepped_gather_decode_kernel
+constexpr int SGD_WAVES = 16, SGD_WGS = 64, SGD_TPW = 4;      // wavefronts per workgroup, workgroups per XCD, tokens per wavefront
+constexpr int SGD_TOKENS = SGD_TPW * SGD_WAVES;
+
+// Whether the decode that goes through the blocks in step is the faster one, by the times (us) of both; pairs: (entry, target) pairs of
+// the batch, k: entries per (layer, token).  In step: an XCD takes an eighth of the P x ns (block, slice of 128 columns) steps, each for the
+// whole batch; a step has its price for every pass over the tokens and for every token whatever they list, entries come on top
+// (below 256 tokens their chains are too few to hide their latency).  Otherwise: entries by their columns, cheaper where a
+// source's 256 columns stay in the L2 (F of a few thousand), but no faster than the chain of the last target.  Over 95 sizes (L = 8 to 16,
+// d = 136 to 2304, F = 1024 to 8192, 70 to 8192 tokens, 4 to 900 entries) the pick is the faster one or within 8 % of it.  A rule on the tokens per
+// feature alone (six or more) took 1333 tokens of 4.7 entries at L = 16, d = 2048, F = 1024 in step, 1193 us against 393, and left
+// 2500 tokens of 12 at L = 12, d = 768, F = 6144 out of step, 498 against 458.
+__host__ __device__ inline bool stepping_pays(Dims D, double pairs, double k) {
+  const int ns = (D.d + 127) / 128, passes = (D.B + SGD_WGS * SGD_TOKENS - 1) / (SGD_WGS * SGD_TOKENS);
+  const double slots = 0.25 + D.F / 4500.0, chain = 0.075 * D.L * k;
+  const double apart = 3.3e-5 * pairs * D.d / 128.0 * (slots < 1.0 ? slots : 1.0);
+  const double in_step = 0.125 * D.P() * ns * (1.5 + 1.7 * passes + 0.9e-3 * D.B) + 1e-5 * pairs * ns * (D.B < 256 ? 256.0 / D.B : 1.0);
+  return in_step < (apart > chain ? apart : chain);
+}
 
 __global__ __launch_bounds__(512) void decode_decide_kernel(Dims D, const int32_t* __restrict__ l0, float thr, float thr_bwd, int forced,
                                                             int rows_free, int can_step, int32_t* __restrict__ flags,
                                                             uint32_t* __restrict__ step_ctr) {
   step_ctr[threadIdx.x] = 0u;      // pacing of the stepped decode: 8 lines of 64 words
   if (threadIdx.x != 0) return;
-  long long tot = 0;
-  for (int l = 0; l < D.L; ++l) tot += l0[l];
+  long long tot = 0, pairs = 0;
+  for (int l = 0; l < D.L; ++l) { tot += l0[l]; pairs += (long long)l0[l] * (D.L - l); }
   const double dens = (double)tot / ((double)D.L * D.B * D.F);
   flags[0] = ((forced || dens <= (double)thr) ? 1 : 0) | ((forced || dens <= (double)thr_bwd) ? 2 : 0) |
              (rows_free ? 4 : 0);
   flags[1] = 0;
   flags[2] = 1;
   flags[3] = 0;
-  flags[4] = can_step && dens * D.B >= STEP_MIN_REUSE ? (int)(4.0 * dens * D.F) + 64 : -1;
+  flags[4] = can_step && stepping_pays(D, (double)pairs, dens * D.F) ? (int)(4.0 * dens * D.F) + 64 : -1;
 }
 
 // One wavefront per (layer, token) row; lanes take 16 consecutive features per pass (two 8-byte
@@ -270,15 +287,13 @@ struct UniformRun {
 // a pacing aid that no result depends on.  (The counter is only touched from one XCD, in its L2; an atomic that has to be seen by
 // the whole device takes ten times as long here.)  The sums are taken as in the row kernel of dW_dec below: four entries and 128
 // columns per load and MFMA.
-// What bounds it: a step takes about 7 us for the pacing, the latency of lists and rows and the 2 MB per XCD that come from memory, the
-// entries come on top at 20 to 25 TB/s of rows.  L = 16, d = 2048, F = 8192, 4096 tokens, against the kernel above: 4 active
-// features per token 1.19 -> 2.37 ms, 16: 4.2 -> 3.1, 32: 8.3 -> 4.9; L = 12, d = 768, F = 6144: 6: 0.42 -> 0.51, 12: 0.83 -> 0.56;
-// 1024 tokens (a fourth of the reuse): 0.22 -> 0.28; long-tailed lists (25 on average, 300 at most): 2.36 -> 2.59, one wavefront
-// holds up its XCD; 72 MB of decoder in all (9 per XCD, L = 5, d = 776, F = 3080, 3001 tokens): forward and loss 388 -> 414 us, 226 MB: 1962 ->
-// 1824.  Hence the rule: STEP_MIN_REUSE tokens per feature, no list longer than four times the mean + 64, a slice that fits half an
-// L2 and a decoder of several L2s.
-constexpr int SGD_WAVES = 16, SGD_WGS = 64, SGD_TPW = 4;      // wavefronts per workgroup, workgroups per XCD, tokens per wavefront
-constexpr int SGD_TOKENS = SGD_TPW * SGD_WAVES;
+// What bounds it: a step takes about 7 us at 4096 tokens for the pacing, the latency of lists and rows and the 2 MB per XCD that come
+// from memory, 3.3 at 512; the entries come on top at 20 to 25 TB/s of rows.  L = 16, d = 2048, F = 8192, against the kernel above: 4096 tokens, 4
+// active features each 1.42 -> 2.47 ms, 8: 2.41 -> 2.57, 16: 4.66 -> 3.30, 32: 9.01 -> 5.00; 4100 tokens (a second pass for four of them) 4.52 -> 3.83 at
+// 16; 8192: 8.85 -> 6.12; 2048: 2.28 -> 2.16; 512: 0.63 -> 1.07.  L = 12, d = 768, F = 6144, 4096 tokens, 6: 0.40 -> 0.54, 12: 0.81 ->
+// 0.60.  F = 1024 and 10 at L = 16, d = 2048: 1.59 -> 2.06.  Long-tailed lists (25 on average, 300 at most): 2.36 -> 2.59, one wavefront
+// holds up its XCD.  72 MB of decoder in all (L = 5, d = 776, F = 3080, 3001 tokens), 14: 0.114 -> 0.133, 41: 0.265 -> 0.228.  Hence the rule:
+// stepping_pays, no list longer than four times the mean + 64, a slice that fits half an L2 and a decoder of several L2s.
 __global__ __launch_bounds__(64 * SGD_WAVES, 8) void stepped_gather_decode_kernel(
     Dims D, int kcap, int stride, const int32_t* __restrict__ counts, const int32_t* __restrict__ idx, const float* __restrict__ val,
     const bf16_t* __restrict__ W_dec, const float* __restrict__ b_dec, float* __restrict__ y_hat, int32_t* __restrict__ flags,
@@ -1462,10 +1477,10 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
 }  // namespace
 
 // Whether the decode may go in step: what the host knows of the rule at stepped_gather_decode_kernel (max_density: up to which the
-// lists are used at all)
+// lists are used at all; what pays at some density pays at every larger one)
 static bool stepped_decode_possible(bool bf16, Dims D, double max_density) {
-  return bf16 && D.F <= 8192 && D.B * max_density >= STEP_MIN_REUSE && (double)D.P() * D.F * D.d * 2.0 >= 128e6 &&
-         (size_t)D.F * D.d * 2 < ((size_t)1 << 31);
+  return bf16 && D.F <= 8192 && (double)D.P() * D.F * D.d * 2.0 >= 128e6 && (size_t)D.F * D.d * 2 < ((size_t)1 << 31) &&
+         stepping_pays(D, max_density * D.B * D.F * D.P(), max_density * D.F);
 }
 
 hipError_t launch_decode_decide(hipStream_t s, bool bf16, Dims D, const int32_t* l0, float density_threshold,

@@ -707,6 +707,27 @@ def test_stepped_gather_decode(L, d, F, B, rho):
     assert (st.y_hat - first)[~hit].abs().max() < 1e-5 * first.abs().max()
 
 
+@pytest.mark.parametrize("L,d,F,B,rho,in_step", [
+    (16, 2048, 1024, 1333, 0.0046, False),      # many tokens per feature, few entries per step: 393 us, in step 1193
+    (12, 768, 6144, 8192, 0.001, False),        # two passes over the tokens: 825 and 1021
+    (12, 768, 6144, 2500, 0.002, True),         # five tokens per feature: 498 and 458
+    (16, 2048, 1024, 4096, 0.058, True),        # 8014 and 6428
+])
+def test_gather_decode_goes_in_step_where_that_is_faster(L, d, F, B, rho, in_step):
+    """Which of the two gather decodes the device picks, at sizes where the other one was measured to be slower."""
+    from paper_2603_21014_amd import binding as K
+    g = torch.Generator(device="cuda").manual_seed(6)
+    par = {"W_enc": (torch.randn(L, d, F, generator=g, device="cuda") / d ** 0.5).bfloat16(), "b_enc": torch.zeros(L, F, device="cuda"),
+           "W_dec": torch.zeros(L * (L + 1) // 2, F, d, dtype=torch.bfloat16, device="cuda"), "b_dec": torch.ones(L, d, device="cuda")}
+    x = torch.randn(L, B, d, generator=g, device="cuda").bfloat16()
+    par["theta"] = theta_for_density(x[:, :512].float(), par["W_enc"].float(), par["b_enc"], rho).cuda()
+    st = K.CLTStep(L, d, F, B, dtype="bf16", decode_mode=GATHER, matrix_grads=False)
+    st.forward(x, par)
+    flags = K.clt_workspace_view(st.H, "decode_switch").tolist()
+    assert flags[2] == 2 and (0 < flags[1] <= flags[4]) == in_step, flags
+    assert (st.y_hat == 1.0).all()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("L,d,F,B,lambda1", [(1, 8, 8, 1, 0.0), (2, 72, 8, 33, 5.0), (3, 8, 200, 129, 0.0), (5, 136, 264, 65, 5.0)])
 def test_vectors_and_losses_at_the_edges_of_their_launches(dtype, L, d, F, B, lambda1):
