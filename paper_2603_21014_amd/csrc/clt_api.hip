@@ -196,7 +196,7 @@ Plan make_plan(const clt_config* c) {
   if (c->decode_mode == CLT_DECODE_AUTO)      // what the backward threshold admits, a quarter more for window entries
     per_token = std::min(FUSED_DZ_ENTRIES_PER_TOKEN_MAX, (int)(1.25 * backward_threshold(c) * F) + 32);
   p.ecap = (int)(B * (size_t)std::min(p.kcap, per_token));
-  p.dz_part = o;    o += align_up((L * (L + 1) / 2) * (size_t)dz_slices(bf16, c->d) * p.ecap * 4);
+  p.dz_part = o;    o += align_up((L * (L + 1) / 2) * (size_t)dz_slices(bf16, c->d, c->B) * p.ecap * 4);
   // fp32 partial sums of the dense decode where its K ranges are cut
   if (c->decode_mode != CLT_DECODE_GATHER) {
     const Dims D{c->L, c->d, c->F, c->B};

@@ -368,8 +368,17 @@ hipError_t init_gather();   // once per process, after the device is chosen
 // (0 for the window-only ones; transpose of the row lists; with bf16 storage the active and window bits in the value's low bits).
 // Layer l's entries start at l * B * kcap; off is layer-local.  seg holds FL_SEGS x L*F partial counts.
 constexpr int FL_SEGS = 16;
-// Column slices that the row kernel of dW_dec cuts the rows into, and so partial dot products of dz per entry and target
-__host__ __device__ inline int dz_slices(bool bf16, int d) { return !bf16 || d > 1024 ? 8 : d > 512 ? 4 : d > 256 ? 2 : 1; }
+// Column slices that the row kernel of dW_dec cuts the rows into, and so partial dot products of dz per entry and target.  bf16: as
+// few as hold at most 256 columns each; twice as many where a target's d y_hat columns would not fit the 4 MB of an L2 by far and 128
+// columns are left.  L = 4, F = 8192, 65 entries per token: 16384 tokens of d = 1024 in 4 slices (8 MB each) 2190 us, in 8 1715; d = 512 in 2
+// 1121, in 4 886; d = 256 whole 617, in 2 464; half of the tokens (4 MB) 894 and 984, 470 and 515, 255 and 262.  With fewer columns
+// lanes idle and slices share cache lines: d = 768, 16384 tokens, in 4 slices of 6 MB 1370, in 8 of 96 columns 1618; d = 240, 32768, whole
+// 1539, in 2 of 120 1734.
+__host__ __device__ inline int dz_slices(bool bf16, int d, int B) {
+  int S = !bf16 || d > 1024 ? 8 : d > 512 ? 4 : d > 256 ? 2 : 1;
+  while (S < 8 && d >= 256 * S && (double)B * d * 2.0 / S > 6e6) S *= 2;
+  return S;
+}
 // dz_part / ecap: room for the partial dot products of the fused dz (see fused_dz_selected), P x dz_slices x ecap floats.
 struct FeatureLists { int32_t* off; int32_t* cnt; int32_t* tok; float* val; int32_t* seg; int kcap; float* dz_part; int ecap; };
 // flags[3] = longest per-layer total of the feature lists (raised by launch_feature_lists, cleared by

@@ -1156,7 +1156,7 @@ __global__ __launch_bounds__(256, MASTER ? 5 : 6) void sparse_dwdec_sliced_kerne
 
 // bf16 storage: slices of at most 256 columns where eight of them make up d, fewer slices for smaller d (with eight of 32 columns at d =
 // 256 a wavefront's 64 lanes held 8 quads of columns): slices, and columns of a slice in whole runs of 8.
-__host__ __device__ inline int slice_cols(int d) { const int S = dz_slices(true, d); return (d + 8 * S - 1) / (8 * S) * 8; }
+__host__ __device__ inline int slice_cols(Dims D) { const int S = dz_slices(true, D.d, D.B); return (D.d + 8 * S - 1) / (8 * S) * 8; }
 
 // bf16 storage.  What bounds it: the bytes that come back through the vector caches, state and gathered rows added up (a wavefront's
 // loads return in order, so rows that wait in the L2 do not overtake state on its way from HBM), and below a few tokens per
@@ -1194,8 +1194,8 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
   // the B operand's diagonal: lane (t, n) holds z_t at k = n of its run of 8
   const uint32_t half = i16 >= 8 ? 0u : (i16 & 1) ? 0xffff0000u : 0x0000ffffu;
   // (gridDim.x is a multiple of 8.  With fewer slices than XCDs 8 / S of them take the same slice, each its share of the features)
-  const int S = dz_slices(true, D.d), slice = blockIdx.x & (S - 1), wg = blockIdx.x / S, nwg = gridDim.x / S;
-  const int sw = slice_cols(D.d), slots = 8 * ((D.d + 2047) / 2048) / S, passes = NH == 4 ? (sw + COLS - 1) / COLS : 1;
+  const int S = dz_slices(true, D.d, D.B), slice = blockIdx.x & (S - 1), wg = blockIdx.x / S, nwg = gridDim.x / S;
+  const int sw = slice_cols(D), slots = 8 * ((D.d + 2047) / 2048) / S, passes = NH == 4 ? (sw + COLS - 1) / COLS : 1;
   const int F4 = (D.F + 3) / 4;
   const bool dz_on = fused_dz_selected(flags, fl);
   const uint32_t row_bytes = (uint32_t)D.d * 2;
@@ -1414,7 +1414,7 @@ __global__ __launch_bounds__(256) void dz_from_partials_kernel(Dims D, FeatureLi
   __syncthreads();
   const int e0 = off_s[0], e1 = off_s[nf - 1] + cnt_s[nf - 1];
   const size_t lists = (size_t)l * D.B * fl.kcap;
-  const int S = dz_slices(sizeof(T) == 2, D.d);
+  const int S = dz_slices(sizeof(T) == 2, D.d, D.B);
   float* const part = fl.dz_part + (size_t)packed_index(l, l, D.L) * S * fl.ecap;      // the targets' partials follow each other
   const int n = (D.L - l) * S;
   for (int e = e0 + threadIdx.x; e < e1; e += 256) {
@@ -1610,7 +1610,7 @@ template <int NH>
 static hipError_t launch_sparse_dwdec_mfma(hipStream_t s, Dims D, const FeatureLists& fl, const DWdecArgs& a, float* n2,
                                            const int32_t* flags) {
   // (every workgroup takes SDM_ITEMS quads of features while the grid allows it)
-  const size_t wgs = (((D.F + 3) / 4 + SDM_ITEMS - 1) / SDM_ITEMS * dz_slices(true, D.d) + 7) / 8, most = (size_t)1 << 19;
+  const size_t wgs = (((D.F + 3) / 4 + SDM_ITEMS - 1) / SDM_ITEMS * dz_slices(true, D.d, D.B) + 7) / 8, most = (size_t)1 << 19;
   const dim3 grid(8 * (unsigned)(wgs < most ? wgs : most), D.P());
 #define CLT_SDM(ADAM)                                                                                                 \
   hipLaunchKernelGGL((sparse_dwdec_mfma_kernel<NH, ADAM>), grid, dim3(256), 0, s, D, fl, (const bf16_t*)a.d_yhat,     \
@@ -1626,7 +1626,7 @@ hipError_t launch_sparse_dwdec(hipStream_t s, bool bf16, Dims D, FeatureLists fl
   float* n2 = (bf16 && a.fuse.m && D.d % 256 == 0) ? a.n2_part : nullptr;
   if (sparse_dwdec_sliced(bf16, D)) {
     if (bf16) {
-      const int runs = (slice_cols(D.d) + 127) / 128;
+      const int runs = (slice_cols(D) + 127) / 128;
       return runs <= 1 ? launch_sparse_dwdec_mfma<1>(s, D, fl, a, n2, flags) : runs == 2 ? launch_sparse_dwdec_mfma<2>(s, D, fl, a, n2, flags)
              : runs == 3 ? launch_sparse_dwdec_mfma<3>(s, D, fl, a, n2, flags) : launch_sparse_dwdec_mfma<4>(s, D, fl, a, n2, flags);
     }

@@ -769,6 +769,23 @@ def test_row_sums_left_by_the_row_kernel_for_every_number_of_slices(d):
     assert rel_l2(a.norms, b.norms) < 1e-6
 
 
+@pytest.mark.parametrize("d,B", [(256, 11800), (512, 11800), (1024, 11800)])
+def test_more_column_slices_for_many_tokens(monkeypatch, d, B):
+    """Just beyond the number of tokens from which rows of bf16 are cut into twice as many slices: gradients, d pre and the row sums
+    against the kernel that takes whole rows and the separate dz kernel (bf16 rounding of d pre and of the weights)."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="bf16", L=2, d=d, F=256, B=B, seed=96)
+    theta = sparse_theta(w, 0.02)
+    params = S.make_params(w)
+    x, y = S.make_inputs(w)
+    a = GpuRun(w, params, x, y, theta=theta, fused=True, pre_steps=1, reuse_decoder_norms=True, decode_mode=GATHER)
+    monkeypatch.setenv("CLT_SD_ROWS", "1")
+    b = GpuRun(w, params, x, y, theta=theta, fused=True, pre_steps=1, decode_mode=GATHER)
+    assert a.decode_switch[2] == 2 and a.decode_switch[3] > B
+    assert rel_l2(a.norms, b.norms) < 1e-5
+    for k in O.PARAM_NAMES:
+        assert rel_l2(a.new_m[k], b.new_m[k]) < 4e-3 and rel_l2(a.new_v[k], b.new_v[k]) < 8e-3, k
+
+
 @pytest.mark.parametrize("L,d,F,B,master,int8", [
     (1, 8, 8, 1, False, False),            # one chunk of one step: the update alone is moved out
     (3, 80, 264, 130, True, False),        # ragged tiles and tokens
