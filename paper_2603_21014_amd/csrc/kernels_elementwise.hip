@@ -363,17 +363,22 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ part, in
 }
 
 // What is left of the loss after its row blocks: the first workgroup adds up the loss terms, the others the column partials
-// of the norms' gradient, G[c] = lambda0/B sum_r sp[r][c] (+ lambda1/B sum_r dead[r][c]).
+// of the norms' gradient, G[c] = sp_scale sum_r sp[r][c] (+ dead_scale sum_r dead[r][c]), scales lambda0/B and lambda1/B.
 __global__ __launch_bounds__(256) void loss_finish_kernel(const double* __restrict__ part_rec, int n_rec, const double* __restrict__ part_sp,
                                                           int n_sp, const double* __restrict__ part_dead, float inv_B, float lambda0,
-                                                          float lambda1, float* __restrict__ loss_dev, const float* __restrict__ sp_cols,
+                                                          float lambda1, float sp_scale, float dead_scale,
+                                                          float* __restrict__ loss_dev, const float* __restrict__ sp_cols,
                                                           const float* __restrict__ dead_cols, int nparts, int ncols,
                                                           float* __restrict__ G) {
   __shared__ float lds[3][64];
   if (blockIdx.x > 0) {
     const int c = ((int)blockIdx.x - 1) * 64 + (threadIdx.x & 63);
-    float g = (lambda0 * inv_B) * sum_partials(sp_cols, nparts, ncols, c, lds);
-    if (part_dead) g += (lambda1 * inv_B) * sum_partials(dead_cols, nparts, ncols, c, lds);
+    float g = sp_scale * sum_partials(sp_cols, nparts, ncols, c, lds);
+    if (part_dead) {
+#pragma clang fp contract(off)
+      const float q = dead_scale * sum_partials(dead_cols, nparts, ncols, c, lds);
+      g = g + q;
+    }
     if (threadIdx.x < 64 && c < ncols) G[c] = g;
     return;
   }
@@ -972,7 +977,7 @@ hipError_t launch_loss_finish(hipStream_t s, Dims D, const double* part_rec, int
                               const float* sp_cols, const float* dead_cols, int nparts, float* G) {
   const int ncols = D.L * D.F;
   hipLaunchKernelGGL(loss_finish_kernel, dim3(1 + (ncols + 63) / 64), dim3(256), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
-                     inv_B, lambda0, lambda1, loss_dev, sp_cols, dead_cols, nparts, ncols, G);
+                     inv_B, lambda0, lambda1, lambda0 / (float)D.B, lambda1 / (float)D.B, loss_dev, sp_cols, dead_cols, nparts, ncols, G);
   return hipGetLastError();
 }
 

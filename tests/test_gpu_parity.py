@@ -739,6 +739,27 @@ def test_vectors_and_losses_at_the_edges_of_their_launches(dtype, L, d, F, B, la
         show(f"vectors {dtype} L={L} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL[dtype]))
 
 
+def test_norm_gradient_sums_are_scaled_by_lambda_over_the_batch():
+    """G is its column sums times lambda / B, each rounded once: with lambda = B the sums themselves, and exactly
+    fl(fl(lambda / B) * sum) for any other lambda (0.1 / 300 differs from 0.1 * (1 / 300)); the dead-feature sums are added to it."""
+    from paper_2603_21014_amd import binding as K
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="f32", L=2, d=64, F=128, B=300, seed=97)
+    gp = {k: v.to("cuda", torch.float32) for k, v in S.make_params(w).items()}
+    x, y = (t.to("cuda") for t in S.make_inputs(w))
+    step = K.CLTStep(w.L, w.d, w.F, w.B, dtype="f32", C_=w.C, ste_bandwidth=w.ste_eps, device="cuda")
+
+    def G(lambda0, lambda1):
+        step.forward(x, gp)
+        step.loss(y, lambda0, None, False, lambda1, gp)
+        return K.clt_workspace_view(step.H, "G").cpu().numpy().copy()
+
+    sums, dead = G(300.0, 0.0), G(0.0, 300.0)
+    r0, r1 = np.float32(0.1) / np.float32(300), np.float32(0.7) / np.float32(300)
+    assert (sums != 0).any() and (dead != 0).any()
+    assert (G(0.1, 0.0) == r0 * sums).all()
+    assert (G(0.1, 0.7) == r0 * sums + r1 * dead).all()
+
+
 @pytest.mark.parametrize("workload,d,F,B,topk", [("tiny", 72, 520, 130, 0), ("llama1b_int8", 264, 328, 300, 0), ("tiny", 256, 72, 66, 0),
                                                  ("tiny", 136, 264, 90, 6)])
 def test_list_backward_finished_from_the_lists(workload, d, F, B, topk):
