@@ -349,7 +349,7 @@ __global__ __launch_bounds__(256) void loss_kernel(Dims D, LossArgs a) {
 // are added in order.  Valid in the first wavefront.  (One thread per column walking 128 partials: 34 us at 73728 columns,
 // bound by the chain of loads; 5 us now, also because there are a quarter as many partials.)
 __device__ __forceinline__ float sum_partials(const float* __restrict__ part, int nparts, int ncols, int c, float (&lds)[3][64]) {
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = (threadIdx.x >> 6) & 3, lane = threadIdx.x & 63;      // (larger workgroups: four wavefronts each, with an lds of their own)
   const int per = (nparts + 3) / 4, r0 = min(nparts, w * per), r1 = min(nparts, r0 + per);
   float s = 0.f;
   if (c < ncols) {
@@ -364,36 +364,45 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ part, in
 
 // What is left of the loss after its row blocks: the first workgroup adds up the loss terms, the others the column partials
 // of the norms' gradient, G[c] = sp_scale sum_r sp[r][c] (+ dead_scale sum_r dead[r][c]), scales lambda0/B and lambda1/B.
-__global__ __launch_bounds__(256) void loss_finish_kernel(const double* __restrict__ part_rec, int n_rec, const double* __restrict__ part_sp,
+// 1024 lanes: the loss terms are one workgroup's chains of loads, which outlast the columns (L = 16, d = 2048, F = 8192, 4096 tokens:
+// 21.4 us with 256 lanes, 12.4; 10.7 and 7.4 as two launches.  L = 6, d = 2056, F = 8200 with the dead-feature term 18.0 -> 11.1).
+constexpr int LF_LANES = 1024, LF_COLS = LF_LANES / 256 * 64;
+__global__ __launch_bounds__(LF_LANES) void loss_finish_kernel(const double* __restrict__ part_rec, int n_rec, const double* __restrict__ part_sp,
                                                           int n_sp, const double* __restrict__ part_dead, float inv_B, float lambda0,
                                                           float lambda1, float sp_scale, float dead_scale,
                                                           float* __restrict__ loss_dev, const float* __restrict__ sp_cols,
                                                           const float* __restrict__ dead_cols, int nparts, int ncols,
                                                           float* __restrict__ G) {
-  __shared__ float lds[3][64];
   if (blockIdx.x > 0) {
-    const int c = ((int)blockIdx.x - 1) * 64 + (threadIdx.x & 63);
-    float g = sp_scale * sum_partials(sp_cols, nparts, ncols, c, lds);
+    __shared__ float lds[LF_LANES / 256][3][64];
+    const int part = threadIdx.x >> 8, c = ((int)blockIdx.x - 1) * LF_COLS + part * 64 + (threadIdx.x & 63);
+    float g = sp_scale * sum_partials(sp_cols, nparts, ncols, c, lds[part]);
     if (part_dead) {
 #pragma clang fp contract(off)
-      const float q = dead_scale * sum_partials(dead_cols, nparts, ncols, c, lds);
+      const float q = dead_scale * sum_partials(dead_cols, nparts, ncols, c, lds[part]);
       g = g + q;
     }
-    if (threadIdx.x < 64 && c < ncols) G[c] = g;
+    if ((threadIdx.x & 255) < 64 && c < ncols) G[c] = g;
     return;
   }
-  auto sum = [&](const double* p, int n) {
-    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};      // eight chains keep eight loads in flight
-    for (int i = threadIdx.x; i < n; i += 2048) {
+  __shared__ double sh[3][LF_LANES / 64];
+  auto sum = [&](const double* p, int n, int slot) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};      // four chains keep four loads in flight
+    for (int i = threadIdx.x; i < n; i += 4 * LF_LANES) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (i + 256 * q < n) s[q] += p[i + 256 * q];
+      for (int q = 0; q < 4; ++q)
+        if (i + LF_LANES * q < n) s[q] += p[i + LF_LANES * q];
     }
-    __syncthreads();      // (the sum before this one has been read)
-    return block_sum_256(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
+    const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+    if ((threadIdx.x & 63) == 0) sh[slot][threadIdx.x >> 6] = t;
   };
-  const double a = sum(part_rec, n_rec), b = sum(part_sp, n_sp), c = part_dead ? sum(part_dead, n_sp) : 0.0;
+  sum(part_rec, n_rec, 0);
+  sum(part_sp, n_sp, 1);
+  sum(part_dead, part_dead ? n_sp : 0, 2);
+  __syncthreads();
   if (threadIdx.x == 0) {
+    double a = 0.0, b = 0.0, c = 0.0;
+    for (int i = 0; i < LF_LANES / 64; ++i) { a += sh[0][i]; b += sh[1][i]; c += sh[2][i]; }
     const double rec = a * (double)inv_B, sp = b * (double)inv_B * (double)lambda0;
     const double dead = c * (double)inv_B * (double)lambda1;
     loss_dev[0] = (float)(rec + sp + dead);
@@ -976,7 +985,7 @@ hipError_t launch_loss_finish(hipStream_t s, Dims D, const double* part_rec, int
                               const double* part_dead_or_null, float inv_B, float lambda0, float lambda1, float* loss_dev,
                               const float* sp_cols, const float* dead_cols, int nparts, float* G) {
   const int ncols = D.L * D.F;
-  hipLaunchKernelGGL(loss_finish_kernel, dim3(1 + (ncols + 63) / 64), dim3(256), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
+  hipLaunchKernelGGL(loss_finish_kernel, dim3(1 + (ncols + LF_COLS - 1) / LF_COLS), dim3(LF_LANES), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
                      inv_B, lambda0, lambda1, lambda0 / (float)D.B, lambda1 / (float)D.B, loss_dev, sp_cols, dead_cols, nparts, ncols, G);
   return hipGetLastError();
 }
