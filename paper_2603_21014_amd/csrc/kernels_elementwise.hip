@@ -810,8 +810,8 @@ __global__ __launch_bounds__(256) void topk_select_kernel(Dims D, const float* _
 // token vectors over the first batches.  Stage 1: grid = (row blocks, L), one wave per row, each
 // block leaves the sum of its rows' norms; stage 2 adds the blocks of a layer, in order, to the
 // running sum.  int8 rows: the norm of the codes times |row scale|.
-// A wave takes four rows at a time, 16 bytes (int8: 8) per lane and row in flight.  L = 16, d = 2048, 4096 tokens of bf16: the
-// kernel reads 268 MB in 71 us; its second stage was one chain of loads per layer before, 12 us.
+// A wave takes four rows at a time, 16 bytes (int8: 8) per lane and row in flight.  L = 16, d = 2048, 4096 tokens of bf16: both
+// stages read 268 MB in 59 us, 81 behind plain stores of another 268 MB; the second stage was one chain of loads per layer before, 12 us.
 template <typename T, bool INT8>
 __global__ __launch_bounds__(256) void row_norm_sum_kernel(Dims D, const void* __restrict__ av,
                                                            const float* __restrict__ a_scale,
@@ -887,9 +887,11 @@ __global__ void normalise_scale_kernel(Dims D, const double* __restrict__ norm_s
 }
 
 // native rows: a_out = a_in / c[l] (a_out may be a_in); grid = (chunks of a layer, L).  Bound by memory.  STREAM: non-temporal stores,
-// for batches that do not fit the 256 MB Infinity Cache together with the result: plain ones push out what is still to be read
-// (L = 16, d = 2048, 4096 tokens of bf16, sum and division: 155.5 -> 123.8 us; in fp32 with L = 8 142 -> 128; 75 MB: 41 either way,
-// and the forward pass that follows may find the result there).
+// for batches that do not fit the 256 MB Infinity Cache together with the result.  The division itself hardly gains (L = 16, d = 2048, 4096
+// tokens of bf16: 81.5 -> 79.6 us); what gains is the next reading, here the norm sum of the batch after, which does not wait behind the
+// write-back any more (81 -> 59 us).  Both, another batch each time: 159.9 -> 135.4 us, in fp32 with L = 8 153.2 -> 133.6; the same batch
+// again, part of it still in the cache, 154.5 -> 124.4 and 143.5 -> 127.7.  75 MB: 51 and 41 us with either, and the forward pass that follows may
+// find the result in the cache.
 constexpr int NORM_LOADS = 4;      // 16-byte pieces per lane
 template <typename T, bool STREAM>
 __global__ __launch_bounds__(256) void normalise_rows_kernel(Dims D, const double* __restrict__ norm_sum,

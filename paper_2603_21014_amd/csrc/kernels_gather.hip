@@ -8,9 +8,11 @@
 //   compact   turns every (layer, token) row of z into an ordered list of
 //             (feature, value) pairs, plus the inactive features inside the
 //             threshold window (needed by the threshold gradient);
-//   gather decode   one workgroup per (token, target layer): walks the sources
-//             l <= l' and their lists, streams the 2d-byte decoder rows with
-//             16-byte loads per lane and accumulates in fp32 registers;
+//   gather decode   one wavefront per (token, target layer, run of 256 columns): walks
+//             the sources l <= l' and their lists, four columns of the listed decoder
+//             rows per lane, and accumulates in fp32 registers;
+//   stepped gather decode   the same sums with all tokens of the batch at one (source,
+//             target) block at a time, so that its rows come out of the L2;
 //   gather dz       one workgroup per (layer, token): dot products of the listed
 //             features' decoder rows with the token's d y_hat rows;
 //   feature lists   transpose of the row lists: per (layer, feature) the tokens on
@@ -1389,8 +1391,8 @@ __global__ __launch_bounds__(256, (NH == 1 ? 7 : NH == 2 ? 5 : 3) - (ADAM == 2 ?
   }
 }
 
-// Fused dz, second half: an entry's partial dot products summed over the targets and the eight column slices, always in that
-// order, plus the gradient of the sparsity term.  Bound by the partials, 8 floats per entry and target: a workgroup takes the
+// Fused dz, second half: an entry's partial dot products summed over the targets and the column slices, always in that
+// order, plus the gradient of the sparsity term.  Bound by the partials, a float per entry, target and slice: a workgroup takes the
 // entries of 64 consecutive features one per lane, which reads them in whole lines (16 lanes per feature, in pieces of 64 bytes at
 // 4 KB and more from each other: 0.80 ms at L = 16, 41 entries per feature and layer; 0.40 now).
 // FINAL (bf16 storage, no dead-feature term): what ste_reduce_kernel does elsewhere in a scan of the dense arrays (0.43 ms there): the
@@ -1587,7 +1589,7 @@ hipError_t launch_feature_lists(hipStream_t s, bool bf16, Dims D, const uint8_t*
   return hipGetLastError();
 }
 
-// The sliced kernels: d in eight slices (fp32: of whole lane quads), and one target's d y_hat within reach of a 32-bit byte offset
+// The sliced kernels: d in slices (fp32: eight of whole lane quads), and one target's d y_hat within reach of a 32-bit byte offset
 static bool sparse_dwdec_sliced(bool bf16, Dims D) {
   return (bf16 || D.d % 32 == 0) && (size_t)D.B * D.d * 2 < ((size_t)1 << 31) && !getenv("CLT_SD_ROWS");
 }

@@ -732,7 +732,7 @@ static hipError_t launch_dwdec_mode(hipStream_t s, Dims D, const DWdecArgs& a) {
 // contraction's own epilogue does the rest.  One tile of 256 x 256 keeps one CU busy through all the tokens, and then through the
 // update: 1.3 MB and more of weights and moments at the 45 GB/s or so that a CU moves, while most of the chip waits.  Cut (one
 // chunk: the update alone is moved out), the partial sums and the second launch cost traffic but run on every CU.
-// The costs, us: a K step of 32 tokens 1.6; the epilogue 8, with the update 30; cut: the epilogue of partial sums and the second launch
+// The costs, us: a K step of TK = 64 tokens 1.6; the epilogue 8, with the update 30; cut: the epilogue of partial sums and the second launch
 // 13, their traffic at 7 TB/s (it stays in the Infinity Cache).  Cut where the model says 15 % less or better.  Whole steps, uncut -> cut (us):
 // 4 layers of width 80, 768 features: 500 tokens 147 -> 102, 1920 tokens 218 -> 135; width 256, 1024 features: 400 tokens 162 -> 131,
 // 4096 tokens 387 -> 256; 6 layers of width 136, 264 features, 130 tokens 145 -> 109; 2 layers of width 1024, 2048 features, 4096

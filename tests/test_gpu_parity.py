@@ -888,7 +888,7 @@ def test_sparse_backward_fused_adam(dtype, master):
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 256), ("f32", 96), ("bf16", 2304)])
 def test_sparse_backward_column_slices_match_whole_rows(monkeypatch, dtype, d):
-    """The row kernel of dW_dec cut into eight column slices (one per XCD; d a multiple of 32) against the kernel that
+    """The row kernel of dW_dec cut into column slices (fp32: eight, one per XCD, d a multiple of 32) against the kernel that
     takes whole rows.  With fp32 storage both sum a feature's tokens in the same order, one multiply-add each:
     gradients and the fused update must agree bit for bit; with bf16 storage the slices use packed dot products and
     agree to rounding.  d = 2304: two passes of lanes per slice, the second one ragged."""
