@@ -364,9 +364,12 @@ __device__ __forceinline__ float sum_partials(const float* __restrict__ part, in
 
 // What is left of the loss after its row blocks: the first workgroup adds up the loss terms, the others the column partials
 // of the norms' gradient, G[c] = sp_scale sum_r sp[r][c] (+ dead_scale sum_r dead[r][c]), scales lambda0/B and lambda1/B.
-// 1024 lanes: the loss terms are one workgroup's chains of loads, which outlast the columns (L = 16, d = 2048, F = 8192, 4096 tokens:
-// 21.4 us with 256 lanes, 12.4; 10.7 and 7.4 as two launches.  L = 6, d = 2056, F = 8200 with the dead-feature term 18.0 -> 11.1).
-constexpr int LF_LANES = 1024, LF_COLS = LF_LANES / 256 * 64;
+// The loss terms are one workgroup's chains of loads, which outlast the columns where there are many of them: L = 16, d = 2048, F = 8192,
+// 4096 tokens 21.4 us with 256 lanes, 12.4 with 1024 (10.7 and 7.4 as two launches); L = 6, d = 2056, F = 8200 with the dead-feature term
+// 18.0 and 11.1; L = 12, d = 768, F = 6144, 1024 tokens of fp32 9.0 and 7.2.  Up to 2048 terms each, one round of 256 lanes, the larger workgroup only
+// costs its barriers (whole steps of 70 to 150 us are 0.7 to 1 us longer).
+constexpr int LF_FEW = 2048;
+template <int LF_LANES>
 __global__ __launch_bounds__(LF_LANES) void loss_finish_kernel(const double* __restrict__ part_rec, int n_rec, const double* __restrict__ part_sp,
                                                           int n_sp, const double* __restrict__ part_dead, float inv_B, float lambda0,
                                                           float lambda1, float sp_scale, float dead_scale,
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(LF_LANES) void loss_finish_kernel(const double* __r
                                                           float* __restrict__ G) {
   if (blockIdx.x > 0) {
     __shared__ float lds[LF_LANES / 256][3][64];
-    const int part = threadIdx.x >> 8, c = ((int)blockIdx.x - 1) * LF_COLS + part * 64 + (threadIdx.x & 63);
+    const int part = threadIdx.x >> 8, c = ((int)blockIdx.x - 1) * (LF_LANES / 4) + part * 64 + (threadIdx.x & 63);
     float g = sp_scale * sum_partials(sp_cols, nparts, ncols, c, lds[part]);
     if (part_dead) {
 #pragma clang fp contract(off)
@@ -387,13 +390,14 @@ __global__ __launch_bounds__(LF_LANES) void loss_finish_kernel(const double* __r
   }
   __shared__ double sh[3][LF_LANES / 64];
   auto sum = [&](const double* p, int n, int slot) {
-    double s[4] = {0.0, 0.0, 0.0, 0.0};      // four chains keep four loads in flight
-    for (int i = threadIdx.x; i < n; i += 4 * LF_LANES) {
+    constexpr int N = LF_LANES == 256 ? 8 : 4;      // chains, to keep as many loads in flight
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < n; i += N * LF_LANES) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < N; ++q)
         if (i + LF_LANES * q < n) s[q] += p[i + LF_LANES * q];
     }
-    const double t = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+    const double t = wave_sum(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
     if ((threadIdx.x & 63) == 0) sh[slot][threadIdx.x >> 6] = t;
   };
   sum(part_rec, n_rec, 0);
@@ -987,8 +991,11 @@ hipError_t launch_loss_finish(hipStream_t s, Dims D, const double* part_rec, int
                               const double* part_dead_or_null, float inv_B, float lambda0, float lambda1, float* loss_dev,
                               const float* sp_cols, const float* dead_cols, int nparts, float* G) {
   const int ncols = D.L * D.F;
-  hipLaunchKernelGGL(loss_finish_kernel, dim3(1 + (ncols + LF_COLS - 1) / LF_COLS), dim3(LF_LANES), 0, s, part_rec, n_rec, part_sp, n_sp, part_dead_or_null,
-                     inv_B, lambda0, lambda1, lambda0 / (float)D.B, lambda1 / (float)D.B, loss_dev, sp_cols, dead_cols, nparts, ncols, G);
+  const bool few = std::max(n_rec, n_sp) <= LF_FEW;
+  const int cols = few ? 64 : 256;
+  hipLaunchKernelGGL(few ? loss_finish_kernel<256> : loss_finish_kernel<1024>, dim3(1 + (ncols + cols - 1) / cols), dim3(4 * cols), 0, s,
+                     part_rec, n_rec, part_sp, n_sp, part_dead_or_null, inv_B, lambda0, lambda1, lambda0 / (float)D.B, lambda1 / (float)D.B,
+                     loss_dev, sp_cols, dead_cols, nparts, ncols, G);
   return hipGetLastError();
 }
 

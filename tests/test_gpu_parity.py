@@ -739,6 +739,15 @@ def test_vectors_and_losses_at_the_edges_of_their_launches(dtype, L, d, F, B, la
         show(f"vectors {dtype} L={L} d={d} F={F} B={B} fused={fused}", compare_step(w, g, o, TOL[dtype]))
 
 
+@pytest.mark.parametrize("lambda1", [0.0, 5.0])
+@pytest.mark.parametrize("B", [16384, 16385])
+def test_loss_sums_by_few_and_by_many_lanes(B, lambda1):
+    """2048 partial sums of each loss are added up by 256 lanes, 2064 by 1024."""
+    w = S.scaled(S.WORKLOADS["tiny"], dtype="f32", L=16, d=8, F=8, B=B, seed=98, lambda1=lambda1)
+    g, o = run_both(w)
+    show(f"losses B={B} lambda1={lambda1}", compare_step(w, g, o, TOL["f32"]))
+
+
 def test_norm_gradient_sums_are_scaled_by_lambda_over_the_batch():
     """G is its column sums times lambda / B, each rounded once: with lambda = B the sums themselves, and exactly
     fl(fl(lambda / B) * sum) for any other lambda (0.1 / 300 differs from 0.1 * (1 / 300)); the dead-feature sums are added to it."""
