@@ -57,7 +57,10 @@ def _compile(src: str) -> str:
     with tempfile.TemporaryDirectory() as tmp:          # -save-temps: the device code's assembly on its way to the object
         cmd = [HIPCC, *FLAGS, "-save-temps", "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True, cwd=tmp)
-        for f in glob.glob(os.path.join(tmp, "*gfx950.s")) if r.returncode == 0 else ():
+        listing = glob.glob(os.path.join(tmp, "*gfx950.s"))
+        if r.returncode == 0 and len(listing) != 1:
+            raise RuntimeError(f"{src}: one listing of the device code expected, found {listing}")
+        for f in listing if r.returncode == 0 else ():
             with open(f) as h:
                 lost = vector_work_without_lanes(h.read())
             if lost:
